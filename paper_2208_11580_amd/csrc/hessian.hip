@@ -2,194 +2,258 @@
 // second moment that the sequential variant (appendix "Sequential Quantization with OBQ")
 // accumulates beside it.
 //
-// A dense symmetric rank-N contraction, so it runs on the fp32 matrix cores:
-// v_mfma_f32_32x32x2_f32, 128x128 output tiles per 256-thread workgroup (four waves, each
-// 64x64 = 2x2 MFMA tiles), X staged through LDS k-major so that the MFMA operand reads are
-// bank-conflict free.  Only tiles on or above the block diagonal are computed; the
-// contraction length N is cut into S slices so that small d still fills 256 CUs.  Slices go
-// to a workspace and are summed in a fixed order by a second kernel, which also mirrors the
-// upper tiles into the lower triangle (H comes out exactly symmetric) -- no float atomics,
-// results are deterministic.
+// A dense (symmetric) rank-N contraction of fp32 inputs.  Every input is the exact sum of three bf16
+// numbers, x = h + m + l (8 bits of the 24 each), so the contraction runs on the bf16 matrix cores as
+// six of the nine products -- h h, h m, m h, m m, h l, l h; what is left out is below 2^-24 of x y --
+// at 16 times the fp32 rate each.  v_mfma_f32_32x32x16_bf16, square output tiles of 128 (four waves,
+// two workgroups per CU) or 256 (eight waves), the split done in registers on the way into LDS, two
+// LDS stages, one barrier per 16 samples.  A slab's products are summed from zero and added to the
+// running sums once, so a sum takes N / 16 roundings (the fp32 MFMA's took N / 2): against fp64 the
+// relative error is 0.6e-7 .. 1.2e-7 (fp32 MFMA: 1.0e-7 .. 4.3e-7) over d = 32 .. 3072, N = 256 ..
+// 50 000.
+//
+// Only tiles on or above the block diagonal are computed; the contraction length N is cut into S
+// slices so that small d still fills 256 CUs.  Slices go to a workspace and are summed in a fixed
+// order by a second kernel, which also mirrors the upper tiles into the lower triangle (H comes out
+// exactly symmetric) -- no float atomics, results are deterministic.
+//
+// Bound by the matrix cores' issue and the loads' latency (half of the bf16 rate): 2304 x 50 000 in
+// 1.50 ms, 177 TFLOP/s of the d^2 N flop (fp32 MFMA: 2.37 ms, 112); 576 x 50 000 0.148 ms (0.326).
 #include "common.h"
 
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float's address
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = 128;       // tile edge
-constexpr int BK = 16;        // k-slab per LDS stage
-constexpr int LDT = BM + 4;   // padded LDS row
+constexpr int BK = 16;                // samples per slab: one MFMA deep
+constexpr int kHalf = 32 * 16 + 32;   // bytes of 32 rows x 8 samples of a plane, plus 32: see stash
+constexpr int kFrag = 2 * kHalf;      // bytes of 32 rows x 16 samples of a plane
 
-__host__ __device__ inline int tiles_of(int d) { return (d + BM - 1) / BM; }
+__host__ __device__ inline int tiles_of(int d, int tile) { return (d + tile - 1) / tile; }
 
-// How many slices of the sample axis, and how long each is (multiple of BK), for a launch of
-// `ntri` output tiles of `tile_elems` results each.  Workgroups are dealt evenly to the 256 CUs,
-// which work on several at a time, so the launch lasts as long as the CU with the most
-// workgroups: ceil(ntri S / 256) of them, each 1 / S of a tile's contraction.  More slices even
-// that out but cost S partial results written and read back; the plan minimises the sum of both
-// (matrix-core time at ~120 TFLOP/s, partial traffic at ~4 TB/s).
-inline void split_plan_tiles(int64_t ntri, int64_t N, int *S, int64_t *kchunk, double tile_elems = (double)BM * BM)
+// The launch of a contraction: square output tiles of edge `tile`, S slices of `kchunk` samples
+// (multiple of BK).
+struct Plan {
+    int tile, S;
+    int64_t kchunk;
+};
+
+// `ntiles(tile)` output tiles of that edge.  Time of a launch as measured, in microseconds: a slab
+// takes 1.28 with two 128-tile workgroups on a CU and 0.73 with one (latency), 2.5 with one 256-tile
+// workgroup; 3 to start a round of workgroups; and the partial results are written and read back at
+// about 4 TB/s.  The large tile wins by 6 % where both fill the chip (d = 2304, 3072), the small one
+// where they do not (576 x 50 000: 148 against 199 us).
+template <class Count>
+inline Plan make_plan(Count ntiles, int64_t N)
 {
-    const int64_t smax = (N + 2047) / 2048 > 0 ? (N + 2047) / 2048 : 1;
-    const double flops_tile = 2.0 * tile_elems * (double)N;
-    const double cu_rate = 120e12 / 256.0;
-    double best = 0.0;
-    int64_t s = 1;
-    for (int64_t c = 1; c <= smax && c <= 64; ++c) {
-        double per_cu = (double)((ntri * c + 255) / 256);   // workgroups on the busiest CU
-        if (per_cu < 4.0) per_cu = 4.0;                     // fewer than ~4 resident do not go faster
-        const double cost = per_cu * (flops_tile / (double)c) / cu_rate
-                            + (double)c * (double)ntri * tile_elems * 8.0 / 4e12;
-        if (c == 1 || cost < best) { best = cost; s = c; }
+    Plan best = {128, 1, 0};
+    double best_cost = 0.0;
+    const int64_t smax = N / (2 * BK) < 1 ? 1 : N / (2 * BK) < 64 ? N / (2 * BK) : 64;
+    for (int tile = 128; tile <= 256; tile += 128) {
+        const int64_t n = ntiles(tile);
+        for (int64_t c = 1; c <= smax; ++c) {
+            const double slabs = (double)(((N + c - 1) / c + BK - 1) / BK);
+            const int64_t w = n * c;
+            double cost;
+            if (tile == 128) {
+                const int64_t left = w % 512;
+                cost = (double)(w / 512) * (1.28 * slabs + 3.0)
+                       + (left > 256 ? 1.28 * slabs + 3.0 : left > 0 ? 0.73 * slabs + 3.0 : 0.0);
+            } else {
+                cost = (double)((w + 255) / 256) * (2.5 * slabs + 3.0);
+            }
+            cost += (double)w * tile * tile * 8.0 / 4e6 + 0.1 * (double)c;
+            if (best_cost == 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best.tile = tile;
+                best.S = (int)c;
+            }
+        }
     }
-    int64_t kc = (N + s - 1) / s;
+    int64_t kc = (N + best.S - 1) / best.S;
     kc = (kc + BK - 1) / BK * BK;
-    if (kc < BK) kc = BK;
-    s = (N + kc - 1) / kc;
-    if (s < 1) s = 1;
-    *S = (int)s;
-    *kchunk = kc;
+    best.kchunk = kc;
+    best.S = (int)((N + kc - 1) / kc);
+    return best;
 }
 
-inline void split_plan(int d, int64_t N, int *S, int64_t *kchunk)
+inline Plan hessian_plan(int d, int64_t N)
 {
-    int nt = tiles_of(d);
-    split_plan_tiles((int64_t)nt * (nt + 1) / 2, N, S, kchunk);
+    return make_plan([&](int tile) { const int64_t nt = tiles_of(d, tile); return nt * (nt + 1) / 2; }, N);
+}
+
+inline Plan cross_plan(int d_row, int d_col, int64_t N)
+{
+    return make_plan([&](int tile) { return (int64_t)tiles_of(d_row, tile) * tiles_of(d_col, tile); }, N);
 }
 
 // One slice of P = Ya Xb^T over the samples [kbeg, kend): Ya is da x N (leading dimension lda),
 // Xb is db x N (ldb).  SYM: Ya and Xb are the same matrix and only the tiles on or above the block
-// diagonal are formed.
-template <bool SYM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void nt_partial_kernel(const float *__restrict__ Ya, int da,
-                                                         int64_t lda, const float *__restrict__ Xb,
-                                                         int db, int64_t ldb, int64_t N,
-                                                         int64_t kchunk, float *__restrict__ partial,
-                                                         int vec_ok)
+// diagonal are formed.  WR x WC waves, each MT x NT accumulators of 32 x 32.
+template <bool SYM, int WR, int WC, int MT, int NT>
+__global__ __launch_bounds__(WR *WC * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const float *__restrict__ Xb, int db,
+                       int64_t ldb, int64_t N, int S, int64_t kchunk, float *__restrict__ partial)
 {
-    __shared__ float As[BK][LDT];
-    __shared__ float Bs[BK][LDT];
+    constexpr int TILE = WR * MT * 32, T = WR * WC * 64;
+    static_assert(WC * NT * 32 == TILE && TILE * 4 == 2 * T, "square tiles, two quads per thread and operand");
+    __shared__ __align__(16) uint8_t lds[2][2][3][TILE / 32][kFrag];   // stage, operand, plane, 32 rows
 
-    const int tile_id = blockIdx.x, slice = blockIdx.y;
+    // Workgroups go round-robin to the 8 XCDs: each XCD takes a run of the (slice, tile) list, so
+    // that the workgroups that share a slice of X run side by side and find it in their L2.
+    const int ntri = SYM ? tiles_of(da, TILE) * (tiles_of(da, TILE) + 1) / 2 : tiles_of(da, TILE) * tiles_of(db, TILE);
+    const int unit = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (unit >= ntri * S) return;
+    const int tile_id = unit % ntri, slice = unit / ntri;
     int ti, tj;
     if (SYM) {
         // upper-triangular tile enumeration: tile_id -> (ti <= tj)
-        const int nt = tiles_of(da);
-        int t = tile_id, rowlen = nt;
+        int t = tile_id, rowlen = tiles_of(da, TILE);
         ti = 0;
         while (t >= rowlen) { t -= rowlen; ++ti; --rowlen; }
         tj = ti + t;
     } else {
-        const int ntb = tiles_of(db);
+        const int ntb = tiles_of(db, TILE);
         ti = tile_id / ntb;
         tj = tile_id % ntb;
     }
-    const bool on_diag = SYM && (ti == tj);
 
     const int64_t kbeg = (int64_t)slice * kchunk;
     const int64_t kend = (kbeg + kchunk < N) ? kbeg + kchunk : N;
+    const int nslab = kend > kbeg ? (int)((kend - kbeg + BK - 1) / BK) : 0;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WC, wn = wave % WC;
 
-    floatx16 acc[2][2];
+    floatx16 acc[MT][NT];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NT; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-    // loader: a 128 x 16 slab is 512 float4; thread takes quads tid and tid + 256
-    float4 ra[2], rb[2];
-    auto fetch = [&](const float *M, int rows, int64_t ld, int tile, int64_t k0, float4(&r)[2]) {
+    // loader: four threads take the 64 bytes of a row's slab, 16 bytes each; a thread has two rows
+    // of each operand.  Rows beyond the matrix re-read its last row: their products only reach
+    // outputs that are never stored.
+    const int q = tid & 3, r0 = tid >> 2;
+    const float *src[2][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int f = tid + h * 256;
-            int row = tile * BM + (f >> 2);
-            int64_t k = k0 + (f & 3) * 4;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (row < rows) {
-                const float *src = M + (int64_t)row * ld + k;
-                if (vec_ok && k + 3 < kend) {
-                    v = *reinterpret_cast<const float4 *>(src);
-                } else {
-                    if (k + 0 < kend) v.x = src[0];
-                    if (k + 1 < kend) v.y = src[1];
-                    if (k + 2 < kend) v.z = src[2];
-                    if (k + 3 < kend) v.w = src[3];
-                }
+    for (int h = 0; h < 2; ++h) {
+        const int ra = ti * TILE + r0 + h * (T / 4), rb = tj * TILE + r0 + h * (T / 4);
+        src[0][h] = Ya + (int64_t)(ra < da ? ra : da - 1) * lda + kbeg + q * 4;
+        src[1][h] = Xb + (int64_t)(rb < db ? rb : db - 1) * ldb + kbeg + q * 4;
+    }
+    floatx4u reg[2][2];
+    auto fetch = [&](int op, int h, int slab) {
+        reg[op][h] = *reinterpret_cast<const floatx4u *>(src[op][h] + (int64_t)slab * BK);
+    };
+    auto fetch_tail = [&](int op, int h, int slab) {
+        const float *p = src[op][h] + (int64_t)slab * BK;
+        const int64_t left = kend - kbeg - (int64_t)slab * BK - q * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) reg[op][h][i] = (i < left) ? p[i] : 0.f;
+    };
+    auto fetch_any = [&](int op, int h, int slab) {
+        if ((int64_t)(slab + 1) * BK <= kend - kbeg) fetch(op, h, slab);
+        else fetch_tail(op, h, slab);
+    };
+    // Split into three bf16 planes and store.  A plane's 32 rows x 16 samples lie as the MFMA
+    // operand is read: lane l finds row l % 32, samples 8 (l / 32) .. + 7 in 16 bytes at
+    // (l / 32) kHalf + (l % 32) 16.  The 32 bytes between the halves spread the four quads of a row
+    // over different banks.
+    auto stash = [&](int stage, int op, int h) {
+        const int r = r0 + h * (T / 4);
+        uint8_t *dst = &lds[stage][op][0][r >> 5][(q >> 1) * kHalf + (r & 31) * 16 + (q & 1) * 8];
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = reg[op][h][i];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+            uintx2 w;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                typedef float floatx2 __attribute__((ext_vector_type(2)));
+                const floatx2 f = {v[2 * i], v[2 * i + 1]};
+                w[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
+                v[2 * i] = __fsub_rn(v[2 * i], __uint_as_float(w[i] << 16));
+                v[2 * i + 1] = __fsub_rn(v[2 * i + 1], __uint_as_float(w[i] & 0xffff0000u));
             }
-            r[h] = v;
+            *reinterpret_cast<uintx2 *>(dst + pl * (TILE / 32) * kFrag) = w;
         }
     };
-    auto stash = [&](float(&T)[BK][LDT], const float4(&r)[2]) {
+    const int loff = (lane >> 5) * kHalf + (lane & 31) * 16;
+    auto frag = [&](int stage, int op, int pl, int g) {
+        return *reinterpret_cast<const bf16x8 *>(&lds[stage][op][pl][g][loff]);
+    };
+    // One slab's six products, the smallest first, summed from zero on the matrix cores and added to
+    // the running sums by the vector ALU.  (Fed straight into the running sums, the small products
+    // would each be lost below their last bit: m m, always positive on the diagonal, left a bias of
+    // -2e-6 there.)  `between(b)` runs after the b-th column of accumulators.
+    auto mma = [&](int stage, auto between) {
+        bf16x8 fa[3][MT];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int f = tid + h * 256;
-            int row = f >> 2, kq = (f & 3) * 4;
-            T[kq + 0][row] = r[h].x;
-            T[kq + 1][row] = r[h].y;
-            T[kq + 2][row] = r[h].z;
-            T[kq + 3][row] = r[h].w;
+        for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+            for (int a = 0; a < MT; ++a) fa[pl][a] = frag(stage, 0, pl, wm * MT + a);
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            bf16x8 fb[3];
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) fb[pl] = frag(stage, 1, pl, wn * NT + b);
+            floatx16 t[MT];
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t[a][v] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int a = 0; a < MT; ++a)
+                    t[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa[i]][a], fb[pb[i]], t[a], 0, 0, 0);
+            between(b);
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[a][b][v] = __fadd_rn(acc[a][b][v], t[a][v]);
+            __builtin_amdgcn_sched_barrier(0);   // (one column at a time: registers)
         }
     };
 
-    // A slab that lies wholly inside the slice is fetched without a per-lane condition (rows beyond
-    // the matrix re-read its last row: their products only reach outputs that are never stored), so
-    // that the loop body is straight-line code and the loads overlap with the MFMAs; the slab at the
-    // end of the slice and unaligned inputs take the general loader.
-    auto fetch_full = [&](const float *M, int rows, int64_t ld, int tile, int64_t k0, float4(&r)[2]) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int f = tid + h * 256;
-            int row = tile * BM + (f >> 2);
-            row = row < rows ? row : rows - 1;
-            r[h] = *reinterpret_cast<const float4 *>(M + (int64_t)row * ld + k0 + (f & 3) * 4);
-        }
-    };
-    const float(*Bt)[LDT] = on_diag ? As : Bs;
-    const int kl = lane >> 5, il = lane & 31;
-    auto mma_slab = [&]() {
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float a0 = As[kk + kl][wm * 64 + il];
-            float a1 = As[kk + kl][wm * 64 + 32 + il];
-            float b0 = Bt[kk + kl][wn * 64 + il];
-            float b1 = Bt[kk + kl][wn * 64 + 32 + il];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-    };
-
-    if (kbeg < kend) {
-        fetch(Ya, da, lda, ti, kbeg, ra);
-        if (!on_diag) fetch(Xb, db, ldb, tj, kbeg, rb);
+    if (nslab > 0) {
+        for (int h = 0; h < 2; ++h) { fetch_any(0, h, 0); fetch_any(1, h, 0); }
+        for (int h = 0; h < 2; ++h) { stash(0, 0, h); stash(0, 1, h); }
+        if (nslab > 1)
+            for (int h = 0; h < 2; ++h) { fetch_any(0, h, 1); fetch_any(1, h, 1); }
     }
-    int64_t k0 = kbeg;
-    if (vec_ok) {
-        // slabs whose successor is a full slab
-        for (; k0 + 2 * BK <= kend; k0 += BK) {
-            stash(As, ra);
-            if (!on_diag) stash(Bs, rb);
-            __syncthreads();
-            fetch_full(Ya, da, lda, ti, k0 + BK, ra);
-            if (!on_diag) fetch_full(Xb, db, ldb, tj, k0 + BK, rb);
-            mma_slab();
-            __syncthreads();
-        }
-    }
-    for (; k0 < kend; k0 += BK) {
-        stash(As, ra);
-        if (!on_diag) stash(Bs, rb);
+    __syncthreads();
+    // Stage s holds slab s, the registers hold slab s + 1: it is split and stored into the other
+    // stage, and slab s + 2 requested, among slab s's matrix instructions.  One barrier per slab.
+    int s = 0;
+    for (; (int64_t)(s + 3) * BK <= kend - kbeg; ++s) {
+        const int cur = s & 1;
+        mma(cur, [&](int b) {
+#pragma unroll
+            for (int i = 4 / NT * b; i < 4 / NT * (b + 1); ++i) {
+                stash(cur ^ 1, i >> 1, i & 1);
+                fetch(i >> 1, i & 1, s + 2);
+            }
+        });
         __syncthreads();
-        if (k0 + BK < kend) {
-            fetch(Ya, da, lda, ti, k0 + BK, ra);
-            if (!on_diag) fetch(Xb, db, ldb, tj, k0 + BK, rb);
-        }
-        mma_slab();
+    }
+    for (; s < nslab; ++s) {
+        const int cur = s & 1;
+        if (s + 1 < nslab)
+            for (int h = 0; h < 2; ++h) { stash(cur ^ 1, 0, h); stash(cur ^ 1, 1, h); }
+        if (s + 2 < nslab)
+            for (int h = 0; h < 2; ++h) { fetch_any(0, h, s + 2); fetch_any(1, h, s + 2); }
+        mma(cur, [](int) {});
         __syncthreads();
     }
 
@@ -197,63 +261,76 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     // row 8 * (v / 4) + 4 * (lane / 32) + v % 4
     float *out = partial + (int64_t)slice * da * db;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NT; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                int i = ti * BM + wm * 64 + a * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                int j = tj * BM + wn * 64 + b * 32 + (lane & 31);
+                int i = ti * TILE + (wm * MT + a) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                int j = tj * TILE + (wn * NT + b) * 32 + (lane & 31);
                 if (i < da && j < db) out[(int64_t)i * db + j] = acc[a][b][v];
             }
 }
 
-// H (+)= 2 * sum_s partial[s] on the tiles on or above the block diagonal, slices added in index
-// order, and the mirror image below it.  One workgroup per 32 x 32 piece of such a tile: the sums
-// are read and written along rows, the mirrored piece goes through LDS so that it is written
-// along rows too.
+// What the split cannot represent -- an infinity, or a finite value beyond the largest bf16 -- comes
+// out as a NaN; such an entry is formed again from the inputs themselves, so that it has the value
+// plain fp32 arithmetic gives it (a NaN ends the sum: nothing changes it any more).
+__device__ float plain_dot(const float *a, const float *b, int64_t N)
+{
+    float s = 0.f;
+    for (int64_t k = 0; k < N && s == s; ++k) s = fmaf(a[k], b[k], s);
+    return s;
+}
+
+// H (+)= 2 * sum_s partial[s] on and above the diagonal, slices added in index order, and the mirror
+// image below it.  One workgroup per 32 x 32 piece: the sums are read and written along rows, the
+// mirrored piece goes through LDS so that it is written along rows too.  (Below the diagonal of a
+// diagonal piece the mirror image is taken as well: the two halves of such a tile add their cross
+// products in opposite order.)
 __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restrict__ partial, int S,
-                                                          int d, int accumulate,
-                                                          float *__restrict__ H)
+                                                          int d, int accumulate, const float *X, int64_t ldx,
+                                                          int64_t N, float *__restrict__ H)
 {
     __shared__ float Tt[32][33];
     const int pi = blockIdx.y, pj = blockIdx.x;           // 32 x 32 piece (pi, pj)
-    if (pi / (BM / 32) > pj / (BM / 32)) return;          // its 128-tile lies below the block diagonal
+    if (pi > pj) return;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const bool mirror = (pi / (BM / 32) != pj / (BM / 32));
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = pi * 32 + ty + 8 * r, j = pj * 32 + tx;
+        if (i > j || j >= d) continue;
+        const int64_t e = (int64_t)i * d + j;
         float s = 0.f;
-        if (i < d && j < d) {
-            const int64_t e = (int64_t)i * d + j;
-            for (int k = 0; k < S; ++k) s += partial[(int64_t)k * d * d + e];
-            s *= 2.f;
-            H[e] = accumulate ? H[e] + s : s;
-        }
+#pragma unroll 8
+        for (int k = 0; k < S; ++k) s += partial[(int64_t)k * d * d + e];
+        if (s != s) s = plain_dot(X + (int64_t)i * ldx, X + (int64_t)j * ldx, N);
+        s *= 2.f;
+        H[e] = accumulate ? H[e] + s : s;
         Tt[ty + 8 * r][tx] = s;
     }
-    if (!mirror) return;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = pj * 32 + ty + 8 * r, j = pi * 32 + tx;   // (i, j) of the mirrored piece
-        if (i < d && j < d) {
-            const int64_t e = (int64_t)i * d + j;
-            const float s = Tt[tx][ty + 8 * r];
-            H[e] = accumulate ? H[e] + s : s;
-        }
+        if (i <= j || i >= d) continue;
+        const int64_t e = (int64_t)i * d + j;
+        const float s = Tt[tx][ty + 8 * r];
+        H[e] = accumulate ? H[e] + s : s;
     }
 }
 
 // C[e] (+)= 2 * sum_s partial[s][e] over a dense da x db result, slices added in index order.
 __global__ __launch_bounds__(256) void nt_reduce_kernel(const float *__restrict__ partial, int S,
-                                                        int64_t n, int accumulate, float *__restrict__ C)
+                                                        int64_t n, int d_col, int accumulate, const float *Y,
+                                                        int64_t ldy, const float *X, int64_t ldx, int64_t N,
+                                                        float *__restrict__ C)
 {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     float s = 0.f;
+#pragma unroll 8
     for (int k = 0; k < S; ++k) s += partial[(int64_t)k * n + e];
+    if (s != s) s = plain_dot(Y + e / d_col * ldy, X + e % d_col * ldx, N);
     s *= 2.f;
     C[e] = accumulate ? C[e] + s : s;
 }
@@ -274,6 +351,22 @@ __global__ __launch_bounds__(1024) void dampen_kernel(float *__restrict__ H, int
     for (int j = threadIdx.x; j < d; j += blockDim.x) H[(int64_t)j * d + j] += lam;
 }
 
+// The slices of the contraction into partial (S x da x db).
+template <bool SYM>
+int launch_nt(obc_ctx *ctx, const Plan &p, const float *Ya, int da, int64_t lda, const float *Xb, int db, int64_t ldb,
+              int64_t N, float *partial)
+{
+    const int64_t nt = tiles_of(da, p.tile);
+    const int64_t n = SYM ? nt * (nt + 1) / 2 : nt * tiles_of(db, p.tile);
+    const unsigned grid = (unsigned)((n * p.S + 7) / 8 * 8);
+    if (p.tile == 256)
+        nt_partial_kernel<SYM, 4, 2, 2, 4><<<grid, 512, 0, ctx->stream>>>(Ya, da, lda, Xb, db, ldb, N, p.S, p.kchunk, partial);
+    else
+        nt_partial_kernel<SYM, 2, 2, 2, 2><<<grid, 256, 0, ctx->stream>>>(Ya, da, lda, Xb, db, ldb, N, p.S, p.kchunk, partial);
+    OBC_LAUNCH_CHECK(ctx, "nt_partial_kernel");
+    return OBC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -281,10 +374,8 @@ extern "C" {
 int obc_hessian_workspace_bytes(int d, int64_t N, size_t *bytes)
 {
     if (!bytes || d <= 0 || N < 0) return OBC_ERR_BAD_ARG;
-    int S;
-    int64_t kc;
-    split_plan(d, N > 0 ? N : 1, &S, &kc);
-    *bytes = obc_align_up((size_t)S * d * d * sizeof(float), 256);
+    const Plan p = hessian_plan(d, N > 0 ? N : 1);
+    *bytes = obc_align_up((size_t)p.S * d * d * sizeof(float), 256);
     return OBC_OK;
 }
 
@@ -300,18 +391,12 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_hessian: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
-    int S;
-    int64_t kchunk;
-    split_plan(d, N, &S, &kchunk);
-    const int nt = tiles_of(d);
-    const int ntri = nt * (nt + 1) / 2;
-    const int vec_ok = (ldx % 4 == 0) && (((uintptr_t)X & 15) == 0);
+    const Plan p = hessian_plan(d, N);
     float *partial = (float *)ws;
-
-    nt_partial_kernel<true><<<dim3(ntri, S), 256, 0, ctx->stream>>>(X, d, ldx, X, d, ldx, N, kchunk, partial, vec_ok);
-    OBC_LAUNCH_CHECK(ctx, "nt_partial_kernel");
+    int rc = launch_nt<true>(ctx, p, X, d, ldx, X, d, ldx, N, partial);
+    if (rc != OBC_OK) return rc;
     const unsigned np32 = (unsigned)((d + 31) / 32);
-    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, S, d, accumulate, H);
+    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, p.S, d, accumulate, X, ldx, N, H);
     OBC_LAUNCH_CHECK(ctx, "syrk_reduce_kernel");
     if (damp_rel >= 0.f) {
         dampen_kernel<<<1, 1024, 0, ctx->stream>>>(H, d, damp_rel);
@@ -320,18 +405,11 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     return OBC_OK;
 }
 
-static void cross_plan(int d_row, int d_col, int64_t N, int *S, int64_t *kchunk)
-{
-    split_plan_tiles((int64_t)tiles_of(d_row) * tiles_of(d_col), N, S, kchunk);
-}
-
 int obc_cross_workspace_bytes(int d_row, int d_col, int64_t N, size_t *bytes)
 {
     if (!bytes || d_row <= 0 || d_col <= 0 || N < 0) return OBC_ERR_BAD_ARG;
-    int S;
-    int64_t kc;
-    cross_plan(d_row, d_col, N > 0 ? N : 1, &S, &kc);
-    *bytes = obc_align_up((size_t)S * d_row * d_col * sizeof(float), 256);
+    const Plan p = cross_plan(d_row, d_col, N > 0 ? N : 1);
+    *bytes = obc_align_up((size_t)p.S * d_row * d_col * sizeof(float), 256);
     return OBC_OK;
 }
 
@@ -350,16 +428,12 @@ int obc_cross(obc_ctx *ctx, const float *X, const float *Y, int d_col, int d_row
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_cross: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
-    int S;
-    int64_t kchunk;
-    cross_plan(d_row, d_col, N, &S, &kchunk);
-    const int ntiles = tiles_of(d_row) * tiles_of(d_col);
-    const int vec_ok = (ldx % 4 == 0) && (ldy % 4 == 0) && (((uintptr_t)X & 15) == 0) && (((uintptr_t)Y & 15) == 0);
+    const Plan p = cross_plan(d_row, d_col, N);
     float *partial = (float *)ws;
-    nt_partial_kernel<false><<<dim3(ntiles, S), 256, 0, ctx->stream>>>(Y, d_row, ldy, X, d_col, ldx, N, kchunk, partial, vec_ok);
-    OBC_LAUNCH_CHECK(ctx, "nt_partial_kernel");
+    int rc = launch_nt<false>(ctx, p, Y, d_row, ldy, X, d_col, ldx, N, partial);
+    if (rc != OBC_OK) return rc;
     const int64_t n = (int64_t)d_row * d_col;
-    nt_reduce_kernel<<<(unsigned)((n + 255) / 256), 256, 0, ctx->stream>>>(partial, S, n, accumulate, C);
+    nt_reduce_kernel<<<(unsigned)((n + 255) / 256), 256, 0, ctx->stream>>>(partial, p.S, n, d_col, accumulate, Y, ldy, X, ldx, N, C);
     OBC_LAUNCH_CHECK(ctx, "nt_reduce_kernel");
     return OBC_OK;
 }

@@ -58,6 +58,46 @@ def test_hessian_matches_oracle(obc, orc, d, N, pad):
     assert np.linalg.norm(_np(Hacc) - ref0) / np.linalg.norm(ref0) < 2e-6
 
 
+@pytest.mark.parametrize("d,N,off,pad", [(1, 1, 0, 0), (5, 15, 1, 1), (127, 16, 0, 1), (128, 17, 2, 2), (129, 33, 3, 0),
+                                         (256, 64, 0, 3), (1153, 1000, 1, 0), (2049, 49, 0, 1)])
+def test_second_moments_at_tile_edges(obc, d, N, off, pad):
+    """Edges of the 128 / 256 tiles and of the 16-sample slabs, rows at any float's address; values
+    over many binades, so that every one of the split's terms counts.  Both sums of N products
+    (obc_cross shares the kernel).  Bound: a product loses at most 3 * 2^-24 to the split, a sum of
+    N / 16 slabs half a unit per slab, everything relative to the sum of the magnitudes."""
+    gen = torch.Generator(device="cuda").manual_seed(d + N)
+    buf = torch.randn(d * (N + pad) + off, generator=gen, device="cuda")
+    buf *= torch.exp2(torch.randint(-12, 13, buf.shape, generator=gen, device="cuda").float())
+    X = buf[off:].view(d, N + pad)[:, :N]
+    r = min(d, 130)
+    Y = torch.randn(r, N + pad, generator=gen, device="cuda")[:, :N]
+    H, C = obc.obc_hessian(X, damp_rel=-1.0), obc.obc_cross(X, Y)
+    assert torch.equal(H, H.T)
+    eps = 3 * 2.0 ** -24 + 2.0 ** -24 * (N / 16 + 8)
+    Xd, Yd = X.cpu().double(), Y.cpu().double()
+    for got, a in ((H, Xd), (C, Yd)):
+        err = (got.cpu().double() - 2 * a @ Xd.T).abs()
+        assert bool((err <= eps * 2 * (a.abs() @ Xd.abs().T)).all()), float(err.max())
+
+
+def test_second_moments_of_values_beyond_the_split(obc):
+    """Infinities, NaN and values that round to infinity in bf16 come out as fp32 arithmetic has them."""
+    X = torch.rand(140, 40, device="cuda") + 0.5
+    X[3, 7] = float("inf")
+    X[9, 0], X[9, 5] = float("inf"), float("-inf")
+    X[70, 39] = float("nan")
+    X[135, 11] = 3.4e38
+    X[:, 11][:130] *= 1e-38
+    H, C = obc.obc_hessian(X, damp_rel=-1.0), obc.obc_cross(X, X[:20].contiguous())
+    ref = (2 * X.cpu().double() @ X.cpu().double().T)
+    ref = torch.where(ref.abs() > 3.4028234e38, ref.sign() * float("inf"), ref)
+    for got, want in ((H.cpu().double(), ref), (C.cpu().double(), ref[:20])):
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+        ok = want.isfinite()
+        assert torch.allclose(got[ok], want[ok], rtol=1e-5)
+        assert torch.equal(got[want.isinf()] > 0, want[want.isinf()] > 0)
+
+
 def test_hessian_on_correlated_relu_inputs(obc, orc):
     W, X = _layer("conv64x576", n_samples=10000)
     H = obc.obc_hessian(X)
