@@ -8,6 +8,11 @@
 
 namespace obc_blocked {
 
+// Panels for live sizes above this share a flush with others: they find the vectors of the outer
+// block's earlier panels in memory.
+constexpr int kOldVectorsAbove = 2304;
+constexpr int kBeyond = 0x40000000;   // a byte offset beyond any row's matrix: the load returns 0
+
 // Per-thread state of the panel: everything indexed by the owned element e (compact index
 // tid + e*T) or by the step r inside the block.  All indices are compile-time constants once the
 // step loop is unrolled (panel_steps below), so the arrays live in registers.
@@ -28,12 +33,18 @@ struct PanelShared {
     unsigned long long red_k[2][16];
     __attribute__((aligned(16))) float cvec[BMAX];
     float invd_s[BMAX];
-    int pivs[BMAX];
-    double bc_g, bc_invapp;
-    int bc_o, bc_ok;
-    float bc_loss, bc_target;   // the step's records, written out after the barrier
-    int bc_code;
-    double blk_loss;   // block pruning: loss of the block being eliminated, summed over its weights
+    __attribute__((aligned(16))) float cold[UCAP];   // coefficients of the outer block's earlier vectors ...
+    __attribute__((aligned(16))) float invd_old[UCAP];                            // ... and their 1 / a_r
+    int live[16 * 16];   // survivors per (owned element, wave)
+    // the step's scalars: the update of the weights, 1 / a_pp, the index's original position, whether
+    // the pivot is usable
+    double g, invapp;
+    int o, ok;
+    // What the steps' records are made of when the panel ends (original index, weight, 1 / a_pp): made
+    // and stored in every step they would lengthen the chain that the whole workgroup waits for, and
+    // the owner's wait for its fetched row would be one for its stores too.
+    int rec_o[BMAX];
+    double rec_w[BMAX], rec_invapp[BMAX];
 };
 
 // order-preserving map of a float onto unsigned integers
@@ -129,12 +140,104 @@ __device__ __forceinline__ unsigned row16_umin_all(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)row16_umin(v), 15);
 }
 
+// acc += sum_i c_i u[i], i < N: coefficient i is in lane L + i of every 16-lane row of c.  The
+// coefficient is taken from its lane by the multiply-add itself (DPP row_newbcast): no lane read, no
+// scalar register (64 of those next to the kernel's other scalars spilled a hundred times a step).
+// A DPP operand must not have been written by the vector ALU within two cycles; the compiler does
+// not look into the block, so it waits itself.
+template <int L, int N>
+__device__ __forceinline__ void fma_bcast(float &acc, float c, const float (&u)[N])
+{
+#define OBC_FB(op, lane) "v_fmac_f32_dpp %0, %1, %" #op " row_newbcast:%" #lane " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (N == 8)
+        asm("s_nop 1\n\t" OBC_FB(2, 10) OBC_FB(3, 11) OBC_FB(4, 12) OBC_FB(5, 13) OBC_FB(6, 14) OBC_FB(7, 15)
+                OBC_FB(8, 16) OBC_FB(9, 17)
+            : "+v"(acc)
+            : "v"(c), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "v"(u[4]), "v"(u[5]), "v"(u[6]), "v"(u[7]), "n"(L),
+              "n"(L + 1), "n"(L + 2), "n"(L + 3), "n"(L + 4), "n"(L + 5), "n"(L + 6), "n"(L + 7));
+    else if constexpr (N == 4)
+        asm("s_nop 1\n\t" OBC_FB(2, 6) OBC_FB(3, 7) OBC_FB(4, 8) OBC_FB(5, 9)
+            : "+v"(acc)
+            : "v"(c), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+    else if constexpr (N == 2)
+        asm("s_nop 1\n\t" OBC_FB(2, 4) OBC_FB(3, 5)
+            : "+v"(acc)
+            : "v"(c), "v"(u[0]), "v"(u[1]), "n"(L), "n"(L + 1));
+    else
+        asm("s_nop 1\n\t" OBC_FB(2, 3) : "+v"(acc) : "v"(c), "v"(u[0]), "n"(L));
+#undef OBC_FB
+}
+
+// acc += sum_{R0 <= r < S} c_r u(r): coefficient r in lane r % 16 of c[r / 16]
+template <int S, int R0, int NC, typename U>
+__device__ __forceinline__ void fma_bcast_all(float &acc, const float (&c)[NC], U u)
+{
+    if constexpr (R0 < S) {
+        constexpr int N = S - R0 >= 8 ? 8 : S - R0 >= 4 ? 4 : S - R0 >= 2 ? 2 : 1;
+        float v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = u(R0 + i);
+        fma_bcast<R0 % 16, N>(acc, c[R0 / 16], v);
+        fma_bcast_all<S, R0 + N>(acc, c, u);
+    }
+}
+
 struct PanelRow {
     const float *Acur;
     float *gU;
-    int ld, swz, d, m, done, total, ndead, row;
+    int ld, swz, d, m, done, total, ndead, row, old, ldu;
     double qd, qo, qmax, iqd;
+    float nm_inv;   // 1 / M
+    // the row's matrix for raw buffer loads: resource, bytes between an element of a row and the next,
+    // row_base of the thread's first index
+    __amdgpu_buffer_rsrc_t rsrc;
+    int es, rb_tid;
+    int nw;         // waves launched (one owned element per thread: as many as the live size needs)
 };
+
+// byte offset of element (i, 0) of the row's matrix
+__device__ __forceinline__ int row_base(int i, const PanelRow &pr)
+{
+    return pr.swz ? ((i >> 2) * pr.ld * 4 + (i & 3)) * 4 : i * pr.ld * 4;
+}
+
+// o / M for 0 <= o < 2^20: (o + 1/2) / M is at least 1 / (2 M) away from every integer, many times
+// the rounding of this product (an integer division would be some twenty instructions of the step's
+// dependent chain)
+__device__ __forceinline__ int nm_block(int o, float nm_inv) { return (int)(((float)o + 0.5f) * nm_inv); }
+
+// The score of owned element e as an order-preserving integer (all ones when it is no candidate) and,
+// except in block pruning, its error (target - w).
+template <int MODE, int EPT, int BR>
+__device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const PanelRow &pr, const PanelRegs<EPT, BR> &st,
+                                                  const uint8_t *blk, int e, double &er)
+{
+    float sc;
+    er = 0.0;
+    if constexpr (MODE == MODE_BLOCK) {
+        sc = (float)quad_block_score(st.w[e], st.dg[e], st.ob[e]);
+        if (!st.alive[e]) return ~0u;
+    } else {
+        if (!st.alive[e]) return ~0u;
+        if (st.og[e] < 0) {
+            sc = -__builtin_inff();   // dead indices go first, before any outlier
+        } else {
+            if (a.nm_m > 0 && blk[nm_block(st.og[e], pr.nm_inv)] >= a.nm_m - a.nm_n) return ~0u;
+            double tq = 0.0;
+            if (MODE == MODE_QUANT) {
+                double c = rint((st.w[e] - pr.qo) * pr.iqd);
+                c = fmin(fmax(c, 0.0), pr.qmax);
+                tq = pr.qo + pr.qd * c;
+            }
+            er = tq - st.w[e];
+            sc = (float)(er * er) * __builtin_amdgcn_rcpf((float)st.dg[e]);
+            // outlier heuristic: a weight whose error exceeds half a grid step sorts before every
+            // non-outlier
+            if (MODE == MODE_QUANT && a.outliers && fabs(er) > 0.5 * pr.qd) sc = outlier_first(sc);
+        }
+    }
+    return sc == sc ? score_bits(sc) : ~0u;   // a NaN score is no candidate
+}
 
 // One greedy step, S-th of the block.  Returns 0 to continue, 1 when the row has no step left,
 // 2 on a numeric failure.  Every thread of the workgroup returns the same value.
@@ -144,7 +247,6 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 {
     // u_r[j] for r >= BR is kept at ul[(r - BR) * (T * EPT) + j]; only the owner of j touches it
     constexpr int CAP = T * EPT;
-    constexpr int NW = T / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (pr.done + S >= pr.total) return 1;
 
@@ -155,44 +257,18 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     // the lowest index is taken in two unsigned 32-bit minima: the least score, then the least
     // index among the candidates that have it.  All ones = no candidate.
     unsigned cs = ~0u, ci = ~0u;
-    if constexpr (MODE == MODE_BLOCK) {
-        // a block is chosen every fourth step; the three steps after it take its other weights
-        if constexpr (S % 4 == 0) {
+    double cer = 0.0;   // error of the thread's best candidate
+    if constexpr (MODE != MODE_BLOCK || S % 4 == 0) {   // (a block is chosen every fourth step)
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const float sc = (float)quad_block_score(st.w[e], st.dg[e], st.ob[e]);
-                if (st.alive[e] && sc == sc) {
-                    const unsigned b = score_bits(sc);
-                    if (b < cs) { cs = b; ci = (unsigned)((tid & ~3) + e * T); }   // (indices ascend with e)
-                }
+        for (int e = 0; e < EPT; ++e) {
+            double er;
+            const unsigned b = candidate_key<MODE>(a, pr, st, blk, e, er);
+            if (b < cs) {   // (indices ascend with e)
+                cs = b;
+                ci = (unsigned)((MODE == MODE_BLOCK ? tid & ~3 : tid) + e * T);
+                cer = er;
             }
         }
-    } else {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        if (!st.alive[e]) continue;
-        float sc;
-        if (st.og[e] < 0) {
-            sc = -__builtin_inff();   // dead indices go first, before any outlier
-        } else {
-            if (a.nm_m > 0 && blk[st.og[e] / a.nm_m] >= a.nm_m - a.nm_n) continue;
-            double tq = 0.0;
-            if (MODE == MODE_QUANT) {
-                double c = rint((st.w[e] - pr.qo) * pr.iqd);
-                c = fmin(fmax(c, 0.0), pr.qmax);
-                tq = pr.qo + pr.qd * c;
-            }
-            double er = tq - st.w[e];
-            sc = (float)(er * er) * __builtin_amdgcn_rcpf((float)st.dg[e]);
-            // outlier heuristic: a weight whose error exceeds half a grid step sorts before every
-            // non-outlier
-            if (MODE == MODE_QUANT && a.outliers && fabs(er) > 0.5 * pr.qd) sc = outlier_first(sc);
-        }
-        if (sc == sc) {   // a NaN score is no candidate
-            const unsigned b = score_bits(sc);
-            if (b < cs) { cs = b; ci = (unsigned)(tid + e * T); }   // (indices ascend with e)
-        }
-    }
     }
     int p;
     if constexpr (MODE == MODE_BLOCK && S % 4 != 0) {
@@ -205,7 +281,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
             if (lane == 0) sh.red_k[S & 1][wave] = ((unsigned long long)ws << 32) | wi;
         }
         __syncthreads();
-        const unsigned long long wk = (lane & 15) < NW ? sh.red_k[S & 1][lane & 15] : ~0ull;
+        const unsigned long long wk = (lane & 15) < pr.nw ? sh.red_k[S & 1][lane & 15] : ~0ull;
         const unsigned gs = row16_umin_all((unsigned)(wk >> 32));
         if (gs == ~0u) return 2;
         p = (int)row16_umin_all((unsigned)(wk >> 32) == gs ? (unsigned)wk : ~0u);
@@ -215,121 +291,120 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     // ---- (2) fetch the owned part of row p of A0.  Only the lower triangle of A0 is kept up to
     // date (the matrix is symmetric): entry (p, j) is read as (max(p, j), min(p, j)), i.e. along
     // row p up to the diagonal and down column p below it.
+    // Byte offsets: element (i, j), j <= i, lies at row_base(i) + j es, so both parts are affine in the
+    // owned element; raw buffer loads take 32-bit offsets.
+    const int ep = p / T, pt = p - ep * T;   // p's owner: element ep of thread pt
     float col[EPT];
+    {
+        const int along = tid * pr.es + row_base(p, pr), down = pr.rb_tid + p * pr.es;
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        int j = tid + e * T;
-        const int hi = (j <= p) ? p : j, lo = (j <= p) ? j : p;
-        // (a row's matrix has at most 4608^2 entries: 32-bit index arithmetic)
-        const unsigned off = pr.swz ? (((unsigned)(hi >> 2) * (unsigned)pr.ld + (unsigned)lo) << 2) + (unsigned)(hi & 3)
-                                    : (unsigned)hi * (unsigned)pr.ld + (unsigned)lo;
-        col[e] = (j < pr.m) ? __builtin_nontemporal_load(&pr.Acur[off]) : 0.f;
-    }
-    // the owner of p publishes the pivot's data, the step's scalars and the coefficients
-    // u_r[p] / a_r of the earlier steps of this block
-    const bool owner = (tid == p % T);
-    if (owner) {
-        const int ep = p / T;
-        double wp = 0.0, ap = 1.0, target = 0.0, code = 0.0;
-        int op = 0;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e)
-            if (e == ep) { wp = st.w[e]; ap = st.dg[e]; op = st.og[e]; }
-        if (op < 0) target = wp;
-        else if (MODE == MODE_QUANT) {
-            code = rint((wp - pr.qo) * pr.iqd);   // same expression as in the selection
-            code = fmin(fmax(code, 0.0), pr.qmax);
-            target = pr.qo + pr.qd * code;
+        for (int e = 0; e < EPT; ++e) {
+            int off = tid <= p - e * T ? along + e * T * pr.es : down + e * T * pr.ld * 4;
+            if (EPT > 1 && tid >= pr.m - e * T) off = kBeyond;   // indices beyond m: no memory access, 0
+            col[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr.rsrc, off, 0, 2));
         }
-        const bool ok = (ap > 0.0) && (ap < __builtin_inf());
-        const double invapp = 1.0 / ap;           // the step's only division
-        const double er = target - wp;
-        sh.bc_loss = (float)(0.5 * er * er * invapp);
-        sh.bc_target = (float)target;
-        sh.bc_code = (int)code;
-        sh.bc_g = (wp - target) * invapp;
-        sh.bc_invapp = invapp;
-        sh.bc_o = op;
-        sh.bc_ok = ok ? 1 : 0;
-        sh.pivs[S] = p;
-        sh.invd_s[S] = (float)invapp;
-        // coefficients of the vectors kept in registers: only the owner has their entry p.  One
-        // branch per owned element, then four coefficients per LDS read / write.
-        constexpr int SREG = S < BR ? S : BR;
+    }
+    // the owner of p publishes the pivot's data and its entries of the earlier vectors of this block
+    if (tid == pt) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             if (e != ep) continue;
+            // entries p of the vectors kept in registers, four per LDS write
+            constexpr int SREG = S < BR ? S : BR;
 #pragma unroll
             for (int r4 = 0; r4 < SREG; r4 += 4) {
-                const float4 iv = *reinterpret_cast<const float4 *>(&sh.invd_s[r4]);
                 float4 v;
-                v.x = __fmul_rn(st.u[r4][e], iv.x);
-                v.y = (r4 + 1 < SREG) ? __fmul_rn(st.u[r4 + 1 < BR ? r4 + 1 : 0][e], iv.y) : 0.f;
-                v.z = (r4 + 2 < SREG) ? __fmul_rn(st.u[r4 + 2 < BR ? r4 + 2 : 0][e], iv.z) : 0.f;
-                v.w = (r4 + 3 < SREG) ? __fmul_rn(st.u[r4 + 3 < BR ? r4 + 3 : 0][e], iv.w) : 0.f;
+                v.x = st.u[r4][e];
+                v.y = (r4 + 1 < SREG) ? st.u[r4 + 1 < BR ? r4 + 1 : 0][e] : 0.f;
+                v.z = (r4 + 2 < SREG) ? st.u[r4 + 2 < BR ? r4 + 2 : 0][e] : 0.f;
+                v.w = (r4 + 3 < SREG) ? st.u[r4 + 3 < BR ? r4 + 3 : 0][e] : 0.f;
                 *reinterpret_cast<float4 *>(&sh.cvec[r4]) = v;
             }
+            const double ap = st.dg[e];
+            // 1 / ap: the hardware's estimate and two Newton steps (a division's scaling and fix-up
+            // steps would only lengthen the chain that everybody waits for)
+            double invapp = __builtin_amdgcn_rcp(ap);
+            invapp = fma(fma(-ap, invapp, 1.0), invapp, invapp);
+            invapp = fma(fma(-ap, invapp, 1.0), invapp, invapp);
+            const double wp = st.w[e];
+            sh.g = (MODE == MODE_BLOCK ? wp : -cer) * invapp;
+            sh.invapp = invapp;
+            sh.o = st.og[e];
+            sh.ok = (ap > 0.0) && (ap < __builtin_inf()) ? 1 : 0;
+            sh.invd_s[S] = (float)invapp;
+            sh.rec_o[S] = st.og[e];
+            sh.rec_w[S] = wp;
+            sh.rec_invapp[S] = invapp;
+            if (a.nm_m > 0 && st.og[e] >= 0) blk[nm_block(st.og[e], pr.nm_inv)] += 1;
         }
-        if (a.nm_m > 0 && op >= 0) blk[op / a.nm_m] += 1;
     }
-    // coefficients of the vectors kept in LDS: one lane each
+    // coefficients of the earlier panels' vectors, which are in memory: one lane each
+    if constexpr (CAP > kOldVectorsAbove) {
+        if (tid < pr.old) sh.cold[tid] = pr.gU[(size_t)tid * pr.ldu + p];
+    }
+    // entries p of the vectors kept in LDS: one lane each
     if constexpr (S > BR) {
         const int r = BR + tid;
-        if (r < S) sh.cvec[r] = __fmul_rn(ul[(r - BR) * CAP + p], sh.invd_s[r]);
+        if (r < S) sh.cvec[r] = ul[(r - BR) * CAP + p];
     }
     __syncthreads();
-    if (!sh.bc_ok) return 2;
-    // the step's records are written here, while everybody waits for the fetched row anyway
-    if (owner) {
-        const int op = sh.bc_o;
-        if (MODE == MODE_BLOCK) {
-            // the block's loss is the sum of its four single losses (owners of consecutive steps
-            // are separated by the step's barriers)
-            const double acc = (S % 4 == 0) ? (double)sh.bc_loss : sh.blk_loss + (double)sh.bc_loss;
-            sh.blk_loss = acc;
-            a.W_out[(size_t)pr.row * pr.d + op] = 0.f;
-            if (S % 4 == 3) {
-                const int t = (pr.done + S) / 4;
-                a.order[(size_t)pr.row * a.out_ld + t] = op / 4;
-                a.loss[(size_t)pr.row * a.out_ld + t] = (float)acc;
+    const double g = sh.g, invapp = sh.invapp;
+    const bool isdead = sh.o < 0;
+    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ... (what
+    // lies beyond S is never used)
+    constexpr int NC = S > 0 ? (S + 15) / 16 : 1;
+    float cv[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) cv[k] = S > 0 ? __fmul_rn(sh.cvec[16 * k + (lane & 15)], sh.invd_s[16 * k + (lane & 15)]) : 0.f;
+
+    if (!sh.ok) return 2;   // (after the reads above are on their way)
+
+    // ---- (3) bring the fetched row up to date, keep it, update w and the diagonal.
+    // The correction is summed on its own and subtracted once: its roundings are then relative to
+    // the (small) correction instead of to the matrix entry, and the sum does not wait for the
+    // fetched row.
+    if constexpr (CAP > kOldVectorsAbove) {
+        // The earlier panels' vectors, panel by panel, exactly as their flush would have applied them:
+        // entry (i, j), i >= j, gets sum_k (-u_k[i] / a_k) u_k[j], summed from zero in k order (which is
+        // how the fp32 matrix instruction sums) and added once.  (Indices beyond m read what lies behind
+        // the vector -- a row's UCAP vectors are longer than any index -- and only reach values that are
+        // never used.)
+#pragma unroll 1
+        for (int r0 = 0; r0 < pr.old; r0 += BR + BL) {
+            float sum[EPT];
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) sum[e] = 0.f;
+#pragma unroll 1
+            for (int r = r0; r < r0 + BR + BL; r += 2) {
+                const float2 o2 = *reinterpret_cast<const float2 *>(&sh.cold[r]);
+                const float2 i2 = *reinterpret_cast<const float2 *>(&sh.invd_old[r]);
+                const float *u = pr.gU + (size_t)r * pr.ldu + tid;
+                float v[2][EPT];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) v[q][e] = u[(size_t)q * pr.ldu + e * T];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float up = q ? o2.y : o2.x, ni = -(q ? i2.y : i2.x), fp = __fmul_rn(up, ni);
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) {
+                        const bool along = tid <= p - e * T;     // (p, j) with j <= p, else (j, p)
+                        sum[e] = fmaf(along ? fp : up, along ? v[q][e] : __fmul_rn(v[q][e], ni), sum[e]);
+                    }
+                }
             }
-        } else if (op >= 0) {
-            const int t = pr.done + S - pr.ndead;
-            a.order[(size_t)pr.row * a.out_ld + t] = op;
-            a.loss[(size_t)pr.row * a.out_ld + t] = sh.bc_loss;
-            a.W_out[(size_t)pr.row * pr.d + op] = sh.bc_target;
-            if (MODE == MODE_QUANT) a.codes[(size_t)pr.row * pr.d + op] = sh.bc_code;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) col[e] = __fadd_rn(col[e], sum[e]);
         }
     }
-    const double g = sh.bc_g, invapp = sh.bc_invapp;
-    const bool isdead = sh.bc_o < 0;
-    // coefficients of this step, once, into scalar registers (they are the same for every lane;
-    // as vector registers they would take up to B of them next to the block vectors)
-    float cv[S > 0 ? S : 1];
-    auto uni = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
-#pragma unroll
-    for (int r4 = 0; r4 < S; r4 += 4) {
-        float4 c4 = *reinterpret_cast<const float4 *>(&sh.cvec[r4]);
-        cv[r4] = uni(c4.x);
-        if (r4 + 1 < S) cv[r4 + 1] = uni(c4.y);
-        if (r4 + 2 < S) cv[r4 + 2] = uni(c4.z);
-        if (r4 + 3 < S) cv[r4 + 3] = uni(c4.w);
-    }
-
-    // ---- (3) bring the fetched row up to date, keep it, update w and the diagonal
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         int j = tid + e * T;
-        // the correction is summed on its own and subtracted once: its roundings are then relative
-        // to the (small) correction instead of to the matrix entry, and the sum does not wait for
-        // the fetched row
         float corr = 0.f;
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-            float ur = (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * CAP + j];
-            corr = fmaf(cv[r], ur, corr);
-        }
+        fma_bcast_all<S, 0>(corr, cv, [&](int r) { return (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * CAP + j]; });
         float c = __fsub_rn(col[e], corr);
+        if constexpr (EPT >= 3) __builtin_amdgcn_sched_barrier(0);   // one element at a time: registers
         if constexpr (S < BR) st.u[S < BR ? S : 0][e] = c;
         else ul[(S - BR) * CAP + j] = c;
         if constexpr (MODE == MODE_BLOCK) {
@@ -345,8 +420,8 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
                 st.alive[e] = false;
             } else {
                 double cd = (double)c;
-                st.w[e] -= cd * g;
-                st.dg[e] -= cd * cd * invapp;
+                st.w[e] = fma(-cd, g, st.w[e]);
+                st.dg[e] = fma(-(cd * cd), invapp, st.dg[e]);
             }
         }
     }
@@ -383,9 +458,11 @@ __device__ __forceinline__ int panel_steps(const PanelArgs &a, const PanelRow &p
 }
 
 template <int MODE, int T, int EPT, int BR, int BL>
-__global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 ? (EPT == 1 ? 4 : 3) : T / 256)))
+void panel_kernel(PanelArgs a)
 {
     constexpr int B = BR + BL;
+    static_assert(BR % 4 == 0, "the owner publishes four entries at a time");
     __shared__ PanelShared sh;
     // dynamic LDS: BL vectors of T * EPT floats, then the N:M counters (d / M bytes) when nm_m > 0
     extern __shared__ __align__(16) uint8_t dyn_lds[];
@@ -408,7 +485,13 @@ __global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
     pr.Acur = a.A_cur + (size_t)row * a.a_row_stride;
     pr.ld = a.ld;
     pr.swz = a.swz;
-    pr.gU = a.ws.U + (size_t)row * BMAX * a.ws.ldu;
+    pr.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)pr.Acur, 0, (int)(((size_t)d * d + 3) / 4 * 16), 0x00020000u);
+    pr.es = a.swz ? 16 : 4;
+    pr.rb_tid = row_base(tid, pr);
+    pr.nw = blockDim.x >> 6;
+    pr.gU = a.ws.U + (size_t)row * UCAP * a.ws.ldu;
+    pr.ldu = a.ws.ldu;
+    pr.old = a.old;
     double *gw = a.ws.w + (size_t)row * d;
     double *gd = a.ws.diag + (size_t)row * d;
     int *go = a.ws.orig + (size_t)row * d;
@@ -417,11 +500,12 @@ __global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         int j = tid + e * T;
-        st.alive[e] = j < m;
+        st.og[e] = j < m ? go[j] : kGone;
+        st.alive[e] = st.og[e] != kGone;
         st.w[e] = st.alive[e] ? gw[j] : 0.0;
         st.dg[e] = st.alive[e] ? gd[j] : 1.0;
-        st.og[e] = st.alive[e] ? go[j] : 0;
     }
+    for (int r = tid; r < a.old; r += blockDim.x) sh.invd_old[r] = a.ws.invd[(size_t)row * UCAP + r];
     if constexpr (MODE == MODE_BLOCK) {
         // the element's row of its 4 x 4 diagonal block, from the lower triangle of the matrix
 #pragma unroll
@@ -435,13 +519,36 @@ __global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
                 st.ob[e][k] = (j < m) ? pr.Acur[off] : 0.f;
             }
         }
+        if constexpr (T * EPT > kOldVectorsAbove) {
+            // ... and the outer block's earlier eliminations, as their flush would have applied them
+            __syncthreads();
+#pragma unroll 1
+            for (int r0 = 0; r0 < a.old; r0 += B) {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) {
+                    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+                    const int q = tid & 3;
+#pragma unroll 2
+                    for (int r = r0; r < r0 + B; ++r) {
+                        const float u = pr.gU[(size_t)r * pr.ldu + tid + e * T], f = __fmul_rn(u, -sh.invd_old[r]);
+                        sum[0] = fmaf(f, quad_bcast<0>(u), sum[0]);      // (j, j0): j is the larger index
+                        sum[1] = fmaf(q >= 1 ? f : quad_bcast<1>(f), q >= 1 ? quad_bcast<1>(u) : u, sum[1]);
+                        sum[2] = fmaf(q >= 2 ? f : quad_bcast<2>(f), q >= 2 ? quad_bcast<2>(u) : u, sum[2]);
+                        sum[3] = fmaf(q >= 3 ? f : quad_bcast<3>(f), q >= 3 ? quad_bcast<3>(u) : u, sum[3]);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) st.ob[e][k] = __fadd_rn(st.ob[e][k], sum[k]);
+                }
+            }
+        }
         st.p0 = 0;
     }
     const int nmb = a.nm_m > 0 ? d / a.nm_m : 0;
-    for (int b = tid; b < nmb; b += T) blk[b] = a.ws.blk[(size_t)row * d + b];
+    for (int b = tid; b < nmb; b += blockDim.x) blk[b] = a.ws.blk[(size_t)row * d + b];
     pr.qd = 1.0;
     pr.qo = 0.0;
     pr.qmax = (double)a.maxq;
+    pr.nm_inv = a.nm_m > 0 ? 1.0f / (float)a.nm_m : 0.f;
     if (MODE == MODE_QUANT) { pr.qd = (double)a.delta[row]; pr.qo = (double)a.offset[row]; }
     pr.iqd = 1.0 / pr.qd;
     __syncthreads();
@@ -450,37 +557,114 @@ __global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
     const int nbv = panel_steps<MODE, T, EPT, BR, BL, 0>(a, pr, st, sh, blk, ul, &failed);
     __syncthreads();
 
-    // ---- block epilogue: drop this block's pivots from the compact index space
-    for (int r = tid; r < nbv; r += T) {
-        a.ws.invd[(size_t)row * BMAX + r] = sh.invd_s[r];
-        a.ws.piv[(size_t)row * BMAX + r] = sh.pivs[r];
+    // ---- block epilogue.  Before the outer block's last panel the state stays in the present index
+    // space; the last one drops the eliminated indices from it.
+    for (int r = tid; r < nbv; r += blockDim.x) a.ws.invd[(size_t)row * UCAP + a.old + r] = sh.invd_s[r];
+    float *Wo = a.W_out + (size_t)row * d;
+    // the steps' records
+    if (tid < nbv) {
+        auto step_loss = [&](int r, double target) {
+            const double er = target - sh.rec_w[r];
+            return (float)(0.5 * er * er * sh.rec_invapp[r]);
+        };
+        const int op = sh.rec_o[tid];
+        if (MODE == MODE_BLOCK) {
+            Wo[op] = 0.f;
+            if (tid % 4 == 3) {
+                // the block's loss is the sum of its four single losses
+                double acc = (double)step_loss(tid - 3, 0.0);
+                for (int q = 2; q >= 0; --q) acc += (double)step_loss(tid - q, 0.0);
+                const size_t t = (size_t)row * a.out_ld + (pr.done + tid) / 4;
+                a.order[t] = op / 4;
+                a.loss[t] = (float)acc;
+            }
+        } else if (op >= 0) {
+            double code = 0.0, target = 0.0;
+            if (MODE == MODE_QUANT) {
+                code = rint((sh.rec_w[tid] - pr.qo) * pr.iqd);   // same expression as in the selection
+                code = fmin(fmax(code, 0.0), pr.qmax);
+                target = pr.qo + pr.qd * code;
+            }
+            const size_t t = (size_t)row * a.out_ld + (pr.done + tid - pr.ndead);
+            a.order[t] = op;
+            a.loss[t] = step_loss(tid, target);
+            Wo[op] = (float)target;
+            if (MODE == MODE_QUANT) a.codes[(size_t)row * d + op] = (int)code;
+        }
+    }
+    int jn[EPT];           // new index, or -1
+    int live = 0;          // survivors at lower indices of the workgroup so far
+    if (a.last) {
+        constexpr int NW = T / 64;
+        const int lane = tid & 63, wave = tid >> 6;
+        static_assert(EPT * NW <= 16 * 16, "survivor counts");
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const unsigned long long bal = __ballot(st.alive[e]);
+            jn[e] = __popcll(bal & ((1ull << lane) - 1ull));
+            if (lane == 0) sh.live[e * NW + wave] = __popcll(bal);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            int here = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int n = w < pr.nw ? sh.live[e * NW + w] : 0;
+                if (w < wave) here += n;
+                if (w == wave) jn[e] += live + here;
+                if (w >= wave) here += n;
+            }
+            live += here;
+            if (!st.alive[e]) jn[e] = -1;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) jn[e] = tid + e * T < m ? tid + e * T : -1;
     }
     int *gmap = a.ws.map + (size_t)row * d;
-    float *Wo = a.W_out + (size_t)row * d;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-        int j = tid + e * T;
-        if (j < m && st.alive[e]) {
-            int below = 0;
-            for (int r = 0; r < nbv; ++r) below += (sh.pivs[r] < j) ? 1 : 0;
-            int jn = j - below;
-            gw[jn] = st.w[e];
-            gd[jn] = st.dg[e];
-            go[jn] = st.og[e];
-            gmap[jn] = j;
-            if (st.og[e] >= 0) Wo[st.og[e]] = (float)st.w[e];
-            // this block's vectors u_r, already in the new compact order, for the flush
+        const int j = tid + e * T;
+        if (jn[e] >= 0) {
+            gw[jn[e]] = st.w[e];
+            gd[jn[e]] = st.dg[e];
+            go[jn[e]] = st.alive[e] ? st.og[e] : kGone;
+            gmap[jn[e]] = j;
+            if (st.alive[e] && st.og[e] >= 0) Wo[st.og[e]] = (float)st.w[e];
+            // this panel's vectors u_r, in the new index order
 #pragma unroll
             for (int r = 0; r < B; ++r)
                 if (r < nbv)
-                    pr.gU[(size_t)r * a.ws.ldu + jn] = (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * (T * EPT) + j];
+                    pr.gU[(size_t)(a.old + r) * a.ws.ldu + jn[e]] =
+                        (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * (T * EPT) + j];
         }
     }
-    for (int b = tid; b < nmb; b += T) a.ws.blk[(size_t)row * d + b] = blk[b];
+    if constexpr (T * EPT > kOldVectorsAbove) {
+        // the earlier panels' vectors move to the new order in place: a group of them is read
+        // whole before any of it is written
+        if (a.last) {
+#pragma unroll 1
+            for (int r = 0; r < a.old; r += 2) {
+                float v[2][EPT];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) v[q][e] = pr.gU[(size_t)(r + q) * pr.ldu + tid + e * T];
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e)
+                        if (jn[e] >= 0) pr.gU[(size_t)(r + q) * pr.ldu + jn[e]] = v[q][e];
+            }
+        }
+    }
+    for (int b = tid; b < nmb; b += blockDim.x) a.ws.blk[(size_t)row * d + b] = blk[b];
     if (tid == 0) {
-        a.ws.m[row] = m - nbv;
+        if (a.last) a.ws.m[row] = live;
         a.ws.done[row] = pr.done + nbv;
-        a.ws.nb[row] = nbv;
+        a.ws.nb[row] = a.old + nbv;
         if (failed) {
             a.ws.total[row] = pr.done + nbv;   // the row stops here
             obc_latch(a.status, OBC_ERR_NUMERIC);
@@ -488,6 +672,8 @@ __global__ __launch_bounds__(T) void panel_kernel(PanelArgs a)
     }
 }
 
+
+static_assert(sizeof(PanelShared) <= 160 * 1024 - kPanelDynLds, "a CU's LDS");
 
 // A kernel's dynamic LDS limit is a per-device attribute: `done` remembers, one bit per device, where
 // it has been raised for `fn`.  Safe from several host threads (raising it twice is harmless).
@@ -497,17 +683,19 @@ inline int panel_raise_lds_limit(const void *fn, std::atomic<unsigned long long>
     if (hipGetDevice(&dev) != hipSuccess) return -1;
     const unsigned long long bit = 1ull << (dev & 63);
     if (done.load(std::memory_order_acquire) & bit) return 0;
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - 2048)) != hipSuccess)
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelDynLds) != hipSuccess)
         return -1;
     done.fetch_or(bit, std::memory_order_release);
     return 0;
 }
 
+// With one owned element per thread a launch has as many waves as the largest live size needs: a
+// step is bound by instruction issue, and a wave without live elements issues as many as the others.
 #define OBC_DEFINE_PANEL(T, EPT, BR, BL)                                                            \
     int launch_panel_##T##_##EPT##_##BR##_##BL(int mode, int R, size_t lds_nm, hipStream_t st,      \
                                                const PanelArgs &a)                                  \
     {                                                                                               \
-        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                     \
+        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                         \
         auto kp = panel_kernel<MODE_PRUNE, T, EPT, BR, BL>;                                         \
         auto kq = panel_kernel<MODE_QUANT, T, EPT, BR, BL>;                                         \
         static std::atomic<unsigned long long> raised_p{0}, raised_q{0};                            \
@@ -515,8 +703,8 @@ inline int panel_raise_lds_limit(const void *fn, std::atomic<unsigned long long>
             if (mode == MODE_PRUNE && panel_raise_lds_limit((const void *)kp, raised_p) != 0) return -1; \
             if (mode != MODE_PRUNE && panel_raise_lds_limit((const void *)kq, raised_q) != 0) return -1; \
         }                                                                                           \
-        if (mode == MODE_PRUNE) hipLaunchKernelGGL(kp, dim3(R), dim3(T), lds, st, a);               \
-        else hipLaunchKernelGGL(kq, dim3(R), dim3(T), lds, st, a);                                  \
+        if (mode == MODE_PRUNE) hipLaunchKernelGGL(kp, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);               \
+        else hipLaunchKernelGGL(kq, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);                                  \
         return 0;                                                                                   \
     }
 
@@ -525,11 +713,11 @@ inline int panel_raise_lds_limit(const void *fn, std::atomic<unsigned long long>
     int launch_panel_block_##T##_##EPT##_##BR##_##BL(int, int R, size_t lds_nm, hipStream_t st,     \
                                                      const PanelArgs &a)                            \
     {                                                                                               \
-        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                     \
+        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                         \
         auto kb = panel_kernel<MODE_BLOCK, T, EPT, BR, BL>;                                         \
         static std::atomic<unsigned long long> raised{0};                                           \
         if (lds > 48 * 1024 && panel_raise_lds_limit((const void *)kb, raised) != 0) return -1;     \
-        hipLaunchKernelGGL(kb, dim3(R), dim3(T), lds, st, a);                                       \
+        hipLaunchKernelGGL(kb, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);                                       \
         return 0;                                                                                   \
     }
 

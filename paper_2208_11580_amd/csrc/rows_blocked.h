@@ -11,7 +11,10 @@ using namespace obc_rows;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int BMAX = 64;       // largest block; leading dimension of the per-row U / pivot arrays
+constexpr int BMAX = 64;       // most steps of one panel, and rank of a bulk elimination of pruned indices
+constexpr int UCAP = 2 * BMAX; // vectors per row in U: an outer block's, or a bulk elimination's in and out
+constexpr int kGone = (int)0x80000000;   // `orig` of an index eliminated since the last compaction
+constexpr int kPanelDynLds = 160 * 1024 - 6144;   // what a panel's static LDS leaves of a CU's
 constexpr int FT = 128;        // flush tile edge
 constexpr int FLD = FT + 4;    // padded LDS row of the flush operand tiles
 
@@ -27,22 +30,22 @@ __host__ __device__ inline size_t quad_index(int i, int j, int ld)
 
 struct BlockedWs {
     float *Abuf[2];     // R x d x d each
-    float *U;           // R x BMAX x ldu
+    float *U;           // R x UCAP x ldu
     int ldu;            // leading dimension of U: d rounded up to a multiple of 4 (16-byte rows)
-    float *invd;        // R x BMAX
-    int *piv;           // R x BMAX  (compact index of each pivot of the current block)
+    float *invd;        // R x UCAP   1 / a_r of U's vectors
     int *map;           // R x d     (new compact index -> old compact index)
     double *w;          // R x d     (compact)
     double *diag;       // R x d
-    int *orig;          // R x d     compact -> original index; ~index for an already-pruned weight
+    int *orig;          // R x d     compact -> original index; ~index for an already-pruned weight; kGone
     int *m;             // R   live size
     int *done;          // R   steps done (including up-front eliminations)
     int *total;         // R   steps to do
     int *ndead;         // R   up-front eliminations
-    int *nb;            // R   steps done in the last panel
+    int *nb;            // R   steps done since the last flush
     uint8_t *blk;       // R x d  N:M counters (d / M used)
     // bulk elimination of already-pruned indices, BMAX at a time (rows_blocked.hip)
-    float *G;           // R x BMAX x ldu  rows of the matrix at the block's pivots
+    // (the rows of the matrix at the block's pivots are parked in vectors BMAX .. of U, their
+    // positions in the block's slots of invd until the vectors are formed)
     double *Mb;         // R x BMAX x BMAX the pivots' principal submatrix, then its Cholesky factor
     double *Tb;         // R x BMAX x BMAX inverse of that factor
     int *scal;          // [0] smallest number of up-front eliminations over the rows, [1] the most eliminations any row does
@@ -54,6 +57,9 @@ struct PanelArgs {
     size_t a_row_stride;     // elements between two rows' matrices (0: all rows share H^-1)
     int ld;                  // leading dimension of A_cur
     int swz;                 // 0: A_cur is plain row-major (the shared H^-1); 1: row-quad layout
+    int old;                 // vectors of this outer block already in U (every row still running has all of them)
+    int threads;             // threads of the launch (variants with one owned index per thread)
+    int last;                // the outer block's last panel: a flush follows
     int d;                   // original width (stride of the per-row state arrays)
     int nm_n, nm_m;
     const float *delta, *offset;

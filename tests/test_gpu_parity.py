@@ -223,6 +223,14 @@ def test_prune_rows_streamed_sizes(obc, orc, strategy, d, R, k):
     _check_prune(obc, orc, W, Hinv, k, (0, 0), strategy, want_trace=(d <= 320))
 
 
+@pytest.mark.parametrize("d,k", [(2305, 90), (2344, 100), (3073, 100), (3200, 130), (4097, 60), (4608, 130)])
+def test_panels_that_share_a_flush(obc, orc, d, k):
+    """Widths above 2304: several panels per flush, the group cut short where the live size changes the
+    variant, the last step inside a group."""
+    W, X = _layer("conv64x576", d_col=d, d_row=2, n_samples=2 * d)
+    _check_prune(obc, orc, W, _hinv(obc, X), k, (0, 0), 2, rows=[1])
+
+
 @pytest.mark.parametrize("strategy", [1, 2])
 @pytest.mark.parametrize("nm", [(2, 4), (4, 8)])
 def test_prune_rows_n_m(obc, orc, strategy, nm):
