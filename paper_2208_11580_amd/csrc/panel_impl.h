@@ -469,23 +469,39 @@ void panel_kernel(PanelArgs a)
     float *ul = reinterpret_cast<float *>(dyn_lds);
     uint8_t *blk = dyn_lds + (size_t)BL * T * EPT * sizeof(float);
 
+    // Rows of at most BMAX weights are through after one panel: it takes its state from the caller's
+    // arrays and leaves nothing for a next one (one launch instead of a set-up and a panel, and no
+    // workspace).  One wave per row.
+    constexpr bool CAN_DIRECT = EPT == 1 && BL == 0 && T == 256;
+    const bool direct = CAN_DIRECT && a.direct;
+
     const int row = blockIdx.x, tid = threadIdx.x;
     PanelRow pr;
     pr.row = row;
     pr.d = a.d;
-    pr.m = a.ws.m[row];
-    pr.done = a.ws.done[row];
-    pr.total = a.ws.total[row];
-    pr.ndead = a.ws.ndead[row];
-    if (pr.done >= pr.total) {
-        if (tid == 0) a.ws.nb[row] = 0;
-        return;
+    bool live0 = true;          // direct: the caller's mask
+    if (direct) {
+        live0 = tid < a.d && (MODE == MODE_BLOCK || !a.live_in || a.live_in[(size_t)row * a.d + tid] != 0);
+        pr.m = a.d;
+        pr.done = 0;
+        pr.ndead = a.d - __popcll(__ballot(live0));
+        pr.total = panel_total(MODE, a.d, a.d - pr.ndead, a.k_steps, a.stop_counts, row);
+    } else {
+        pr.m = a.ws.m[row];
+        pr.done = a.ws.done[row];
+        pr.total = a.ws.total[row];
+        pr.ndead = a.ws.ndead[row];
+        if (pr.done >= pr.total) {
+            if (tid == 0) a.ws.nb[row] = 0;
+            return;
+        }
     }
     const int d = a.d, m = pr.m;
     pr.Acur = a.A_cur + (size_t)row * a.a_row_stride;
     pr.ld = a.ld;
     pr.swz = a.swz;
-    pr.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)pr.Acur, 0, (int)(((size_t)d * d + 3) / 4 * 16), 0x00020000u);
+    pr.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)pr.Acur, 0, (int)(a.swz ? ((size_t)d * d + 3) / 4 * 16 : (size_t)d * d * 4),
+                                                0x00020000u);
     pr.es = a.swz ? 16 : 4;
     pr.rb_tid = row_base(tid, pr);
     pr.nw = blockDim.x >> 6;
@@ -500,10 +516,17 @@ void panel_kernel(PanelArgs a)
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         int j = tid + e * T;
-        st.og[e] = j < m ? go[j] : kGone;
-        st.alive[e] = st.og[e] != kGone;
-        st.w[e] = st.alive[e] ? gw[j] : 0.0;
-        st.dg[e] = st.alive[e] ? gd[j] : 1.0;
+        if (direct) {
+            st.og[e] = j < m ? (live0 ? j : ~j) : kGone;
+            st.alive[e] = j < m;
+            st.w[e] = live0 ? (double)a.W[(size_t)row * d + j] : 0.0;
+            st.dg[e] = j < m ? (double)pr.Acur[(size_t)j * d + j] : 1.0;
+        } else {
+            st.og[e] = j < m ? go[j] : kGone;
+            st.alive[e] = st.og[e] != kGone;
+            st.w[e] = st.alive[e] ? gw[j] : 0.0;
+            st.dg[e] = st.alive[e] ? gd[j] : 1.0;
+        }
     }
     for (int r = tid; r < a.old; r += blockDim.x) sh.invd_old[r] = a.ws.invd[(size_t)row * UCAP + r];
     if constexpr (MODE == MODE_BLOCK) {
@@ -544,7 +567,7 @@ void panel_kernel(PanelArgs a)
         st.p0 = 0;
     }
     const int nmb = a.nm_m > 0 ? d / a.nm_m : 0;
-    for (int b = tid; b < nmb; b += blockDim.x) blk[b] = a.ws.blk[(size_t)row * d + b];
+    for (int b = tid; b < nmb; b += blockDim.x) blk[b] = direct ? 0 : a.ws.blk[(size_t)row * d + b];
     pr.qd = 1.0;
     pr.qo = 0.0;
     pr.qmax = (double)a.maxq;
@@ -559,8 +582,13 @@ void panel_kernel(PanelArgs a)
 
     // ---- block epilogue.  Before the outer block's last panel the state stays in the present index
     // space; the last one drops the eliminated indices from it.
-    for (int r = tid; r < nbv; r += blockDim.x) a.ws.invd[(size_t)row * UCAP + a.old + r] = sh.invd_s[r];
+    if (!direct)
+        for (int r = tid; r < nbv; r += blockDim.x) a.ws.invd[(size_t)row * UCAP + a.old + r] = sh.invd_s[r];
     float *Wo = a.W_out + (size_t)row * d;
+    if (direct && tid < d) {
+        if (st.alive[0] || !live0) Wo[tid] = live0 ? (float)st.w[0] : 0.f;
+        if (MODE == MODE_QUANT && (st.alive[0] || !live0)) a.codes[(size_t)row * d + tid] = -1;
+    }
     // the steps' records
     if (tid < nbv) {
         auto step_loss = [&](int r, double target) {
@@ -591,6 +619,10 @@ void panel_kernel(PanelArgs a)
             Wo[op] = (float)target;
             if (MODE == MODE_QUANT) a.codes[(size_t)row * d + op] = (int)code;
         }
+    }
+    if (direct) {
+        if (failed && tid == 0) obc_latch(a.status, OBC_ERR_NUMERIC);
+        return;
     }
     int jn[EPT];           // new index, or -1
     int live = 0;          // survivors at lower indices of the workgroup so far

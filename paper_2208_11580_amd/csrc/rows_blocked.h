@@ -52,6 +52,20 @@ struct BlockedWs {
 };
 
 
+// Eliminations of a row with `survivors` live weights: the already-pruned indices and the greedy
+// steps (block pruning: 4 per block step).
+__device__ inline int panel_total(int mode, int d, int survivors, int k_steps, const int32_t *stop_counts, int row)
+{
+    int steps = (mode == MODE_QUANT) ? survivors : (k_steps < survivors ? k_steps : survivors);
+    if (stop_counts) {
+        int sc = stop_counts[row];
+        sc = sc < 0 ? 0 : sc;
+        if (mode == MODE_BLOCK) sc = sc > d / 4 ? d : sc * 4;
+        steps = sc < steps ? sc : steps;
+    }
+    return d - survivors + steps;
+}
+
 struct PanelArgs {
     const float *A_cur;      // matrix buffer the rows are read from
     size_t a_row_stride;     // elements between two rows' matrices (0: all rows share H^-1)
@@ -73,6 +87,12 @@ struct PanelArgs {
     float *trace;
     int out_ld;
     int *status;
+    // rows that fit one panel (d <= BMAX) start from the caller's arrays and need no workspace
+    int direct;
+    const float *W;
+    const uint8_t *live_in;
+    const int32_t *stop_counts;
+    int k_steps;
 };
 
 // launchers defined in panel_<T>x<EPT>x<BR>x<BL>.hip (pruning and OBQ) and

@@ -104,17 +104,7 @@ __global__ __launch_bounds__(256) void blocked_init_kernel(InitArgs a)
     atomicAdd(&cnt, dead_local);
     __syncthreads();
     if (tid == 0) {
-        // steps on the survivors, in single eliminations (block pruning: 4 per block step); the
-        // eliminations of the already-pruned indices come on top
-        const int survivors = d - cnt;
-        int steps = (a.mode == MODE_QUANT) ? survivors : (a.k_steps < survivors ? a.k_steps : survivors);
-        if (a.stop_counts) {
-            int sc = a.stop_counts[row];
-            sc = sc < 0 ? 0 : sc;
-            if (a.mode == MODE_BLOCK) sc = sc > d / 4 ? d : sc * 4;
-            steps = sc < steps ? sc : steps;
-        }
-        const int total = cnt + steps;
+        const int total = panel_total(a.mode, d, d - cnt, a.k_steps, a.stop_counts, row);
         a.ws.m[row] = d;
         a.ws.done[row] = 0;
         a.ws.total[row] = total;
@@ -617,6 +607,9 @@ const Variant *pick_variant(int m, int R)
 
 namespace obc_rows {
 
+// up to this width a call with a mask waits for nothing (it can be captured)
+constexpr int kNoWaitMaxD = 192;
+
 int blocked_max_d() { return kVariants[kNumVariants - 1].cap; }
 
 size_t blocked_workspace_bytes(int R, int d) { return carve(nullptr, nullptr, R, d); }
@@ -626,22 +619,27 @@ int potrf64_batched_launch(obc_ctx *ctx, double *M, double *T, int R);   // inve
 int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, int R, int d, int k_steps,
                    int nm_n, int nm_m, const int32_t *stop_counts, const float *delta,
                    const float *offset, int maxq, const uint8_t *live, int flags, int32_t *order, float *loss,
-                   int32_t *codes, float *W_out, float *trace, int out_ld, void *ws, size_t ws_bytes)
+                   int32_t *codes, float *W_out, float *trace, int out_ld, void *ws, size_t ws_bytes, int need_ws)
 {
     if (d > blocked_max_d())
         return obc_fail(ctx, OBC_ERR_BAD_SHAPE, "row solver (blocked): d = %d exceeds the supported %d", d, blocked_max_d());
     BlockedWs bw;
+    // One panel is the whole of such a row: no set-up launch, and no workspace (which only a caller who
+    // names the strategy is still held to).
+    const bool direct = d <= BMAX;
     size_t need = carve(&bw, ws, R, d);
-    if (!ws || ws_bytes < need)
+    if ((!ws || ws_bytes < need) && !(direct && need_ws == 0))
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "row solver: workspace of %zu bytes needed, %zu given", need, ws_bytes);
     hipStream_t st = ctx->stream;
     ctx->chain_fresh = false;   // the set-up kernels below are not timed: the first timed launch records its own start
 
-    InitArgs ia;
-    ia.W = W; ia.Hinv = Hinv; ia.live_in = live; ia.stop_counts = stop_counts; ia.d = d;
-    ia.k_steps = k_steps; ia.mode = mode; ia.ws = bw; ia.codes = codes; ia.W_out = W_out;
-    blocked_init_kernel<<<R, 256, 0, st>>>(ia);
-    OBC_LAUNCH_CHECK(ctx, "blocked_init_kernel");
+    if (!direct) {
+        InitArgs ia;
+        ia.W = W; ia.Hinv = Hinv; ia.live_in = live; ia.stop_counts = stop_counts; ia.d = d;
+        ia.k_steps = k_steps; ia.mode = mode; ia.ws = bw; ia.codes = codes; ia.W_out = W_out;
+        blocked_init_kernel<<<R, 256, 0, st>>>(ia);
+        OBC_LAUNCH_CHECK(ctx, "blocked_init_kernel");
+    }
     if (trace && k_steps > 0) {
         size_t n = (size_t)R * out_ld * d;
         unsigned blocks = (unsigned)((n / 4 + 256 * 8 - 1) / (256 * 8));
@@ -655,11 +653,23 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     pa.d = d; pa.nm_n = nm_n; pa.nm_m = nm_m; pa.delta = delta; pa.offset = offset; pa.maxq = maxq;
     pa.ws = bw; pa.order = order; pa.loss = loss; pa.codes = codes; pa.W_out = W_out; pa.trace = trace;
     pa.out_ld = out_ld; pa.status = ctx->d_status; pa.outliers = (flags & OBC_QUANT_OUTLIERS) ? 1 : 0;
+    pa.direct = direct ? 1 : 0; pa.W = W; pa.live_in = live; pa.stop_counts = stop_counts; pa.k_steps = k_steps;
+    const size_t lds_nm = nm_m > 0 ? obc_align_up((size_t)(d / nm_m), 16) : 0;
+    if (direct) {
+        pa.A_cur = Hinv; pa.a_row_stride = 0; pa.ld = d; pa.swz = 0; pa.old = 0; pa.last = 1; pa.threads = BMAX;
+        const Variant &v = kVariants[0];
+        {
+            obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * d * 4.0 * d, (double)R * d * (double)d * d);
+            if ((mode == MODE_BLOCK ? v.launch_block : v.launch)(mode, R, lds_nm, st, pa) != 0)
+                return obc_fail(ctx, OBC_ERR_HIP, "panel kernel: cannot set its dynamic LDS size");
+        }
+        OBC_LAUNCH_CHECK(ctx, "panel_kernel");
+        return OBC_OK;
+    }
     FlushArgs fa;
     fa.d = d; fa.R = R; fa.ws = bw;
 
     int host_total = (mode == MODE_QUANT || live) ? d : k_steps;   // upper bound over the rows
-    const size_t lds_nm = nm_m > 0 ? obc_align_up((size_t)(d / nm_m), 16) : 0;
     const size_t mat_stride = obc_align_up((size_t)d * d, 4);   // floats between two rows' matrices
     int host_done = 0;
     int cur = -1;            // -1: the shared H^-1; otherwise index into Abuf
@@ -714,7 +724,8 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
 
     // ---- already-pruned indices, BMAX at a time, as long as every row has that many left.  The
     // smallest count over the rows is read back once (the only wait in this call).
-    if (live && mode != MODE_BLOCK) {
+    // (Not at widths that a call without any wait has always served: there the panels do it all.)
+    if (live && mode != MODE_BLOCK && d > kNoWaitMaxD) {
         int scal[2] = {0, 0};
         min_ndead_kernel<<<1, 256, 0, st>>>(bw.ndead, bw.total, R, bw.scal);
         OBC_LAUNCH_CHECK(ctx, "min_ndead_kernel");

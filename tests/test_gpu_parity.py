@@ -223,6 +223,42 @@ def test_prune_rows_streamed_sizes(obc, orc, strategy, d, R, k):
     _check_prune(obc, orc, W, Hinv, k, (0, 0), strategy, want_trace=(d <= 320))
 
 
+@pytest.mark.parametrize("d", [1, 4, 63, 64, 65, 128, 129, 190, 193])
+def test_small_widths_take_the_blocked_solver(obc, orc, d):
+    """Rows of one panel (up to 64 columns, no workspace), and widths that also fit the rank-1 solver's
+    LDS: pruning with its trace, stop counts, OBQ dense and on survivors, blocks of four."""
+    W, X = _layer("conv64x576", d_col=d, d_row=5, n_samples=max(200, 4 * d))
+    Hinv = _hinv(obc, X)
+    full, _ = _check_prune(obc, orc, W, Hinv, d, (0, 0), 0, want_trace=True)
+    stop = torch.tensor([0, 1, d // 2, d, d + 3], dtype=torch.int32, device="cuda")
+    cut = obc.obc_prune_rows(W, Hinv, stop_counts=stop, want_trace=True)
+    for i, n in enumerate(stop.clamp(max=d).tolist()):
+        assert torch.equal(cut["order"][i, :n], full["order"][i, :n]) and bool((cut["order"][i, n:] == -1).all())
+        assert torch.equal(cut["trace"][i, :n], full["trace"][i, :n]) and not bool(cut["trace"][i, n:].any())
+        assert torch.equal(cut["W"][i], full["trace"][i, n - 1] if n else W[i])
+    _check_quant(obc, orc, W, Hinv, 4, 0)
+    live = (torch.arange(5 * d, device="cuda").view(5, d) % 3 != 0).to(torch.uint8)
+    live[4] = 0
+    q, _ = _check_quant(obc, orc, W, Hinv, 3, 0, live=live, rows=range(4) if d > 1 else [])
+    assert bool((q["codes"][live == 0] == -1).all()) and not bool(q["W"][live == 0].any())
+    if d % 4 == 0:
+        _check_blocks(obc, orc, W, Hinv, 4, d // 4, 0, want_trace=True)
+
+
+def test_small_widths_without_a_workspace(obc, orc):
+    """A call that brings less than the blocked solver's workspace is served by the rank-1 solver."""
+    import paper_2208_11580_amd as pkg
+    W, X = _layer("conv64x576", d_col=150, d_row=4, n_samples=800)
+    Hinv = _hinv(obc, X)
+    ctx = pkg.Context()
+    ctx.rows_workspace_bytes = lambda *a: 256
+    a, b = ctx.obc_prune_rows(W, Hinv), obc.obc_prune_rows(W, Hinv, strategy=pkg.STRATEGY_RANK1)
+    assert all(torch.equal(a[k], b[k]) for k in ("order", "loss", "W"))
+    with pytest.raises(pkg.ObcError):
+        ctx.obc_prune_rows(W, Hinv, strategy=pkg.STRATEGY_BLOCKED)
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,k", [(2305, 90), (2344, 100), (3073, 100), (3200, 130), (4097, 60), (4608, 130)])
 def test_panels_that_share_a_flush(obc, orc, d, k):
     """Widths above 2304: several panels per flush, the group cut short where the live size changes the
