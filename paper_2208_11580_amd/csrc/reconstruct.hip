@@ -9,16 +9,21 @@
 //
 // Everything in fp64 (the principal submatrix of H^-1 on half of the indices is as ill-conditioned as
 // H^-1 itself, and its fp32 entries are exact inputs), all rows of the layer side by side:
-//   1. per row: the list P of its pruned indices, G = (H^-1)[P, P] (lower triangle) and w_P in the
-//      workspace (recon_prepare_kernel)
-//   2. G = L L^T for all rows at once, block column by block column of 64, three launches per step
-//      (host loop up to the caller's bound on the pruned count; a row that is through skips): the
-//      diagonal blocks on one wavefront each (factor + inverse of the factor), the panels below them
-//      and the trailing updates as 64 x 64 tile products on the fp64 matrix core -- the device code
-//      obc_invert uses, here with one grid dimension running over the rows
-//   3. per row: L y = w_P and L^T z = y block by block with the inverted diagonal factors, then
-//      w_hat = w - H^-1[:, P] z along rows of H^-1 (it is symmetric), pruned entries set to 0
-//      (recon_solve_kernel)
+//   1. per row: the list P of its pruned indices and w_P (recon_list_kernel), then G = (H^-1)[P, P]
+//      (lower triangle, recon_gather_kernel: a workgroup per 64 of its rows)
+//   2. G = L L^T for all rows at once, block column by block column of 64, two launches each (host loop
+//      up to the caller's bound on the pruned count; a row that is through skips).  Left-looking: a
+//      64 x 64 tile is formed once, from the block columns before it (64-deep slabs, the next one
+//      requested while this one is multiplied, two workgroups per CU), so G is read and written once instead of once per block column.  The
+//      diagonal tiles' workgroups factor them and invert the factor; the tiles below are multiplied by
+//      that inverse before they are stored.
+//   3. per row: L y = w_P and L^T z = y block by block with the inverted diagonal factors
+//      (recon_solve_kernel), then w_hat = w - H^-1[:, P] z, pruned entries set to 0: for all rows in one
+//      product Z H^-1 on the fp64 matrix core, z spread over the row's d columns (where the pruned share
+//      is small, along rows of H^-1 by the row's own workgroup instead)
+// Bound by the fp64 matrix core (c^3 / 3 flop per row): 768 x 3072 at 50 %, 0.93 TFLOP, in 28.5 ms for
+// the factorisation (33 TFLOP/s of the 47 this unit sustains; 43.5 with a right-looking update of all
+// of G per block column) and 33.8 ms in all (61.3); 256 x 4608 34 ms (72.5).
 #include "dense64.h"
 
 namespace {
@@ -32,14 +37,16 @@ struct ReconArgs {
     float *W_out;
     double *G;       // R x ldg x ldg
     double *Linv;    // R x (ldg / 64) x 64 x 64
-    double *vec;     // R x ldg   (w_P, then y, then z)
+    double *vec;     // R x ldg   (w_P, then z)
+    double *Z;       // R x d     z spread over the columns (in G's place, which is through by then), or null
+    int R;
     int *idx;        // R x ldg
     int *cnt;        // R     pruned weights of the row (0: nothing to do)
     int *status;
 };
 
-// ---- 1. pruned indices (ascending), their count, G and the right-hand side
-__global__ __launch_bounds__(256) void recon_prepare_kernel(ReconArgs a)
+// ---- 1. pruned indices (ascending), their count and the right-hand side
+__global__ __launch_bounds__(256) void recon_list_kernel(ReconArgs a)
 {
     __shared__ int wcnt[4];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -48,7 +55,6 @@ __global__ __launch_bounds__(256) void recon_prepare_kernel(ReconArgs a)
     float *wo = a.W_out + (size_t)row * d;
     const uint8_t *mk_row = a.mask + (size_t)row * d;
     int *idx = a.idx + (size_t)row * ldg;
-    double *G = a.G + (size_t)row * ldg * ldg;
     double *v = a.vec + (size_t)row * ldg;
 
     int c = 0;                               // (every thread ends with the same count)
@@ -80,117 +86,241 @@ __global__ __launch_bounds__(256) void recon_prepare_kernel(ReconArgs a)
     if (c == 0) return;
     __threadfence_block();
     __syncthreads();
-    for (int i = 0; i < c; ++i) {
-        const float *hrow = a.Hinv + (size_t)idx[i] * d;
-        for (int j = tid; j <= i; j += 256) G[(size_t)i * ldg + j] = (double)hrow[idx[j]];
-    }
     for (int i = tid; i < c; i += 256) v[i] = (double)w[idx[i]];
 }
 
-// ---- 2. one block column (first index k0) of the factorisation, for every row that still has it
-__global__ __launch_bounds__(64) void recon_potrf_kernel(ReconArgs a, int k0)
+// The tile of a workgroup: `nt` tiles per row, the rows dealt to the 8 XCDs, so that all tiles of a row
+// -- they read the same block rows of L -- run on one XCD, one after the other.
+__device__ __forceinline__ void recon_tile(int nt, int &row, int &tile)
 {
-    __shared__ double lds[POTRF_LDS];
-    const int row = blockIdx.x;
-    const int c = a.cnt[row];
-    if (k0 >= c) return;
-    const int bs = (c - k0 < NB) ? c - k0 : NB;
-    double *G = a.G + (size_t)row * a.ldg * a.ldg;
-    double *Lk = a.Linv + ((size_t)row * (a.ldg / NB) + k0 / NB) * NB * NB;
-    potrf_wave(G + (size_t)k0 * a.ldg + k0, a.ldg, bs, Lk, a.status, OBC_ERR_NUMERIC, lds);
+    const int w = blockIdx.x / 8;
+    row = w / nt * 8 + blockIdx.x % 8;
+    tile = w % nt;
 }
 
-// panel (trailing == 0): L21 = A21 Linv_kk^T, one workgroup per 64 rows of it (each overwrites exactly
-// what it has read); trailing (== 1): A22 -= L21 L21^T, one workgroup per lower 64 x 64 tile
-// (blockIdx.x enumerates the tiles of the largest row; smaller rows skip what they do not have)
-__global__ __launch_bounds__(256) void recon_update_kernel(ReconArgs a, int k0, int trailing)
+// 64 rows of G: each wave takes a row at a time, its lanes the row's entries
+__global__ __launch_bounds__(256) void recon_gather_kernel(ReconArgs a, int nt)
 {
-    __shared__ double lds[GEMM_LDS];
-    const int row = blockIdx.y;
-    const int c = a.cnt[row];
-    const int m = c - k0 - NB;               // rows below a full diagonal block
-    if (m <= 0) return;
-    const int ldg = a.ldg;
+    int row, tile;
+    recon_tile(nt, row, tile);
+    if (row >= a.R) return;
+    const int c = a.cnt[row], ldg = a.ldg;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int *idx = a.idx + (size_t)row * ldg;
     double *G = a.G + (size_t)row * ldg * ldg;
-    const double *Lk = a.Linv + ((size_t)row * (ldg / NB) + k0 / NB) * NB * NB;
-    double *A21 = G + (size_t)(k0 + NB) * ldg + k0;
-    if (!trailing) {
-        const int ti = blockIdx.x;
-        if (ti * NB >= m) return;
-        gemm64_tile(mk(m, NB, NB, 1.0, A21, ldg, 1, Lk, 1, NB, 0.0, A21, ldg, 0, 0, nullptr), ti, 0, lds);
-    } else {
-        // tile number -> (ti, tj), tj <= ti
-        int t = blockIdx.x, ti = 0;
-        while (t > ti) { t -= ti + 1; ++ti; }
-        const int tj = t;
-        if (ti * NB >= m) return;
-        double *A22 = G + (size_t)(k0 + NB) * ldg + (k0 + NB);
-        gemm64_tile(mk(m, m, NB, -1.0, A21, ldg, 1, A21, 1, ldg, 1.0, A22, ldg, 1, 0, nullptr), ti, tj, lds);
+    for (int i = tile * NB + wave; i < c && i < (tile + 1) * NB; i += 4) {
+        const float *hrow = a.Hinv + (size_t)idx[i] * a.d;
+#pragma unroll 4
+        for (int j = lane; j <= i; j += 64) G[(size_t)i * ldg + j] = (double)hrow[idx[j]];
     }
 }
 
-// ---- 3. L y = w_P, L^T z = y (v holds w_P, y and z in turn), then w_hat = w - H^-1[:, P] z
-__global__ __launch_bounds__(256) void recon_solve_kernel(ReconArgs a)
+// ---- 2. tile (i0, k0) of block column k0: C = G - sum_{k < k0} L_ik L_jk^T.  DIAG: the diagonal tile,
+// which is then factored (the inverse of its factor goes to Linv; the factor itself is not needed
+// again).  Else a tile below it: L = C Linv_kk^T.
+template <bool DIAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void recon_column_kernel(ReconArgs a, int k0, int nt)
 {
-    __shared__ double blk[NB];
+    __shared__ double lds[DIAG ? POTRF_WG_LDS : 2 * NB * PL];
+    double *As = lds, *Bs = lds + NB * PL;
+    int row, tile = 0;
+    if (DIAG) row = blockIdx.x;
+    else recon_tile(nt, row, tile);
+    if (row >= a.R) return;
+    const int c = a.cnt[row], ldg = a.ldg;
+    const int i0 = DIAG ? k0 : k0 + NB * (1 + tile);
+    if (i0 >= c) return;
+    const int Mi = (c - i0 < NB) ? c - i0 : NB, Nj = (c - k0 < NB) ? c - k0 : NB;
+    double *G = a.G + (size_t)row * ldg * ldg;
+    double *Lk = a.Linv + ((size_t)row * (ldg / NB) + k0 / NB) * NB * NB;
+    const double *Li = G + (size_t)i0 * ldg, *Lj = G + (size_t)k0 * ldg;
+
+    doublex4 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double ra[16], rb[16];
+    auto fetch = [&](int k) {
+        tile_fetch(ra, Li + k, ldg, Mi, NB);
+        if (!DIAG) tile_fetch(rb, Lj + k, ldg, Nj, NB);
+    };
+    if (k0 > 0) fetch(0);
+    for (int k = 0; k < k0; k += NB) {
+        tile_park<true>(As, ra);
+        if (!DIAG) tile_park<true>(Bs, rb);
+        __syncthreads();
+        if (k + NB < k0) fetch(k + NB);
+        tile_mma<true>(acc, As, DIAG ? As : Bs);
+        __syncthreads();
+    }
+    double *C = G + (size_t)i0 * ldg + k0;
+    doublex4 old[2][2];
+    tile_fill(old, [&](int i, int j) { return (i < Mi && j < Nj && (!DIAG || j <= i)) ? C[(size_t)i * ldg + j] : 0.0; });
+    if (DIAG) {
+        // the factorisation's LDS layout: lower triangle, identity where the block is padded; the
+        // inverse's area cleared
+        tile_each2(acc, old, [&](int i, int j, double v, double o) {
+            As[i * PL + j] = (i < Mi && j <= i) ? o - v : (i == j ? 1.0 : 0.0);
+            Bs[i * PL + j] = 0.0;
+        });
+        __syncthreads();
+        potrf_wg_core(Lk, a.status, OBC_ERR_NUMERIC, lds);
+    } else {
+        double rl[16];
+        tile_fetch(rl, Lk, NB, NB, NB);
+        tile_each2(acc, old, [&](int i, int j, double v, double o) { As[j * PL + i] = o - v; });   // a(i, k) = C[i][k]
+        tile_park<true>(Bs, rl);                                                                   // b(k, j) = Linv[j][k]
+        __syncthreads();
+        tile_mma(acc, As, Bs);
+        tile_each(acc, [&](int i, int j, double v) { if (i < Mi && j < Nj) C[(size_t)i * ldg + j] = v; });
+    }
+}
+
+// ---- 3. L y = w_P, L^T z = y; w_P, y and z in turn in LDS.  Rows of L are read by eight lanes each (64
+// bytes a lane) on the way down, along their entries on the way up.
+__global__ __launch_bounds__(512) void recon_solve_kernel(ReconArgs a)
+{
+    extern __shared__ double v[];            // ldg
+    __shared__ double blk[NB], red[8][NB];
     const int row = blockIdx.x, tid = threadIdx.x;
     const int d = a.d, ldg = a.ldg;
     const int c = a.cnt[row];
     if (c == 0) return;
-    const float *w = a.W + (size_t)row * d;
-    float *wo = a.W_out + (size_t)row * d;
-    const int *idx = a.idx + (size_t)row * ldg;
     const double *G = a.G + (size_t)row * ldg * ldg;
     const double *Li = a.Linv + (size_t)row * (ldg / NB) * NB * NB;
-    double *v = a.vec + (size_t)row * ldg;
+    double *gv = a.vec + (size_t)row * ldg;
+    for (int i = tid; i < ldg; i += 512) v[i] = i < c ? gv[i] : 0.0;
+    __syncthreads();
     const int nblk = (c + NB - 1) / NB;
+    const int part = tid & 7, slot = tid >> 3;
     for (int kb = 0; kb < nblk; ++kb) {
         const int k0 = kb * NB;
-        const int bs = (c - k0 < NB) ? c - k0 : NB;
-        const double *Lk = Li + (size_t)kb * NB * NB;
-        if (tid < bs) {
-            double acc = 0.0;
-            for (int j = 0; j <= tid; ++j) acc = fma(Lk[tid * NB + j], v[k0 + j], acc);
-            blk[tid] = acc;
-        }
+        const double *Lk = Li + (size_t)kb * NB * NB;     // (zeros above the diagonal, identity beyond the row)
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc = fma(Lk[slot * NB + part * 8 + q], v[k0 + part * 8 + q], acc);
+        acc += __shfl_xor(acc, 1, 64);
+        acc += __shfl_xor(acc, 2, 64);
+        acc += __shfl_xor(acc, 4, 64);
+        if (part == 0) blk[slot] = acc;
         __syncthreads();
-        if (tid < bs) v[k0 + tid] = blk[tid];
-        for (int i = k0 + bs + tid; i < c; i += 256) {
-            const double *gi = G + (size_t)i * ldg + k0;
-            double acc = 0.0;
-            for (int j = 0; j < bs; ++j) acc = fma(gi[j], blk[j], acc);
-            v[i] -= acc;
+        if (tid < NB) v[k0 + tid] = blk[tid];
+        double b8[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) b8[q] = blk[part * 8 + q];
+#pragma unroll 2
+        for (int i = k0 + NB + slot; i < c; i += 64) {    // (all eight lanes of a row together)
+            const double *gi = G + (size_t)i * ldg + k0 + part * 8;
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s = fma(gi[q], b8[q], s);
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
+            s += __shfl_xor(s, 4, 64);
+            if (part == 0) v[i] -= s;
         }
-        __threadfence_block();
         __syncthreads();
     }
     for (int kb = nblk - 1; kb >= 0; --kb) {
         const int k0 = kb * NB;
         const int bs = (c - k0 < NB) ? c - k0 : NB;
         const double *Lk = Li + (size_t)kb * NB * NB;
-        if (tid < bs) {
-            double acc = 0.0;
-            for (int j = tid; j < bs; ++j) acc = fma(Lk[j * NB + tid], v[k0 + j], acc);
-            blk[tid] = acc;
+        const int col = tid & 63, grp = tid >> 6;
+        double acc = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc = fma(Lk[(grp * 8 + q) * NB + col], v[k0 + grp * 8 + q], acc);
+        red[grp][col] = acc;
+        __syncthreads();
+        if (tid < NB) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s += red[q][tid];
+            blk[tid] = tid < bs ? s : 0.0;
+            v[k0 + tid] = blk[tid];
         }
         __syncthreads();
-        if (tid < bs) v[k0 + tid] = blk[tid];
-        for (int i = tid; i < k0; i += 256) {
-            double acc = 0.0;
-            for (int r = 0; r < bs; ++r) acc = fma(G[(size_t)(k0 + r) * ldg + i], blk[r], acc);
-            v[i] -= acc;
+        for (int i = tid; i < k0; i += 512) {
+            double s = 0.0;
+            if (bs == NB) {
+#pragma unroll 16
+                for (int r = 0; r < NB; ++r) s = fma(G[(size_t)(k0 + r) * ldg + i], blk[r], s);
+            } else {
+                for (int r = 0; r < bs; ++r) s = fma(G[(size_t)(k0 + r) * ldg + i], blk[r], s);
+            }
+            v[i] -= s;
         }
-        __threadfence_block();
         __syncthreads();
     }
+    if (a.Z) {
+        for (int i = tid; i < c; i += 512) gv[i] = v[i];
+        return;
+    }
     // (row idx[t] of the symmetric H^-1 is its column idx[t])
-    for (int j = tid; j < d; j += 256) {
+    const float *w = a.W + (size_t)row * d;
+    float *wo = a.W_out + (size_t)row * d;
+    const int *idx = a.idx + (size_t)row * ldg;
+    for (int j = tid; j < d; j += 512) {
         double acc = 0.0;
+#pragma unroll 8
         for (int t = 0; t < c; ++t) acc = fma((double)a.Hinv[(size_t)idx[t] * d + j], v[t], acc);
         wo[j] = (float)((double)w[j] - acc);
     }
     __syncthreads();
-    for (int t = tid; t < c; t += 256) wo[idx[t]] = 0.f;
+    for (int t = tid; t < c; t += 512) wo[idx[t]] = 0.f;
+}
+
+__global__ __launch_bounds__(256) void recon_spread_kernel(ReconArgs a)
+{
+    const int row = blockIdx.x, c = a.cnt[row];
+    double *z = a.Z + (size_t)row * a.d;
+    for (int j = threadIdx.x; j < a.d; j += 256) z[j] = 0.0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < c; t += 256) z[a.idx[(size_t)row * a.ldg + t]] = a.vec[(size_t)row * a.ldg + t];
+}
+
+// W_out = W - Z H^-1, pruned entries 0: a 64 x 64 tile per workgroup, slabs as above
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void recon_product_kernel(ReconArgs a)
+{
+    __shared__ double lds[2 * NB * PL];
+    double *As = lds, *Bs = lds + NB * PL;
+    const int i0 = blockIdx.y * NB, j0 = blockIdx.x * NB, d = a.d;
+    const int Mi = (a.R - i0 < NB) ? a.R - i0 : NB, Nj = (d - j0 < NB) ? d - j0 : NB;
+    doublex4 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double ra[16];
+    float rb[16];
+    auto fetch = [&](int k) {
+        const int kr = (d - k < NB) ? d - k : NB;
+        tile_fetch(ra, a.Z + (size_t)i0 * d + k, d, Mi, kr);          // (i, k)
+#pragma unroll
+        for (int h = 0; h < 16; ++h) {                                // (k, j)
+            const int e = threadIdx.x + h * 256;
+            rb[h] = ((e >> 6) < kr && (e & 63) < Nj) ? a.Hinv[(size_t)(k + (e >> 6)) * d + j0 + (e & 63)] : 0.f;
+        }
+    };
+    fetch(0);
+    for (int k = 0; k < d; k += NB) {
+        tile_park<true>(As, ra);
+#pragma unroll
+        for (int h = 0; h < 16; ++h) {
+            const int e = threadIdx.x + h * 256;
+            Bs[(e >> 6) * PL + (e & 63)] = (double)rb[h];
+        }
+        __syncthreads();
+        if (k + NB < d) fetch(k + NB);
+        tile_mma<true>(acc, As, Bs);
+        __syncthreads();
+    }
+    tile_each(acc, [&](int i, int j, double v) {
+        if (i >= Mi || j >= Nj) return;
+        const size_t e = (size_t)(i0 + i) * d + j0 + j;
+        const bool off = a.mask[e] != 0 && a.cnt[i0 + i] > 0;
+        a.W_out[e] = off ? 0.f : (float)((double)a.W[e] - v);
+    });
 }
 
 size_t recon_carve(ReconArgs *a, void *base, int R, int cmax)
@@ -239,17 +369,27 @@ int obc_reconstruct_rows(obc_ctx *ctx, const float *W, const float *Hinv, const 
     if (R == 0) return OBC_OK;
     a.W = W; a.Hinv = Hinv; a.mask = mask; a.d = d; a.cmax = max_pruned; a.W_out = W_out; a.status = ctx->d_status;
     hipStream_t st = ctx->stream;
-    recon_prepare_kernel<<<R, 256, 0, st>>>(a);
-    OBC_LAUNCH_CHECK(ctx, "recon_prepare_kernel");
-    for (int k0 = 0; k0 < max_pruned; k0 += NB) {
-        recon_potrf_kernel<<<R, 64, 0, st>>>(a, k0);
-        const int mt = (max_pruned - k0 - NB + NB - 1) / NB;      // 64-row tiles below the block, at most
-        if (mt > 0) {
-            recon_update_kernel<<<dim3(mt, R), 256, 0, st>>>(a, k0, 0);
-            recon_update_kernel<<<dim3(mt * (mt + 1) / 2, R), 256, 0, st>>>(a, k0, 1);
-        }
+    a.R = R;
+    // Z takes G's place; the product over all d columns pays where a row's pruned share is not small
+    a.Z = (max_pruned >= d / 8 && (size_t)d <= (size_t)a.ldg * (a.ldg + NB)) ? a.G : nullptr;
+    const unsigned rows8 = (unsigned)((R + 7) / 8 * 8);
+    const int nt = (max_pruned + NB - 1) / NB;                    // 64-row tiles of the largest row
+    recon_list_kernel<<<R, 256, 0, st>>>(a);
+    if (nt > 0) recon_gather_kernel<<<rows8 * nt, 256, 0, st>>>(a, nt);
+    OBC_LAUNCH_CHECK(ctx, "recon_gather_kernel");
+    for (int k = 0; k < nt; ++k) {
+        recon_column_kernel<true><<<R, 256, 0, st>>>(a, k * NB, 1);
+        const int below = nt - 1 - k;
+        if (below > 0) recon_column_kernel<false><<<rows8 * below, 256, 0, st>>>(a, k * NB, below);
     }
-    recon_solve_kernel<<<R, 256, 0, st>>>(a);
+    const size_t lds = (size_t)a.ldg * sizeof(double);
+    if (lds > 48 * 1024)
+        OBC_HIP(ctx, hipFuncSetAttribute((const void *)recon_solve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    recon_solve_kernel<<<R, 512, lds, st>>>(a);
+    if (a.Z) {
+        recon_spread_kernel<<<R, 256, 0, st>>>(a);
+        recon_product_kernel<<<dim3((d + NB - 1) / NB, (R + NB - 1) / NB), 256, 0, st>>>(a);
+    }
     OBC_LAUNCH_CHECK(ctx, "closed-form recovery kernels");
     return OBC_OK;
 }
