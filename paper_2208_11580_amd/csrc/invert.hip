@@ -248,11 +248,41 @@ __global__ __launch_bounds__(256) void chol_step_kernel(StepArgs s)
     tile_each(acc, [&](int i, int j, double v) { s.Gnext[i * NB + j] = v; });
 }
 
-// Y = identity (d x d)
-__global__ void eye_f64_kernel(double *__restrict__ dst, int d)
+// Set-up: A = double(H), Y = identity, by all workgroups but the first, which factors the first
+// diagonal block meanwhile (T and G = T^T T of it, as chol_step_kernel leaves them for the others).
+// A matrix that is one block only (`out`, one workgroup) is through here: its inverse is G.
+// (Conversion, identity, factorisation on one wavefront and its product were launches of their own:
+// 70 us at d = 2304, 54 at d = 32.)
+__global__ __launch_bounds__(256) void chol_first_kernel(const float *H, int d, double *__restrict__ A,
+                                                         double *__restrict__ Y, double *__restrict__ T,
+                                                         double *__restrict__ G, float *out, int *status)
 {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < (int64_t)d * d) dst[e] = (e / d == e % d) ? 1.0 : 0.0;
+    __shared__ double lds[POTRF_WG_LDS];
+    if (blockIdx.x > 0) {
+        const int64_t n = (int64_t)d * d;
+        for (int64_t e = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x; e < n; e += (int64_t)(gridDim.x - 1) * 256) {
+            A[e] = (double)H[e];
+            Y[e] = (e / d == e % d) ? 1.0 : 0.0;
+        }
+        return;
+    }
+    double *As = lds, *Bs = lds + NB * PL;
+    const int bs = d < NB ? d : NB;
+#pragma unroll
+    for (int h = 0; h < 16; ++h) {
+        const int e = threadIdx.x + h * 256, i = e >> 6, j = e & 63;
+        As[i * PL + j] = (i < bs && j <= i) ? (double)H[(int64_t)i * d + j] : (i == j ? 1.0 : 0.0);
+        Bs[i * PL + j] = 0.0;
+    }
+    __syncthreads();
+    potrf_wg_core(T, status, OBC_ERR_NOT_SPD, lds);
+    __syncthreads();
+    doublex4 acc[2][2];
+    tile_mma(acc, Bs, Bs);
+    tile_each(acc, [&](int i, int j, double v) {
+        if (!out) G[i * NB + j] = v;
+        else if (i < d && j < d) out[(int64_t)i * d + j] = (float)v;
+    });
 }
 
 inline dim3 grid64(int M, int N) { return dim3((N + NB - 1) / NB, (M + NB - 1) / NB); }
@@ -286,23 +316,15 @@ int factor_inverse(obc_ctx *ctx, const float *H, int d, void *ws, double **Yout)
     double *A = (double *)base;
     double *Y = (double *)(base + mat);
     double *Lb = (double *)(base + 2 * mat);
-    const int64_t n = (int64_t)d * d;
-
-    f32_to_f64_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(H, A, n);
-    eye_f64_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(Y, d);
-    OBC_LAUNCH_CHECK(ctx, "f32_to_f64_kernel");
-
     // 1 + 2. Cholesky A = L L^T and Y = L^-1 together, block column by block column, one launch per
-    // step (chol_step_kernel); the first diagonal block and the last block row have launches of
-    // their own.  (Y starts as the identity: forward substitution on the identity, right-looking;
+    // step (chol_step_kernel); the first diagonal block comes with the set-up, the last block row
+    // has launches of its own.  (Y starts as the identity: forward substitution on the identity, right-looking;
     // before step kb its block row kb holds I_kb - sum_{j<kb} L[kb,j] Y[j], non-zero only in columns
     // < k0 + bs.)
     double *Gb = Lb + (int64_t)nblk * NB * NB;
-    {
-        const int bs0 = d < NB ? d : NB;
-        potrf_wave_kernel<<<1, 64, 0, st>>>(A, d, bs0, Lb, ctx->d_status, 0, 0, OBC_ERR_NOT_SPD);
-        gemm64_kernel<<<1, 256, 0, st>>>(mk(NB, NB, NB, 1.0, Lb, 1, NB, Lb, NB, 1, 0.0, Gb, NB, 0, 0, nullptr));
-    }
+    const int64_t per = ((int64_t)d * d + 1023) / 1024;          // workgroups at four elements a thread
+    chol_first_kernel<<<1 + (unsigned)(per < 2048 ? per : 2048), 256, 0, st>>>(H, d, A, Y, Lb, Gb, nullptr, ctx->d_status);
+    OBC_LAUNCH_CHECK(ctx, "chol_first_kernel");
     int kprev0 = 0, bsprev = 0;
     for (int kb = 0; kb < nblk; ++kb) {
         const int k0 = kb * NB;
@@ -376,6 +398,12 @@ int obc_invert(obc_ctx *ctx, float *H, int d, void *ws, size_t ws_bytes)
     obc_invert_workspace_bytes(d, &need);
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_invert: workspace of %zu bytes needed, %zu given", need, ws_bytes);
+    if (d <= NB) {
+        double *T = (double *)ws + 2 * obc_align_up((size_t)d * d * sizeof(double), 256) / sizeof(double);
+        chol_first_kernel<<<1, 256, 0, ctx->stream>>>(H, d, nullptr, nullptr, T, nullptr, H, ctx->d_status);
+        OBC_LAUNCH_CHECK(ctx, "chol_first_kernel");
+        return obc_check(ctx);
+    }
     double *Y;
     int rc = factor_inverse(ctx, H, d, ws, &Y);
     if (rc != OBC_OK) return rc;
