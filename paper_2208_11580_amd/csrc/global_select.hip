@@ -88,23 +88,36 @@ __global__ __launch_bounds__(256) void sel_hist_kernel(const unsigned int *__res
     if (h[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// choose the byte bucket that holds the wanted rank; clear the histogram for the next pass
-__global__ void sel_pick_kernel(SelState *st, int pass)
+// Inclusive prefix sums of 256 values, one per thread of the first four waves (`sums`: 4 values of LDS;
+// contains barriers, all threads call it).
+__device__ __forceinline__ unsigned scan256(unsigned v, unsigned *sums)
 {
-    __shared__ unsigned int h[256];
-    h[threadIdx.x] = st->hist[threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long rem = st->remaining;   // 1-based rank inside the current bucket
-        unsigned int b = 0;
-        for (; b < 255; ++b) {
-            if (rem <= h[b]) break;
-            rem -= h[b];
-        }
-        st->remaining = rem;
-        st->prefix |= b << (pass * 8);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned o = __shfl_up(v, off, 64);
+        if (lane >= off) v += o;
     }
+    if (lane == 63 && wave < 4) sums[wave] = v;
     __syncthreads();
+    for (int wv = 0; wv < wave && wv < 4; ++wv) v += sums[wv];
+    __syncthreads();
+    return v;
+}
+
+// choose the byte bucket that holds the wanted rank; clear the histogram for the next pass.  (The
+// buckets' prefix sums by all threads: a walk over them by one took 8 .. 11 us a pass, now 2.)
+__global__ __launch_bounds__(256) void sel_pick_kernel(SelState *st, int pass)
+{
+    __shared__ unsigned sums[4];
+    const unsigned h = st->hist[threadIdx.x];
+    const unsigned long long rem = st->remaining;   // 1-based rank inside the current bucket
+    const unsigned incl = scan256(h, sums), excl = incl - h;
+    // (scan256 ends with a barrier: everybody has read the state)
+    if (excl < rem && (rem <= incl || threadIdx.x == 255)) {
+        st->remaining = rem - excl;
+        st->prefix |= (unsigned)threadIdx.x << (pass * 8);
+    }
     st->hist[threadIdx.x] = 0;
 }
 
@@ -172,6 +185,102 @@ __global__ __launch_bounds__(1024) void assign_counts_kernel(const int *__restri
         if (tid == 1023) base_s += scan[1023];
         __syncthreads();
     }
+}
+
+// The whole step for small layers (n = R d <= kSmallKeys keys, R <= 1024 rows) in one workgroup with the
+// keys in LDS: what the kernels above do in twelve launches, at 2 .. 8 us each, takes a tiny layer far
+// longer than its arithmetic (16 x 32: 58 us; one launch: 8).
+constexpr int kSmallKeys = 16384;
+
+__global__ __launch_bounds__(1024) void select_small_kernel(const float *__restrict__ loss,
+                                                            const int32_t *__restrict__ order, int R, int d,
+                                                            unsigned k, int *__restrict__ counts,
+                                                            uint8_t *__restrict__ mask)
+{
+    extern __shared__ unsigned int keys[];   // R x d
+    __shared__ unsigned hist[256], sums[4], state[2];
+    __shared__ int c_lt[1024], c_eq[1024], total_lt[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = R * d;
+    for (int e = tid; e < n; e += 1024) mask[e] = 0;
+    // prefix maxima, a wave per row
+    for (int row = wave; row < R; row += 16) {
+        float carry = -__builtin_inff();
+        for (int base = 0; base < d; base += 64) {
+            const int j = base + lane;
+            float v = (j < d) ? loss[(size_t)row * d + j] : -__builtin_inff();
+            if (v != v) v = __builtin_inff();   // a NaN loss sorts last
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const float o = __shfl_up(v, off, 64);
+                if (lane >= off) v = fmaxf(v, o);
+            }
+            v = fmaxf(v, carry);
+            carry = __shfl(v, 63, 64);
+            if (j < d) keys[row * d + j] = float_key(v);
+        }
+    }
+    if (tid == 0) { state[0] = k; state[1] = 0; }
+    for (int pass = 3; pass >= 0; --pass) {
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+        const int shift = pass * 8;
+        const unsigned rem = state[0], prefix = state[1];
+        const unsigned himask = (pass == 3) ? 0u : (0xffffffffu << (shift + 8));
+        for (int e = tid; e < n; e += 1024) {
+            const unsigned u = keys[e];
+            if ((u & himask) == (prefix & himask)) atomicAdd(&hist[(u >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        const unsigned h = tid < 256 ? hist[tid] : 0;
+        const unsigned incl = scan256(h, sums), excl = incl - h;
+        if (tid < 256 && excl < rem && (rem <= incl || tid == 255)) {
+            state[0] = rem - excl;
+            state[1] = prefix | ((unsigned)tid << shift);
+        }
+    }
+    __syncthreads();
+    const unsigned v = state[1];
+    int lt_sum = 0;
+    for (int row = wave; row < R; row += 16) {
+        int lt = 0, eq = 0;
+        for (int base = 0; base < d; base += 64) {
+            const int j = base + lane;
+            const unsigned u = (j < d) ? keys[row * d + j] : 0xffffffffu;
+            lt += __popcll(__ballot(j < d && u < v));
+            eq += __popcll(__ballot(j < d && u == v));
+        }
+        if (lane == 0) { c_lt[row] = lt; c_eq[row] = eq; }
+        lt_sum += lt;
+    }
+    if (lane == 0) total_lt[wave] = lt_sum;
+    __syncthreads();
+    int need = (int)k;                          // ties still to hand out, to the rows in index order
+    for (int wv = 0; wv < 16; ++wv) need -= total_lt[wv];
+    const int eq = tid < R ? c_eq[tid] : 0;
+    int incl = eq;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    __syncthreads();                            // everybody has read total_lt
+    if (lane == 63) total_lt[wave] = incl;
+    __syncthreads();
+    for (int wv = 0; wv < wave; ++wv) incl += total_lt[wv];
+    if (tid < R) {
+        int take = need - (incl - eq);
+        take = take < 0 ? 0 : (take > eq ? eq : take);
+        const int c = c_lt[tid] + take;
+        counts[tid] = c;
+        c_lt[tid] = c;
+    }
+    __syncthreads();
+    for (int row = wave; row < R; row += 16)
+        for (int t = lane; t < c_lt[row]; t += 64) {
+            const int p = order[(size_t)row * d + t];
+            if (p >= 0 && p < d) mask[(size_t)row * d + p] = 1;
+        }
 }
 
 __global__ __launch_bounds__(256) void zero_u8_kernel(uint8_t *p, int64_t n)
@@ -253,6 +362,14 @@ static int global_select_enqueue(obc_ctx *ctx, const float *loss, const int32_t 
     off += obc_align_up((size_t)R * sizeof(int), 256);
     SelState *sel = (SelState *)(base + off);
 
+    if (k > 0 && n <= kSmallKeys && R <= 1024) {
+        const size_t lds = (size_t)n * sizeof(unsigned int);
+        if (lds > 48 * 1024)
+            OBC_HIP(ctx, hipFuncSetAttribute((const void *)select_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        select_small_kernel<<<1, 1024, lds, st>>>(loss, order, R, d, (unsigned)k, counts, mask);
+        OBC_LAUNCH_CHECK(ctx, "select_small_kernel");
+        return OBC_OK;
+    }
     zero_u8_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mask, n);
     if (k == 0) {
         fill_i32_kernel<<<(R + 255) / 256, 256, 0, st>>>(counts, R, 0);

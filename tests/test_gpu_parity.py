@@ -563,6 +563,22 @@ def test_global_select_matches_algorithm_2(obc, orc):
         _check_global(obc, orc, res["loss"], res["order"], k)
 
 
+@pytest.mark.parametrize("R,d", [(1, 1), (1, 65), (3, 7), (128, 128), (1024, 16), (1025, 15), (129, 128), (17, 1000)])
+def test_global_select_sizes(obc, orc, R, d):
+    """Both sides of the one-workgroup form (16384 keys, 1024 rows), ties and a NaN among the losses."""
+    gen = torch.Generator(device="cuda").manual_seed(R * d)
+    loss = torch.randint(0, 40, (R, d), generator=gen, device="cuda").float() / 8
+    if d > 4:
+        loss[R // 2, 4] = float("nan")
+    order = torch.argsort(torch.rand(R, d, generator=gen, device="cuda"), dim=1).to(torch.int32)
+    ref = torch.nan_to_num(loss, nan=float("inf"))
+    for k in sorted({1, R * d // 3, R * d // 2 + 1, R * d} - {0}):
+        counts, mask = obc.obc_global_select(loss, order, k)
+        want = orc.global_select(_np(ref).astype(np.float64), k)
+        assert np.array_equal(_np(counts), want), k
+        assert np.array_equal(_np(mask), orc.mask_from_counts(_np(order), want, d))
+
+
 def test_global_select_non_monotone_and_tied_traces(obc, orc):
     rng = np.random.default_rng(0)
     R, d = 1100, 24   # more rows than one scan chunk
