@@ -43,7 +43,7 @@ struct Plan {
 };
 
 // `ntiles(tile)` output tiles of that edge.  Time of a launch as measured, in microseconds: a slab
-// takes 1.28 with two 128-tile workgroups on a CU and 0.73 with one (latency), 2.5 with one 256-tile
+// takes 1.36 with two 128-tile workgroups on a CU and 0.75 with one (latency), 2.5 with one 256-tile
 // workgroup; 3 to start a round of workgroups; and the partial results are written and read back at
 // about 4 TB/s.  The large tile wins by 6 % where both fill the chip (d = 2304, 3072), the small one
 // where they do not (576 x 50 000: 148 against 199 us).
@@ -61,8 +61,8 @@ inline Plan make_plan(Count ntiles, int64_t N)
             double cost;
             if (tile == 128) {
                 const int64_t left = w % 512;
-                cost = (double)(w / 512) * (1.28 * slabs + 3.0)
-                       + (left > 256 ? 1.28 * slabs + 3.0 : left > 0 ? 0.73 * slabs + 3.0 : 0.0);
+                cost = (double)(w / 512) * (1.36 * slabs + 3.0)
+                       + (left > 256 ? 1.36 * slabs + 3.0 : left > 0 ? 0.75 * slabs + 3.0 : 0.0);
             } else {
                 cost = (double)((w + 255) / 256) * (2.5 * slabs + 3.0);
             }
