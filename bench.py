@@ -45,6 +45,7 @@ DEFAULT_WORKLOAD = "conv256x2304-obq4"
 SECOND_WORKLOAD = "ffn768x3072-prune50"     # the other layer the target quotes its roofline figure on
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3
+MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6             # dense bf16, six products per fp32 product (the Hessian)
 # fp32 vector peak of the code as it is compiled here: 256 compute units x 4 SIMDs x 16 lanes x 2 flop
 # (one FMA) x 2.4 GHz = 78.6 TFLOP/s.  The published 157.3 TFLOP/s counts two FMAs per lane and clock,
 # which only the packed fp32 instructions reach; the library is built with them switched off.
@@ -225,7 +226,7 @@ def run_workload(ctx, pkg, workload, steps, warmup, strategy, recover="auto"):
     return dict(workload=workload, task=task, R=R, d=d, N=N, k_steps=k_steps, nm=nm, row_steps=row_steps,
                 ms_per_step=1e3 * wall / steps, value=row_steps / (wall / steps),
                 stages_ms={k: float(np.mean(v)) for k, v in stage_ms.items() if v}, roofline=roofline,
-                hessian_mfma_frac=hess_tf / MFMA_F32_PEAK_TFLOPS,
+                hessian_mfma_frac=hess_tf / MFMA_SPLIT_PEAK_TFLOPS,
                 W=(Wfit if task == "seqobq4" else W), Hinv=H, out=out, grid=grid)
 
 

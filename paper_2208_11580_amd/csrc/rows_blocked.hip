@@ -14,6 +14,11 @@
 // sequence of exact OBS steps; only the order of fp32 roundings inside A differs from the
 // rank-1 strategy.
 //
+// Where a CU only holds the vectors of a few steps (above 2304 columns) several panels share a flush:
+// the later ones find the earlier ones' vectors in memory and apply them to the fetched row with the
+// flush's own roundings, so that the results do not depend on the grouping.  Rows of at most 64
+// weights are one panel, which starts from the caller's arrays.
+//
 // Two kernels alternate on the stream (host loop, no host synchronisation):
 //
 //   panel_kernel  one workgroup per row, B greedy steps.  Thread t owns the compact indices
