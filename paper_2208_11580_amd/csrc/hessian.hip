@@ -2,15 +2,17 @@
 // second moment that the sequential variant (appendix "Sequential Quantization with OBQ")
 // accumulates beside it.
 //
-// A dense (symmetric) rank-N contraction of fp32 inputs.  Every input is the exact sum of three bf16
-// numbers, x = h + m + l (8 bits of the 24 each), so the contraction runs on the bf16 matrix cores as
-// six of the nine products -- h h, h m, m h, m m, h l, l h; what is left out is below 2^-24 of x y --
-// at 16 times the fp32 rate each.  v_mfma_f32_32x32x16_bf16, square output tiles of 128 (four waves,
-// two workgroups per CU) or 256 (eight waves), the split done in registers on the way into LDS, two
+// A dense (symmetric) rank-N contraction of fp32 inputs.  An input of 2^-110 and more is the exact sum of
+// three bf16 numbers, x = h + m + l (8 bits of the 24 each), so the contraction runs on the bf16 matrix
+// cores as six of the nine products -- h h, h m, m h, m m, h l, l h; what is left out is below 2^-24 of
+// x y -- at 16 times the fp32 rate each.  v_mfma_f32_32x32x16_bf16, square output tiles of 128 (four
+// waves, two workgroups per CU) or 256 (eight waves), the split done in registers on the way into LDS, two
 // LDS stages, one barrier per 16 samples.  A slab's products are summed from zero and added to the
 // running sums once, so a sum takes N / 16 roundings (the fp32 MFMA's took N / 2): against fp64 the
 // relative error is 0.6e-7 .. 1.2e-7 (fp32 MFMA: 1.0e-7 .. 4.3e-7) over d = 32 .. 3072, N = 256 ..
-// 50 000.
+// 50 000.  A workgroup that meets what the split cannot hold -- a smaller value, an infinity, a product
+// that overflows -- forms its piece again on the fp32 matrix instructions; to notice it costs 1 .. 2 % of
+// the kernel (576 x 20 001: 79 -> 80.5 us, 3072 x 20 001: 1034 -> 1043 us).
 //
 // Only tiles on or above the block diagonal are computed; the contraction length N is cut into S
 // slices so that small d still fills 256 CUs.  Slices go to a workspace and are summed in a fixed
@@ -102,6 +104,7 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
     constexpr int TILE = WR * MT * 32, T = WR * WC * 64;
     static_assert(WC * NT * 32 == TILE && TILE * 4 == 2 * T, "square tiles, two quads per thread and operand");
     __shared__ __align__(16) uint8_t lds[2][2][3][TILE / 32][kFrag];   // stage, operand, plane, 32 rows
+    __shared__ int redo_s;
 
     // Workgroups go round-robin to the 8 XCDs: each XCD takes a run of the (slice, tile) list, so
     // that the workgroups that share a slice of X run side by side and find it in their L2.
@@ -163,6 +166,9 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
         if ((int64_t)(slab + 1) * BK <= kend - kbeg) fetch(op, h, slab);
         else fetch_tail(op, h, slab);
     };
+    // The least magnitude but zero that passes through the split, as 2 |bits| - 1 (zero wraps to the top):
+    // below 2^-110 the third plane may fall under the smallest bf16.
+    unsigned least = ~0u;
     // Split into three bf16 planes and store.  A plane's 32 rows x 16 samples lie as the MFMA
     // operand is read: lane l finds row l % 32, samples 8 (l / 32) .. + 7 in 16 bytes at
     // (l / 32) kHalf + (l % 32) 16.  The 32 bytes between the halves spread the four quads of a row
@@ -172,7 +178,10 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
         uint8_t *dst = &lds[stage][op][0][r >> 5][(q >> 1) * kHalf + (r & 31) * 16 + (q & 1) * 8];
         float v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = reg[op][h][i];
+        for (int i = 0; i < 4; ++i) {
+            v[i] = reg[op][h][i];
+            least = min(least, (__float_as_uint(v[i]) << 1) - 1u);
+        }
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) {
             uintx2 w;
@@ -226,6 +235,7 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
         }
     };
 
+    if (tid == 0) redo_s = 0;
     if (nslab > 0) {
         for (int h = 0; h < 2; ++h) { fetch_any(0, h, 0); fetch_any(1, h, 0); }
         for (int h = 0; h < 2; ++h) { stash(0, 0, h); stash(0, 1, h); }
@@ -257,6 +267,57 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
         __syncthreads();
     }
 
+    // The plain form of the piece: where an input was too small to split, or where a NaN came out -- an
+    // infinity and a finite value that rounds to infinity in bf16 leave one, a product that overflows may --
+    // it is formed again from the inputs themselves by fp32 matrix instructions.
+    bool lost = least < (17u << 24) - 1u;
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) lost |= __builtin_isunordered(acc[a][b][v], acc[a][b][v + 1]);
+    if (lost) redo_s = 1;
+    __syncthreads();
+    if (__builtin_expect(redo_s, 0)) {
+        constexpr int LD = TILE + 4;
+        static_assert(sizeof(lds) >= 2 * BK * LD * sizeof(float), "the plain form's stage");
+        float *stage = reinterpret_cast<float *>(lds);       // operand, sample, row
+#pragma unroll
+        for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+        for (int h = 0; h < 2; ++h) { fetch_any(0, h, 0); fetch_any(1, h, 0); }
+#pragma unroll 1
+        for (s = 0; s < nslab; ++s) {
+#pragma unroll
+            for (int op = 0; op < 2; ++op)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) stage[(op * BK + q * 4 + i) * LD + r0 + h * (T / 4)] = reg[op][h][i];
+            __syncthreads();
+            if (s + 1 < nslab)
+                for (int h = 0; h < 2; ++h) { fetch_any(0, h, s + 1); fetch_any(1, h, s + 1); }
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += 2) {
+                float fa[MT], fb[NT];
+#pragma unroll
+                for (int a = 0; a < MT; ++a) fa[a] = stage[(kk + (lane >> 5)) * LD + (wm * MT + a) * 32 + (lane & 31)];
+#pragma unroll
+                for (int b = 0; b < NT; ++b) fb[b] = stage[(BK + kk + (lane >> 5)) * LD + (wn * NT + b) * 32 + (lane & 31)];
+#pragma unroll
+                for (int a = 0; a < MT; ++a)
+#pragma unroll
+                    for (int b = 0; b < NT; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[a], fb[b], acc[a][b], 0, 0, 0);
+            }
+            __syncthreads();
+        }
+    }
+
     // accumulator layout of the 32x32 MFMA: lane holds column (lane % 32) and, for register v,
     // row 8 * (v / 4) + 4 * (lane / 32) + v % 4
     float *out = partial + (int64_t)slice * da * db;
@@ -272,24 +333,13 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
             }
 }
 
-// What the split cannot represent -- an infinity, or a finite value beyond the largest bf16 -- comes
-// out as a NaN; such an entry is formed again from the inputs themselves, so that it has the value
-// plain fp32 arithmetic gives it (a NaN ends the sum: nothing changes it any more).
-__device__ float plain_dot(const float *a, const float *b, int64_t N)
-{
-    float s = 0.f;
-    for (int64_t k = 0; k < N && s == s; ++k) s = fmaf(a[k], b[k], s);
-    return s;
-}
-
 // H (+)= 2 * sum_s partial[s] on and above the diagonal, slices added in index order, and the mirror
 // image below it.  One workgroup per 32 x 32 piece: the sums are read and written along rows, the
 // mirrored piece goes through LDS so that it is written along rows too.  (Below the diagonal of a
 // diagonal piece the mirror image is taken as well: the two halves of such a tile add their cross
 // products in opposite order.)
 __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restrict__ partial, int S,
-                                                          int d, int accumulate, const float *X, int64_t ldx,
-                                                          int64_t N, float *__restrict__ H)
+                                                          int d, int accumulate, float *__restrict__ H)
 {
     __shared__ float Tt[32][33];
     const int pi = blockIdx.y, pj = blockIdx.x;           // 32 x 32 piece (pi, pj)
@@ -303,7 +353,6 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restric
         float s = 0.f;
 #pragma unroll 8
         for (int k = 0; k < S; ++k) s += partial[(int64_t)k * d * d + e];
-        if (s != s) s = plain_dot(X + (int64_t)i * ldx, X + (int64_t)j * ldx, N);
         s *= 2.f;
         H[e] = accumulate ? H[e] + s : s;
         Tt[ty + 8 * r][tx] = s;
@@ -321,16 +370,13 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restric
 
 // C[e] (+)= 2 * sum_s partial[s][e] over a dense da x db result, slices added in index order.
 __global__ __launch_bounds__(256) void nt_reduce_kernel(const float *__restrict__ partial, int S,
-                                                        int64_t n, int d_col, int accumulate, const float *Y,
-                                                        int64_t ldy, const float *X, int64_t ldx, int64_t N,
-                                                        float *__restrict__ C)
+                                                        int64_t n, int accumulate, float *__restrict__ C)
 {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     float s = 0.f;
 #pragma unroll 8
     for (int k = 0; k < S; ++k) s += partial[(int64_t)k * n + e];
-    if (s != s) s = plain_dot(Y + e / d_col * ldy, X + e % d_col * ldx, N);
     s *= 2.f;
     C[e] = accumulate ? C[e] + s : s;
 }
@@ -396,7 +442,7 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     int rc = launch_nt<true>(ctx, p, X, d, ldx, X, d, ldx, N, partial);
     if (rc != OBC_OK) return rc;
     const unsigned np32 = (unsigned)((d + 31) / 32);
-    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, p.S, d, accumulate, X, ldx, N, H);
+    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, p.S, d, accumulate, H);
     OBC_LAUNCH_CHECK(ctx, "syrk_reduce_kernel");
     if (damp_rel >= 0.f) {
         dampen_kernel<<<1, 1024, 0, ctx->stream>>>(H, d, damp_rel);
@@ -433,7 +479,7 @@ int obc_cross(obc_ctx *ctx, const float *X, const float *Y, int d_col, int d_row
     int rc = launch_nt<false>(ctx, p, Y, d_row, ldy, X, d_col, ldx, N, partial);
     if (rc != OBC_OK) return rc;
     const int64_t n = (int64_t)d_row * d_col;
-    nt_reduce_kernel<<<(unsigned)((n + 255) / 256), 256, 0, ctx->stream>>>(partial, p.S, n, d_col, accumulate, Y, ldy, X, ldx, N, C);
+    nt_reduce_kernel<<<(unsigned)((n + 255) / 256), 256, 0, ctx->stream>>>(partial, p.S, n, accumulate, C);
     OBC_LAUNCH_CHECK(ctx, "nt_reduce_kernel");
     return OBC_OK;
 }

@@ -98,6 +98,30 @@ def test_second_moments_of_values_beyond_the_split(obc):
         assert torch.equal(got[want.isinf()] > 0, want[want.isinf()] > 0)
 
 
+@pytest.mark.parametrize("e", [-100, -109, -112, -118, -126, -135, -142])
+def test_second_moments_of_values_below_the_split(obc, e):
+    """Values whose third bf16 plane would fall under the smallest bf16, alone in their rows or met by a
+    partner that is zero everywhere else: fp32 arithmetic holds them.  Bound: half a unit per fp32 addition,
+    N of them, relative to the sum of the magnitudes, and half of the smallest fp32 each where they underflow."""
+    gen = torch.Generator(device="cuda").manual_seed(-e)
+    N = 333
+    X = torch.randn(150, N, generator=gen, device="cuda")
+    Y = torch.randn(40, N, generator=gen, device="cuda")
+    Y[:30] = (Y[:30].double() * 2.0 ** e).float()
+    Y[30:, 200] = (Y[30:, 200].double() * 2.0 ** e).float()
+    X[140:] = 0.0
+    X[140:, 200] = 1.0
+    Z = torch.cat([Y, X])
+    Z[:30, :5] *= 2.0 ** 60
+    Xd, Yd, Zd = (t.cpu().double() for t in (X, Y, Z))
+    H, C = obc.obc_hessian(Z, damp_rel=-1.0), obc.obc_cross(X, Y)
+    assert torch.equal(H, H.T)
+    for got, a, b in ((C, Yd, Xd), (H, Zd, Zd)):
+        err = (got.cpu().double() - 2 * a @ b.T).abs()
+        bound = 2.0 ** -24 * N * 2 * (a.abs() @ b.abs().T) + 2.0 ** -150 * 2 * N
+        assert bool((err <= bound).all()), float((err / bound).max())
+
+
 def test_hessian_on_correlated_relu_inputs(obc, orc):
     W, X = _layer("conv64x576", n_samples=10000)
     H = obc.obc_hessian(X)
