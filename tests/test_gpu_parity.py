@@ -122,6 +122,18 @@ def test_second_moments_of_values_below_the_split(obc, e):
         assert bool((err <= bound).all()), float((err / bound).max())
 
 
+@pytest.mark.parametrize("N", [1, 2])
+def test_second_moments_of_one_or_two_samples(obc, N):
+    """One fp32 rounding per product: N half units relative to the sum of the magnitudes."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    X, Y = torch.randn(700, N, generator=gen, device="cuda"), torch.randn(90, N, generator=gen, device="cuda")
+    H, C = obc.obc_hessian(X, damp_rel=-1.0), obc.obc_cross(X, Y)
+    Xd, Yd = X.cpu().double(), Y.cpu().double()
+    for got, a in ((H, Xd), (C, Yd)):
+        err = (got.cpu().double() - 2 * a @ Xd.T).abs()
+        assert bool((err <= N * 2.0 ** -24 * 2 * (a.abs() @ Xd.abs().T)).all())
+
+
 def test_hessian_on_correlated_relu_inputs(obc, orc):
     W, X = _layer("conv64x576", n_samples=10000)
     H = obc.obc_hessian(X)
