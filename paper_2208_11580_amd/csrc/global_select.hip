@@ -90,12 +90,13 @@ __global__ __launch_bounds__(256) void sel_hist_kernel(const unsigned int *__res
 
 // Inclusive prefix sums of 256 values, one per thread of the first four waves (`sums`: 4 values of LDS;
 // contains barriers, all threads call it).
-__device__ __forceinline__ unsigned scan256(unsigned v, unsigned *sums)
+template <typename T>
+__device__ __forceinline__ T scan256(T v, T *sums)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const unsigned o = __shfl_up(v, off, 64);
+        const T o = __shfl_up(v, off, 64);
         if (lane >= off) v += o;
     }
     if (lane == 63 && wave < 4) sums[wave] = v;
@@ -106,13 +107,14 @@ __device__ __forceinline__ unsigned scan256(unsigned v, unsigned *sums)
 }
 
 // choose the byte bucket that holds the wanted rank; clear the histogram for the next pass.  (The
-// buckets' prefix sums by all threads: a walk over them by one took 8 .. 11 us a pass, now 2.)
+// buckets' prefix sums by all threads: a walk over them by one took 8 .. 11 us a pass, now 2.  In 64 bits:
+// a layer may have more than 2^32 weights (a single bucket, whose count is 32 bits, may not).)
 __global__ __launch_bounds__(256) void sel_pick_kernel(SelState *st, int pass)
 {
-    __shared__ unsigned sums[4];
-    const unsigned h = st->hist[threadIdx.x];
+    __shared__ unsigned long long sums[4];
+    const unsigned long long h = st->hist[threadIdx.x];
     const unsigned long long rem = st->remaining;   // 1-based rank inside the current bucket
-    const unsigned incl = scan256(h, sums), excl = incl - h;
+    const unsigned long long incl = scan256(h, sums), excl = incl - h;
     // (scan256 ends with a barrier: everybody has read the state)
     if (excl < rem && (rem <= incl || threadIdx.x == 255)) {
         st->remaining = rem - excl;

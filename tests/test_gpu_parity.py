@@ -615,6 +615,22 @@ def test_global_select_sizes(obc, orc, R, d):
         assert np.array_equal(_np(mask), orc.mask_from_counts(_np(order), want, d))
 
 
+def test_global_select_beyond_32_bit_sums(obc):
+    """More than 2^32 weights, each bucket of the selection below that: the ranks need 64 bits."""
+    R, d = 65537, 65536
+    loss = torch.ones(R, d, device="cuda")
+    loss[:, d // 2:] = 2.0
+    order = torch.arange(d, dtype=torch.int32, device="cuda").expand(R, d).contiguous()
+    counts, mask = obc.obc_global_select(loss, order, R * d - 10)
+    want = torch.full((R,), d, dtype=torch.int32, device="cuda")
+    want[-1] = d - 10                       # ties go to the rows in index order
+    assert torch.equal(counts, want)
+    assert bool(mask[:-1].all()) and bool(mask[-1, :d - 10].all()) and not bool(mask[-1, d - 10:].any())
+    del loss, order, counts, mask
+    obc.release_workspace()
+    torch.cuda.empty_cache()
+
+
 def test_global_select_non_monotone_and_tied_traces(obc, orc):
     rng = np.random.default_rng(0)
     R, d = 1100, 24   # more rows than one scan chunk
