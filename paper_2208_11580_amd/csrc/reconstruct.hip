@@ -279,7 +279,10 @@ __global__ __launch_bounds__(256) void recon_spread_kernel(ReconArgs a)
     for (int t = threadIdx.x; t < c; t += 256) z[a.idx[(size_t)row * a.ldg + t]] = a.vec[(size_t)row * a.ldg + t];
 }
 
-// W_out = W - Z H^-1, pruned entries 0: a 64 x 64 tile per workgroup, slabs as above
+// W_out = W - Z H^-1, pruned entries 0: a 64 x 64 tile per workgroup, slabs as above.  The product meets
+// every row of H^-1, also those that a row of W does not use (times the zeros of Z): where it is not finite
+// the entry is summed again over the row's own indices, so that an infinity or NaN in H^-1 reaches what it
+// is a part of and nothing else.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void recon_product_kernel(ReconArgs a)
 {
     __shared__ double lds[2 * NB * PL];
@@ -315,12 +318,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
         tile_mma<true>(acc, As, Bs);
         __syncthreads();
     }
-    tile_each(acc, [&](int i, int j, double v) {
-        if (i >= Mi || j >= Nj) return;
+    auto store = [&](int i, int j, double v) {
         const size_t e = (size_t)(i0 + i) * d + j0 + j;
         const bool off = a.mask[e] != 0 && a.cnt[i0 + i] > 0;
         a.W_out[e] = off ? 0.f : (float)((double)a.W[e] - v);
+    };
+    unsigned again = 0;                      // of the thread's 16 entries
+    int n = 0;
+    tile_each(acc, [&](int i, int j, double v) {
+        if (i < Mi && j < Nj) {
+            if (fabs(v) < __builtin_inf()) store(i, j, v);
+            else again |= 1u << n;
+        }
+        ++n;
     });
+#pragma unroll 1
+    for (; again != 0; again &= again - 1) {
+        int i = 0, j = 0, k = 0;
+        const int want = __ffs(again) - 1;
+        tile_each(acc, [&](int ii, int jj, double) {
+            if (k++ == want) { i = ii; j = jj; }
+        });
+        const int *idx = a.idx + (size_t)(i0 + i) * a.ldg;
+        const double *z = a.vec + (size_t)(i0 + i) * a.ldg;
+        double v = 0.0;
+#pragma unroll 1
+        for (int t = 0; t < a.cnt[i0 + i]; ++t) v = fma((double)a.Hinv[(size_t)idx[t] * d + j0 + j], z[t], v);
+        store(i, j, v);
+    }
 }
 
 size_t recon_carve(ReconArgs *a, void *base, int R, int cmax)
