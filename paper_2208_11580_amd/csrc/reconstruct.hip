@@ -177,11 +177,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
     }
 }
 
-// ---- 3. L y = w_P, L^T z = y; w_P, y and z in turn in LDS.  Rows of L are read by eight lanes each (64
-// bytes a lane) on the way down, along their entries on the way up.
+// ---- 3. L y = w_P, L^T z = y; w_P, y and z in turn in LDS, or in the workspace where they are longer than
+// that (IN_LDS false).  Rows of L are read by eight lanes each (64 bytes a lane) on the way down, along
+// their entries on the way up.
+constexpr int kSolveLdsMax = (160 * 1024 - (NB + 8 * NB) * 8) / 8;   // doubles next to blk and red
+
+template <bool IN_LDS>
 __global__ __launch_bounds__(512) void recon_solve_kernel(ReconArgs a)
 {
-    extern __shared__ double v[];            // ldg
+    extern __shared__ double v_lds[];        // ldg
     __shared__ double blk[NB], red[8][NB];
     const int row = blockIdx.x, tid = threadIdx.x;
     const int d = a.d, ldg = a.ldg;
@@ -190,6 +194,7 @@ __global__ __launch_bounds__(512) void recon_solve_kernel(ReconArgs a)
     const double *G = a.G + (size_t)row * ldg * ldg;
     const double *Li = a.Linv + (size_t)row * (ldg / NB) * NB * NB;
     double *gv = a.vec + (size_t)row * ldg;
+    double *v = IN_LDS ? v_lds : gv;
     for (int i = tid; i < ldg; i += 512) v[i] = i < c ? gv[i] : 0.0;
     __syncthreads();
     const int nblk = (c + NB - 1) / NB;
@@ -253,7 +258,8 @@ __global__ __launch_bounds__(512) void recon_solve_kernel(ReconArgs a)
         __syncthreads();
     }
     if (a.Z) {
-        for (int i = tid; i < c; i += 512) gv[i] = v[i];
+        if (IN_LDS)
+            for (int i = tid; i < c; i += 512) gv[i] = v[i];
         return;
     }
     // (row idx[t] of the symmetric H^-1 is its column idx[t])
@@ -407,10 +413,14 @@ int obc_reconstruct_rows(obc_ctx *ctx, const float *W, const float *Hinv, const 
         const int below = nt - 1 - k;
         if (below > 0) recon_column_kernel<false><<<rows8 * below, 256, 0, st>>>(a, k * NB, below);
     }
-    const size_t lds = (size_t)a.ldg * sizeof(double);
-    if (lds > 48 * 1024)
-        OBC_HIP(ctx, hipFuncSetAttribute((const void *)recon_solve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    recon_solve_kernel<<<R, 512, lds, st>>>(a);
+    if (a.ldg <= kSolveLdsMax) {
+        const size_t lds = (size_t)a.ldg * sizeof(double);
+        if (lds > 48 * 1024)
+            OBC_HIP(ctx, hipFuncSetAttribute((const void *)recon_solve_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        recon_solve_kernel<true><<<R, 512, lds, st>>>(a);
+    } else {
+        recon_solve_kernel<false><<<R, 512, 0, st>>>(a);
+    }
     if (a.Z) {
         recon_spread_kernel<<<R, 256, 0, st>>>(a);
         recon_product_kernel<<<dim3((d + NB - 1) / NB, (R + NB - 1) / NB), 256, 0, st>>>(a);

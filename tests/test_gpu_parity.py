@@ -908,6 +908,31 @@ def test_reconstruct_rows_edge_cases(obc, orc):
         obc.obc_reconstruct_rows(W, Hinv, mask, max_pruned=d + 1)
 
 
+@pytest.mark.parametrize("d,keep", [(19904, 5), (20032, 70)])
+def test_reconstruct_rows_at_the_edge_of_lds(obc, d, keep):
+    """The longest row whose solve fits LDS and one beyond it.  H^-1 = I + u u^T: the closed form is
+    w_S - u_S (u_P . w_P) / (1 + u_P . u_P) by Sherman-Morrison.  H^-1 is rounded to fp32 (2^-24 of entries
+    of at most u_i u_j), which moves the result by a few units of that."""
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    u = torch.randn(d, generator=gen, device="cuda") / 32
+    Hinv = torch.outer(u, u)
+    Hinv.diagonal().add_(1.0)
+    W = torch.randn(1, d, generator=gen, device="cuda")
+    mask = torch.ones(1, d, dtype=torch.uint8, device="cuda")
+    at = torch.randperm(d, generator=gen, device="cuda")[:keep]
+    mask[0, at] = 0
+    got = obc.obc_reconstruct_rows(W, Hinv, mask)
+    obc.obc_check()
+    P = mask[0].bool()
+    ud, wd = u.double(), W[0].double()
+    want = wd - ud * (ud[P] @ wd[P]) / (1.0 + ud[P] @ ud[P])
+    assert not bool(got[0, P].any())
+    assert float((got[0, ~P].double() - want[~P]).norm() / want[~P].norm()) < 1e-5
+    del Hinv
+    obc.release_workspace()
+    torch.cuda.empty_cache()
+
+
 # ------------------------------------------------------------------------------ boundary errors
 def test_argument_errors(obc):
     import paper_2208_11580_amd as pkg
