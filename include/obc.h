@@ -112,7 +112,8 @@ int obc_mfmabench(obc_ctx *ctx, int kind, int iters, int reps, double *ms_per_pa
  * H: d x d fp32.  accumulate == 0: H = 2 X X^T;  accumulate != 0: H += 2 X X^T (calibration
  * data arriving in batches; samples only ever need to be accumulated once).
  * damp_rel >= 0: after the product, add damp_rel * mean(diag(H)) to the diagonal (call with
- * damp_rel < 0 for all batches but the last).  The sum over samples is not divided by N. */
+ * damp_rel < 0 for all batches but the last).  The sum over samples is not divided by N.  A workspace
+ * that is enough for N samples is enough for fewer (obc_cross likewise). */
 int obc_hessian_workspace_bytes(int d, int64_t N, size_t *bytes);
 int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, float damp_rel,
                 int accumulate, float *H, void *ws, size_t ws_bytes);

@@ -39,9 +39,9 @@ constexpr int kFrag = 2 * kHalf;      // bytes of 32 rows x 16 samples of a plan
 __host__ __device__ inline int tiles_of(int d, int tile) { return (d + tile - 1) / tile; }
 
 // The launch of a contraction: square output tiles of edge `tile`, S slices of `kchunk` samples
-// (multiple of BK).
+// (multiple of BK); the workspace holds `cap` >= S slices.
 struct Plan {
-    int tile, S;
+    int tile, S, cap;
     int64_t kchunk;
 };
 
@@ -50,28 +50,44 @@ struct Plan {
 // workgroup; 3 to start a round of workgroups; and the partial results are written and read back at
 // about 4 TB/s.  The large tile wins by 6 % where both fill the chip (d = 2304, 3072), the small one
 // where they do not (576 x 50 000: 148 against 199 us).
+//
+// A workspace for N samples has to serve every smaller batch, but the best S goes up and down with N
+// (whole slabs only).  So S is bounded by the S that is best for fractions of slabs, and the workspace
+// sized by that: its cost is N g(S) + h(S) with h growing, which makes it grow with N.
 template <class Count>
 inline Plan make_plan(Count ntiles, int64_t N)
 {
-    Plan best = {128, 1, 0};
+    auto cost = [&](int tile, int64_t n, int64_t c, double slabs) {
+        const int64_t w = n * c;
+        double t;
+        if (tile == 128) {
+            const int64_t left = w % 512;
+            t = (double)(w / 512) * (1.36 * slabs + 3.0)
+                + (left > 256 ? 1.36 * slabs + 3.0 : left > 0 ? 0.75 * slabs + 3.0 : 0.0);
+        } else {
+            t = (double)((w + 255) / 256) * (2.5 * slabs + 3.0);
+        }
+        return t + (double)w * tile * tile * 8.0 / 4e6 + 0.1 * (double)c;
+    };
+    Plan best = {128, 1, 1, 0};
     double best_cost = 0.0;
     const int64_t smax = N / (2 * BK) < 1 ? 1 : N / (2 * BK) < 64 ? N / (2 * BK) : 64;
     for (int tile = 128; tile <= 256; tile += 128) {
         const int64_t n = ntiles(tile);
-        for (int64_t c = 1; c <= smax; ++c) {
-            const double slabs = (double)(((N + c - 1) / c + BK - 1) / BK);
-            const int64_t w = n * c;
-            double cost;
-            if (tile == 128) {
-                const int64_t left = w % 512;
-                cost = (double)(w / 512) * (1.36 * slabs + 3.0)
-                       + (left > 256 ? 1.36 * slabs + 3.0 : left > 0 ? 0.75 * slabs + 3.0 : 0.0);
-            } else {
-                cost = (double)((w + 255) / 256) * (2.5 * slabs + 3.0);
+        int64_t bound = 1;
+        double bound_cost = cost(tile, n, 1, (double)N / BK);
+        for (int64_t c = 2; c <= smax; ++c) {
+            const double t = cost(tile, n, c, (double)N / (double)(BK * c));
+            if (t < bound_cost) {
+                bound_cost = t;
+                bound = c;
             }
-            cost += (double)w * tile * tile * 8.0 / 4e6 + 0.1 * (double)c;
-            if (best_cost == 0.0 || cost < best_cost) {
-                best_cost = cost;
+        }
+        if (bound > best.cap) best.cap = (int)bound;
+        for (int64_t c = 1; c <= bound; ++c) {
+            const double t = cost(tile, n, c, (double)(((N + c - 1) / c + BK - 1) / BK));
+            if (best_cost == 0.0 || t < best_cost) {
+                best_cost = t;
                 best.tile = tile;
                 best.S = (int)c;
             }
@@ -426,7 +442,7 @@ int obc_hessian_workspace_bytes(int d, int64_t N, size_t *bytes)
 {
     if (!bytes || d <= 0 || N < 0) return OBC_ERR_BAD_ARG;
     const Plan p = hessian_plan(d, N > 0 ? N : 1);
-    *bytes = obc_align_up((size_t)p.S * d * d * sizeof(float), 256);
+    *bytes = obc_align_up((size_t)p.cap * d * d * sizeof(float), 256);
     return OBC_OK;
 }
 
@@ -460,7 +476,7 @@ int obc_cross_workspace_bytes(int d_row, int d_col, int64_t N, size_t *bytes)
 {
     if (!bytes || d_row <= 0 || d_col <= 0 || N < 0) return OBC_ERR_BAD_ARG;
     const Plan p = cross_plan(d_row, d_col, N > 0 ? N : 1);
-    *bytes = obc_align_up((size_t)p.S * d_row * d_col * sizeof(float), 256);
+    *bytes = obc_align_up((size_t)p.cap * d_row * d_col * sizeof(float), 256);
     return OBC_OK;
 }
 

@@ -40,6 +40,25 @@ def test_library_exports_every_declared_symbol(lib):
         assert hasattr(lib, name), name
 
 
+def test_second_moment_workspaces_serve_smaller_batches(lib):
+    """Calibration data arrives in batches, the last one ragged: what is enough for N samples is enough for
+    fewer."""
+    n = ctypes.c_size_t()
+    for d in (16, 64, 200, 576, 768, 1283, 2304, 3072, 4608):
+        most = 0
+        for N in list(range(1, 3000, 7)) + list(range(3000, 60000, 233)) + [10 ** 6, 10 ** 7]:
+            assert lib.obc_hessian_workspace_bytes(d, N, ctypes.byref(n)) == 0
+            assert n.value >= most, (d, N)
+            most = n.value
+        assert most <= 64 * d * d * 4 + 256
+    for d_row, d_col in ((1, 64), (16, 576), (256, 2304)):
+        most = 0
+        for N in range(1, 60000, 97):
+            assert lib.obc_cross_workspace_bytes(d_row, d_col, N, ctypes.byref(n)) == 0
+            assert n.value >= most, (d_row, d_col, N)
+            most = n.value
+
+
 def test_host_only_calls(lib):
     assert b"gfx950" in lib.obc_version()
     n = ctypes.c_size_t()
