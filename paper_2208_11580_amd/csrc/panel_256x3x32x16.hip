@@ -4,5 +4,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL(256, 3, 32, 16)
+OBC_DEFINE_PANEL(launch_panel, false, 256, 3, 32, 16)
 }

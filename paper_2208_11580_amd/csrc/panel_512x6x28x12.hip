@@ -3,5 +3,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL(512, 6, 28, 12)
+OBC_DEFINE_PANEL(launch_panel, false, 512, 6, 28, 12)
 }

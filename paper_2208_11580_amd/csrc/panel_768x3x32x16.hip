@@ -3,5 +3,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL(768, 3, 32, 16)
+OBC_DEFINE_PANEL(launch_panel, false, 768, 3, 32, 16)
 }

@@ -3,5 +3,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL_BLOCK(256, 1, 64, 0)
+OBC_DEFINE_PANEL_BLOCK(false, 256, 1, 64, 0)
 }

@@ -3,5 +3,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL_BLOCK(512, 3, 48, 16)
+OBC_DEFINE_PANEL_BLOCK(false, 512, 3, 48, 16)
 }

@@ -3,5 +3,5 @@
 #include "panel_impl.h"
 
 namespace obc_blocked {
-OBC_DEFINE_PANEL_BLOCK(512, 9, 16, 8)
+OBC_DEFINE_PANEL_BLOCK(true, 512, 9, 16, 8)
 }

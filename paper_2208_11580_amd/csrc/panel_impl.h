@@ -8,9 +8,6 @@
 
 namespace obc_blocked {
 
-// Panels for live sizes above this share a flush with others: they find the vectors of the outer
-// block's earlier panels in memory.
-constexpr int kOldVectorsAbove = 2304;
 constexpr int kBeyond = 0x40000000;   // a byte offset beyond any row's matrix: the load returns 0
 
 // Per-thread state of the panel: everything indexed by the owned element e (compact index
@@ -239,9 +236,10 @@ __device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const Pane
     return sc == sc ? score_bits(sc) : ~0u;   // a NaN score is no candidate
 }
 
-// One greedy step, S-th of the block.  Returns 0 to continue, 1 when the row has no step left,
+// One greedy step, S-th of the block.  OLD: the panel follows others of its outer block, whose vectors it
+// finds in memory.  Returns 0 to continue, 1 when the row has no step left,
 // 2 on a numeric failure.  Every thread of the workgroup returns the same value.
-template <int MODE, int T, int EPT, int BR, int BL, int S>
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int S>
 __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
                                           PanelShared &sh, uint8_t *blk, float *ul)
 {
@@ -318,6 +316,11 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
                 v.y = (r4 + 1 < SREG) ? st.u[r4 + 1 < BR ? r4 + 1 : 0][e] : 0.f;
                 v.z = (r4 + 2 < SREG) ? st.u[r4 + 2 < BR ? r4 + 2 : 0][e] : 0.f;
                 v.w = (r4 + 3 < SREG) ? st.u[r4 + 3 < BR ? r4 + 3 : 0][e] : 0.f;
+                // (copies: stored from where they are, the four would have to be an aligned group of
+                // registers all along, and next to block pruning's state there is no room for that --
+                // in scratch memory they cost 16 x 2600 in blocks 12 % of its time)
+                if constexpr (MODE == MODE_BLOCK && EPT >= 6 && EPT < 9)
+                    asm("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
                 *reinterpret_cast<float4 *>(&sh.cvec[r4]) = v;
             }
             const double ap = st.dg[e];
@@ -339,7 +342,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         }
     }
     // coefficients of the earlier panels' vectors, which are in memory: one lane each
-    if constexpr (CAP > kOldVectorsAbove) {
+    if constexpr (OLD) {
         if (tid < pr.old) sh.cold[tid] = pr.gU[(size_t)tid * pr.ldu + p];
     }
     // entries p of the vectors kept in LDS: one lane each
@@ -363,7 +366,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     // The correction is summed on its own and subtracted once: its roundings are then relative to
     // the (small) correction instead of to the matrix entry, and the sum does not wait for the
     // fetched row.
-    if constexpr (CAP > kOldVectorsAbove) {
+    if constexpr (OLD) {
         // The earlier panels' vectors, panel by panel, exactly as their flush would have applied them:
         // entry (i, j), i >= j, gets sum_k (-u_k[i] / a_k) u_k[j], summed from zero in k order (which is
         // how the fp32 matrix instruction sums) and added once.  (Indices beyond m read what lies behind
@@ -441,23 +444,27 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 }
 
 // Compile-time unrolled step loop; returns the number of steps done and sets *failed.
-template <int MODE, int T, int EPT, int BR, int BL, int S>
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int S>
 __device__ __forceinline__ int panel_steps(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
                                            PanelShared &sh, uint8_t *blk, float *ul, bool *failed)
 {
     if constexpr (S < BR + BL) {
-        int rc = panel_step<MODE, T, EPT, BR, BL, S>(a, pr, st, sh, blk, ul);
+        int rc = panel_step<MODE, T, EPT, BR, BL, OLD, S>(a, pr, st, sh, blk, ul);
         if (rc != 0) {
             *failed = (rc == 2);
             return S;
         }
-        return panel_steps<MODE, T, EPT, BR, BL, S + 1>(a, pr, st, sh, blk, ul, failed);
+        return panel_steps<MODE, T, EPT, BR, BL, OLD, S + 1>(a, pr, st, sh, blk, ul, failed);
     } else {
         return BR + BL;
     }
 }
 
-template <int MODE, int T, int EPT, int BR, int BL>
+// OLD: an instance that can follow others of its outer block (a.old > 0).  At six elements a thread the
+// panels that do not are instances without it: what re-reading the earlier vectors takes does not fit the
+// registers next to a step's state (8 x 2600, 240 steps with a flush each 40: 2.12 against 2.15 ms; 8 x 2600 in
+// blocks, where nothing shares a flush, 2.70 against 3.08 ms).
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 ? (EPT == 1 ? 4 : 3) : T / 256)))
 void panel_kernel(PanelArgs a)
 {
@@ -542,7 +549,7 @@ void panel_kernel(PanelArgs a)
                 st.ob[e][k] = (j < m) ? pr.Acur[off] : 0.f;
             }
         }
-        if constexpr (T * EPT > kOldVectorsAbove) {
+        if constexpr (OLD) {
             // ... and the outer block's earlier eliminations, as their flush would have applied them
             __syncthreads();
 #pragma unroll 1
@@ -577,7 +584,7 @@ void panel_kernel(PanelArgs a)
     __syncthreads();
 
     bool failed = false;
-    const int nbv = panel_steps<MODE, T, EPT, BR, BL, 0>(a, pr, st, sh, blk, ul, &failed);
+    const int nbv = panel_steps<MODE, T, EPT, BR, BL, OLD, 0>(a, pr, st, sh, blk, ul, &failed);
     __syncthreads();
 
     // ---- block epilogue.  Before the outer block's last panel the state stays in the present index
@@ -672,7 +679,7 @@ void panel_kernel(PanelArgs a)
                         (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * (T * EPT) + j];
         }
     }
-    if constexpr (T * EPT > kOldVectorsAbove) {
+    if constexpr (OLD) {
         // the earlier panels' vectors move to the new order in place: a group of them is read
         // whole before any of it is written
         if (a.last) {
@@ -723,34 +730,31 @@ inline int panel_raise_lds_limit(const void *fn, std::atomic<unsigned long long>
 
 // With one owned element per thread a launch has as many waves as the largest live size needs: a
 // step is bound by instruction issue, and a wave without live elements issues as many as the others.
-#define OBC_DEFINE_PANEL(T, EPT, BR, BL)                                                            \
-    int launch_panel_##T##_##EPT##_##BR##_##BL(int mode, int R, size_t lds_nm, hipStream_t st,      \
-                                               const PanelArgs &a)                                  \
-    {                                                                                               \
-        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                         \
-        auto kp = panel_kernel<MODE_PRUNE, T, EPT, BR, BL>;                                         \
-        auto kq = panel_kernel<MODE_QUANT, T, EPT, BR, BL>;                                         \
-        static std::atomic<unsigned long long> raised_p{0}, raised_q{0};                            \
-        if (lds > 48 * 1024) {                                                                      \
-            if (mode == MODE_PRUNE && panel_raise_lds_limit((const void *)kp, raised_p) != 0) return -1; \
-            if (mode != MODE_PRUNE && panel_raise_lds_limit((const void *)kq, raised_q) != 0) return -1; \
-        }                                                                                           \
-        if (mode == MODE_PRUNE) hipLaunchKernelGGL(kp, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);               \
-        else hipLaunchKernelGGL(kq, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);                                  \
-        return 0;                                                                                   \
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD>
+int panel_launch(int R, size_t lds_nm, hipStream_t st, const PanelArgs &a)
+{
+    const size_t lds = (size_t)BL * T * EPT * sizeof(float) + lds_nm;
+    auto kernel = panel_kernel<MODE, T, EPT, BR, BL, OLD>;
+    static std::atomic<unsigned long long> raised{0};
+    if (lds > 48 * 1024 && panel_raise_lds_limit((const void *)kernel, raised) != 0) return -1;
+    hipLaunchKernelGGL(kernel, dim3(R), dim3(EPT == 1 ? a.threads : T), lds, st, a);
+    return 0;
+}
+
+// NAME: launch_panel, or launch_panel_old where a variant has an instance of its own for OLD
+#define OBC_DEFINE_PANEL(NAME, OLD, T, EPT, BR, BL)                                                     \
+    int NAME##_##T##_##EPT##_##BR##_##BL(int mode, int R, size_t lds_nm, hipStream_t st, const PanelArgs &a) \
+    {                                                                                                   \
+        return mode == MODE_PRUNE ? panel_launch<MODE_PRUNE, T, EPT, BR, BL, OLD>(R, lds_nm, st, a)     \
+                                  : panel_launch<MODE_QUANT, T, EPT, BR, BL, OLD>(R, lds_nm, st, a);    \
     }
 
 // The block-pruning instance of a variant, in a translation unit of its own.
-#define OBC_DEFINE_PANEL_BLOCK(T, EPT, BR, BL)                                                      \
-    int launch_panel_block_##T##_##EPT##_##BR##_##BL(int, int R, size_t lds_nm, hipStream_t st,     \
-                                                     const PanelArgs &a)                            \
-    {                                                                                               \
-        const size_t lds = (size_t)(BL) * (T) * (EPT) * sizeof(float) + lds_nm;                         \
-        auto kb = panel_kernel<MODE_BLOCK, T, EPT, BR, BL>;                                         \
-        static std::atomic<unsigned long long> raised{0};                                           \
-        if (lds > 48 * 1024 && panel_raise_lds_limit((const void *)kb, raised) != 0) return -1;     \
-        hipLaunchKernelGGL(kb, dim3(R), dim3((EPT) == 1 ? a.threads : (T)), lds, st, a);                                       \
-        return 0;                                                                                   \
+#define OBC_DEFINE_PANEL_BLOCK(OLD, T, EPT, BR, BL)                                                     \
+    int launch_panel_block_##T##_##EPT##_##BR##_##BL(int, int R, size_t lds_nm, hipStream_t st,         \
+                                                     const PanelArgs &a)                                \
+    {                                                                                                   \
+        return panel_launch<MODE_BLOCK, T, EPT, BR, BL, OLD>(R, lds_nm, st, a);                         \
     }
 
 }  // namespace obc_blocked

@@ -599,18 +599,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 struct Variant {
     int cap;   // largest live size it handles (T * EPT)
     int B;     // steps per panel
-    int J;     // most panels per outer block: one flush applies their eliminations
-    int (*launch)(int, int, size_t, hipStream_t, const PanelArgs &);
-    int (*launch_block)(int, int, size_t, hipStream_t, const PanelArgs &);   // block pruning
+    PanelLaunch *launch;
+    PanelLaunch *launch_block;       // block pruning
+    // panels that follow others of their outer block: one flush applies the eliminations of up to J
+    int J;
+    PanelLaunch *launch_old;
+    PanelLaunch *launch_block_old;   // null: block pruning flushes after every panel
 };
 
-#define OBC_VARIANT(T, EPT, BR, BL, J)                                        \
-    { (T) * (EPT), (BR) + (BL), J, launch_panel_##T##_##EPT##_##BR##_##BL,       \
-      launch_panel_block_##T##_##EPT##_##BR##_##BL }
+#define OBC_VARIANT(T, EPT, BR, BL)                                              \
+    (T) * (EPT), (BR) + (BL), launch_panel_##T##_##EPT##_##BR##_##BL,            \
+        launch_panel_block_##T##_##EPT##_##BR##_##BL
 
 const Variant kVariants[] = {
-    OBC_VARIANT(256, 1, 64, 0, 1), OBC_VARIANT(1024, 1, 64, 0, 1), OBC_VARIANT(512, 3, 48, 16, 1), OBC_VARIANT(512, 4, 40, 16, 1),
-    OBC_VARIANT(768, 3, 32, 16, 1), OBC_VARIANT(512, 6, 28, 12, 2), OBC_VARIANT(512, 8, 20, 8, 3), OBC_VARIANT(512, 9, 16, 8, 4),
+    {OBC_VARIANT(256, 1, 64, 0)},
+    {OBC_VARIANT(1024, 1, 64, 0)},
+    {OBC_VARIANT(512, 3, 48, 16)},
+    {OBC_VARIANT(512, 4, 40, 16)},
+    {OBC_VARIANT(768, 3, 32, 16)},
+    {OBC_VARIANT(512, 6, 28, 12), 2, launch_panel_old_512_6_28_12, nullptr},
+    {OBC_VARIANT(512, 8, 20, 8), 3, launch_panel_512_8_20_8, launch_panel_block_512_8_20_8},
+    {OBC_VARIANT(512, 9, 16, 8), 4, launch_panel_512_9_16_8, launch_panel_block_512_9_16_8},
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -619,7 +628,7 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // three rows per CU on -- the 768 x 768 layer 7.6 -> 7.1 ms, its panels 3.5 -> 2.4 ms while the
 // shorter blocks make its flushes 2.2 -> 2.9 ms; below that the shorter blocks cost more than the
 // overlap brings).
-const Variant kSharedCuVariant = OBC_VARIANT(256, 3, 32, 16, 1);
+const Variant kSharedCuVariant = {OBC_VARIANT(256, 3, 32, 16)};
 constexpr int kSharedCuMinRows = 768;
 
 const Variant *pick_variant(int m, int R)
@@ -795,7 +804,9 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         // index space keeps its size, and a panel finds the earlier ones' vectors in memory.
         // (What a flush saves must exceed the re-reading: 40 steps at up to 3072 gain 5 % of the
         // 768 x 3072 layer, but not with block pruning's larger state, 40 x 3000: 22.4 against 22.7 ms.)
-        const int most = (mode == MODE_BLOCK && v->cap <= 3072) ? 1 : v->J;
+        PanelLaunch *first = mode == MODE_BLOCK ? v->launch_block : v->launch;
+        PanelLaunch *next = mode == MODE_BLOCK ? v->launch_block_old : v->launch_old;
+        const int most = next ? v->J : 1;
         int panels = 1;
         while (panels < most && host_done + panels * v->B < host_total &&
                pick_variant(m_max - panels * v->B, R) == v) ++panels;
@@ -808,7 +819,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
                 const int steps = (host_total - host_done < v->B) ? host_total - host_done : v->B;
                 obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * steps * 4.0 * m_max,
                              (double)R * steps * (double)(steps + 2 * pa.old) * m_max);
-                if ((mode == MODE_BLOCK ? v->launch_block : v->launch)(mode, R, lds_nm, st, pa) != 0)
+                if ((j == 0 ? first : next)(mode, R, lds_nm, st, pa) != 0)
                     return obc_fail(ctx, OBC_ERR_HIP, "panel kernel: cannot set its dynamic LDS size");
             }
             OBC_LAUNCH_CHECK(ctx, "panel_kernel");
