@@ -802,11 +802,15 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         pa.swz = swz;
         // Panels that share a flush, as long as the live size keeps this variant.  Before the flush the
         // index space keeps its size, and a panel finds the earlier ones' vectors in memory.
-        // (What a flush saves must exceed the re-reading: 40 steps at up to 3072 gain 5 % of the
-        // 768 x 3072 layer, but not with block pruning's larger state, 40 x 3000: 22.4 against 22.7 ms.)
+        // (What a flush saves must exceed the re-reading.  Above 3072 columns, 24 and 28 steps a panel, it
+        // does from one row on.  At 40 steps it depends on the rows and the width -- 240 steps from that
+        // width down, in us, flushed after each panel against shared: 256 x 2600 7528, 6359; 128 x 2600 4446,
+        // 4208; 96 x 2800 4116, 3968; 32 x 3072 2848, 2713; 8 x 3100 2727, 2399; but 64 x 2600 2908, 3139;
+        // 8 x 2600 2119, 2233; 128 x 2400 3748, 3904; 256 x 2400 6444, 6603.  Not with block pruning's larger
+        // state: 40 x 3000 in blocks 22.4 against 22.7 ms.)
         PanelLaunch *first = mode == MODE_BLOCK ? v->launch_block : v->launch;
         PanelLaunch *next = mode == MODE_BLOCK ? v->launch_block_old : v->launch_old;
-        const int most = next ? v->J : 1;
+        const int most = next && (m_max >= 2816 || (R >= 96 && m_max >= 2416)) ? v->J : 1;
         int panels = 1;
         while (panels < most && host_done + panels * v->B < host_total &&
                pick_variant(m_max - panels * v->B, R) == v) ++panels;
