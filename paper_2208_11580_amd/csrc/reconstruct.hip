@@ -19,8 +19,8 @@
 //      that inverse before they are stored.
 //   3. per row: L y = w_P and L^T z = y block by block with the inverted diagonal factors
 //      (recon_solve_kernel), then w_hat = w - H^-1[:, P] z, pruned entries set to 0: for all rows in one
-//      product Z H^-1 on the fp64 matrix core, z spread over the row's d columns (where the pruned share
-//      is small, along rows of H^-1 by the row's own workgroup instead)
+//      product Z H^-1 on the fp64 matrix core, z spread over the row's d columns (up to 640
+//      pruned weights, along rows of H^-1 by the row's own workgroup instead: the same sums)
 // Bound by the fp64 matrix core (c^3 / 3 flop per row): 768 x 3072 at 50 %, 0.93 TFLOP, in 28.5 ms for
 // the factorisation (33 TFLOP/s of the 47 this unit sustains; 43.5 with a right-looking update of all
 // of G per block column) and 33.8 ms in all (61.3); 256 x 4608 34 ms (72.5).
@@ -401,8 +401,12 @@ int obc_reconstruct_rows(obc_ctx *ctx, const float *W, const float *Hinv, const 
     a.W = W; a.Hinv = Hinv; a.mask = mask; a.d = d; a.cmax = max_pruned; a.W_out = W_out; a.status = ctx->d_status;
     hipStream_t st = ctx->stream;
     a.R = R;
-    // Z takes G's place; the product over all d columns pays where a row's pruned share is not small
-    a.Z = (max_pruned >= d / 8 && (size_t)d <= (size_t)a.ldg * (a.ldg + NB)) ? a.G : nullptr;
+    // Z takes G's place.  The product over all d columns costs two launches and the columns that no row has;
+    // the rows' own sums read H^-1 once per row.  In us, rows' own against product, half of each row pruned:
+    // 300 x 64 41, 51; 256 x 576 394, 419; 768 x 576 895, 888; 256 x 1024 965, 987; 768 x 1024 2564, 2519;
+    // 8 x 2304 2036, 1827; 256 x 2304 6385, 6229; a third: 256 x 2304 2494, 2418; a fifth: 984, 988; an eighth:
+    // 482, 523.
+    a.Z = (max_pruned >= 640 && (size_t)d <= (size_t)a.ldg * (a.ldg + NB)) ? a.G : nullptr;
     const unsigned rows8 = (unsigned)((R + 7) / 8 * 8);
     const int nt = (max_pruned + NB - 1) / NB;                    // 64-row tiles of the largest row
     recon_list_kernel<<<R, 256, 0, st>>>(a);

@@ -908,6 +908,31 @@ def test_reconstruct_rows_edge_cases(obc, orc):
         obc.obc_reconstruct_rows(W, Hinv, mask, max_pruned=d + 1)
 
 
+def test_reconstruct_rows_on_both_sides_of_the_product(obc, orc):
+    """The bound from which the closing product runs over all columns (640): the same weights, bit for bit,
+    from both sides of it, and a row beyond its bound unchanged on both."""
+    import paper_2208_11580_amd as pkg
+
+    d = 1000
+    W, X = _layer("conv64x576", d_col=d, d_row=6, n_samples=2 * d)
+    Hinv = _hinv(obc, X)
+    mask = torch.zeros(6, d, dtype=torch.uint8, device="cuda")
+    for i, c in enumerate((0, 1, 64, 65, 600, 639)):
+        mask[i, torch.randperm(d, generator=torch.Generator().manual_seed(i))[:c].cuda()] = 1
+    got = [obc.obc_reconstruct_rows(W, Hinv, mask, max_pruned=m) for m in (639, 640, d)]
+    obc.obc_check()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    ref = orc.reconstruct_closed_form(_np(Hinv), _np(W), _np(mask))
+    assert np.linalg.norm(_np(got[0]) - ref) <= 1e-6 * np.linalg.norm(ref)
+    mask[5] = 1
+    for m in (60, 639, 640):
+        cut = obc.obc_reconstruct_rows(W, Hinv, mask, max_pruned=m)
+        with pytest.raises(pkg.ObcError):
+            obc.obc_check()
+        over = mask.sum(dim=1) > m
+        assert torch.equal(cut[over], W[over]) and torch.equal(cut[~over], got[0][~over])
+
+
 @pytest.mark.parametrize("d,keep", [(19904, 5), (20032, 70)])
 def test_reconstruct_rows_at_the_edge_of_lds(obc, d, keep):
     """The longest row whose solve fits LDS and one beyond it.  H^-1 = I + u u^T: the closed form is
