@@ -561,10 +561,13 @@ void panel_kernel(PanelArgs a)
 #pragma unroll 2
                     for (int r = r0; r < r0 + B; ++r) {
                         const float u = pr.gU[(size_t)r * pr.ldu + tid + e * T], f = __fmul_rn(u, -sh.invd_old[r]);
-                        sum[0] = fmaf(f, quad_bcast<0>(u), sum[0]);      // (j, j0): j is the larger index
-                        sum[1] = fmaf(q >= 1 ? f : quad_bcast<1>(f), q >= 1 ? quad_bcast<1>(u) : u, sum[1]);
-                        sum[2] = fmaf(q >= 2 ? f : quad_bcast<2>(f), q >= 2 ? quad_bcast<2>(u) : u, sum[2]);
-                        sum[3] = fmaf(q >= 3 ? f : quad_bcast<3>(f), q >= 3 ? quad_bcast<3>(u) : u, sum[3]);
+                        // (all lanes read their neighbours before any of them chooses)
+                        const float u0 = quad_bcast<0>(u), u1 = quad_bcast<1>(u), u2 = quad_bcast<2>(u), u3 = quad_bcast<3>(u);
+                        const float f1 = quad_bcast<1>(f), f2 = quad_bcast<2>(f), f3 = quad_bcast<3>(f);
+                        sum[0] = fmaf(f, u0, sum[0]);      // (j, j0): j is the larger index
+                        sum[1] = fmaf(q >= 1 ? f : f1, q >= 1 ? u1 : u, sum[1]);
+                        sum[2] = fmaf(q >= 2 ? f : f2, q >= 2 ? u2 : u, sum[2]);
+                        sum[3] = fmaf(q >= 3 ? f : f3, q >= 3 ? u3 : u, sum[3]);
                     }
 #pragma unroll
                     for (int k = 0; k < 4; ++k) st.ob[e][k] = __fadd_rn(st.ob[e][k], sum[k]);
