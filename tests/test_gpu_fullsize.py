@@ -318,11 +318,12 @@ def test_width_4608_quantize_survivors(obc, orc):
     assert int(c[live != 0].min()) >= 0 and int(c[live != 0].max()) <= maxq
 
 
-@pytest.mark.parametrize("d_col,kb", [(2400, 30), (3200, 14), (4200, 12)])
+@pytest.mark.parametrize("d_col,kb", [(2400, 30), (3200, 32), (4200, 36)])
 def test_wide_block_pruning_first_blocks(obc, orc, d_col, kb):
     """Block pruning (blocks of 4) above 2304 columns runs on the panel variants with six, eight and
-    nine owned indices per thread (blocks of 40, 28 and 24 steps); the oracle replays the first
-    block steps (two to three such blocks of steps) of one row."""
+    nine owned indices per thread (blocks of 40, 28 and 24 steps, which share a flush in threes and fours
+    at the latter two); the oracle replays the first block steps (three of the 40, more than one such
+    group and its flush of the others) of one row."""
     W, X, _ = obc_inputs.make_layer("ffn768x3072", device="cuda", d_row=2, d_col=d_col, n_samples=8000)
     R, d = W.shape
     assert d == d_col
@@ -335,11 +336,11 @@ def test_wide_block_pruning_first_blocks(obc, orc, d_col, kb):
 
 def test_width_3200_first_steps(obc, orc):
     """Live sizes 3073..4096 run on the panel variant with eight owned indices per thread and blocks of
-    28 steps; the oracle replays the first 60 steps (two blocks and a flush each, then a part) of one
-    row."""
+    28 steps; the oracle replays the first 130 steps (three blocks that share a flush, then a part of the
+    next group) of one row."""
     W, X, _ = obc_inputs.make_layer("ffn768x3072", device="cuda", d_row=2, d_col=3200, n_samples=8000)
     Hinv = obc.obc_invert(obc.obc_hessian(X))
-    k = 60
+    k = 130
     res = obc.obc_prune_rows(W, Hinv, k_steps=k)
     obc.obc_check()
     st = RowParity()

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import obc_inputs
-from tests.parity import RowParity, check_block_row, check_row
+from tests.parity import FP32_ORDER_GAP, RowParity, check_block_row, check_row
 
 pytestmark = pytest.mark.gpu
 
@@ -301,6 +301,46 @@ def test_panels_that_share_a_flush(obc, orc, d, k):
     variant, the last step inside a group."""
     W, X = _layer("conv64x576", d_col=d, d_row=2, n_samples=2 * d)
     _check_prune(obc, orc, W, _hinv(obc, X), k, (0, 0), 2, rows=[1])
+
+
+@pytest.mark.parametrize("d,k", [(3200, 130), (4200, 150)])
+def test_wide_quantization_and_n_m_first_steps(obc, orc, d, k):
+    """OBQ and the N:M rule on panels that share a flush, past one group of three or four: the first steps
+    of a row against the oracle (OBQ follows the GPU's order; a pick may be above the least score by no
+    more than fp32 storage explains)."""
+    W, X = _layer("conv64x576", d_col=d, d_row=2, n_samples=2 * d)
+    Hinv = _hinv(obc, X)
+    _check_prune(obc, orc, W, Hinv, k, (2, 4), 2, rows=[1])
+    delta, offset, maxq = obc.obc_minmax_grid(W, 4)
+    res = obc.obc_quant_rows(W, Hinv, delta, offset, maxq)
+    obc.obc_check()
+    order, loss, codes = _np(res["order"][1]), _np(res["loss"][1])[:k], _np(res["codes"][1])
+    ref = orc.quant_row(_np(Hinv).astype(np.float64), _np(W[1]).astype(np.float64),
+                        (float(delta[1]), float(offset[1]), maxq), k_steps=k, forced=order[:k].astype(np.int32))
+    gap = np.abs(ref.pick_score - ref.min_score)
+    assert np.all(gap <= FP32_ORDER_GAP * ref.min_score + 1e-12 * ref.min_score.max())
+    assert abs(loss.sum() - ref.loss.sum()) <= 1e-3 * ref.loss.sum()
+    assert np.array_equal(codes[order[:k]], ref.codes[order[:k]])
+    assert sorted(order.tolist()) == list(range(d))
+
+
+@pytest.mark.parametrize("mode", ["prune", "n_m", "quant"])
+def test_shared_flushes_leave_no_trace(obc, mode):
+    """From 96 rows on two panels of 2416 .. 2815 columns share a flush, with fewer each has its own: the
+    results are the same bit for bit."""
+    W, X = _layer("conv64x576", d_col=2600, d_row=96, n_samples=6000)
+    Hinv = _hinv(obc, X)
+
+    def solve(rows):
+        if mode == "quant":
+            delta, offset, maxq = obc.obc_minmax_grid(rows, 4)
+            r = obc.obc_quant_rows(rows, Hinv, delta, offset, maxq)
+            return r["order"], r["loss"], r["W"], r["codes"]
+        r = obc.obc_prune_rows(rows, Hinv, k_steps=300, nm=(2, 4) if mode == "n_m" else (0, 0))
+        return r["order"], r["loss"], r["W"]
+
+    for many, few in zip(solve(W), solve(W[:8].contiguous())):
+        assert torch.equal(many[:8], few)
 
 
 @pytest.mark.parametrize("strategy", [1, 2])
