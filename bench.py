@@ -226,7 +226,8 @@ def run_workload(ctx, pkg, workload, steps, warmup, strategy, recover="auto"):
     return dict(workload=workload, task=task, R=R, d=d, N=N, k_steps=k_steps, nm=nm, row_steps=row_steps,
                 ms_per_step=1e3 * wall / steps, value=row_steps / (wall / steps),
                 stages_ms={k: float(np.mean(v)) for k, v in stage_ms.items() if v}, roofline=roofline,
-                hessian_mfma_frac=hess_tf / MFMA_SPLIT_PEAK_TFLOPS,
+                hessian_mfma_frac=hess_tf / MFMA_F32_PEAK_TFLOPS,          # of the fp32 matrix-core peak (may exceed 1)
+                hessian_split_mfma_frac=hess_tf / MFMA_SPLIT_PEAK_TFLOPS,   # of what six bf16 products leave
                 W=(Wfit if task == "seqobq4" else W), Hinv=H, out=out, grid=grid)
 
 
@@ -362,7 +363,7 @@ def main():
         "config": {"workload": args.workload, "d_row": r["R"], "d_col": r["d"], "n_samples": r["N"], "task": r["task"],
                    "strategy": args.strategy, "row_steps": r["row_steps"], "recover": args.recover},
         "stages_ms": r["stages_ms"],
-        "hessian_mfma_frac": r["hessian_mfma_frac"],
+        "hessian_mfma_frac": r["hessian_mfma_frac"], "hessian_split_mfma_frac": r["hessian_split_mfma_frac"],
         "roofline": r["roofline"],
     }
     # ---- the oracle on the host cores, on a bounded sample of rows of the same layer
@@ -377,7 +378,8 @@ def main():
         line["second_layer"] = {
             "workload": SECOND_WORKLOAD, "d_row": s["R"], "d_col": s["d"], "n_samples": s["N"],
             "value": s["value"], "unit": "row-steps/s", "ms_per_step": s["ms_per_step"], "steps": min(args.steps, 3),
-            "stages_ms": s["stages_ms"], "hessian_mfma_frac": s["hessian_mfma_frac"], "roofline": s["roofline"],
+            "stages_ms": s["stages_ms"], "hessian_mfma_frac": s["hessian_mfma_frac"],
+            "hessian_split_mfma_frac": s["hessian_split_mfma_frac"], "roofline": s["roofline"],
         }
     print(json.dumps(line))
 
