@@ -18,13 +18,15 @@
  *    size comes from the matching *_workspace_bytes query (host call, no GPU work).
  *  - All work is enqueued on the HIP stream given to obc_create and is asynchronous with
  *    respect to the host, except obc_invert, obc_refit and obc_check, which wait for the stream,
- *    and obc_prune_rows / obc_quant_rows when given a live mask, which wait once at their start
- *    (the smallest number of already-pruned weights over the rows is read back).
+ *    and obc_prune_rows / obc_quant_rows when given a live mask of more than 192 columns, which wait once
+ *    at their start (the smallest number of already-pruned weights over the rows is read back).
  *  - Every call returns 0 (OBC_OK) or a negative OBC_ERR_* code; nothing throws or aborts
  *    across this boundary.  obc_last_error gives a text for the last failure on a context.
  *    Conditions only a kernel can see (a non-positive or non-finite pivot [H^-1]_pp) are
  *    latched on the device and reported by obc_check.
- *  - Results are deterministic: the same inputs give bit-identical outputs.
+ *  - Results are deterministic: the same call on the same inputs gives bit-identical outputs.  (The two
+ *    row-solver strategies round differently, and a workspace below the query makes OBC_STRATEGY_AUTO take
+ *    the other one, see there.)
  *  - Matrices and results are fp32.  obc_invert, obc_refit and obc_reconstruct_rows factorise in fp64
  *    internally and round the result; the row solvers keep a row's weights and the diagonal of its
  *    inverse in fp64 and the matrix itself in fp32.
@@ -75,8 +77,10 @@ int obc_check(obc_ctx *ctx);
  * fills one obc_kernel_stat per kernel class: launches, summed duration, and the algorithmic
  * bytes / flops of those launches (what the method needs moved / computed under the schedule
  * the kernel implements: the flush reads and writes one triangle of the surviving m x m part of
- * each row's (symmetric) inverse once per block of B steps, 8 m(m+1)/2 bytes and B m(m+1) flops
- * per row; a panel reads one matrix row per step; the rank-1 kernel moves 8 m^2 bytes per step). */
+ * each row's (symmetric) inverse once per block of B steps, or once for several such blocks above 2304
+ * columns, 8 m(m+1)/2 bytes and m(m+1) flops per step per row; a panel reads one matrix row per step and
+ * the vectors of the blocks since the last flush, 4 m bytes each; the rank-1 kernel moves 8 m^2 bytes
+ * per step). */
 #define OBC_KERNEL_PANEL 0
 #define OBC_KERNEL_FLUSH 1
 #define OBC_KERNEL_RANK1 2
@@ -101,7 +105,7 @@ int obc_membench(obc_ctx *ctx, int kind, int streaming, const void *src, void *d
                  int reps, double *ms_per_pass);
 
 /* What the matrix cores of this GPU sustain on nothing but independent MFMA instructions, four
- * wavefronts on every SIMD: kind 0 = v_mfma_f32_32x32x2_f32 (the Hessian's instruction), kind 1 =
+ * wavefronts on every SIMD: kind 0 = v_mfma_f32_32x32x2_f32 (the flush's instruction), kind 1 =
  * v_mfma_f64_16x16x4_f64 (the factorisation's).  Every wavefront issues 4 * iters instructions per
  * pass; one warm-up pass and `reps` timed ones on the context's stream.  Returns the mean
  * milliseconds per pass and the flops of a pass.  Synchronous. */
@@ -213,7 +217,8 @@ int obc_cross_workspace_bytes(int d_row, int d_col, int64_t N, size_t *bytes);
 
 /* C (d_row x d_col, device, row-major) = 2 Y X^T, or C += 2 Y X^T when accumulate != 0.
  *   X  device, d_col x N, leading dimension ldx >= N;  Y  device, d_row x N, ldy >= N.
- * fp32 matrix cores, fixed summation order (deterministic).  Errors as obc_hessian. */
+ * Matrix cores, the precision of fp32 products and sums, fixed summation order (deterministic).  Errors as
+ * obc_hessian. */
 int obc_cross(obc_ctx *ctx, const float *X, const float *Y, int d_col, int d_row, int64_t N, int64_t ldx,
               int64_t ldy, int accumulate, float *C, void *ws, size_t ws_bytes);
 

@@ -819,9 +819,10 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
             pa.last = j == panels - 1;
             pa.threads = (m_max + 63) / 64 * 64;
             {
-                // a panel reads one (corrected) matrix row per step: 4 m bytes, and does ~B m flops on it
+                // a panel reads one matrix row and the outer block's earlier vectors per step, 4 m bytes each,
+                // and does ~B m flops on it
                 const int steps = (host_total - host_done < v->B) ? host_total - host_done : v->B;
-                obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * steps * 4.0 * m_max,
+                obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * steps * 4.0 * (1 + pa.old) * m_max,
                              (double)R * steps * (double)(steps + 2 * pa.old) * m_max);
                 if ((j == 0 ? first : next)(mode, R, lds_nm, st, pa) != 0)
                     return obc_fail(ctx, OBC_ERR_HIP, "panel kernel: cannot set its dynamic LDS size");

@@ -303,6 +303,17 @@ def test_panels_that_share_a_flush(obc, orc, d, k):
     _check_prune(obc, orc, W, _hinv(obc, X), k, (0, 0), 2, rows=[1])
 
 
+def test_panel_account_counts_the_vectors_read_again(obc):
+    """Three panels of 28 steps that share a flush: a step reads a matrix row and every vector since the last
+    flush, 4 bytes per column each."""
+    W, X = _layer("conv64x576", d_col=3200, d_row=2, n_samples=6400)
+    Hinv = _hinv(obc, X)
+    obc.obc_profile_begin()
+    obc.obc_prune_rows(W, Hinv, k_steps=84, strategy=2)
+    stat = obc.obc_profile_end()["panel"]
+    assert stat["launches"] == 3 and stat["bytes"] == 2 * 28 * 4 * 3200 * (1 + (1 + 28) + (1 + 56))
+
+
 @pytest.mark.parametrize("d,k", [(3200, 130), (4200, 150)])
 def test_wide_quantization_and_n_m_first_steps(obc, orc, d, k):
     """OBQ and the N:M rule on panels that share a flush, past one group of three or four: the first steps
