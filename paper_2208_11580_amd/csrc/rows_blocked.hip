@@ -46,6 +46,10 @@ namespace {
 
 using namespace obc_blocked;
 
+// up to this width a call with a mask waits for nothing (it can be captured): its panels eliminate the
+// pruned indices, and there is no bulk elimination
+constexpr int kNoWaitMaxD = 192;
+
 size_t carve(BlockedWs *ws, void *base, int R, int d)
 {
     size_t off = 0;
@@ -67,8 +71,8 @@ size_t carve(BlockedWs *ws, void *base, int R, int d)
     char *s2 = take((size_t)R * sizeof(int)), *s3 = take((size_t)R * sizeof(int));
     char *s4 = take((size_t)R * sizeof(int));
     char *pb = take((size_t)R * d);
-    char *pmb = take((size_t)R * BMAX * BMAX * sizeof(double));
-    char *ptb = take((size_t)R * BMAX * BMAX * sizeof(double));
+    const size_t bulk = d > kNoWaitMaxD ? (size_t)R * BMAX * BMAX * sizeof(double) : 0;
+    char *pmb = take(bulk), *ptb = take(bulk);
     char *psc = take(256);
     if (ws) {
         ws->Mb = (double *)pmb; ws->Tb = (double *)ptb; ws->scal = (int *)psc;
@@ -642,9 +646,6 @@ const Variant *pick_variant(int m, int R)
 }  // namespace
 
 namespace obc_rows {
-
-// up to this width a call with a mask waits for nothing (it can be captured)
-constexpr int kNoWaitMaxD = 192;
 
 int blocked_max_d() { return kVariants[kNumVariants - 1].cap; }
 

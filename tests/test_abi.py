@@ -40,6 +40,15 @@ def test_library_exports_every_declared_symbol(lib):
         assert hasattr(lib, name), name
 
 
+def test_small_rows_hold_no_bulk_elimination(lib):
+    """Up to 192 columns a row's workspace is two matrices, 128 vectors and its state, without the two 64 x 64
+    fp64 blocks of the bulk elimination."""
+    n = ctypes.c_size_t()
+    for R, d in ((1000, 65), (1000, 100), (1, 192), (5000, 192)):
+        assert lib.obc_rows_workspace_bytes(R, d, 2, ctypes.byref(n)) == 0
+        assert n.value <= R * (2 * 4 * (d * d + 3) + 128 * 4 * (d + 4) + 25 * d + 32) + 20 * 256, (R, d)
+
+
 def test_second_moment_workspaces_serve_smaller_batches(lib):
     """Calibration data arrives in batches, the last one ragged: what is enough for N samples is enough for
     fewer."""
