@@ -1,7 +1,7 @@
 // fp64 building blocks on 64 x 64 blocks, shared by the inverse (invert.hip) and the closed-form
 // recovery of pruned rows (reconstruct.hip): the one-wavefront Cholesky factorisation + inverse of a
-// diagonal block, and a 64 x 64 tile of a strided product on the fp64 matrix core
-// (v_mfma_f64_16x16x4_f64).
+// diagonal block, by one wavefront or by a workgroup of four, and products of 64 x 64 tiles on the fp64
+// matrix core (v_mfma_f64_16x16x4_f64).
 #pragma once
 
 #include "common.h"
@@ -9,7 +9,6 @@
 namespace obc_dense64 {
 
 constexpr int NB = 64;   // block-column width and GEMM tile edge
-constexpr int GK = 16;   // GEMM k-slab
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double readlane_f64(double v, int l)
@@ -518,144 +517,6 @@ __device__ __forceinline__ void potrf_wg_core(double *__restrict__ Linv, int *st
         }
     }
     if (threadIdx.x == 0 && bad) obc_latch(status, err);
-}
-
-// C (M x N, leading dimension ldc) = alpha * sum_k a(i,k) b(k,j) + beta * C, with
-// a(i,k) = A[i*as_i + k*as_k] and b(k,j) = B[k*bs_k + j*bs_j] (strides express transposes).
-//   lower_only : skip tiles strictly above the block diagonal
-//   klo_mode   : 0 = k starts at 0; 1 = at the tile's first column (b is lower triangular);
-//                2 = at max(first row, first column) (a^T and b lower triangular)
-//   out32      : nullable; when given the result is rounded to fp32 there (leading dimension
-//                ldc) and mirrored across the diagonal instead of being written to C
-struct GemmArgs {
-    int M, N, K;
-    double alpha;
-    const double *A;
-    int64_t as_i, as_k;
-    const double *B;
-    int64_t bs_k, bs_j;
-    double beta;
-    double *C;
-    int64_t ldc;
-    int lower_only, klo_mode;
-    float *out32;
-};
-
-constexpr int GEMM_LDS = 2 * GK * (NB + 1);   // doubles: the two operand slabs of a tile
-
-__device__ __forceinline__ void gemm64_tile(const GemmArgs &g, int ti, int tj, double *lds)
-{
-    const int M = g.M, N = g.N, K = g.K;
-    const double alpha = g.alpha, beta = g.beta;
-    const double *A = g.A, *B = g.B;
-    double *C = g.C;
-    const int64_t as_i = g.as_i, as_k = g.as_k, bs_k = g.bs_k, bs_j = g.bs_j, ldc = g.ldc;
-    const int lower_only = g.lower_only, klo_mode = g.klo_mode;
-    float *out32 = g.out32;
-    if (ti * NB >= M || tj * NB >= N) return;
-    if (lower_only && tj > ti) return;
-    double(*As)[NB + 1] = reinterpret_cast<double(*)[NB + 1]>(lds);
-    double(*Bs)[NB + 1] = reinterpret_cast<double(*)[NB + 1]>(lds + GK * (NB + 1));
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;   // 2 x 2 waves, 32 x 32 outputs each (2 x 2 MFMA tiles)
-    const int i0 = ti * NB, j0 = tj * NB;
-    int kbeg = 0;
-    if (klo_mode == 1) kbeg = j0;
-    if (klo_mode == 2) kbeg = i0 > j0 ? i0 : j0;
-    kbeg = kbeg / GK * GK;
-
-    doublex4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = doublex4{0.0, 0.0, 0.0, 0.0};
-
-    const bool a_kfast = (as_k == 1);
-    const bool b_jfast = (bs_j == 1);
-    // the next k-slab is fetched into registers while the current one is multiplied
-    double ra[4], rb[4];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            int e = tid + h * 256;
-            int i, k;
-            if (a_kfast) { i = e / GK; k = e % GK; } else { k = e / NB; i = e % NB; }
-            double v = 0.0;
-            if (i0 + i < M && k0 + k < K) v = A[(int64_t)(i0 + i) * as_i + (int64_t)(k0 + k) * as_k];
-            ra[h] = v;
-            int j, kb;
-            if (b_jfast) { kb = e / NB; j = e % NB; } else { j = e / GK; kb = e % GK; }
-            double u = 0.0;
-            if (j0 + j < N && k0 + kb < K) u = B[(int64_t)(k0 + kb) * bs_k + (int64_t)(j0 + j) * bs_j];
-            rb[h] = u;
-        }
-    };
-    auto stash = [&]() {
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            int e = tid + h * 256;
-            int i, k;
-            if (a_kfast) { i = e / GK; k = e % GK; } else { k = e / NB; i = e % NB; }
-            As[k][i] = ra[h];
-            int j, kb;
-            if (b_jfast) { kb = e / NB; j = e % NB; } else { j = e / GK; kb = e % GK; }
-            Bs[kb][j] = rb[h];
-        }
-    };
-    if (kbeg < K) fetch(kbeg);
-    for (int k0 = kbeg; k0 < K; k0 += GK) {
-        stash();
-        __syncthreads();
-        if (k0 + GK < K) fetch(k0 + GK);
-        // v_mfma_f64_16x16x4: lane l supplies a(i = l % 16, k = l / 16) and b(k = l / 16, j = l % 16)
-        const int kl = lane >> 4, il = lane & 15;
-#pragma unroll
-        for (int kk = 0; kk < GK; kk += 4) {
-            double a0 = As[kk + kl][wm * 32 + il];
-            double a1 = As[kk + kl][wm * 32 + 16 + il];
-            double b0 = Bs[kk + kl][wn * 32 + il];
-            double b1 = Bs[kk + kl][wn * 32 + 16 + il];
-            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // accumulator layout of the fp64 16x16 MFMA: lane holds column (lane % 16) and rows
-    // 4 * r + lane / 16, r = 0..3
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int i = i0 + wm * 32 + mt * 16 + 4 * r + (lane >> 4);
-                int j = j0 + wn * 32 + nt * 16 + (lane & 15);
-                if (i >= M || j >= N) continue;
-                double av = acc[mt][nt][r];
-                if (out32) {
-                    float v = (float)(alpha * av);
-                    out32[(int64_t)i * ldc + j] = v;
-                    if (ti != tj) out32[(int64_t)j * ldc + i] = v;
-                } else {
-                    double v = alpha * av;
-                    if (beta != 0.0) v += beta * C[(int64_t)i * ldc + j];
-                    C[(int64_t)i * ldc + j] = v;
-                }
-            }
-}
-
-__host__ __device__ inline GemmArgs mk(int M, int N, int K, double alpha, const double *A, int64_t as_i, int64_t as_k, const double *B,
-            int64_t bs_k, int64_t bs_j, double beta, double *C, int64_t ldc, int lower_only, int klo_mode,
-            float *out32)
-{
-    GemmArgs g;
-    g.M = M; g.N = N; g.K = K; g.alpha = alpha; g.A = A; g.as_i = as_i; g.as_k = as_k; g.B = B;
-    g.bs_k = bs_k; g.bs_j = bs_j; g.beta = beta; g.C = C; g.ldc = ldc; g.lower_only = lower_only;
-    g.klo_mode = klo_mode; g.out32 = out32;
-    return g;
 }
 
 }  // namespace obc_dense64

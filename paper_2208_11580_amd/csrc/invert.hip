@@ -42,10 +42,27 @@ __global__ __launch_bounds__(64) void potrf_wave_kernel(double *__restrict__ A, 
     potrf_wave(A + (int64_t)blockIdx.x * strideA, lda, bs, Linv + (int64_t)blockIdx.x * strideL, status, err, lds);
 }
 
-__global__ __launch_bounds__(256) void gemm64_kernel(GemmArgs g)
+// A block row's solve: the 64-column tile at Yp of block row k becomes T Yp (T = L_kk^-1, bs x bs, Nc columns);
+// the workgroup overwrites exactly the block it has read.
+__device__ __forceinline__ void solve_tile(const double *T, double *Yp, int d, int bs, int Nc, double *As, double *Bs)
 {
-    __shared__ double lds[GEMM_LDS];
-    gemm64_tile(g, blockIdx.y, blockIdx.x, lds);
+    doublex4 acc[2][2];
+    double ra[16], rb[16];
+    tile_fetch(ra, T, NB, bs, bs);                       // a(i, k) = T[i][k]
+    tile_fetch(rb, Yp, d, bs, Nc);                       // b(k, j) = Y[k][j]
+    tile_park<true>(As, ra);
+    tile_park<false>(Bs, rb);
+    __syncthreads();
+    tile_mma(acc, As, Bs);
+    tile_each(acc, [&](int i, int j, double v) { if (i < bs && j < Nc) Yp[(int64_t)i * d + j] = v; });
+}
+
+// the solve of the block row that starts at row k0
+__global__ __launch_bounds__(256) void solve_row_kernel(const double *__restrict__ T, double *__restrict__ Y, int d, int k0, int bs)
+{
+    __shared__ double lds[2 * NB * PL];
+    const int c0 = blockIdx.x * NB, nc = k0 + bs;
+    solve_tile(T, Y + (int64_t)k0 * d + c0, d, bs, (nc - c0 < NB) ? nc - c0 : NB, lds, lds + NB * PL);
 }
 
 // Step 3: tile (ti, tj), tj <= ti, of H^-1 = Y^T Y with Y = L^-1 lower triangular: the sum runs over
@@ -182,17 +199,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(StepArgs s)
     if (blockIdx.z == 2) {
         const int ncprev = s.kprev0 + s.bsprev, c0 = blockIdx.x * NB;
         if (blockIdx.y != 0 || s.bsprev <= 0 || c0 >= ncprev) return;
-        double *Yp = s.Y + (int64_t)s.kprev0 * d + c0;
-        const int Nc = (ncprev - c0 < NB) ? ncprev - c0 : NB;
-        double ra[16], rb[16];
-        tile_fetch(ra, s.Tprev, NB, s.bsprev, s.bsprev);     // a(i, k) = T[i][k]
-        tile_fetch(rb, Yp, d, s.bsprev, Nc);                 // b(k, j) = Y[k][j]
-        tile_park<true>(As, ra);
-        tile_park<false>(Bs, rb);
-        __syncthreads();
-        tile_mma(acc, As, Bs);
-        // the workgroup overwrites exactly the block it has read
-        tile_each(acc, [&](int i, int j, double v) { if (i < s.bsprev && j < Nc) Yp[(int64_t)i * d + j] = v; });
+        solve_tile(s.Tprev, s.Y + (int64_t)s.kprev0 * d + c0, d, s.bsprev, (ncprev - c0 < NB) ? ncprev - c0 : NB, As, Bs);
         return;
     }
     const int ti = blockIdx.y, tj = blockIdx.x;
@@ -344,14 +351,9 @@ int factor_inverse(obc_ctx *ctx, const float *H, int d, void *ws, double **Yout)
             chol_step_kernel<<<dim3((unsigned)(tm > tc ? tm : tc), (unsigned)tm, 3), 256, 0, st>>>(sa);
         } else {
             // the last block column: finish the previous block row and this one
-            if (bsprev > 0) {
-                double *Yp = Y + (int64_t)kprev0 * d;
-                const int ncp = kprev0 + bsprev;
-                gemm64_kernel<<<grid64(bsprev, ncp), 256, 0, st>>>(
-                    mk(bsprev, ncp, bsprev, 1.0, Tk - (int64_t)NB * NB, NB, 1, Yp, d, 1, 0.0, Yp, d, 0, 0, nullptr));
-            }
-            double *Yk = Y + (int64_t)k0 * d;
-            gemm64_kernel<<<grid64(bs, nc), 256, 0, st>>>(mk(bs, nc, bs, 1.0, Tk, NB, 1, Yk, d, 1, 0.0, Yk, d, 0, 0, nullptr));
+            if (bsprev > 0)
+                solve_row_kernel<<<(kprev0 + bsprev + NB - 1) / NB, 256, 0, st>>>(Tk - (int64_t)NB * NB, Y, d, kprev0, bsprev);
+            solve_row_kernel<<<(nc + NB - 1) / NB, 256, 0, st>>>(Tk, Y, d, k0, bs);
         }
         kprev0 = k0;
         bsprev = bs;
