@@ -53,7 +53,8 @@ extern "C" {
  * d_col = 4608 and the streamed rank-1 solver beyond (as far as its per-row vectors fit in LDS,
  * d_col <= ~5600; larger d_col returns OBC_ERR_BAD_SHAPE).  Where a row's matrix fits in LDS
  * (d_col <= ~190) AUTO needs no workspace: it takes the rank-1 solver when it is given less than the
- * query says (up to d_col = 64 the query says 256 bytes and the blocked solver needs none). */
+ * query says (up to d_col = 64 the query says 256 bytes and the blocked solver needs none), or when
+ * that would be more than 4 GiB. */
 #define OBC_STRATEGY_AUTO 0
 #define OBC_STRATEGY_RANK1 1   /* literal Algorithm 1: one rank-1 elimination per step */
 #define OBC_STRATEGY_BLOCKED 2 /* same arithmetic result, eliminations applied in blocks */
