@@ -285,10 +285,12 @@ __global__ __launch_bounds__(1024) void select_small_kernel(const float *__restr
         }
 }
 
+// (a launch holds fewer than 2^32 threads: larger layers take several turns of it)
+constexpr int64_t kZeroBlocks = 1 << 20;
+
 __global__ __launch_bounds__(256) void zero_u8_kernel(uint8_t *p, int64_t n)
 {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) p[e] = 0;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) p[e] = 0;
 }
 
 __global__ __launch_bounds__(256) void scatter_mask_kernel(const int32_t *__restrict__ order,
@@ -372,7 +374,8 @@ static int global_select_enqueue(obc_ctx *ctx, const float *loss, const int32_t 
         OBC_LAUNCH_CHECK(ctx, "select_small_kernel");
         return OBC_OK;
     }
-    zero_u8_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mask, n);
+    const int64_t zero_blocks = (n + 255) / 256;
+    zero_u8_kernel<<<(unsigned)(zero_blocks < kZeroBlocks ? zero_blocks : kZeroBlocks), 256, 0, st>>>(mask, n);
     if (k == 0) {
         fill_i32_kernel<<<(R + 255) / 256, 256, 0, st>>>(counts, R, 0);
         OBC_LAUNCH_CHECK(ctx, "fill_i32_kernel");

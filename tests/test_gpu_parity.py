@@ -667,11 +667,14 @@ def test_global_select_sizes(obc, orc, R, d):
 
 
 def test_global_select_beyond_32_bit_sums(obc):
-    """More than 2^32 weights, each bucket of the selection below that: the ranks need 64 bits."""
+    """More than 2^32 weights, each bucket of the selection below that: the ranks need 64 bits, and the mask's
+    memory, which held something else before, is cleared to its end."""
     R, d = 65537, 65536
+    used = torch.full((R, d), 7, dtype=torch.uint8, device="cuda")
     loss = torch.ones(R, d, device="cuda")
     loss[:, d // 2:] = 2.0
     order = torch.arange(d, dtype=torch.int32, device="cuda").expand(R, d).contiguous()
+    del used
     counts, mask = obc.obc_global_select(loss, order, R * d - 10)
     want = torch.full((R,), d, dtype=torch.int32, device="cuda")
     want[-1] = d - 10                       # ties go to the rows in index order
