@@ -107,7 +107,7 @@ __device__ __forceinline__ T scan256(T v, T *sums)
 }
 
 // choose the byte bucket that holds the wanted rank; clear the histogram for the next pass.  (The
-// buckets' prefix sums by all threads: a walk over them by one took 8 .. 11 us a pass, now 2.  In 64 bits:
+// buckets' prefix sums by all threads: a walk over them by one took 8 .. 11 us a pass, now 5.  In 64 bits:
 // a layer may have more than 2^32 weights (a single bucket, whose count is 32 bits, may not).)
 __global__ __launch_bounds__(256) void sel_pick_kernel(SelState *st, int pass)
 {

@@ -20,7 +20,7 @@
 // exactly symmetric) -- no float atomics, results are deterministic.
 //
 // Bound by the matrix cores' issue and the loads' latency (half of the bf16 rate): 2304 x 50 000 in
-// 1.50 ms, 177 TFLOP/s of the d^2 N flop (fp32 MFMA: 2.37 ms, 112); 576 x 50 000 0.148 ms (0.326).
+// 1.52 ms, 175 TFLOP/s of the d^2 N flop (fp32 MFMA: 2.37 ms, 112); 576 x 50 000 0.150 ms (0.326).
 #include "common.h"
 
 namespace {
