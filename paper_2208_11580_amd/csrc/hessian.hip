@@ -11,8 +11,8 @@
 // running sums once, so a sum takes N / 16 roundings (the fp32 MFMA's took N / 2): against fp64 the
 // relative error is 0.6e-7 .. 1.2e-7 (fp32 MFMA: 1.0e-7 .. 4.3e-7) over d = 32 .. 3072, N = 256 ..
 // 50 000.  A workgroup that meets what the split cannot hold -- a smaller value, an infinity, a product
-// that overflows -- forms its piece again on the fp32 matrix instructions; to notice it costs 1 .. 2 % of
-// the kernel (576 x 20 001: 79 -> 80.5 us, 3072 x 20 001: 1034 -> 1043 us).
+// that overflows -- forms its piece again on the fp32 matrix instructions; to notice it costs 1 .. 2 % of a
+// large call (576 x 20 001: 79 -> 80.5 us, 3072 x 20 001: 1034 -> 1043 us) and 0.5 .. 1 us of a small one.
 //
 // Only tiles on or above the block diagonal are computed; the contraction length N is cut into S
 // slices so that small d still fills 256 CUs.  Slices go to a workspace and are summed in a fixed
@@ -52,8 +52,9 @@ struct Plan {
 // where they do not (576 x 50 000: 148 against 199 us).
 //
 // A workspace for N samples has to serve every smaller batch, but the best S goes up and down with N
-// (whole slabs only).  So S is bounded by the S that is best for fractions of slabs, and the workspace
-// sized by that: its cost is N g(S) + h(S) with h growing, which makes it grow with N.
+// (whole slabs only).  The S that is best for fractions of slabs grows with N -- its cost is N g(S) + h(S)
+// with h growing -- and S is bounded by a quarter more than that, which leaves the choice as it is without
+// a bound (2500 random sizes); the workspace holds that many.
 template <class Count>
 inline Plan make_plan(Count ntiles, int64_t N)
 {
@@ -72,20 +73,28 @@ inline Plan make_plan(Count ntiles, int64_t N)
     Plan best = {128, 1, 1, 0};
     double best_cost = 0.0;
     const int64_t smax = N / (2 * BK) < 1 ? 1 : N / (2 * BK) < 64 ? N / (2 * BK) : 64;
+    // (a small call waits for this: one division per S)
+    double slabs[65], whole[65];
+    for (int64_t c = 1; c <= smax; ++c) {
+        slabs[c] = (double)N / (double)(BK * c);
+        whole[c] = (double)(int64_t)slabs[c];
+        if (whole[c] < slabs[c]) whole[c] += 1.0;
+    }
     for (int tile = 128; tile <= 256; tile += 128) {
         const int64_t n = ntiles(tile);
         int64_t bound = 1;
-        double bound_cost = cost(tile, n, 1, (double)N / BK);
+        double bound_cost = cost(tile, n, 1, slabs[1]);
         for (int64_t c = 2; c <= smax; ++c) {
-            const double t = cost(tile, n, c, (double)N / (double)(BK * c));
+            const double t = cost(tile, n, c, slabs[c]);
             if (t < bound_cost) {
                 bound_cost = t;
                 bound = c;
             }
         }
+        bound = bound + bound / 4 + 1 < smax ? bound + bound / 4 + 1 : smax;
         if (bound > best.cap) best.cap = (int)bound;
         for (int64_t c = 1; c <= bound; ++c) {
-            const double t = cost(tile, n, c, (double)(((N + c - 1) / c + BK - 1) / BK));
+            const double t = cost(tile, n, c, whole[c]);
             if (best_cost == 0.0 || t < best_cost) {
                 best_cost = t;
                 best.tile = tile;
@@ -453,12 +462,11 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     if (!X || !H) return obc_fail(ctx, OBC_ERR_BAD_ARG, "obc_hessian: null X or H");
     if (d <= 0 || N <= 0) return obc_fail(ctx, OBC_ERR_BAD_ARG, "obc_hessian: d and N must be positive");
     if (ldx < N) return obc_fail(ctx, OBC_ERR_BAD_SHAPE, "obc_hessian: ldx (%lld) < N (%lld)", (long long)ldx, (long long)N);
-    size_t need;
-    obc_hessian_workspace_bytes(d, N, &need);
+    const Plan p = hessian_plan(d, N);
+    const size_t need = obc_align_up((size_t)p.cap * d * d * sizeof(float), 256);
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_hessian: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
-    const Plan p = hessian_plan(d, N);
     float *partial = (float *)ws;
     int rc = launch_nt<true>(ctx, p, X, d, ldx, X, d, ldx, N, partial);
     if (rc != OBC_OK) return rc;
@@ -490,12 +498,11 @@ int obc_cross(obc_ctx *ctx, const float *X, const float *Y, int d_col, int d_row
     if (ldx < N || ldy < N)
         return obc_fail(ctx, OBC_ERR_BAD_SHAPE, "obc_cross: ldx (%lld) or ldy (%lld) < N (%lld)", (long long)ldx,
                         (long long)ldy, (long long)N);
-    size_t need;
-    obc_cross_workspace_bytes(d_row, d_col, N, &need);
+    const Plan p = cross_plan(d_row, d_col, N);
+    const size_t need = obc_align_up((size_t)p.cap * d_row * d_col * sizeof(float), 256);
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_cross: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
-    const Plan p = cross_plan(d_row, d_col, N);
     float *partial = (float *)ws;
     int rc = launch_nt<false>(ctx, p, Y, d_row, ldy, X, d_col, ldx, N, partial);
     if (rc != OBC_OK) return rc;
