@@ -463,7 +463,7 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     if (d <= 0 || N <= 0) return obc_fail(ctx, OBC_ERR_BAD_ARG, "obc_hessian: d and N must be positive");
     if (ldx < N) return obc_fail(ctx, OBC_ERR_BAD_SHAPE, "obc_hessian: ldx (%lld) < N (%lld)", (long long)ldx, (long long)N);
     const Plan p = hessian_plan(d, N);
-    const size_t need = obc_align_up((size_t)p.cap * d * d * sizeof(float), 256);
+    const size_t need = obc_align_up((size_t)p.S * d * d * sizeof(float), 256);   // (what this N takes of the query's)
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_hessian: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
@@ -499,7 +499,7 @@ int obc_cross(obc_ctx *ctx, const float *X, const float *Y, int d_col, int d_row
         return obc_fail(ctx, OBC_ERR_BAD_SHAPE, "obc_cross: ldx (%lld) or ldy (%lld) < N (%lld)", (long long)ldx,
                         (long long)ldy, (long long)N);
     const Plan p = cross_plan(d_row, d_col, N);
-    const size_t need = obc_align_up((size_t)p.cap * d_row * d_col * sizeof(float), 256);
+    const size_t need = obc_align_up((size_t)p.S * d_row * d_col * sizeof(float), 256);
     if (!ws || ws_bytes < need)
         return obc_fail(ctx, OBC_ERR_WORKSPACE, "obc_cross: workspace of %zu bytes needed, %zu given", need, ws_bytes);
 
