@@ -3,22 +3,27 @@
 #pragma once
 
 #include <atomic>
+#include <type_traits>
 
 #include "rows_blocked.h"
 
 namespace obc_blocked {
 
+constexpr int kNmShift = 16;          // above any index
 constexpr int kBeyond = 0x40000000;   // a byte offset beyond any row's matrix: the load returns 0
 
 // Per-thread state of the panel: everything indexed by the owned element e (compact index
-// tid + e*T) or by the step r inside the block.  All indices are compile-time constants once the
-// step loop is unrolled (panel_steps below), so the arrays live in registers.
+// tid + e*T) or by the step r inside the block.  All indices are compile-time constants (panel_step
+// reaches the step's own vector by branches), so the arrays live in registers.
 template <int EPT, int BR>
 struct PanelRegs {
     double w[EPT], dg[EPT];
+    // original index, ~index where it was pruned before, kGone: no live index.  N:M: the weights that its block
+    // has given up are counted in the bits from kNmShift on (every thread counts for its own: in LDS the counters
+    // were a read in the selection's chain).
     int og[EPT];
-    bool alive[EPT];
-    float u[BR][EPT];   // u_r for the first BR steps of the block; later ones live in LDS
+    float u[BR][EPT];   // u_r for the first BR steps of the block (0 before its step); later ones live in LDS
+    float last[EPT];    // one owned element: the last step's vector, not yet in u
     // block pruning only: row j of the 4 x 4 diagonal block of the current inverse that element j
     // belongs to (entry k = A[j][4 (j / 4) + k]; the element's own slot is not used), and the first
     // position of the block being eliminated
@@ -120,6 +125,17 @@ __device__ __forceinline__ unsigned row16_umin(unsigned v)
     return v;
 }
 
+// the same over each N lanes (a power of two, 4 .. 16, whose values every group of N repeats; uniform result)
+template <int N>
+__device__ __forceinline__ unsigned lanes_umin(unsigned v)
+{
+    v = dpp_umin_stage<0x111>(v);
+    v = dpp_umin_stage<0x112>(v);
+    if constexpr (N > 4) v = dpp_umin_stage<0x114>(v);
+    if constexpr (N > 8) v = dpp_umin_stage<0x118>(v);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 15);
+}
+
 // minimum over the wavefront (uniform result)
 __device__ __forceinline__ unsigned wave_umin(unsigned v)
 {
@@ -131,52 +147,46 @@ __device__ __forceinline__ unsigned wave_umin(unsigned v)
     return a2 < a0 ? a2 : a0;
 }
 
-// minimum over the first 16 lanes' values (every row holds the same 16 values; uniform result)
-__device__ __forceinline__ unsigned row16_umin_all(unsigned v)
-{
-    return (unsigned)__builtin_amdgcn_readlane((int)row16_umin(v), 15);
-}
-
-// acc += sum_i c_i u[i], i < N: coefficient i is in lane L + i of every 16-lane row of c.  The
-// coefficient is taken from its lane by the multiply-add itself (DPP row_newbcast): no lane read, no
-// scalar register (64 of those next to the kernel's other scalars spilled a hundred times a step).
-// A DPP operand must not have been written by the vector ALU within two cycles; the compiler does
-// not look into the block, so it waits itself.
+// acc[e] += sum_i c_i u_i[e], i < 4, for N elements: coefficient i is in lane L + i of every 16-lane row
+// of c.  The coefficient is taken from its lane by the multiply-add itself (DPP row_newbcast): no lane
+// read, no scalar register.  A DPP operand must not have been written by the vector ALU within two
+// cycles; the compiler does not look into the block, so it waits itself.
 template <int L, int N>
-__device__ __forceinline__ void fma_bcast(float &acc, float c, const float (&u)[N])
+__device__ __forceinline__ void fma_bcast(float *acc, float c, const float *u0, const float *u1, const float *u2,
+                                          const float *u3)
 {
-#define OBC_FB(op, lane) "v_fmac_f32_dpp %0, %1, %" #op " row_newbcast:%" #lane " row_mask:0xf bank_mask:0xf\n\t"
-    if constexpr (N == 8)
-        asm("s_nop 1\n\t" OBC_FB(2, 10) OBC_FB(3, 11) OBC_FB(4, 12) OBC_FB(5, 13) OBC_FB(6, 14) OBC_FB(7, 15)
-                OBC_FB(8, 16) OBC_FB(9, 17)
-            : "+v"(acc)
-            : "v"(c), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "v"(u[4]), "v"(u[5]), "v"(u[6]), "v"(u[7]), "n"(L),
-              "n"(L + 1), "n"(L + 2), "n"(L + 3), "n"(L + 4), "n"(L + 5), "n"(L + 6), "n"(L + 7));
-    else if constexpr (N == 4)
-        asm("s_nop 1\n\t" OBC_FB(2, 6) OBC_FB(3, 7) OBC_FB(4, 8) OBC_FB(5, 9)
-            : "+v"(acc)
-            : "v"(c), "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(u[3]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
-    else if constexpr (N == 2)
-        asm("s_nop 1\n\t" OBC_FB(2, 4) OBC_FB(3, 5)
-            : "+v"(acc)
-            : "v"(c), "v"(u[0]), "v"(u[1]), "n"(L), "n"(L + 1));
-    else
-        asm("s_nop 1\n\t" OBC_FB(2, 3) : "+v"(acc) : "v"(c), "v"(u[0]), "n"(L));
+#define OBC_FB(acc, c, u, lane) "v_fmac_f32_dpp %" #acc ", %" #c ", %" #u " row_newbcast:%" #lane " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (N >= 3) {
+        asm("s_nop 1\n\t" OBC_FB(0, 3, 4, 16) OBC_FB(1, 3, 5, 16) OBC_FB(2, 3, 6, 16) OBC_FB(0, 3, 7, 17)
+                OBC_FB(1, 3, 8, 17) OBC_FB(2, 3, 9, 17) OBC_FB(0, 3, 10, 18) OBC_FB(1, 3, 11, 18)
+                    OBC_FB(2, 3, 12, 18) OBC_FB(0, 3, 13, 19) OBC_FB(1, 3, 14, 19) OBC_FB(2, 3, 15, 19)
+            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2])
+            : "v"(c), "v"(u0[0]), "v"(u0[1]), "v"(u0[2]), "v"(u1[0]), "v"(u1[1]), "v"(u1[2]), "v"(u2[0]), "v"(u2[1]),
+              "v"(u2[2]), "v"(u3[0]), "v"(u3[1]), "v"(u3[2]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+        if constexpr (N > 3) fma_bcast<L, N - 3>(acc + 3, c, u0 + 3, u1 + 3, u2 + 3, u3 + 3);
+    } else if constexpr (N == 2) {
+        asm("s_nop 1\n\t" OBC_FB(0, 2, 3, 11) OBC_FB(1, 2, 4, 11) OBC_FB(0, 2, 5, 12) OBC_FB(1, 2, 6, 12)
+                OBC_FB(0, 2, 7, 13) OBC_FB(1, 2, 8, 13) OBC_FB(0, 2, 9, 14) OBC_FB(1, 2, 10, 14)
+            : "+v"(acc[0]), "+v"(acc[1])
+            : "v"(c), "v"(u0[0]), "v"(u0[1]), "v"(u1[0]), "v"(u1[1]), "v"(u2[0]), "v"(u2[1]), "v"(u3[0]), "v"(u3[1]),
+              "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+    } else {
+        asm("s_nop 1\n\t" OBC_FB(0, 1, 2, 6) OBC_FB(0, 1, 3, 7) OBC_FB(0, 1, 4, 8) OBC_FB(0, 1, 5, 9)
+            : "+v"(acc[0])
+            : "v"(c), "v"(u0[0]), "v"(u1[0]), "v"(u2[0]), "v"(u3[0]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+    }
 #undef OBC_FB
 }
 
-// acc += sum_{R0 <= r < S} c_r u(r): coefficient r in lane r % 16 of c[r / 16]
-template <int S, int R0, int NC, typename U>
-__device__ __forceinline__ void fma_bcast_all(float &acc, const float (&c)[NC], U u)
+// The least index v among the lanes of `among` that hold the minimum (uniform result).  It nearly always has
+// one holder, whose index is read from its lane; among several the lowest lane's is the least where a thread
+// owns one index, else they are compared (`least`).
+template <int EPT, class Least>
+__device__ __forceinline__ unsigned least_holder(bool holds, unsigned v, unsigned long long among, Least least)
 {
-    if constexpr (R0 < S) {
-        constexpr int N = S - R0 >= 8 ? 8 : S - R0 >= 4 ? 4 : S - R0 >= 2 ? 2 : 1;
-        float v[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = u(R0 + i);
-        fma_bcast<R0 % 16, N>(acc, c[R0 / 16], v);
-        fma_bcast_all<S, R0 + N>(acc, c, u);
-    }
+    const unsigned long long b = __ballot(holds) & among;
+    if (EPT > 1 && (b & (b - 1)) != 0) return least(holds ? v : ~0u);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, __builtin_ctzll(b));
 }
 
 struct PanelRow {
@@ -190,6 +200,7 @@ struct PanelRow {
     __amdgpu_buffer_rsrc_t rsrc;
     int es, rb_tid;
     int nw;         // waves launched (one owned element per thread: as many as the live size needs)
+    int mw;         // live size less the wave's first index
 };
 
 // byte offset of element (i, 0) of the row's matrix
@@ -207,19 +218,19 @@ __device__ __forceinline__ int nm_block(int o, float nm_inv) { return (int)(((fl
 // except in block pruning, its error (target - w).
 template <int MODE, int EPT, int BR>
 __device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const PanelRow &pr, const PanelRegs<EPT, BR> &st,
-                                                  const uint8_t *blk, int e, double &er)
+                                                  int e, double &er)
 {
     float sc;
     er = 0.0;
     if constexpr (MODE == MODE_BLOCK) {
         sc = (float)quad_block_score(st.w[e], st.dg[e], st.ob[e]);
-        if (!st.alive[e]) return ~0u;
+        if (st.og[e] == kGone) return ~0u;
     } else {
-        if (!st.alive[e]) return ~0u;
+        if (st.og[e] == kGone) return ~0u;
         if (st.og[e] < 0) {
             sc = -__builtin_inff();   // dead indices go first, before any outlier
         } else {
-            if (a.nm_m > 0 && blk[nm_block(st.og[e], pr.nm_inv)] >= a.nm_m - a.nm_n) return ~0u;
+            if (MODE == MODE_PRUNE && a.nm_m > 0 && (st.og[e] >> kNmShift) >= a.nm_m - a.nm_n) return ~0u;
             double tq = 0.0;
             if (MODE == MODE_QUANT) {
                 double c = rint((st.w[e] - pr.qo) * pr.iqd);
@@ -236,16 +247,80 @@ __device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const Pane
     return sc == sc ? score_bits(sc) : ~0u;   // a NaN score is no candidate
 }
 
-// One greedy step, S-th of the block.  OLD: the panel follows others of its outer block, whose vectors it
-// finds in memory.  Returns 0 to continue, 1 when the row has no step left,
-// 2 on a numeric failure.  Every thread of the workgroup returns the same value.
-template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int S>
+// The steps of a panel are a loop over groups of four: one body of 20 .. 40 KB instead of 200 .. 400 KB of code
+// that each wave ran through once.  What a step may do depends on its number only through uniform branches: the
+// correction stops at the vectors in use, the new vector reaches its registers by a branch tree.  Unrolled over all
+// steps, the compiler also moved values up to a hundred steps ahead of their use (8000 .. 11 000 scalar spills, up
+// to 700 vector ones).  256 x 2304 at 4 bit 24.3 -> 23.5 ms, in blocks of four 25.1 -> 24.4, 3072 x 768 at 4 bit
+// 16.17 -> 15.73 ms; results bit for bit the same.
+
+// acc[e] += the correction by the register-held vectors from 4 K to 4 LAST - 1, four at a time, as far as the
+// first 4 `quads` go (a group's vectors that are still to come are 0, and so are their coefficients).
+template <int EPT, int BR, int K, int LAST, int NC>
+__device__ __forceinline__ void correct_regs(float *acc, const float (&cv)[NC], const PanelRegs<EPT, BR> &st, int quads)
+{
+    if constexpr (K < LAST) {
+        if (quads <= K) return;
+        fma_bcast<4 * K % 16, EPT>(acc, cv[K / 4], st.u[4 * K], st.u[4 * K + 1], st.u[4 * K + 2], st.u[4 * K + 3]);
+        correct_regs<EPT, BR, K + 1, LAST>(acc, cv, st, quads);
+    }
+}
+
+// ... and by the LDS-held ones before step S
+template <int T, int EPT, int BR, int BL, int L, int NC>
+__device__ __forceinline__ void correct_lds(float (&acc)[EPT], const float (&cv)[NC], const float *ul, int S)
+{
+    if constexpr (L < BL) {
+        if (BR + L >= S) return;
+        float v[4][EPT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) v[i][e] = ul[((L + i) * EPT + e) * T];
+        fma_bcast<(BR + L) % 16, EPT>(acc, cv[(BR + L) / 16], v[0], v[1], v[2], v[3]);
+        correct_lds<T, EPT, BR, BL, L + 4>(acc, cv, ul, S);
+    }
+}
+
+// the calling thread's entries of the register-held vectors, element e, four per LDS write
+template <int EPT, int BR, int K>
+__device__ __forceinline__ void publish_regs(PanelShared &sh, const PanelRegs<EPT, BR> &st, int e, int quads)
+{
+    if constexpr (K < BR / 4) {
+        if (quads <= K) return;
+        *reinterpret_cast<float4 *>(&sh.cvec[4 * K]) =
+            make_float4(st.u[4 * K][e], st.u[4 * K + 1][e], st.u[4 * K + 2][e], st.u[4 * K + 3][e]);
+        publish_regs<EPT, BR, K + 1>(sh, st, e, quads);
+    }
+}
+
+// u[4 quad + SUB] = c, LO <= quad < HI: a branch tree down to the registers (a select per register would
+// be as many instructions as a step has elsewhere)
+template <int EPT, int BR, int SUB, int LO, int HI>
+__device__ __forceinline__ void keep_regs(PanelRegs<EPT, BR> &st, const float (&c)[EPT], int quad)
+{
+    if constexpr (HI - LO == 1) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) asm volatile("v_mov_b32 %0, %1" : "=v"(st.u[4 * LO + SUB][e]) : "v"(c[e]));
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (quad < MID) keep_regs<EPT, BR, SUB, LO, MID>(st, c, quad);
+        else keep_regs<EPT, BR, SUB, MID, HI>(st, c, quad);
+    }
+}
+
+// One greedy step, the S-th of the block, S = 4 quad + SUB; IN_LDS: S >= BR, its vector is kept in LDS.
+// OLD: the panel follows others of its outer block, whose vectors it finds in memory.  Returns 0 to
+// continue, 1 when the row has no step left, 2 on a numeric failure.  Every thread of the workgroup
+// returns the same value.
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int SUB, bool IN_LDS>
 __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
-                                          PanelShared &sh, uint8_t *blk, float *ul)
+                                          PanelShared &sh, float *ul, int quad)
 {
     // u_r[j] for r >= BR is kept at ul[(r - BR) * (T * EPT) + j]; only the owner of j touches it
     constexpr int CAP = T * EPT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int S = 4 * quad + SUB;
     if (pr.done + S >= pr.total) return 1;
 
     // ---- (1) selection.  The error (target - w) is formed in fp64 (for OBQ it is a difference of
@@ -256,11 +331,11 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     // index among the candidates that have it.  All ones = no candidate.
     unsigned cs = ~0u, ci = ~0u;
     double cer = 0.0;   // error of the thread's best candidate
-    if constexpr (MODE != MODE_BLOCK || S % 4 == 0) {   // (a block is chosen every fourth step)
+    if constexpr (MODE != MODE_BLOCK || SUB == 0) {   // (a block is chosen every fourth step)
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             double er;
-            const unsigned b = candidate_key<MODE>(a, pr, st, blk, e, er);
+            const unsigned b = candidate_key<MODE>(a, pr, st, e, er);
             if (b < cs) {   // (indices ascend with e)
                 cs = b;
                 ci = (unsigned)((MODE == MODE_BLOCK ? tid & ~3 : tid) + e * T);
@@ -269,20 +344,26 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         }
     }
     int p;
-    if constexpr (MODE == MODE_BLOCK && S % 4 != 0) {
+    if constexpr (MODE == MODE_BLOCK && SUB != 0) {
         __syncthreads();   // the previous step's readers of the shared step data are done
-        p = st.p0 + S % 4;
+        p = st.p0 + SUB;
     } else {
-        {
-            const unsigned ws = wave_umin(cs);
-            const unsigned wi = wave_umin(cs == ws ? ci : ~0u);
-            if (lane == 0) sh.red_k[S & 1][wave] = ((unsigned long long)ws << 32) | wi;
+        const unsigned ws = wave_umin(cs);
+        const unsigned wi = least_holder<EPT>(cs == ws, ci, MODE == MODE_BLOCK ? 0x1111111111111111ull : ~0ull,
+                                              [](unsigned v) { return wave_umin(v); });
+        unsigned gs = ws;
+        p = (int)wi;
+        if (EPT > 1 || pr.nw > 1) {
+            if (lane == 0) sh.red_k[SUB & 1][wave] = ((unsigned long long)ws << 32) | wi;
+            __syncthreads();
+            constexpr int NW2 = T <= 256 ? 4 : T <= 512 ? 8 : 16;
+            const int l = lane & (NW2 - 1);
+            const unsigned long long wk = l < pr.nw ? sh.red_k[SUB & 1][l] : ~0ull;
+            gs = lanes_umin<NW2>((unsigned)(wk >> 32));
+            p = (int)least_holder<EPT>((unsigned)(wk >> 32) == gs, (unsigned)wk, (1ull << NW2) - 1,
+                                       [](unsigned v) { return lanes_umin<NW2>(v); });
         }
-        __syncthreads();
-        const unsigned long long wk = (lane & 15) < pr.nw ? sh.red_k[S & 1][lane & 15] : ~0ull;
-        const unsigned gs = row16_umin_all((unsigned)(wk >> 32));
         if (gs == ~0u) return 2;
-        p = (int)row16_umin_all((unsigned)(wk >> 32) == gs ? (unsigned)wk : ~0u);
         if constexpr (MODE == MODE_BLOCK) st.p0 = p;
     }
 
@@ -302,27 +383,22 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
             col[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr.rsrc, off, 0, 2));
         }
     }
+    if constexpr (EPT == 1) {
+        // the step before's vector into its registers, while the row is on its way (with more owned elements
+        // there are no registers to hold it until here)
+        if constexpr (SUB > 0) {
+            if constexpr (!IN_LDS) keep_regs<EPT, BR, SUB - 1, 0, BR / 4>(st, st.last, quad);
+        } else if (quad > 0) {
+            keep_regs<EPT, BR, 3, 0, BR / 4>(st, st.last, quad - 1);
+        }
+    }
     // the owner of p publishes the pivot's data and its entries of the earlier vectors of this block
     if (tid == pt) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             if (e != ep) continue;
             // entries p of the vectors kept in registers, four per LDS write
-            constexpr int SREG = S < BR ? S : BR;
-#pragma unroll
-            for (int r4 = 0; r4 < SREG; r4 += 4) {
-                float4 v;
-                v.x = st.u[r4][e];
-                v.y = (r4 + 1 < SREG) ? st.u[r4 + 1 < BR ? r4 + 1 : 0][e] : 0.f;
-                v.z = (r4 + 2 < SREG) ? st.u[r4 + 2 < BR ? r4 + 2 : 0][e] : 0.f;
-                v.w = (r4 + 3 < SREG) ? st.u[r4 + 3 < BR ? r4 + 3 : 0][e] : 0.f;
-                // (copies: stored from where they are, the four would have to be an aligned group of
-                // registers all along, and next to block pruning's state there is no room for that --
-                // in scratch memory they cost 16 x 2600 in blocks 12 % of its time)
-                if constexpr (MODE == MODE_BLOCK && EPT >= 6 && EPT < 9)
-                    asm("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
-                *reinterpret_cast<float4 *>(&sh.cvec[r4]) = v;
-            }
+            publish_regs<EPT, BR, 0>(sh, st, e, IN_LDS ? BR / 4 : quad + (SUB > 0));
             const double ap = st.dg[e];
             // 1 / ap: the hardware's estimate and two Newton steps (a division's scaling and fix-up
             // steps would only lengthen the chain that everybody waits for)
@@ -332,13 +408,16 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
             const double wp = st.w[e];
             sh.g = (MODE == MODE_BLOCK ? wp : -cer) * invapp;
             sh.invapp = invapp;
-            sh.o = st.og[e];
+            const int o = MODE == MODE_PRUNE && st.og[e] >= 0 ? st.og[e] & ((1 << kNmShift) - 1) : st.og[e];
+            sh.o = o;
             sh.ok = (ap > 0.0) && (ap < __builtin_inf()) ? 1 : 0;
             sh.invd_s[S] = (float)invapp;
-            sh.rec_o[S] = st.og[e];
+            sh.rec_o[S] = o;
             sh.rec_w[S] = wp;
             sh.rec_invapp[S] = invapp;
-            if (a.nm_m > 0 && st.og[e] >= 0) blk[nm_block(st.og[e], pr.nm_inv)] += 1;
+            // (keeps the elements' code apart: merged, it copies their vectors into common registers first, which
+            // spill: 3072 x 768 at 4 bit 17.97 instead of 15.9 ms)
+            asm volatile("" ::"v"(wp));
         }
     }
     // coefficients of the earlier panels' vectors, which are in memory: one lane each
@@ -346,21 +425,25 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         if (tid < pr.old) sh.cold[tid] = pr.gU[(size_t)tid * pr.ldu + p];
     }
     // entries p of the vectors kept in LDS: one lane each
-    if constexpr (S > BR) {
+    if constexpr (IN_LDS) {
         const int r = BR + tid;
         if (r < S) sh.cvec[r] = ul[(r - BR) * CAP + p];
     }
     __syncthreads();
     const double g = sh.g, invapp = sh.invapp;
-    const bool isdead = sh.o < 0;
-    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ... (what
-    // lies beyond S is never used)
-    constexpr int NC = S > 0 ? (S + 15) / 16 : 1;
+    const int op = __builtin_amdgcn_readfirstlane(sh.o);
+    const bool isdead = op < 0;
+    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ..., 0 from S on
+    constexpr int NC = ((IN_LDS ? BR + BL : BR) + 15) / 16;
     float cv[NC];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) cv[k] = S > 0 ? __fmul_rn(sh.cvec[16 * k + (lane & 15)], sh.invd_s[16 * k + (lane & 15)]) : 0.f;
+    for (int k = 0; k < NC; ++k) {
+        const int r = 16 * k + (lane & 15);
+        const float c = __fmul_rn(sh.cvec[r], sh.invd_s[r]);
+        cv[k] = r < S ? c : 0.f;
+    }
 
-    if (!sh.ok) return 2;   // (after the reads above are on their way)
+    if (!__builtin_amdgcn_readfirstlane(sh.ok)) return 2;   // (after the reads above are on their way)
 
     // ---- (3) bring the fetched row up to date, keep it, update w and the diagonal.
     // The correction is summed on its own and subtracted once: its roundings are then relative to
@@ -372,92 +455,127 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         // how the fp32 matrix instruction sums) and added once.  (Indices beyond m read what lies behind
         // the vector -- a row's UCAP vectors are longer than any index -- and only reach values that are
         // never used.)
+        auto earlier = [&](auto ne) {
+            constexpr int NE = decltype(ne)::value;      // the wave's elements that hold live indices
 #pragma unroll 1
-        for (int r0 = 0; r0 < pr.old; r0 += BR + BL) {
-            float sum[EPT];
+            for (int r0 = 0; r0 < pr.old; r0 += BR + BL) {
+                float sum[NE];
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) sum[e] = 0.f;
+                for (int e = 0; e < NE; ++e) sum[e] = 0.f;
 #pragma unroll 1
-            for (int r = r0; r < r0 + BR + BL; r += 2) {
-                const float2 o2 = *reinterpret_cast<const float2 *>(&sh.cold[r]);
-                const float2 i2 = *reinterpret_cast<const float2 *>(&sh.invd_old[r]);
-                const float *u = pr.gU + (size_t)r * pr.ldu + tid;
-                float v[2][EPT];
+                for (int r = r0; r < r0 + BR + BL; r += 2) {
+                    const float2 o2 = *reinterpret_cast<const float2 *>(&sh.cold[r]);
+                    const float2 i2 = *reinterpret_cast<const float2 *>(&sh.invd_old[r]);
+                    const float *u = pr.gU + (size_t)r * pr.ldu + tid;
+                    float v[2][NE];
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
+                    for (int q = 0; q < 2; ++q)
 #pragma unroll
-                    for (int e = 0; e < EPT; ++e) v[q][e] = u[(size_t)q * pr.ldu + e * T];
+                        for (int e = 0; e < NE; ++e) v[q][e] = u[(size_t)q * pr.ldu + e * T];
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float up = q ? o2.y : o2.x, ni = -(q ? i2.y : i2.x), fp = __fmul_rn(up, ni);
+                    for (int q = 0; q < 2; ++q) {
+                        const float up = q ? o2.y : o2.x, ni = -(q ? i2.y : i2.x), fp = __fmul_rn(up, ni);
 #pragma unroll
-                    for (int e = 0; e < EPT; ++e) {
-                        const bool along = tid <= p - e * T;     // (p, j) with j <= p, else (j, p)
-                        sum[e] = fmaf(along ? fp : up, along ? v[q][e] : __fmul_rn(v[q][e], ni), sum[e]);
+                        for (int e = 0; e < NE; ++e) {
+                            const bool along = tid <= p - e * T;     // (p, j) with j <= p, else (j, p)
+                            sum[e] = fmaf(along ? fp : up, along ? v[q][e] : __fmul_rn(v[q][e], ni), sum[e]);
+                        }
                     }
                 }
-            }
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) col[e] = __fadd_rn(col[e], sum[e]);
-        }
+                for (int e = 0; e < NE; ++e) col[e] = __fadd_rn(col[e], sum[e]);
+            }
+        };
+        static_assert(EPT > 3, "every live size of the variant reaches the elements before the last two");
+        if ((EPT - 2) * T >= pr.mw) earlier(std::integral_constant<int, EPT - 2>{});
+        else if ((EPT - 1) * T >= pr.mw) earlier(std::integral_constant<int, EPT - 1>{});
+        else earlier(std::integral_constant<int, EPT>{});
+    }
+    float c[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) c[e] = 0.f;
+    if constexpr (!IN_LDS) {
+        correct_regs<EPT, BR, 0, BR / 4>(c, cv, st, SUB == 0 ? quad : quad + 1);
+    } else {
+        correct_regs<EPT, BR, 0, BR / 4>(c, cv, st, BR / 4);
+        correct_lds<T, EPT, BR, BL, 0>(c, cv, ul + tid, S);
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) c[e] = __fsub_rn(col[e], c[e]);
+    if constexpr (EPT == 1) {
+        static_assert(EPT > 1 || BL == 0, "one owned element: all vectors in registers");
+        st.last[0] = c[0];
+    } else if constexpr (!IN_LDS) {
+        keep_regs<EPT, BR, SUB, 0, BR / 4>(st, c, quad);
+    } else {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) ul[(S - BR) * CAP + tid + e * T] = c[e];
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-        int j = tid + e * T;
-        float corr = 0.f;
-        fma_bcast_all<S, 0>(corr, cv, [&](int r) { return (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * CAP + j]; });
-        float c = __fsub_rn(col[e], corr);
-        if constexpr (EPT >= 3) __builtin_amdgcn_sched_barrier(0);   // one element at a time: registers
-        if constexpr (S < BR) st.u[S < BR ? S : 0][e] = c;
-        else ul[(S - BR) * CAP + j] = c;
         if constexpr (MODE == MODE_BLOCK) {
             // Lemma 1 on the element's row of its own 4 x 4 block: A[j][j'] -= u[j] u[j'] / a
-            const float cs = c * (float)invapp;
-            st.ob[e][0] = fmaf(-cs, quad_bcast<0>(c), st.ob[e][0]);
-            st.ob[e][1] = fmaf(-cs, quad_bcast<1>(c), st.ob[e][1]);
-            st.ob[e][2] = fmaf(-cs, quad_bcast<2>(c), st.ob[e][2]);
-            st.ob[e][3] = fmaf(-cs, quad_bcast<3>(c), st.ob[e][3]);
+            const float cs = c[e] * (float)invapp;
+            st.ob[e][0] = fmaf(-cs, quad_bcast<0>(c[e]), st.ob[e][0]);
+            st.ob[e][1] = fmaf(-cs, quad_bcast<1>(c[e]), st.ob[e][1]);
+            st.ob[e][2] = fmaf(-cs, quad_bcast<2>(c[e]), st.ob[e][2]);
+            st.ob[e][3] = fmaf(-cs, quad_bcast<3>(c[e]), st.ob[e][3]);
         }
-        if (st.alive[e]) {
-            if (j == p) {
-                st.alive[e] = false;
+        if (st.og[e] != kGone) {
+            if (tid + e * T == p) {
+                st.og[e] = kGone;
             } else {
-                double cd = (double)c;
+                const double cd = (double)c[e];
                 st.w[e] = fma(-cd, g, st.w[e]);
                 st.dg[e] = fma(-(cd * cd), invapp, st.dg[e]);
             }
         }
     }
-    if (MODE == MODE_BLOCK && a.trace && S % 4 == 3) {
+    if (MODE == MODE_PRUNE && a.nm_m > 0 && !isdead) {
+        const int b = nm_block(op, pr.nm_inv);
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+            if (st.og[e] >= 0 && nm_block(st.og[e] & ((1 << kNmShift) - 1), pr.nm_inv) == b) st.og[e] += 1 << kNmShift;
+    }
+    if (MODE == MODE_BLOCK && a.trace && SUB == 3) {
         float *tr = a.trace + ((size_t)pr.row * a.out_ld + (pr.done + S) / 4) * pr.d;
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-            if (st.alive[e]) tr[st.og[e]] = (float)st.w[e];
+            if (st.og[e] != kGone) tr[st.og[e]] = (float)st.w[e];
     }
     if (MODE == MODE_PRUNE && a.trace && !isdead) {
         float *tr = a.trace + ((size_t)pr.row * a.out_ld + (pr.done + S - pr.ndead)) * pr.d;
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-            if (st.alive[e] && st.og[e] >= 0) tr[st.og[e]] = (float)st.w[e];
+            if (st.og[e] >= 0) tr[st.og[e] & ((1 << kNmShift) - 1)] = (float)st.w[e];
     }
     return 0;
 }
 
-// Compile-time unrolled step loop; returns the number of steps done and sets *failed.
-template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int S>
-__device__ __forceinline__ int panel_steps(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
-                                           PanelShared &sh, uint8_t *blk, float *ul, bool *failed)
+// Four steps from 4 quad on; returns the number of them done and sets *failed.
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, bool IN_LDS>
+__device__ __forceinline__ int panel_quad(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
+                                          PanelShared &sh, float *ul, int quad, bool *failed)
 {
-    if constexpr (S < BR + BL) {
-        int rc = panel_step<MODE, T, EPT, BR, BL, OLD, S>(a, pr, st, sh, blk, ul);
-        if (rc != 0) {
-            *failed = (rc == 2);
-            return S;
+    int rc = panel_step<MODE, T, EPT, BR, BL, OLD, 0, IN_LDS>(a, pr, st, sh, ul, quad);
+    if (rc == 0) {
+        rc = panel_step<MODE, T, EPT, BR, BL, OLD, 1, IN_LDS>(a, pr, st, sh, ul, quad);
+        if (rc == 0) {
+            rc = panel_step<MODE, T, EPT, BR, BL, OLD, 2, IN_LDS>(a, pr, st, sh, ul, quad);
+            if (rc == 0) {
+                rc = panel_step<MODE, T, EPT, BR, BL, OLD, 3, IN_LDS>(a, pr, st, sh, ul, quad);
+                if (rc == 0) return 4;
+                *failed = rc == 2;
+                return 3;
+            }
+            *failed = rc == 2;
+            return 2;
         }
-        return panel_steps<MODE, T, EPT, BR, BL, OLD, S + 1>(a, pr, st, sh, blk, ul, failed);
-    } else {
-        return BR + BL;
+        *failed = rc == 2;
+        return 1;
     }
+    *failed = rc == 2;
+    return 0;
 }
 
 // OLD: an instance that can follow others of its outer block (a.old > 0).  At six elements a thread the
@@ -469,12 +587,11 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 ? (E
 void panel_kernel(PanelArgs a)
 {
     constexpr int B = BR + BL;
-    static_assert(BR % 4 == 0, "the owner publishes four entries at a time");
+    static_assert(BR % 4 == 0 && BL % 4 == 0, "the vectors are used four at a time");
     __shared__ PanelShared sh;
-    // dynamic LDS: BL vectors of T * EPT floats, then the N:M counters (d / M bytes) when nm_m > 0
+    // dynamic LDS: BL vectors of T * EPT floats
     extern __shared__ __align__(16) uint8_t dyn_lds[];
     float *ul = reinterpret_cast<float *>(dyn_lds);
-    uint8_t *blk = dyn_lds + (size_t)BL * T * EPT * sizeof(float);
 
     // Rows of at most BMAX weights are through after one panel: it takes its state from the caller's
     // arrays and leaves nothing for a next one (one launch instead of a set-up and a panel, and no
@@ -512,6 +629,7 @@ void panel_kernel(PanelArgs a)
     pr.es = a.swz ? 16 : 4;
     pr.rb_tid = row_base(tid, pr);
     pr.nw = blockDim.x >> 6;
+    pr.mw = m - __builtin_amdgcn_readfirstlane(tid & ~63);
     pr.gU = a.ws.U + (size_t)row * UCAP * a.ws.ldu;
     pr.ldu = a.ws.ldu;
     pr.old = a.old;
@@ -525,15 +643,21 @@ void panel_kernel(PanelArgs a)
         int j = tid + e * T;
         if (direct) {
             st.og[e] = j < m ? (live0 ? j : ~j) : kGone;
-            st.alive[e] = j < m;
             st.w[e] = live0 ? (double)a.W[(size_t)row * d + j] : 0.0;
             st.dg[e] = j < m ? (double)pr.Acur[(size_t)j * d + j] : 1.0;
         } else {
             st.og[e] = j < m ? go[j] : kGone;
-            st.alive[e] = st.og[e] != kGone;
-            st.w[e] = st.alive[e] ? gw[j] : 0.0;
-            st.dg[e] = st.alive[e] ? gd[j] : 1.0;
+            st.w[e] = st.og[e] != kGone ? gw[j] : 0.0;
+            st.dg[e] = st.og[e] != kGone ? gd[j] : 1.0;
         }
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+#pragma unroll
+        for (int r = 0; r < BR; ++r) st.u[r][e] = 0.f;
+        st.last[e] = 0.f;
+#pragma unroll
+        for (int r = 0; r < BL; ++r) ul[r * (T * EPT) + tid + e * T] = 0.f;
     }
     for (int r = tid; r < a.old; r += blockDim.x) sh.invd_old[r] = a.ws.invd[(size_t)row * UCAP + r];
     if constexpr (MODE == MODE_BLOCK) {
@@ -576,18 +700,47 @@ void panel_kernel(PanelArgs a)
         }
         st.p0 = 0;
     }
-    const int nmb = a.nm_m > 0 ? d / a.nm_m : 0;
-    for (int b = tid; b < nmb; b += blockDim.x) blk[b] = direct ? 0 : a.ws.blk[(size_t)row * d + b];
     pr.qd = 1.0;
     pr.qo = 0.0;
     pr.qmax = (double)a.maxq;
     pr.nm_inv = a.nm_m > 0 ? 1.0f / (float)a.nm_m : 0.f;
+    if (MODE == MODE_PRUNE && a.nm_m > 0 && !direct) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+            if (st.og[e] >= 0) st.og[e] |= (int)a.ws.blk[(size_t)row * d + nm_block(st.og[e], pr.nm_inv)] << kNmShift;
+    }
     if (MODE == MODE_QUANT) { pr.qd = (double)a.delta[row]; pr.qo = (double)a.offset[row]; }
     pr.iqd = 1.0 / pr.qd;
     __syncthreads();
 
     bool failed = false;
-    const int nbv = panel_steps<MODE, T, EPT, BR, BL, OLD, 0>(a, pr, st, sh, blk, ul, &failed);
+    int nbv = 0;
+    bool more = true;
+#pragma unroll 1
+    for (int quad = 0; more && quad < BR / 4; ++quad) {
+        const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, quad, &failed);
+        nbv += n;
+        more = n == 4;
+    }
+    if constexpr (EPT == 1) {
+        if (nbv > 0) {
+            const int quad = (nbv - 1) >> 2;
+            switch ((nbv - 1) & 3) {
+            case 0: keep_regs<EPT, BR, 0, 0, BR / 4>(st, st.last, quad); break;
+            case 1: keep_regs<EPT, BR, 1, 0, BR / 4>(st, st.last, quad); break;
+            case 2: keep_regs<EPT, BR, 2, 0, BR / 4>(st, st.last, quad); break;
+            default: keep_regs<EPT, BR, 3, 0, BR / 4>(st, st.last, quad);
+            }
+        }
+    }
+    if constexpr (BL > 0) {
+#pragma unroll 1
+        for (int quad = BR / 4; more && quad < (BR + BL) / 4; ++quad) {
+            const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, true>(a, pr, st, sh, ul, quad, &failed);
+            nbv += n;
+            more = n == 4;
+        }
+    }
     __syncthreads();
 
     // ---- block epilogue.  Before the outer block's last panel the state stays in the present index
@@ -596,8 +749,8 @@ void panel_kernel(PanelArgs a)
         for (int r = tid; r < nbv; r += blockDim.x) a.ws.invd[(size_t)row * UCAP + a.old + r] = sh.invd_s[r];
     float *Wo = a.W_out + (size_t)row * d;
     if (direct && tid < d) {
-        if (st.alive[0] || !live0) Wo[tid] = live0 ? (float)st.w[0] : 0.f;
-        if (MODE == MODE_QUANT && (st.alive[0] || !live0)) a.codes[(size_t)row * d + tid] = -1;
+        if (st.og[0] != kGone || !live0) Wo[tid] = live0 ? (float)st.w[0] : 0.f;
+        if (MODE == MODE_QUANT && (st.og[0] != kGone || !live0)) a.codes[(size_t)row * d + tid] = -1;
     }
     // the steps' records
     if (tid < nbv) {
@@ -642,7 +795,7 @@ void panel_kernel(PanelArgs a)
         static_assert(EPT * NW <= 16 * 16, "survivor counts");
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const unsigned long long bal = __ballot(st.alive[e]);
+            const unsigned long long bal = __ballot(st.og[e] != kGone);
             jn[e] = __popcll(bal & ((1ull << lane) - 1ull));
             if (lane == 0) sh.live[e * NW + wave] = __popcll(bal);
         }
@@ -658,7 +811,7 @@ void panel_kernel(PanelArgs a)
                 if (w >= wave) here += n;
             }
             live += here;
-            if (!st.alive[e]) jn[e] = -1;
+            if (st.og[e] == kGone) jn[e] = -1;
         }
     } else {
 #pragma unroll
@@ -669,11 +822,17 @@ void panel_kernel(PanelArgs a)
     for (int e = 0; e < EPT; ++e) {
         const int j = tid + e * T;
         if (jn[e] >= 0) {
+            if (MODE == MODE_PRUNE && st.og[e] >= 0) {
+                // N:M: all live weights of a block hold its count
+                if (a.nm_m > 0)
+                    a.ws.blk[(size_t)row * d + nm_block(st.og[e] & ((1 << kNmShift) - 1), pr.nm_inv)] = (uint8_t)(st.og[e] >> kNmShift);
+                st.og[e] &= (1 << kNmShift) - 1;
+            }
             gw[jn[e]] = st.w[e];
             gd[jn[e]] = st.dg[e];
-            go[jn[e]] = st.alive[e] ? st.og[e] : kGone;
+            go[jn[e]] = st.og[e];
             gmap[jn[e]] = j;
-            if (st.alive[e] && st.og[e] >= 0) Wo[st.og[e]] = (float)st.w[e];
+            if (st.og[e] >= 0) Wo[st.og[e]] = (float)st.w[e];
             // this panel's vectors u_r, in the new index order
 #pragma unroll
             for (int r = 0; r < B; ++r)
@@ -702,7 +861,6 @@ void panel_kernel(PanelArgs a)
             }
         }
     }
-    for (int b = tid; b < nmb; b += blockDim.x) a.ws.blk[(size_t)row * d + b] = blk[b];
     if (tid == 0) {
         if (a.last) a.ws.m[row] = live;
         a.ws.done[row] = pr.done + nbv;
@@ -734,9 +892,9 @@ inline int panel_raise_lds_limit(const void *fn, std::atomic<unsigned long long>
 // With one owned element per thread a launch has as many waves as the largest live size needs: a
 // step is bound by instruction issue, and a wave without live elements issues as many as the others.
 template <int MODE, int T, int EPT, int BR, int BL, bool OLD>
-int panel_launch(int R, size_t lds_nm, hipStream_t st, const PanelArgs &a)
+int panel_launch(int R, hipStream_t st, const PanelArgs &a)
 {
-    const size_t lds = (size_t)BL * T * EPT * sizeof(float) + lds_nm;
+    const size_t lds = (size_t)BL * T * EPT * sizeof(float);
     auto kernel = panel_kernel<MODE, T, EPT, BR, BL, OLD>;
     static std::atomic<unsigned long long> raised{0};
     if (lds > 48 * 1024 && panel_raise_lds_limit((const void *)kernel, raised) != 0) return -1;
@@ -746,18 +904,18 @@ int panel_launch(int R, size_t lds_nm, hipStream_t st, const PanelArgs &a)
 
 // NAME: launch_panel, or launch_panel_old where a variant has an instance of its own for OLD
 #define OBC_DEFINE_PANEL(NAME, OLD, T, EPT, BR, BL)                                                     \
-    int NAME##_##T##_##EPT##_##BR##_##BL(int mode, int R, size_t lds_nm, hipStream_t st, const PanelArgs &a) \
+    int NAME##_##T##_##EPT##_##BR##_##BL(int mode, int R, hipStream_t st, const PanelArgs &a) \
     {                                                                                                   \
-        return mode == MODE_PRUNE ? panel_launch<MODE_PRUNE, T, EPT, BR, BL, OLD>(R, lds_nm, st, a)     \
-                                  : panel_launch<MODE_QUANT, T, EPT, BR, BL, OLD>(R, lds_nm, st, a);    \
+        return mode == MODE_PRUNE ? panel_launch<MODE_PRUNE, T, EPT, BR, BL, OLD>(R, st, a)     \
+                                  : panel_launch<MODE_QUANT, T, EPT, BR, BL, OLD>(R, st, a);    \
     }
 
 // The block-pruning instance of a variant, in a translation unit of its own.
 #define OBC_DEFINE_PANEL_BLOCK(OLD, T, EPT, BR, BL)                                                     \
-    int launch_panel_block_##T##_##EPT##_##BR##_##BL(int, int R, size_t lds_nm, hipStream_t st,         \
+    int launch_panel_block_##T##_##EPT##_##BR##_##BL(int, int R, hipStream_t st,         \
                                                      const PanelArgs &a)                                \
     {                                                                                                   \
-        return panel_launch<MODE_BLOCK, T, EPT, BR, BL, OLD>(R, lds_nm, st, a);                         \
+        return panel_launch<MODE_BLOCK, T, EPT, BR, BL, OLD>(R, st, a);                         \
     }
 
 }  // namespace obc_blocked

@@ -42,7 +42,7 @@ struct BlockedWs {
     int *total;         // R   steps to do
     int *ndead;         // R   up-front eliminations
     int *nb;            // R   steps done since the last flush
-    uint8_t *blk;       // R x d  N:M counters (d / M used)
+    uint8_t *blk;       // R x d  N:M counters (d / M used), between two panels
     // bulk elimination of already-pruned indices, BMAX at a time (rows_blocked.hip)
     // (the rows of the matrix at the block's pivots are parked in vectors BMAX .. of U, their
     // positions in the block's slots of invd until the vectors are formed)
@@ -98,7 +98,7 @@ struct PanelArgs {
 // launchers defined in panel_<T>x<EPT>x<BR>x<BL>.hip (pruning and OBQ) and
 // panel_block_<T>x<EPT>x<BR>x<BL>.hip (block pruning, blocks of 4): T threads, EPT owned indices per thread,
 // blocks of BR + BL steps (BR vectors in registers, BL in LDS).  Return 0 or -1 (HIP error).
-typedef int PanelLaunch(int mode, int R, size_t lds_nm, hipStream_t st, const PanelArgs &a);
+typedef int PanelLaunch(int mode, int R, hipStream_t st, const PanelArgs &a);
 #define OBC_DECLARE_PANEL(T, EPT, BR, BL) \
     PanelLaunch launch_panel_##T##_##EPT##_##BR##_##BL, launch_panel_block_##T##_##EPT##_##BR##_##BL
 OBC_DECLARE_PANEL(256, 1, 64, 0);

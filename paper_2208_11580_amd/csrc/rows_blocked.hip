@@ -691,13 +691,12 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     pa.ws = bw; pa.order = order; pa.loss = loss; pa.codes = codes; pa.W_out = W_out; pa.trace = trace;
     pa.out_ld = out_ld; pa.status = ctx->d_status; pa.outliers = (flags & OBC_QUANT_OUTLIERS) ? 1 : 0;
     pa.direct = direct ? 1 : 0; pa.W = W; pa.live_in = live; pa.stop_counts = stop_counts; pa.k_steps = k_steps;
-    const size_t lds_nm = nm_m > 0 ? obc_align_up((size_t)(d / nm_m), 16) : 0;
     if (direct) {
         pa.A_cur = Hinv; pa.a_row_stride = 0; pa.ld = d; pa.swz = 0; pa.old = 0; pa.last = 1; pa.threads = BMAX;
         const Variant &v = kVariants[0];
         {
             obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * d * 4.0 * d, (double)R * d * (double)d * d);
-            if ((mode == MODE_BLOCK ? v.launch_block : v.launch)(mode, R, lds_nm, st, pa) != 0)
+            if ((mode == MODE_BLOCK ? v.launch_block : v.launch)(mode, R, st, pa) != 0)
                 return obc_fail(ctx, OBC_ERR_HIP, "panel kernel: cannot set its dynamic LDS size");
         }
         OBC_LAUNCH_CHECK(ctx, "panel_kernel");
@@ -825,7 +824,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
                 const int steps = (host_total - host_done < v->B) ? host_total - host_done : v->B;
                 obc_scope sc(ctx, OBC_KERNEL_PANEL, (double)R * steps * 4.0 * (1 + pa.old) * m_max,
                              (double)R * steps * (double)(steps + 2 * pa.old) * m_max);
-                if ((j == 0 ? first : next)(mode, R, lds_nm, st, pa) != 0)
+                if ((j == 0 ? first : next)(mode, R, st, pa) != 0)
                     return obc_fail(ctx, OBC_ERR_HIP, "panel kernel: cannot set its dynamic LDS size");
             }
             OBC_LAUNCH_CHECK(ctx, "panel_kernel");
