@@ -327,6 +327,7 @@ struct FlushArgs {
     size_t new_row_stride;
     int ld_new;
     int d, R, strips;
+    int keep;                // the new matrices stay in the caches
     int chunks;              // panels whose vectors this flush applies, KMAX each
     BlockedWs ws;
 };
@@ -352,6 +353,11 @@ constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: 
 // loads made the kernel 25 % slower.
 constexpr int kMatLoadPolicy = 0;
 constexpr int kMatStorePolicy = 2 | 16;
+
+// Cached instead, up to this many bytes of all rows' new matrices, the next panels find the rows that they fetch
+// nearer: 203 x 1283 at 8 bit 5.50 -> 5.27 ms, 64 x 576 2:4 528 -> 519 us; above, the displaced lines cost more
+// (256 x 2304 23.96 -> 24.05 ms at 800 MB, 24.9 without a limit).
+const double kKeepBytes = 640e6;
 
 // K is the block size: every row that still has steps to do has exactly K deferred eliminations
 // (a row with fewer has finished and is skipped).  A strip is HALVES x 128 rows tall: the U tile
@@ -585,7 +591,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 if (on_diag && jcol > qrow + 3) continue;                   // wholly above the diagonal
                 uintx4 v4 = {__float_as_uint(old[mt][4 * q]), __float_as_uint(old[mt][4 * q + 1]),
                              __float_as_uint(old[mt][4 * q + 2]), __float_as_uint(old[mt][4 * q + 3])};
-                __builtin_amdgcn_raw_buffer_store_b128(v4, rnew, quad * ldn * 16 + colB, 0, kMatStorePolicy);
+                if (a.keep) __builtin_amdgcn_raw_buffer_store_b128(v4, rnew, quad * ldn * 16 + colB, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b128(v4, rnew, quad * ldn * 16 + colB, 0, kMatStorePolicy);
             }
         if (!more) break;
         if (new_col) {
@@ -731,6 +738,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         // strips of 256 rows where two workgroups' tiles fit in a CU's LDS, else 128
         const int halves = (K <= 48 && chunks == 1) ? 2 : 1;
         fa.chunks = chunks;
+        fa.keep = (double)R * m_next * m_next * 2.0 <= kKeepBytes;
         fa.strips = (m_next + halves * FT - 1) / (halves * FT);
         const int rows8 = (R + 7) / 8 * 8;
         {
