@@ -31,10 +31,13 @@ struct PanelRegs {
     int p0;
 };
 
+// B: steps of the panel
+template <int B>
 struct PanelShared {
+    static constexpr int PMAX = (B + 15) / 16 * 16;
     unsigned long long red_k[2][16];
-    __attribute__((aligned(16))) float cvec[BMAX];
-    float invd_s[BMAX];
+    __attribute__((aligned(16))) float cvec[PMAX];
+    float invd_s[PMAX];
     __attribute__((aligned(16))) float cold[UCAP];   // coefficients of the outer block's earlier vectors ...
     __attribute__((aligned(16))) float invd_old[UCAP];                            // ... and their 1 / a_r
     int live[16 * 16];   // survivors per (owned element, wave)
@@ -45,8 +48,8 @@ struct PanelShared {
     // What the steps' records are made of when the panel ends (original index, weight, 1 / a_pp): made
     // and stored in every step they would lengthen the chain that the whole workgroup waits for, and
     // the owner's wait for its fetched row would be one for its stores too.
-    int rec_o[BMAX];
-    double rec_w[BMAX], rec_invapp[BMAX];
+    int rec_o[PMAX];
+    double rec_w[PMAX], rec_invapp[PMAX];
 };
 
 // order-preserving map of a float onto unsigned integers
@@ -284,13 +287,13 @@ __device__ __forceinline__ void correct_lds(float (&acc)[EPT], const float (&cv)
 
 // the calling thread's entries of the register-held vectors, element e, four per LDS write
 template <int EPT, int BR, int K>
-__device__ __forceinline__ void publish_regs(PanelShared &sh, const PanelRegs<EPT, BR> &st, int e, int quads)
+__device__ __forceinline__ void publish_regs(float *cvec, const PanelRegs<EPT, BR> &st, int e, int quads)
 {
     if constexpr (K < BR / 4) {
         if (quads <= K) return;
-        *reinterpret_cast<float4 *>(&sh.cvec[4 * K]) =
+        *reinterpret_cast<float4 *>(&cvec[4 * K]) =
             make_float4(st.u[4 * K][e], st.u[4 * K + 1][e], st.u[4 * K + 2][e], st.u[4 * K + 3][e]);
-        publish_regs<EPT, BR, K + 1>(sh, st, e, quads);
+        publish_regs<EPT, BR, K + 1>(cvec, st, e, quads);
     }
 }
 
@@ -315,7 +318,7 @@ __device__ __forceinline__ void keep_regs(PanelRegs<EPT, BR> &st, const float (&
 // returns the same value.
 template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int SUB, bool IN_LDS>
 __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
-                                          PanelShared &sh, float *ul, int quad)
+                                          PanelShared<BR + BL> &sh, float *ul, int quad)
 {
     // u_r[j] for r >= BR is kept at ul[(r - BR) * (T * EPT) + j]; only the owner of j touches it
     constexpr int CAP = T * EPT;
@@ -398,7 +401,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         for (int e = 0; e < EPT; ++e) {
             if (e != ep) continue;
             // entries p of the vectors kept in registers, four per LDS write
-            publish_regs<EPT, BR, 0>(sh, st, e, IN_LDS ? BR / 4 : quad + (SUB > 0));
+            publish_regs<EPT, BR, 0>(sh.cvec, st, e, IN_LDS ? BR / 4 : quad + (SUB > 0));
             const double ap = st.dg[e];
             // 1 / ap: the hardware's estimate and two Newton steps (a division's scaling and fix-up
             // steps would only lengthen the chain that everybody waits for)
@@ -555,7 +558,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 // Four steps from 4 quad on; returns the number of them done and sets *failed.
 template <int MODE, int T, int EPT, int BR, int BL, bool OLD, bool IN_LDS>
 __device__ __forceinline__ int panel_quad(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
-                                          PanelShared &sh, float *ul, int quad, bool *failed)
+                                          PanelShared<BR + BL> &sh, float *ul, int quad, bool *failed)
 {
     int rc = panel_step<MODE, T, EPT, BR, BL, OLD, 0, IN_LDS>(a, pr, st, sh, ul, quad);
     if (rc == 0) {
@@ -588,7 +591,8 @@ void panel_kernel(PanelArgs a)
 {
     constexpr int B = BR + BL;
     static_assert(BR % 4 == 0 && BL % 4 == 0, "the vectors are used four at a time");
-    __shared__ PanelShared sh;
+    static_assert(sizeof(PanelShared<B>) <= 160 * 1024 - kPanelDynLds && BL * T * EPT * sizeof(float) <= kPanelDynLds, "a CU's LDS");
+    __shared__ PanelShared<B> sh;
     // dynamic LDS: BL vectors of T * EPT floats
     extern __shared__ __align__(16) uint8_t dyn_lds[];
     float *ul = reinterpret_cast<float *>(dyn_lds);
@@ -872,8 +876,6 @@ void panel_kernel(PanelArgs a)
     }
 }
 
-
-static_assert(sizeof(PanelShared) <= 160 * 1024 - kPanelDynLds, "a CU's LDS");
 
 // A kernel's dynamic LDS limit is a per-device attribute: `done` remembers, one bit per device, where
 // it has been raised for `fn`.  Safe from several host threads (raising it twice is harmless).

@@ -11,7 +11,7 @@ using namespace obc_rows;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int BMAX = 64;       // most steps of one panel, and rank of a bulk elimination of pruned indices
+constexpr int BMAX = 64;       // rank of a bulk elimination of pruned indices, and widest row that is one panel
 constexpr int UCAP = 2 * BMAX; // vectors per row in U: an outer block's, or a bulk elimination's in and out
 constexpr int kGone = (int)0x80000000;   // `orig` of an index eliminated since the last compaction
 constexpr int kPanelDynLds = 160 * 1024 - 6144;   // what a panel's static LDS leaves of a CU's
@@ -104,12 +104,12 @@ typedef int PanelLaunch(int mode, int R, hipStream_t st, const PanelArgs &a);
 OBC_DECLARE_PANEL(256, 1, 64, 0);
 OBC_DECLARE_PANEL(256, 3, 32, 16);
 OBC_DECLARE_PANEL(1024, 1, 64, 0);
-OBC_DECLARE_PANEL(512, 3, 48, 16);
+OBC_DECLARE_PANEL(512, 3, 48, 24);
 OBC_DECLARE_PANEL(512, 4, 40, 16);
 OBC_DECLARE_PANEL(768, 3, 32, 16);
 OBC_DECLARE_PANEL(512, 6, 28, 12);
 OBC_DECLARE_PANEL(512, 8, 20, 8);
 OBC_DECLARE_PANEL(512, 9, 16, 8);
-PanelLaunch launch_panel_old_512_6_28_12;
+PanelLaunch launch_panel_256_2_56_24, launch_panel_old_512_6_28_12;
 
 }  // namespace obc_blocked

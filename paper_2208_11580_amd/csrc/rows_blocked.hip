@@ -611,7 +611,7 @@ struct Variant {
     int cap;   // largest live size it handles (T * EPT)
     int B;     // steps per panel
     PanelLaunch *launch;
-    PanelLaunch *launch_block;       // block pruning
+    PanelLaunch *launch_block;       // block pruning (null: not served)
     // panels that follow others of their outer block: one flush applies the eliminations of up to J
     int J;
     PanelLaunch *launch_old;
@@ -622,10 +622,12 @@ struct Variant {
     (T) * (EPT), (BR) + (BL), launch_panel_##T##_##EPT##_##BR##_##BL,            \
         launch_panel_block_##T##_##EPT##_##BR##_##BL
 
+// (512 x 3: 24 vectors in LDS, 72 steps -- 203 x 1283 at 8 bit 5.10 -> 4.93 ms, 256 x 2304 at 4 bit 23.4 -> 23.1 against
+// 16 and 64.)
 const Variant kVariants[] = {
     {OBC_VARIANT(256, 1, 64, 0)},
     {OBC_VARIANT(1024, 1, 64, 0)},
-    {OBC_VARIANT(512, 3, 48, 16)},
+    {OBC_VARIANT(512, 3, 48, 24)},
     {OBC_VARIANT(512, 4, 40, 16)},
     {OBC_VARIANT(768, 3, 32, 16)},
     {OBC_VARIANT(512, 6, 28, 12), 2, launch_panel_old_512_6_28_12, nullptr},
@@ -639,12 +641,21 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // three rows per CU on -- the 768 x 768 layer 7.6 -> 7.1 ms, its panels 3.5 -> 2.4 ms while the
 // shorter blocks make its flushes 2.2 -> 2.9 ms; below that the shorter blocks cost more than the
 // overlap brings).
-const Variant kSharedCuVariant = {OBC_VARIANT(256, 3, 32, 16)};
+// With two owned indices the same registers and LDS hold 80 steps (3072 x 768, 4 bit: 15.71 -> 15.31 ms; 768 x 768
+// 5.29 -> 5.14).  For fewer rows the variants with one index a thread are the faster ones up to 1024 (64 x 576 2:4:
+// 519 us; 588 with 256 x 2 below 512, 555 with 512 x 2 and 96 steps a flush, 541 with 768 x 1 and 96).  Block pruning's
+// state does not fit beside them (3072 x 512 in blocks of four 8.26 -> 8.58 ms).
+const Variant kSharedCuVariants[] = {
+    {512, 80, launch_panel_256_2_56_24, nullptr},
+    {OBC_VARIANT(256, 3, 32, 16)},
+};
 constexpr int kSharedCuMinRows = 768;
 
-const Variant *pick_variant(int m, int R)
+const Variant *pick_variant(int m, int R, int mode)
 {
-    if (R >= kSharedCuMinRows && m <= kSharedCuVariant.cap && m > 256) return &kSharedCuVariant;
+    if (R >= kSharedCuMinRows && m > 256)
+        for (const Variant &v : kSharedCuVariants)
+            if (m <= v.cap && (mode != MODE_BLOCK || v.launch_block)) return &v;
     for (int i = 0; i < kNumVariants; ++i)
         if (m <= kVariants[i].cap) return &kVariants[i];
     return nullptr;
@@ -726,6 +737,10 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     };
     // rank-K update and compaction of every row's matrix into the other buffer
     auto launch_flush = [&](int K, int chunks) -> int {
+        if (K > 72) {      // (the operand tiles of two workgroups have to fit in a CU's LDS)
+            K /= 2;
+            chunks *= 2;
+        }
         const int m_next = d - host_done;
         const int nxt = (cur < 0) ? 0 : 1 - cur;
         int swz;
@@ -754,6 +769,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
             case 48: flush_kernel<48, 2, 1><<<grid, 512, 0, st>>>(fa); break;
             case 56: flush_kernel<56, 1, 1><<<grid, 512, 0, st>>>(fa); break;
             case 64: flush_kernel<64, 1, 1><<<grid, 512, 0, st>>>(fa); break;
+            case 72: flush_kernel<72, 1, 1><<<grid, 512, 0, st>>>(fa); break;
             case -24: flush_kernel<24, 1, 4><<<grid, 512, 0, st>>>(fa); break;
             case -28: flush_kernel<28, 1, 3><<<grid, 512, 0, st>>>(fa); break;
             case -40: flush_kernel<40, 1, 2><<<grid, 512, 0, st>>>(fa); break;
@@ -803,7 +819,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
 
     while (host_done < host_total) {
         const int m_max = d - host_done;
-        const Variant *v = pick_variant(m_max, R);
+        const Variant *v = pick_variant(m_max, R, mode);
         int swz;
         cur_matrix(&pa.A_cur, &pa.a_row_stride, &swz);
         pa.ld = ld_cur;
@@ -821,7 +837,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         const int most = next && (m_max >= 2816 || (R >= 96 && m_max >= 2416)) ? v->J : 1;
         int panels = 1;
         while (panels < most && host_done + panels * v->B < host_total &&
-               pick_variant(m_max - panels * v->B, R) == v) ++panels;
+               pick_variant(m_max - panels * v->B, R, mode) == v) ++panels;
         for (int j = 0; j < panels; ++j) {
             pa.old = j * v->B;
             pa.last = j == panels - 1;

@@ -1064,6 +1064,20 @@ def test_rows_many_more_rows_than_cus(obc, orc):
     assert torch.all(blk["W"] == 0)
 
 
+@pytest.mark.parametrize("R,d,k", [(768, 257, 257), (769, 512, 170), (768, 600, 260), (2, 1025, 150), (3, 1536, 150)])
+def test_panels_of_72_and_80_steps(obc, orc, R, d, k):
+    """The ends of the variants whose flush applies 72 vectors at once or 80 as two groups: both sides of the
+    change to the next smaller one, the last step inside a group; the N:M counts carried from panel to panel."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
+    Hinv = _hinv(obc, X)
+    rows = [0, R - 1]
+    _check_prune(obc, orc, W, Hinv, k, (0, 0), 2, rows=rows)
+    if d % 4 == 0:
+        _check_prune(obc, orc, W, Hinv, k, (2, 4), 2, rows=rows)
+    if d <= 600:
+        _check_quant(obc, orc, W, Hinv, 4, 2, rows=rows)
+
+
 def test_edge_cases_of_the_widened_entry_points(obc, orc):
     """Smallest shapes and degenerate masks: one sample, one column, one block, rows whose weights are
     all pruned already, every row with enough pruned weights for the bulk elimination."""
