@@ -581,6 +581,20 @@ __device__ __forceinline__ int panel_quad(const PanelArgs &a, const PanelRow &pr
     return 0;
 }
 
+// all steps of a panel whose vectors are in registers, without a loop; returns the number of them done
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int QUAD>
+__device__ __forceinline__ int panel_unrolled(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
+                                              PanelShared<BR + BL> &sh, float *ul, bool *failed)
+{
+    if constexpr (QUAD < BR / 4) {
+        const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, QUAD, failed);
+        if (n < 4) return 4 * QUAD + n;
+        return panel_unrolled<MODE, T, EPT, BR, BL, OLD, QUAD + 1>(a, pr, st, sh, ul, failed);
+    } else {
+        return BR;
+    }
+}
+
 // OLD: an instance that can follow others of its outer block (a.old > 0).  At six elements a thread the
 // panels that do not are instances without it: what re-reading the earlier vectors takes does not fit the
 // registers next to a step's state (8 x 2600, 240 steps with a flush each 40: 2.12 against 2.15 ms; 8 x 2600 in
@@ -720,11 +734,17 @@ void panel_kernel(PanelArgs a)
     bool failed = false;
     int nbv = 0;
     bool more = true;
+    if constexpr (T == 256 && EPT == 1) {
+        // (Rows whose matrices a cache holds, one to four waves each: here the branches are what a step waits for.
+        // All steps of 16 x 32 25.3 us, as a loop 30.0; 64 x 128 132 against 154, 64 x 200 241 against 273.)
+        nbv = panel_unrolled<MODE, T, EPT, BR, BL, OLD, 0>(a, pr, st, sh, ul, &failed);
+    } else {
 #pragma unroll 1
-    for (int quad = 0; more && quad < BR / 4; ++quad) {
-        const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, quad, &failed);
-        nbv += n;
-        more = n == 4;
+        for (int quad = 0; more && quad < BR / 4; ++quad) {
+            const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, quad, &failed);
+            nbv += n;
+            more = n == 4;
+        }
     }
     if constexpr (EPT == 1) {
         if (nbv > 0) {
