@@ -23,7 +23,6 @@ struct PanelRegs {
     // were a read in the selection's chain).
     int og[EPT];
     float u[BR][EPT];   // u_r for the first BR steps of the block (0 before its step); later ones live in LDS
-    float last[EPT];    // one owned element: the last step's vector, not yet in u
     // block pruning only: row j of the 4 x 4 diagonal block of the current inverse that element j
     // belongs to (entry k = A[j][4 (j / 4) + k]; the element's own slot is not used), and the first
     // position of the block being eliminated
@@ -181,6 +180,37 @@ __device__ __forceinline__ void fma_bcast(float *acc, float c, const float *u0, 
 #undef OBC_FB
 }
 
+// The same for one owned element and the vectors R0 .. S - 1: coefficient r in lane r % 16 of c[r / 16].
+template <int S, int R0, int NC, int BR>
+__device__ __forceinline__ void fma_bcast_all(float &acc, const float (&c)[NC], const float (&u)[BR][1])
+{
+#define OBC_FB(op, lane) "v_fmac_f32_dpp %0, %1, %" #op " row_newbcast:%" #lane " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (R0 < S) {
+        constexpr int N = S - R0 >= 8 ? 8 : S - R0 >= 4 ? 4 : S - R0 >= 2 ? 2 : 1, L = R0 % 16;
+        const float ck = c[R0 / 16];
+        if constexpr (N == 8)
+            asm("s_nop 1\n\t" OBC_FB(2, 10) OBC_FB(3, 11) OBC_FB(4, 12) OBC_FB(5, 13) OBC_FB(6, 14) OBC_FB(7, 15)
+                    OBC_FB(8, 16) OBC_FB(9, 17)
+                : "+v"(acc)
+                : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "v"(u[R0 + 2][0]), "v"(u[R0 + 3][0]), "v"(u[R0 + 4][0]),
+                  "v"(u[R0 + 5][0]), "v"(u[R0 + 6][0]), "v"(u[R0 + 7][0]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3),
+                  "n"(L + 4), "n"(L + 5), "n"(L + 6), "n"(L + 7));
+        else if constexpr (N == 4)
+            asm("s_nop 1\n\t" OBC_FB(2, 6) OBC_FB(3, 7) OBC_FB(4, 8) OBC_FB(5, 9)
+                : "+v"(acc)
+                : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "v"(u[R0 + 2][0]), "v"(u[R0 + 3][0]), "n"(L), "n"(L + 1),
+                  "n"(L + 2), "n"(L + 3));
+        else if constexpr (N == 2)
+            asm("s_nop 1\n\t" OBC_FB(2, 4) OBC_FB(3, 5)
+                : "+v"(acc)
+                : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "n"(L), "n"(L + 1));
+        else
+            asm("s_nop 1\n\t" OBC_FB(2, 3) : "+v"(acc) : "v"(ck), "v"(u[R0][0]), "n"(L));
+        fma_bcast_all<S, R0 + N>(acc, c, u);
+    }
+#undef OBC_FB
+}
+
 // The least index v among the lanes of `among` that hold the minimum (uniform result).  It nearly always has
 // one holder, whose index is read from its lane; among several the lowest lane's is the least where a thread
 // owns one index, else they are compared (`least`).
@@ -250,7 +280,7 @@ __device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const Pane
     return sc == sc ? score_bits(sc) : ~0u;   // a NaN score is no candidate
 }
 
-// The steps of a panel are a loop over groups of four: one body of 20 .. 40 KB instead of 200 .. 400 KB of code
+// With two or more owned elements the steps of a panel are a loop over groups of four: one body of 20 .. 40 KB instead of 200 .. 400 KB of code
 // that each wave ran through once.  What a step may do depends on its number only through uniform branches: the
 // correction stops at the vectors in use, the new vector reaches its registers by a branch tree.  Unrolled over all
 // steps, the compiler also moved values up to a hundred steps ahead of their use (8000 .. 11 000 scalar spills, up
@@ -312,16 +342,18 @@ __device__ __forceinline__ void keep_regs(PanelRegs<EPT, BR> &st, const float (&
     }
 }
 
-// One greedy step, the S-th of the block, S = 4 quad + SUB; IN_LDS: S >= BR, its vector is kept in LDS.
+// One greedy step, the S-th of the block, S = 4 quad + SUB; IN_LDS: S >= BR, its vector is kept in LDS.  QUAD:
+// quad where the steps are not a loop (one owned element), else -1.
 // OLD: the panel follows others of its outer block, whose vectors it finds in memory.  Returns 0 to
 // continue, 1 when the row has no step left, 2 on a numeric failure.  Every thread of the workgroup
 // returns the same value.
-template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int SUB, bool IN_LDS>
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int SUB, bool IN_LDS, int QUAD>
 __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
                                           PanelShared<BR + BL> &sh, float *ul, int quad)
 {
     // u_r[j] for r >= BR is kept at ul[(r - BR) * (T * EPT) + j]; only the owner of j touches it
     constexpr int CAP = T * EPT;
+    static_assert((EPT == 1) == (QUAD >= 0), "one owned element: no loop");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = 4 * quad + SUB;
     if (pr.done + S >= pr.total) return 1;
@@ -386,15 +418,6 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
             col[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr.rsrc, off, 0, 2));
         }
     }
-    if constexpr (EPT == 1) {
-        // the step before's vector into its registers, while the row is on its way (with more owned elements
-        // there are no registers to hold it until here)
-        if constexpr (SUB > 0) {
-            if constexpr (!IN_LDS) keep_regs<EPT, BR, SUB - 1, 0, BR / 4>(st, st.last, quad);
-        } else if (quad > 0) {
-            keep_regs<EPT, BR, 3, 0, BR / 4>(st, st.last, quad - 1);
-        }
-    }
     // the owner of p publishes the pivot's data and its entries of the earlier vectors of this block
     if (tid == pt) {
 #pragma unroll
@@ -420,7 +443,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
             sh.rec_invapp[S] = invapp;
             // (keeps the elements' code apart: merged, it copies their vectors into common registers first, which
             // spill: 3072 x 768 at 4 bit 17.97 instead of 15.9 ms)
-            asm volatile("" ::"v"(wp));
+            if constexpr (EPT > 1) asm volatile("" ::"v"(wp));
         }
     }
     // coefficients of the earlier panels' vectors, which are in memory: one lane each
@@ -436,14 +459,15 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     const double g = sh.g, invapp = sh.invapp;
     const int op = __builtin_amdgcn_readfirstlane(sh.o);
     const bool isdead = op < 0;
-    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ..., 0 from S on
-    constexpr int NC = ((IN_LDS ? BR + BL : BR) + 15) / 16;
-    float cv[NC];
+    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ..., from S on 0 in the
+    // loop and never used without it
+    constexpr int NC = QUAD >= 0 ? (4 * QUAD + SUB + 15) / 16 : ((IN_LDS ? BR + BL : BR) + 15) / 16;
+    float cv[NC > 0 ? NC : 1];
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
         const int r = 16 * k + (lane & 15);
         const float c = __fmul_rn(sh.cvec[r], sh.invd_s[r]);
-        cv[k] = r < S ? c : 0.f;
+        cv[k] = QUAD >= 0 || r < S ? c : 0.f;
     }
 
     if (!__builtin_amdgcn_readfirstlane(sh.ok)) return 2;   // (after the reads above are on their way)
@@ -497,7 +521,9 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     float c[EPT];
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = 0.f;
-    if constexpr (!IN_LDS) {
+    if constexpr (EPT == 1) {
+        fma_bcast_all<4 * QUAD + SUB, 0>(c[0], cv, st.u);
+    } else if constexpr (!IN_LDS) {
         correct_regs<EPT, BR, 0, BR / 4>(c, cv, st, SUB == 0 ? quad : quad + 1);
     } else {
         correct_regs<EPT, BR, 0, BR / 4>(c, cv, st, BR / 4);
@@ -506,8 +532,8 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = __fsub_rn(col[e], c[e]);
     if constexpr (EPT == 1) {
-        static_assert(EPT > 1 || BL == 0, "one owned element: all vectors in registers");
-        st.last[0] = c[0];
+        static_assert(BL == 0 || EPT > 1, "one owned element: all vectors in registers");
+        st.u[4 * QUAD + SUB][0] = c[0];
     } else if constexpr (!IN_LDS) {
         keep_regs<EPT, BR, SUB, 0, BR / 4>(st, c, quad);
     } else {
@@ -556,17 +582,17 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 }
 
 // Four steps from 4 quad on; returns the number of them done and sets *failed.
-template <int MODE, int T, int EPT, int BR, int BL, bool OLD, bool IN_LDS>
+template <int MODE, int T, int EPT, int BR, int BL, bool OLD, bool IN_LDS, int QUAD = -1>
 __device__ __forceinline__ int panel_quad(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
                                           PanelShared<BR + BL> &sh, float *ul, int quad, bool *failed)
 {
-    int rc = panel_step<MODE, T, EPT, BR, BL, OLD, 0, IN_LDS>(a, pr, st, sh, ul, quad);
+    int rc = panel_step<MODE, T, EPT, BR, BL, OLD, 0, IN_LDS, QUAD>(a, pr, st, sh, ul, quad);
     if (rc == 0) {
-        rc = panel_step<MODE, T, EPT, BR, BL, OLD, 1, IN_LDS>(a, pr, st, sh, ul, quad);
+        rc = panel_step<MODE, T, EPT, BR, BL, OLD, 1, IN_LDS, QUAD>(a, pr, st, sh, ul, quad);
         if (rc == 0) {
-            rc = panel_step<MODE, T, EPT, BR, BL, OLD, 2, IN_LDS>(a, pr, st, sh, ul, quad);
+            rc = panel_step<MODE, T, EPT, BR, BL, OLD, 2, IN_LDS, QUAD>(a, pr, st, sh, ul, quad);
             if (rc == 0) {
-                rc = panel_step<MODE, T, EPT, BR, BL, OLD, 3, IN_LDS>(a, pr, st, sh, ul, quad);
+                rc = panel_step<MODE, T, EPT, BR, BL, OLD, 3, IN_LDS, QUAD>(a, pr, st, sh, ul, quad);
                 if (rc == 0) return 4;
                 *failed = rc == 2;
                 return 3;
@@ -587,7 +613,7 @@ __device__ __forceinline__ int panel_unrolled(const PanelArgs &a, const PanelRow
                                               PanelShared<BR + BL> &sh, float *ul, bool *failed)
 {
     if constexpr (QUAD < BR / 4) {
-        const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, QUAD, failed);
+        const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false, QUAD>(a, pr, st, sh, ul, QUAD, failed);
         if (n < 4) return 4 * QUAD + n;
         return panel_unrolled<MODE, T, EPT, BR, BL, OLD, QUAD + 1>(a, pr, st, sh, ul, failed);
     } else {
@@ -673,7 +699,6 @@ void panel_kernel(PanelArgs a)
     for (int e = 0; e < EPT; ++e) {
 #pragma unroll
         for (int r = 0; r < BR; ++r) st.u[r][e] = 0.f;
-        st.last[e] = 0.f;
 #pragma unroll
         for (int r = 0; r < BL; ++r) ul[r * (T * EPT) + tid + e * T] = 0.f;
     }
@@ -734,9 +759,12 @@ void panel_kernel(PanelArgs a)
     bool failed = false;
     int nbv = 0;
     bool more = true;
-    if constexpr (T == 256 && EPT == 1) {
-        // (Rows whose matrices a cache holds, one to four waves each: here the branches are what a step waits for.
-        // All steps of 16 x 32 25.3 us, as a loop 30.0; 64 x 128 132 against 154, 64 x 200 241 against 273.)
+    if constexpr (EPT == 1) {
+        // (Up to 1024 columns: a step is short, and the loop's branches, its corrections by whole groups of four and the
+        // select of their coefficients are what it waits for, above all where a CU holds one row.  In us, as a loop
+        // against without: 64 x 576 2:4 520, 503; 12 x 1000 1894, 1785; 64 x 768 at 4 bit 1318, 1273; in blocks of four
+        // 12 x 516 697, 626, 64 x 768 1216, 1132.  Up to 256 columns against steps without a loop that kept those
+        // corrections, the select and a copy per step: 64 x 128 132.5, 128.8; 64 x 200 244.5, 238.0.)
         nbv = panel_unrolled<MODE, T, EPT, BR, BL, OLD, 0>(a, pr, st, sh, ul, &failed);
     } else {
 #pragma unroll 1
@@ -744,17 +772,6 @@ void panel_kernel(PanelArgs a)
             const int n = panel_quad<MODE, T, EPT, BR, BL, OLD, false>(a, pr, st, sh, ul, quad, &failed);
             nbv += n;
             more = n == 4;
-        }
-    }
-    if constexpr (EPT == 1) {
-        if (nbv > 0) {
-            const int quad = (nbv - 1) >> 2;
-            switch ((nbv - 1) & 3) {
-            case 0: keep_regs<EPT, BR, 0, 0, BR / 4>(st, st.last, quad); break;
-            case 1: keep_regs<EPT, BR, 1, 0, BR / 4>(st, st.last, quad); break;
-            case 2: keep_regs<EPT, BR, 2, 0, BR / 4>(st, st.last, quad); break;
-            default: keep_regs<EPT, BR, 3, 0, BR / 4>(st, st.last, quad);
-            }
         }
     }
     if constexpr (BL > 0) {

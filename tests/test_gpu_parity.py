@@ -366,6 +366,19 @@ def test_prune_rows_n_m(obc, orc, strategy, nm):
     assert np.all(zeros == nm[1] - nm[0])
 
 
+@pytest.mark.parametrize("d,nm", [(32, (2, 4)), (64, (3, 8)), (64, (10, 64)), (240, (20, 60)), (250, (50, 250)),
+                                  (264, (2, 4)), (765, (100, 255))])
+def test_n_m_counts_and_trace(obc, orc, d, nm):
+    """N:M in rows of one panel (which load no counters) and of several, whose counts travel from panel to
+    panel; M up to the largest.  The trace is written at the indices that the counts share a word with."""
+    W, X = _layer("conv64x576", d_col=d, d_row=3, n_samples=4 * d)
+    Hinv = _hinv(obc, X)
+    k = d // nm[1] * (nm[1] - nm[0])
+    res, _ = _check_prune(obc, orc, W, Hinv, k, nm, 2, want_trace=True)
+    zeros = (res["W"] == 0).reshape(3, d // nm[1], nm[1]).sum(dim=2)
+    assert bool((zeros == nm[1] - nm[0]).all())
+
+
 @pytest.mark.parametrize("strategy", [1, 2])
 def test_prune_rows_zero_weights_and_ties(obc, orc, strategy):
     d = 96
