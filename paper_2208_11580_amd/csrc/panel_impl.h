@@ -152,7 +152,8 @@ __device__ __forceinline__ unsigned wave_umin(unsigned v)
 // acc[e] += sum_i c_i u_i[e], i < 4, for N elements: coefficient i is in lane L + i of every 16-lane row
 // of c.  The coefficient is taken from its lane by the multiply-add itself (DPP row_newbcast): no lane
 // read, no scalar register.  A DPP operand must not have been written by the vector ALU within two
-// cycles; the compiler does not look into the block, so it waits itself.
+// cycles; the compiler does not look into the block, so it waits itself.  (The sums are written before the last
+// vector is read: without "&" one still to come, known to be 0, could share the register of a sum that starts at 0.)
 template <int L, int N>
 __device__ __forceinline__ void fma_bcast(float *acc, float c, const float *u0, const float *u1, const float *u2,
                                           const float *u3)
@@ -162,19 +163,19 @@ __device__ __forceinline__ void fma_bcast(float *acc, float c, const float *u0, 
         asm("s_nop 1\n\t" OBC_FB(0, 3, 4, 16) OBC_FB(1, 3, 5, 16) OBC_FB(2, 3, 6, 16) OBC_FB(0, 3, 7, 17)
                 OBC_FB(1, 3, 8, 17) OBC_FB(2, 3, 9, 17) OBC_FB(0, 3, 10, 18) OBC_FB(1, 3, 11, 18)
                     OBC_FB(2, 3, 12, 18) OBC_FB(0, 3, 13, 19) OBC_FB(1, 3, 14, 19) OBC_FB(2, 3, 15, 19)
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2])
+            : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2])
             : "v"(c), "v"(u0[0]), "v"(u0[1]), "v"(u0[2]), "v"(u1[0]), "v"(u1[1]), "v"(u1[2]), "v"(u2[0]), "v"(u2[1]),
               "v"(u2[2]), "v"(u3[0]), "v"(u3[1]), "v"(u3[2]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
         if constexpr (N > 3) fma_bcast<L, N - 3>(acc + 3, c, u0 + 3, u1 + 3, u2 + 3, u3 + 3);
     } else if constexpr (N == 2) {
         asm("s_nop 1\n\t" OBC_FB(0, 2, 3, 11) OBC_FB(1, 2, 4, 11) OBC_FB(0, 2, 5, 12) OBC_FB(1, 2, 6, 12)
                 OBC_FB(0, 2, 7, 13) OBC_FB(1, 2, 8, 13) OBC_FB(0, 2, 9, 14) OBC_FB(1, 2, 10, 14)
-            : "+v"(acc[0]), "+v"(acc[1])
+            : "+&v"(acc[0]), "+&v"(acc[1])
             : "v"(c), "v"(u0[0]), "v"(u0[1]), "v"(u1[0]), "v"(u1[1]), "v"(u2[0]), "v"(u2[1]), "v"(u3[0]), "v"(u3[1]),
               "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
     } else {
         asm("s_nop 1\n\t" OBC_FB(0, 1, 2, 6) OBC_FB(0, 1, 3, 7) OBC_FB(0, 1, 4, 8) OBC_FB(0, 1, 5, 9)
-            : "+v"(acc[0])
+            : "+&v"(acc[0])
             : "v"(c), "v"(u0[0]), "v"(u1[0]), "v"(u2[0]), "v"(u3[0]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
     }
 #undef OBC_FB
@@ -191,21 +192,21 @@ __device__ __forceinline__ void fma_bcast_all(float &acc, const float (&c)[NC], 
         if constexpr (N == 8)
             asm("s_nop 1\n\t" OBC_FB(2, 10) OBC_FB(3, 11) OBC_FB(4, 12) OBC_FB(5, 13) OBC_FB(6, 14) OBC_FB(7, 15)
                     OBC_FB(8, 16) OBC_FB(9, 17)
-                : "+v"(acc)
+                : "+&v"(acc)
                 : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "v"(u[R0 + 2][0]), "v"(u[R0 + 3][0]), "v"(u[R0 + 4][0]),
                   "v"(u[R0 + 5][0]), "v"(u[R0 + 6][0]), "v"(u[R0 + 7][0]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3),
                   "n"(L + 4), "n"(L + 5), "n"(L + 6), "n"(L + 7));
         else if constexpr (N == 4)
             asm("s_nop 1\n\t" OBC_FB(2, 6) OBC_FB(3, 7) OBC_FB(4, 8) OBC_FB(5, 9)
-                : "+v"(acc)
+                : "+&v"(acc)
                 : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "v"(u[R0 + 2][0]), "v"(u[R0 + 3][0]), "n"(L), "n"(L + 1),
                   "n"(L + 2), "n"(L + 3));
         else if constexpr (N == 2)
             asm("s_nop 1\n\t" OBC_FB(2, 4) OBC_FB(3, 5)
-                : "+v"(acc)
+                : "+&v"(acc)
                 : "v"(ck), "v"(u[R0][0]), "v"(u[R0 + 1][0]), "n"(L), "n"(L + 1));
         else
-            asm("s_nop 1\n\t" OBC_FB(2, 3) : "+v"(acc) : "v"(ck), "v"(u[R0][0]), "n"(L));
+            asm("s_nop 1\n\t" OBC_FB(2, 3) : "+&v"(acc) : "v"(ck), "v"(u[R0][0]), "n"(L));
         fma_bcast_all<S, R0 + N>(acc, c, u);
     }
 #undef OBC_FB
@@ -280,12 +281,21 @@ __device__ __forceinline__ unsigned candidate_key(const PanelArgs &a, const Pane
     return sc == sc ? score_bits(sc) : ~0u;   // a NaN score is no candidate
 }
 
-// With two or more owned elements the steps of a panel are a loop over groups of four: one body of 20 .. 40 KB instead of 200 .. 400 KB of code
-// that each wave ran through once.  What a step may do depends on its number only through uniform branches: the
-// correction stops at the vectors in use, the new vector reaches its registers by a branch tree.  Unrolled over all
-// steps, the compiler also moved values up to a hundred steps ahead of their use (8000 .. 11 000 scalar spills, up
-// to 700 vector ones).  256 x 2304 at 4 bit 24.3 -> 23.5 ms, in blocks of four 25.1 -> 24.4, 3072 x 768 at 4 bit
-// 16.17 -> 15.73 ms; results bit for bit the same.
+// Where a thread owns two to four elements the steps of a panel are a loop over groups of four: one body of 20 .. 40 KB
+// instead of 200 .. 400 KB of code that each wave would run through once.  What a step may do depends on its number
+// only through uniform branches: the correction stops at the vectors in use, the new vector reaches its registers by a
+// branch tree.  In ms, without a loop and as one: 3072 x 768 at 4 bit 15.59, 15.26, 768 x 768 pruned 4.21, 4.12, 203 x 1283
+// at 4 bit 4.93, 4.90, 256 x 2304 at 4 bit 23.19, 23.10, 12 x 2048 pruned 5.88, 5.84; blocks of four within 1.2 % either way.
+// From six elements on the loop holds all vectors' registers from the first step on, also next to the re-reading of
+// earlier panels' vectors, and its branches cost more than the code.  In ms, as a loop and without: 100 x 4608 pruned
+// 88.1, 86.7, at 4 bit 88.5, 86.3, 2:4 76.1, 75.0, in blocks of four 94.9, 93.4; 64 x 3072 in blocks of four 23.3, 22.7;
+// 100 x 3072 at 4 bit 28.8, 28.1; 8 x 2600 pruned 10.21, 10.11.
+// With one it is a step's latency that the branches lengthen, above all where a CU holds one row; corrections by whole
+// groups of four and the select of their coefficients count there too.  In us, as a loop and without: 64 x 576 2:4
+// 520, 503; 12 x 1000 pruned 1894, 1785; 64 x 768 at 4 bit 1318, 1273; in blocks of four 12 x 516 697, 626, 64 x 768 1216,
+// 1132.  Results are bit for bit the same.
+template <int EPT>
+constexpr bool kStepLoop = EPT >= 2 && EPT <= 4;
 
 // acc[e] += the correction by the register-held vectors from 4 K to 4 LAST - 1, four at a time, as far as the
 // first 4 `quads` go (a group's vectors that are still to come are 0, and so are their coefficients).
@@ -343,7 +353,7 @@ __device__ __forceinline__ void keep_regs(PanelRegs<EPT, BR> &st, const float (&
 }
 
 // One greedy step, the S-th of the block, S = 4 quad + SUB; IN_LDS: S >= BR, its vector is kept in LDS.  QUAD:
-// quad where the steps are not a loop (one owned element), else -1.
+// quad where the steps are not a loop, else -1.
 // OLD: the panel follows others of its outer block, whose vectors it finds in memory.  Returns 0 to
 // continue, 1 when the row has no step left, 2 on a numeric failure.  Every thread of the workgroup
 // returns the same value.
@@ -353,7 +363,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 {
     // u_r[j] for r >= BR is kept at ul[(r - BR) * (T * EPT) + j]; only the owner of j touches it
     constexpr int CAP = T * EPT;
-    static_assert((EPT == 1) == (QUAD >= 0), "one owned element: no loop");
+    static_assert(EPT > 1 || (QUAD >= 0 && BL == 0), "one owned element: all vectors in registers, no loop");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = 4 * quad + SUB;
     if (pr.done + S >= pr.total) return 1;
@@ -459,15 +469,15 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     const double g = sh.g, invapp = sh.invapp;
     const int op = __builtin_amdgcn_readfirstlane(sh.o);
     const bool isdead = op < 0;
-    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ..., from S on 0 in the
-    // loop and never used without it
+    // coefficients u_r[p] / a_r of this step: lane l has those of r = l % 16, l % 16 + 16, ..., from S on 0 (one
+    // owned element: never used)
     constexpr int NC = QUAD >= 0 ? (4 * QUAD + SUB + 15) / 16 : ((IN_LDS ? BR + BL : BR) + 15) / 16;
     float cv[NC > 0 ? NC : 1];
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
         const int r = 16 * k + (lane & 15);
         const float c = __fmul_rn(sh.cvec[r], sh.invd_s[r]);
-        cv[k] = QUAD >= 0 || r < S ? c : 0.f;
+        cv[k] = EPT == 1 || r < S ? c : 0.f;
     }
 
     if (!__builtin_amdgcn_readfirstlane(sh.ok)) return 2;   // (after the reads above are on their way)
@@ -531,9 +541,9 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) c[e] = __fsub_rn(col[e], c[e]);
-    if constexpr (EPT == 1) {
-        static_assert(BL == 0 || EPT > 1, "one owned element: all vectors in registers");
-        st.u[4 * QUAD + SUB][0] = c[0];
+    if constexpr (QUAD >= 0) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) st.u[4 * QUAD + SUB][e] = c[e];
     } else if constexpr (!IN_LDS) {
         keep_regs<EPT, BR, SUB, 0, BR / 4>(st, c, quad);
     } else {
@@ -561,10 +571,14 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
         }
     }
     if (MODE == MODE_PRUNE && a.nm_m > 0 && !isdead) {
-        const int b = nm_block(op, pr.nm_inv);
+        const int b = nm_block(op, pr.nm_inv), pw = p - (pr.m - pr.mw);   // p less the wave's first index
 #pragma unroll
-        for (int e = 0; e < EPT; ++e)
+        for (int e = 0; e < EPT; ++e) {
+            // (original indices ascend with the position: a block's weights lie within M - 1 positions of each other,
+            // and few waves have an element there)
+            if (EPT > 1 && (unsigned)(pw - e * T + a.nm_m - 1) >= 62u + 2 * a.nm_m) continue;
             if (st.og[e] >= 0 && nm_block(st.og[e] & ((1 << kNmShift) - 1), pr.nm_inv) == b) st.og[e] += 1 << kNmShift;
+        }
     }
     if (MODE == MODE_BLOCK && a.trace && SUB == 3) {
         float *tr = a.trace + ((size_t)pr.row * a.out_ld + (pr.done + S) / 4) * pr.d;
@@ -607,7 +621,7 @@ __device__ __forceinline__ int panel_quad(const PanelArgs &a, const PanelRow &pr
     return 0;
 }
 
-// all steps of a panel whose vectors are in registers, without a loop; returns the number of them done
+// all steps of a panel whose vectors are kept in registers, without a loop; returns the number of them done
 template <int MODE, int T, int EPT, int BR, int BL, bool OLD, int QUAD>
 __device__ __forceinline__ int panel_unrolled(const PanelArgs &a, const PanelRow &pr, PanelRegs<EPT, BR> &st,
                                               PanelShared<BR + BL> &sh, float *ul, bool *failed)
@@ -759,13 +773,9 @@ void panel_kernel(PanelArgs a)
     bool failed = false;
     int nbv = 0;
     bool more = true;
-    if constexpr (EPT == 1) {
-        // (Up to 1024 columns: a step is short, and the loop's branches, its corrections by whole groups of four and the
-        // select of their coefficients are what it waits for, above all where a CU holds one row.  In us, as a loop
-        // against without: 64 x 576 2:4 520, 503; 12 x 1000 1894, 1785; 64 x 768 at 4 bit 1318, 1273; in blocks of four
-        // 12 x 516 697, 626, 64 x 768 1216, 1132.  Up to 256 columns against steps without a loop that kept those
-        // corrections, the select and a copy per step: 64 x 128 132.5, 128.8; 64 x 200 244.5, 238.0.)
+    if constexpr (!kStepLoop<EPT>) {
         nbv = panel_unrolled<MODE, T, EPT, BR, BL, OLD, 0>(a, pr, st, sh, ul, &failed);
+        more = nbv == BR;
     } else {
 #pragma unroll 1
         for (int quad = 0; more && quad < BR / 4; ++quad) {

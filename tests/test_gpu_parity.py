@@ -367,7 +367,8 @@ def test_prune_rows_n_m(obc, orc, strategy, nm):
 
 
 @pytest.mark.parametrize("d,nm", [(32, (2, 4)), (64, (3, 8)), (64, (10, 64)), (240, (20, 60)), (250, (50, 250)),
-                                  (264, (2, 4)), (765, (100, 255))])
+                                  (264, (2, 4)), (765, (100, 255)), (1275, (215, 255)), (2310, (225, 231)),
+                                  (4590, (251, 255))])
 def test_n_m_counts_and_trace(obc, orc, d, nm):
     """N:M in rows of one panel (which load no counters) and of several, whose counts travel from panel to
     panel; M up to the largest.  The trace is written at the indices that the counts share a word with."""
