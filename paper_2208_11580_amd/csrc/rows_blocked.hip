@@ -328,7 +328,7 @@ struct FlushArgs {
     int ld_new;
     int d, R, strips;
     int keep;                // the new matrices stay in the caches
-    int chunks;              // panels whose vectors this flush applies, KMAX each
+    int chunks;              // groups of KMAX vectors that this flush applies (one panel each, or half of one above 72 steps)
     BlockedWs ws;
 };
 
@@ -624,7 +624,7 @@ struct Variant {
 
 // (512 x 3: 24 vectors in LDS, 72 steps -- 203 x 1283 at 8 bit 5.10 -> 4.93 ms, 256 x 2304 at 4 bit 23.4 -> 23.1 against
 // 16 and 64.)
-const Variant kVariants[] = {
+constexpr Variant kVariants[] = {
     {OBC_VARIANT(256, 1, 64, 0)},
     {OBC_VARIANT(1024, 1, 64, 0)},
     {OBC_VARIANT(512, 3, 48, 24)},
@@ -645,11 +645,36 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 // 5.29 -> 5.14).  For fewer rows the variants with one index a thread are the faster ones up to 1024 (64 x 576 2:4:
 // 519 us; 588 with 256 x 2 below 512, 555 with 512 x 2 and 96 steps a flush, 541 with 768 x 1 and 96).  Block pruning's
 // state does not fit beside them (3072 x 512 in blocks of four 8.26 -> 8.58 ms).
-const Variant kSharedCuVariants[] = {
+constexpr Variant kSharedCuVariants[] = {
     {512, 80, launch_panel_256_2_56_24, nullptr},
     {OBC_VARIANT(256, 3, 32, 16)},
 };
 constexpr int kSharedCuMinRows = 768;
+
+// A flush applies K vectors at once, or several groups of K one after the other: as many as there is an instance for
+// (0: none).
+constexpr int flush_groups(int K)
+{
+    return K == 24 ? 4 : K == 28 ? 3 : K == 40 ? 2 : K == 48 || K == 56 || K == 64 || K == 72 ? 1 : 0;
+}
+// ... and panels of more than 72 vectors go as two groups (the operand tiles of two workgroups have to fit in a CU's LDS)
+constexpr int flush_split(int B) { return B > 72 ? 2 : 1; }
+
+// what a flush reads has room in U and an instance of the kernel, whatever number of panels it serves
+constexpr bool flush_serves(const Variant &v)
+{
+    const int panels = v.J > 1 ? v.J : 1, split = flush_split(v.B);
+    return panels * v.B <= UCAP && v.B % split == 0 && panels * split <= flush_groups(v.B / split);
+}
+constexpr bool flush_serves_all()
+{
+    for (const Variant &v : kVariants)
+        if (!flush_serves(v)) return false;
+    for (const Variant &v : kSharedCuVariants)
+        if (!flush_serves(v)) return false;
+    return BMAX <= UCAP && flush_split(BMAX) == 1 && flush_groups(BMAX) >= 1;
+}
+static_assert(flush_serves_all(), "a panel's steps, or those of the panels that share a flush, without a flush kernel");
 
 const Variant *pick_variant(int m, int R, int mode)
 {
@@ -737,10 +762,8 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     };
     // rank-K update and compaction of every row's matrix into the other buffer
     auto launch_flush = [&](int K, int chunks) -> int {
-        if (K > 72) {      // (the operand tiles of two workgroups have to fit in a CU's LDS)
-            K /= 2;
-            chunks *= 2;
-        }
+        chunks *= flush_split(K);
+        K /= flush_split(K);
         const int m_next = d - host_done;
         const int nxt = (cur < 0) ? 0 : 1 - cur;
         int swz;
@@ -770,9 +793,9 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
             case 56: flush_kernel<56, 1, 1><<<grid, 512, 0, st>>>(fa); break;
             case 64: flush_kernel<64, 1, 1><<<grid, 512, 0, st>>>(fa); break;
             case 72: flush_kernel<72, 1, 1><<<grid, 512, 0, st>>>(fa); break;
-            case -24: flush_kernel<24, 1, 4><<<grid, 512, 0, st>>>(fa); break;
-            case -28: flush_kernel<28, 1, 3><<<grid, 512, 0, st>>>(fa); break;
-            case -40: flush_kernel<40, 1, 2><<<grid, 512, 0, st>>>(fa); break;
+            case -24: flush_kernel<24, 1, flush_groups(24)><<<grid, 512, 0, st>>>(fa); break;
+            case -28: flush_kernel<28, 1, flush_groups(28)><<<grid, 512, 0, st>>>(fa); break;
+            case -40: flush_kernel<40, 1, flush_groups(40)><<<grid, 512, 0, st>>>(fa); break;
             default: return obc_fail(ctx, OBC_ERR_BAD_ARG, "row solver: no flush kernel for block size %d", K);
             }
         }
