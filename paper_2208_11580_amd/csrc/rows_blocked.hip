@@ -354,13 +354,19 @@ constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: 
 constexpr int kMatLoadPolicy = 0;
 constexpr int kMatStorePolicy = 2 | 16;
 
-// Cached instead, up to this many bytes of all rows' new matrices, the next panels find the rows that they fetch
-// nearer: 203 x 1283 at 8 bit 5.50 -> 5.27 ms, 64 x 576 2:4 528 -> 519 us; above, the displaced lines cost more
-// (256 x 2304 23.96 -> 24.05 ms at 800 MB, 24.9 without a limit).
-const double kKeepBytes = 640e6;
+// They go through the caches in two cases.  (1) The live size is no multiple of 4: a wave's stores then begin and end
+// inside 64-byte sectors, and two waves' halves of a sector meet in L2 only if they are kept there.  In ms, pruned,
+// streaming and cached: 203 x 1283 5.11, 4.90; 768 x 767 4.46, 4.34; 203 x 1999 15.14, 14.20; 100 x 2301 13.81, 13.09;
+// 12 x 4095 32.6, 31.6; 256 x 2303 at 4 bit 26.7, 25.2; 3071 x 765 at 4 bit 16.9, 16.3.  (2) All rows' new matrices
+// together fit the 256 MB memory-side cache, where the next panels find the rows that they fetch: 64 x 576 2:4 507,
+// 500 us; 128 x 1536 5.21, 5.18 ms; 768 x 768 4.05, 4.05.  Larger aligned ones only displace what is of use: with a
+// limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800 6.93 against 6.84; without one 256 x 2304 at 4 bit
+// 23.9 against 22.9.
+constexpr double kKeepBytes = 256e6;
 
-// K is the block size: every row that still has steps to do has exactly K deferred eliminations
-// (a row with fewer has finished and is skipped).  A strip is HALVES x 128 rows tall: the U tile
+// K vectors are applied at once, and up to JMAX groups of K one after the other: every row that still
+// has steps to do has exactly K x chunks deferred eliminations (a row with fewer has finished and is
+// skipped).  A strip is HALVES x 128 rows tall: the U tile
 // of a column block, once in LDS, serves all the strip's halves (loading it is the expensive part
 // of a tile next to the matrix traffic itself), and the F tile covers the whole strip.
 template <int KMAX, int HALVES, int JMAX>
@@ -776,7 +782,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         // strips of 256 rows where two workgroups' tiles fit in a CU's LDS, else 128
         const int halves = (K <= 48 && chunks == 1) ? 2 : 1;
         fa.chunks = chunks;
-        fa.keep = (double)R * m_next * m_next * 2.0 <= kKeepBytes;
+        fa.keep = m_next % 4 != 0 || (double)R * m_next * m_next * 2.0 <= kKeepBytes;
         fa.strips = (m_next + halves * FT - 1) / (halves * FT);
         const int rows8 = (R + 7) / 8 * 8;
         {
