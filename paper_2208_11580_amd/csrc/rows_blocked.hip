@@ -682,11 +682,19 @@ constexpr bool flush_serves_all()
 }
 static_assert(flush_serves_all(), "a panel's steps, or those of the panels that share a flush, without a flush kernel");
 
+// Panels of 80 steps where they reach 256 live columns, from which on a thread owns one index, in fewer panels than
+// those of 48 do; where both take as many (273..304 and 337..352 columns) the shorter ones leave more of the steps to
+// the cheaper variant.  Up to 272 columns 80 steps save one of the panels below 256 instead.  In us, pruned, with 80 and
+// with 48 steps: 1024 x 300 798, 727; 3072 x 288 1944, 1753; 1024 x 344 1111, 1030; 1536 x 344 1394, 1366; 3072 x 320 2126,
+// 2371; 1536 x 416 1838, 2130; 768 x 264 499, 518; 1536 x 264 802, 864 (but 1024 x 264 653, 641).  Both in turn as the rule has
+// it, against 80 throughout: 1536 x 384 1615, 1688; 3072 x 512 5553, 5642; 768 x 512 1582, 1574.
+constexpr bool longer_panels(int m) { return m <= 272 || (m - 256 + 79) / 80 < (m - 256 + 47) / 48; }
+
 const Variant *pick_variant(int m, int R, int mode)
 {
     if (R >= kSharedCuMinRows && m > 256)
         for (const Variant &v : kSharedCuVariants)
-            if (m <= v.cap && (mode != MODE_BLOCK || v.launch_block)) return &v;
+            if (m <= v.cap && (mode != MODE_BLOCK || v.launch_block) && (v.B != 80 || longer_panels(m))) return &v;
     for (int i = 0; i < kNumVariants; ++i)
         if (m <= kVariants[i].cap) return &kVariants[i];
     return nullptr;

@@ -1078,10 +1078,13 @@ def test_rows_many_more_rows_than_cus(obc, orc):
     assert torch.all(blk["W"] == 0)
 
 
-@pytest.mark.parametrize("R,d,k", [(768, 257, 257), (769, 512, 170), (768, 600, 260), (2, 1025, 150), (3, 1536, 150)])
+@pytest.mark.parametrize("R,d,k", [(768, 257, 257), (769, 512, 170), (768, 600, 260), (2, 1025, 150), (3, 1536, 150),
+                                   (768, 272, 136), (768, 273, 273), (768, 304, 150), (768, 305, 305), (770, 336, 130), (768, 337, 337), (768, 352, 170),
+                                   (768, 353, 353)])
 def test_panels_of_72_and_80_steps(obc, orc, R, d, k):
     """The ends of the variants whose flush applies 72 vectors at once or 80 as two groups: both sides of the
-    change to the next smaller one, the last step inside a group; the N:M counts carried from panel to panel."""
+    change to the next smaller one and of the widths at which 48 steps take the place of 80, the last step inside
+    a group; the N:M counts carried from panel to panel."""
     W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
     Hinv = _hinv(obc, X)
     rows = [0, R - 1]
