@@ -1,6 +1,6 @@
 // Declarations shared by the blocked row solver's translation units: workspace layout, kernel
 // argument blocks, and the per-variant panel launchers (one translation unit per variant so that
-// the heavily unrolled panel kernels compile in parallel).
+// they compile in parallel: up to half a minute where the steps are not a loop).
 #pragma once
 
 #include "rows_common.h"
@@ -102,7 +102,6 @@ typedef int PanelLaunch(int mode, int R, hipStream_t st, const PanelArgs &a);
 #define OBC_DECLARE_PANEL(T, EPT, BR, BL) \
     PanelLaunch launch_panel_##T##_##EPT##_##BR##_##BL, launch_panel_block_##T##_##EPT##_##BR##_##BL
 OBC_DECLARE_PANEL(256, 1, 64, 0);
-OBC_DECLARE_PANEL(256, 3, 32, 16);
 OBC_DECLARE_PANEL(1024, 1, 64, 0);
 OBC_DECLARE_PANEL(512, 3, 48, 24);
 OBC_DECLARE_PANEL(512, 4, 40, 16);
@@ -110,6 +109,6 @@ OBC_DECLARE_PANEL(768, 3, 32, 16);
 OBC_DECLARE_PANEL(512, 6, 28, 12);
 OBC_DECLARE_PANEL(512, 8, 20, 8);
 OBC_DECLARE_PANEL(512, 9, 16, 8);
-PanelLaunch launch_panel_256_2_56_24, launch_panel_old_512_6_28_12;
+PanelLaunch launch_panel_256_2_56_24, launch_panel_256_3_32_16, launch_panel_old_512_6_28_12;
 
 }  // namespace obc_blocked

@@ -617,7 +617,7 @@ struct Variant {
     int cap;   // largest live size it handles (T * EPT)
     int B;     // steps per panel
     PanelLaunch *launch;
-    PanelLaunch *launch_block;       // block pruning (null: not served)
+    PanelLaunch *launch_block;       // block pruning (null: never asked for)
     // panels that follow others of their outer block: one flush applies the eliminations of up to J
     int J;
     PanelLaunch *launch_old;
@@ -642,18 +642,18 @@ constexpr Variant kVariants[] = {
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-// Three of these fit on one CU (registers and LDS); with several times more rows than CUs that
-// hides the per-step latency of one row behind the steps of two others (measured: a gain from
-// three rows per CU on -- the 768 x 768 layer 7.6 -> 7.1 ms, its panels 3.5 -> 2.4 ms while the
-// shorter blocks make its flushes 2.2 -> 2.9 ms; below that the shorter blocks cost more than the
-// overlap brings).
-// With two owned indices the same registers and LDS hold 80 steps (3072 x 768, 4 bit: 15.71 -> 15.31 ms; 768 x 768
-// 5.29 -> 5.14).  For fewer rows the variants with one index a thread are the faster ones up to 1024 (64 x 576 2:4:
-// 519 us; 588 with 256 x 2 below 512, 555 with 512 x 2 and 96 steps a flush, 541 with 768 x 1 and 96).  Block pruning's
-// state does not fit beside them (3072 x 512 in blocks of four 8.26 -> 8.58 ms).
+// Three of these fit on one CU (registers and LDS), two where a thread owns one index; with several times more
+// rows than CUs that hides a row's latency behind the steps of two others.  From three rows per CU on, in ms, with
+// 1024 x 1 and with these: 768 x 400 pruned 1.13, 1.00; 768 x 768 pruned 4.25, 4.06, at 4 bit 4.32, 4.05; 1536 x 600 4.95, 4.30;
+// 3072 x 512 at 4 bit 6.09, 5.58; 3072 x 768 pruned 15.98, 15.19, at 4 bit 16.49, 15.26.  Against: a last round of few rows, 1024 x 512
+// 2.02, 2.17; 1024 x 768 5.46, 5.69.  512 rows are two full rounds of the wider ones: 512 x 512 1.16, 1.26, 512 x 768 2.91, 3.11.
+// With two owned indices the same registers and LDS hold 80 steps.
+// Block pruning never takes them: its state does not fit beside them (83 registers in scratch memory at 256 x 3), and the
+// steps of 1024 x 1, which are not a loop, are the faster ones at every width and row count: 768 x 260 497 against 531 us,
+// 3072 x 400 3.86, 4.24 ms; 1536 x 512 2.92, 4.14; 768 x 768 3.99, 5.16; 3072 x 768 15.3, 18.9.
 constexpr Variant kSharedCuVariants[] = {
     {512, 80, launch_panel_256_2_56_24, nullptr},
-    {OBC_VARIANT(256, 3, 32, 16)},
+    {768, 48, launch_panel_256_3_32_16, nullptr},
 };
 constexpr int kSharedCuMinRows = 768;
 
@@ -692,9 +692,9 @@ constexpr bool longer_panels(int m) { return m <= 272 || (m - 256 + 79) / 80 < (
 
 const Variant *pick_variant(int m, int R, int mode)
 {
-    if (R >= kSharedCuMinRows && m > 256)
+    if (R >= kSharedCuMinRows && m > 256 && mode != MODE_BLOCK)
         for (const Variant &v : kSharedCuVariants)
-            if (m <= v.cap && (mode != MODE_BLOCK || v.launch_block) && (v.B != 80 || longer_panels(m))) return &v;
+            if (m <= v.cap && (v.B != 80 || longer_panels(m))) return &v;
     for (int i = 0; i < kNumVariants; ++i)
         if (m <= kVariants[i].cap) return &kVariants[i];
     return nullptr;
