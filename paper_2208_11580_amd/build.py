@@ -36,7 +36,7 @@ def build_lib(force: bool = False, verbose: bool = False) -> str:
         stale = force or not os.path.exists(obj) or os.path.getmtime(obj) < max(os.path.getmtime(src), hdr_time)
         if stale:
             todo.append((src, obj))
-    # at most JOBS compilers at a time, the long ones (the unrolled panel kernels) first
+    # at most JOBS compilers at a time, the long ones (the panel kernels) first
     jobs = max(1, int(os.environ.get("OBC_BUILD_JOBS", min(8, os.cpu_count() or 1))))
     todo.sort(key=lambda so: (0 if "panel_" in os.path.basename(so[0]) else 1, so[0]))
     procs, running = [], []

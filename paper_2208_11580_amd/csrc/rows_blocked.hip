@@ -22,11 +22,12 @@
 // Two kernels alternate on the stream (host loop, no host synchronisation):
 //
 //   panel_kernel  one workgroup per row, B greedy steps.  Thread t owns the compact indices
-//                 t, t+T, ...: their weights and diagonal (fp64) and the B vectors u_r live in its
-//                 registers.  Per step: fp64 score + workgroup argmin (barrier 1), the owner of p
-//                 publishes w_p, a_p and the coefficients u_r[p]/a_r while every thread fetches its
-//                 part of A0[p,:] (barrier 2), then the row is corrected, w / diag are updated and
-//                 u_s is kept (registers) and stored (HBM, for the flush).
+//                 t, t+T, ...: their weights and diagonal (fp64) live in its registers, and of the B
+//                 vectors u_r the first BR; the other BL lie in LDS.  Per step: score + workgroup
+//                 argmin (barrier 1), the owner of p publishes its weight update, 1 / a_p and its
+//                 entries of the vectors while every thread fetches its part of A0[p,:] (barrier 2),
+//                 then the row is corrected, w / diag are updated and u_s is kept.  When the panel
+//                 ends the steps' records and the vectors (for the flush) are written.
 //   flush_kernel  A0_new = compact(A0 - U diag(1/a) U^T): 128x128 tiles on v_mfma_f32_32x32x2_f32,
 //                 one workgroup per strip of 128 or 256 rows of one row's matrix (only the lower
 //                 triangle is kept).  The eliminated rows and columns are dropped while writing
@@ -544,8 +545,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
             need[mt] = j0 + wn * 32 < mn && i0 + r0 + mt * 32 < mn && j0 + wn * 32 <= i0 + r0 + mt * 32 + 31;
-        // (several panels' vectors: each panel's update is summed from zero and added on its own, so
-        // that the matrix comes out as if each had been flushed by itself)
+        // (several groups of vectors: each group's update is summed from zero and added on its own, so that
+        // the matrix comes out as if each had been flushed by itself.  A group is a panel that shares the
+        // flush, or half of a panel of 80 steps.)
         for (int ch = 0; ch < chunks; ++ch) {
             if (JMAX > 1 && ch > 0) {
                 __syncthreads();               // everyone is done reading Us

@@ -393,6 +393,36 @@ def test_prune_rows_zero_weights_and_ties(obc, orc, strategy):
     assert _np(res["order"])[1].tolist() == list(range(d))  # all scores equal: index order
 
 
+@pytest.mark.parametrize("R,d", [(768, 320), (768, 600), (2, 1100), (2, 1700), (2, 2200), (2, 2500), (96, 2500),
+                                 (2, 3400), (2, 4400)])
+def test_ties_among_several_owned_indices(obc, R, d):
+    """Exact ties go to the least index, also where a thread owns several: of a wave's candidates the least
+    may sit on a higher lane than another one, of the waves' candidates in a later wave.  Every variant with
+    more than one index a thread, with panels that share a flush among them."""
+    k, kz = 136, 40
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    Hinv = _hinv(obc, torch.randn(d, 2 * d, generator=gen, device="cuda"))
+    W = torch.randn(R, d, generator=gen, device="cuda")
+    W[0] = 0.0
+    zero = torch.sort(torch.randperm(d, generator=gen, device="cuda")[:kz]).values
+    W[1, zero] = 0.0
+    first = torch.arange(k, device="cuda", dtype=torch.int32)
+    res = obc.obc_prune_rows(W, Hinv, k_steps=k, strategy=2)
+    assert torch.equal(res["order"][0], first)
+    assert torch.equal(res["order"][1, :kz], zero.to(torch.int32))
+    assert not res["W"][0].any() and not res["loss"][0].any() and not res["loss"][1, :kz].any()
+    # weights that lie on the grid: no error, nothing changes
+    codes = torch.randint(0, 16, (R, d), generator=gen, device="cuda")
+    Wq = (codes - 8).float() * 0.125
+    q = obc.obc_quant_rows(Wq, Hinv, torch.full((R,), 0.125, device="cuda"), torch.full((R,), -1.0, device="cuda"), 15,
+                           strategy=2)
+    assert torch.equal(q["order"], torch.arange(d, device="cuda", dtype=torch.int32).expand(R, d))
+    assert torch.equal(q["codes"], codes.to(torch.int32)) and torch.equal(q["W"], Wq)
+    b = obc.obc_prune_blocks(W, Hinv, 4, k_blocks=k // 4, strategy=2)
+    assert torch.equal(b["order"][0], first[:k // 4])
+    obc.obc_check()
+
+
 @pytest.mark.parametrize("strategy", [1, 2])
 def test_prune_rows_is_deterministic(obc, strategy):
     W, X = _layer("conv64x576", d_col=300, d_row=8, n_samples=2000)
@@ -1054,10 +1084,12 @@ def test_argument_errors(obc):
     assert out["order"].shape == (0, 30)
 
 
-def test_rows_many_more_rows_than_cus(obc, orc):
-    """Several times more rows than CUs at a mid-size width: the solver switches to the panel variant
-    of which three workgroups share a CU; sampled rows against the oracle, all rows against invariants."""
-    R, d = 1030, 420
+@pytest.mark.parametrize("d", [420, 600])
+def test_rows_many_more_rows_than_cus(obc, orc, d):
+    """Several times more rows than CUs at a mid-size width: the solver switches to the panel variants
+    of which three workgroups share a CU (two owned indices a thread up to 512 columns, three above);
+    sampled rows against the oracle, all rows against invariants."""
+    R = 1030
     W, X = _layer("attn768x768", d_col=d, d_row=R, n_samples=2000)
     Hinv = _hinv(obc, X)
     rows = [0, 515, 1029]
@@ -1065,8 +1097,11 @@ def test_rows_many_more_rows_than_cus(obc, orc):
     srt = torch.sort(res["order"], dim=1).values
     assert torch.equal(srt, torch.arange(d, device="cuda", dtype=torch.int32).expand(R, d))
     assert torch.all(res["W"] == 0)
-    _check_quant(obc, orc, W, Hinv, 4, 2, rows=rows)
-    # block pruning through the same shared-CU variant
+    q, _ = _check_quant(obc, orc, W, Hinv, 4, 2, rows=rows)
+    srt = torch.sort(q["order"], dim=1).values
+    assert torch.equal(srt, torch.arange(d, device="cuda", dtype=torch.int32).expand(R, d))
+    assert bool(((q["codes"] >= 0) & (q["codes"] <= 15)).all())
+    # block pruning: one owned index a thread
     kb = d // 4
     blk = obc.obc_prune_blocks(W, Hinv, 4, strategy=2)
     obc.obc_check()
