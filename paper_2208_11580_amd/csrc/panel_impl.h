@@ -637,8 +637,8 @@ __device__ __forceinline__ int panel_unrolled(const PanelArgs &a, const PanelRow
 
 // OLD: an instance that can follow others of its outer block (a.old > 0).  At six elements a thread the
 // panels that do not are instances without it: what re-reading the earlier vectors takes does not fit the
-// registers next to a step's state (8 x 2600, 240 steps with a flush each 40: 2.12 against 2.15 ms; 8 x 2600 in
-// blocks, where nothing shares a flush, 2.70 against 3.08 ms).
+// registers next to a step's state (8 x 2600, 240 steps with a flush each 40, without it and with: pruned 2.03,
+// 2.27 ms, in blocks, where nothing shares a flush, 2.14, 2.37; 128 x 2600 4.48, 4.70 and 4.66, 4.85).
 template <int MODE, int T, int EPT, int BR, int BL, bool OLD>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 256 ? (EPT == 1 ? 4 : 3) : T / 256)))
 void panel_kernel(PanelArgs a)

@@ -631,7 +631,8 @@ struct Variant {
         launch_panel_block_##T##_##EPT##_##BR##_##BL
 
 // (512 x 3: 24 vectors in LDS, 72 steps -- 203 x 1283 at 8 bit 5.10 -> 4.93 ms, 256 x 2304 at 4 bit 23.4 -> 23.1 against
-// 16 and 64.)
+// 16 and 64.  The number of steps fixes where the matrix's deferred fp32 sums are cut: with another one the results
+// differ by their rounding, and candidates that are closer than that go in another order.)
 constexpr Variant kVariants[] = {
     {OBC_VARIANT(256, 1, 64, 0)},
     {OBC_VARIANT(1024, 1, 64, 0)},
@@ -866,11 +867,14 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         // Panels that share a flush, as long as the live size keeps this variant.  Before the flush the
         // index space keeps its size, and a panel finds the earlier ones' vectors in memory.
         // (What a flush saves must exceed the re-reading.  Above 3072 columns, 24 and 28 steps a panel, it
-        // does from one row on.  At 40 steps it depends on the rows and the width -- 240 steps from that
-        // width down, in us, flushed after each panel against shared: 256 x 2600 7528, 6359; 128 x 2600 4446,
-        // 4208; 96 x 2800 4116, 3968; 32 x 3072 2848, 2713; 8 x 3100 2727, 2399; but 64 x 2600 2908, 3139;
-        // 8 x 2600 2119, 2233; 128 x 2400 3748, 3904; 256 x 2400 6444, 6603.  Not with block pruning's larger
-        // state: 40 x 3000 in blocks 22.4 against 22.7 ms.)
+        // does from one row on.  At 40 steps it depends on the rows and the width -- 280 steps from that
+        // width down, pruned, in us, flushed after each panel against shared: 192 x 2500 7173, 6560; 128 x 2500
+        // 4941, 4905; 192 x 2800 8633, 7347; 96 x 2650 5061, 4694; 96 x 2800 4881, 4876; 64 x 2950 4488, 4344;
+        // 32 x 3072 3386, 3283; 128 x 3072 7001, 6432; but 96 x 2500 4129, 4215; 64 x 2500 3237, 3413; 64 x 2800
+        // 3781, 3955; 32 x 2500 2629, 2664; 8 x 2800 2522, 2615.  The line is not everywhere the best: 192 x 2400
+        // 6524, 6374 and 512 x 2400 14874, 14915 lie below it, 64 x 3072 4368, 4438 and 8 x 3072 2760, 2806 above.
+        // Not with block pruning's larger state: 40 x 3000 in blocks 18.57 against 19.15 ms, though 240 steps of
+        // 256 x 3000 take 10.4 against 8.5.)
         PanelLaunch *first = mode == MODE_BLOCK ? v->launch_block : v->launch;
         PanelLaunch *next = mode == MODE_BLOCK ? v->launch_block_old : v->launch_old;
         const int most = next && (m_max >= 2816 || (R >= 96 && m_max >= 2416)) ? v->J : 1;
