@@ -1,6 +1,6 @@
 // Declarations shared by the blocked row solver's translation units: workspace layout, kernel
 // argument blocks, and the per-variant panel launchers (one translation unit per variant so that
-// they compile in parallel: up to half a minute where the steps are not a loop).
+// they compile in parallel: a wide one takes over a minute).
 #pragma once
 
 #include "rows_common.h"
