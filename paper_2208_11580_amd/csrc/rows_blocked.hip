@@ -355,14 +355,14 @@ constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: 
 constexpr int kMatLoadPolicy = 0;
 constexpr int kMatStorePolicy = 2 | 16;
 
-// They go through the caches in two cases.  (1) The live size is no multiple of 4: a wave's stores then begin and end
-// inside 64-byte sectors, and two waves' halves of a sector meet in L2 only if they are kept there.  In ms, pruned,
+// The stores go through the caches in two cases.  (1) The live size is no multiple of 4: a wave's stores then begin and
+// end inside 64-byte sectors, and two waves' halves of a sector meet in L2 only if they are kept there.  In ms, pruned,
 // streaming and cached: 203 x 1283 5.11, 4.90; 768 x 767 4.46, 4.34; 203 x 1999 15.14, 14.20; 100 x 2301 13.81, 13.09;
 // 12 x 4095 32.6, 31.6; 256 x 2303 at 4 bit 26.7, 25.2; 3071 x 765 at 4 bit 16.9, 16.3.  (2) All rows' new matrices
 // together fit the 256 MB memory-side cache, where the next panels find the rows that they fetch: 64 x 576 2:4 507,
 // 500 us; 128 x 1536 5.21, 5.18 ms; 768 x 768 4.05, 4.05.  Larger aligned ones only displace what is of use: with a
-// limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800 6.93 against 6.84; without one 256 x 2304 at 4 bit
-// 23.9 against 22.9.
+// limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800 6.93 against 6.84; without one 256 x 2304
+// at 4 bit 23.9 against 22.9.
 constexpr double kKeepBytes = 256e6;
 
 // K vectors are applied at once, and up to JMAX groups of K one after the other: every row that still

@@ -1114,8 +1114,8 @@ def test_rows_many_more_rows_than_cus(obc, orc, d):
 
 
 @pytest.mark.parametrize("R,d,k", [(768, 257, 257), (769, 512, 170), (768, 600, 260), (2, 1025, 150), (3, 1536, 150),
-                                   (768, 272, 136), (768, 273, 273), (768, 304, 150), (768, 305, 305), (770, 336, 130), (768, 337, 337), (768, 352, 170),
-                                   (768, 353, 353)])
+                                   (768, 272, 136), (768, 273, 273), (768, 304, 150), (768, 305, 305), (770, 336, 130),
+                                   (768, 337, 337), (768, 352, 170), (768, 353, 353)])
 def test_panels_of_72_and_80_steps(obc, orc, R, d, k):
     """The ends of the variants whose flush applies 72 vectors at once or 80 as two groups: both sides of the
     change to the next smaller one and of the widths at which 48 steps take the place of 80, the last step inside
