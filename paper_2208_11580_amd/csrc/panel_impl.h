@@ -9,6 +9,8 @@
 
 namespace obc_blocked {
 
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+
 constexpr int kNmShift = 16;          // above any index
 constexpr int kBeyond = 0x40000000;   // a byte offset beyond any row's matrix: the load returns 0
 
@@ -232,6 +234,7 @@ struct PanelRow {
     // the row's matrix for raw buffer loads: resource, bytes between an element of a row and the next,
     // row_base of the thread's first index
     __amdgpu_buffer_rsrc_t rsrc;
+    __amdgpu_buffer_rsrc_t ursrc;   // the row's vectors (u_index)
     int es, rb_tid;
     int nw;         // waves launched (one owned element per thread: as many as the live size needs)
     int mw;         // live size less the wave's first index
@@ -458,7 +461,7 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
     }
     // coefficients of the earlier panels' vectors, which are in memory: one lane each
     if constexpr (OLD) {
-        if (tid < pr.old) sh.cold[tid] = pr.gU[(size_t)tid * pr.ldu + p];
+        if (tid < pr.old) sh.cold[tid] = pr.gU[u_index(tid, p, pr.ldu)];
     }
     // entries p of the vectors kept in LDS: one lane each
     if constexpr (IN_LDS) {
@@ -500,23 +503,29 @@ __device__ __forceinline__ int panel_step(const PanelArgs &a, const PanelRow &pr
 #pragma unroll
                 for (int e = 0; e < NE; ++e) sum[e] = 0.f;
 #pragma unroll 1
-                for (int r = r0; r < r0 + BR + BL; r += 2) {
-                    const float2 o2 = *reinterpret_cast<const float2 *>(&sh.cold[r]);
-                    const float2 i2 = *reinterpret_cast<const float2 *>(&sh.invd_old[r]);
-                    const float *u = pr.gU + (size_t)r * pr.ldu + tid;
-                    float v[2][NE];
+                for (int r = r0; r < r0 + BR + BL; r += 4) {
+                    const float4 o4 = *reinterpret_cast<const float4 *>(&sh.cold[r]);
+                    const float4 i4 = *reinterpret_cast<const float4 *>(&sh.invd_old[r]);
+                    // (half of the elements at a time: what is in flight has to find room in the registers)
+                    constexpr int HE = (NE + 1) / 2;
 #pragma unroll
-                    for (int q = 0; q < 2; ++q)
+                    for (int e0 = 0; e0 < NE; e0 += HE) {
+                        uintx4 v[HE];
 #pragma unroll
-                        for (int e = 0; e < NE; ++e) v[q][e] = u[(size_t)q * pr.ldu + e * T];
+                        for (int e = 0; e < HE; ++e)
+                            if (e0 + e < NE) v[e] = __builtin_amdgcn_raw_buffer_load_b128(pr.ursrc, tid * 16, ((r >> 2) * pr.ldu + (e0 + e) * T) * 16, 0);
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const float up = q ? o2.y : o2.x, ni = -(q ? i2.y : i2.x), fp = __fmul_rn(up, ni);
+                        for (int q = 0; q < 4; ++q) {
+                            const float up = q == 0 ? o4.x : q == 1 ? o4.y : q == 2 ? o4.z : o4.w;
+                            const float ni = -(q == 0 ? i4.x : q == 1 ? i4.y : q == 2 ? i4.z : i4.w), fp = __fmul_rn(up, ni);
 #pragma unroll
-                        for (int e = 0; e < NE; ++e) {
-                            const bool along = tid <= p - e * T;     // (p, j) with j <= p, else (j, p)
-                            sum[e] = fmaf(along ? fp : up, along ? v[q][e] : __fmul_rn(v[q][e], ni), sum[e]);
+                            for (int e = e0; e < e0 + HE && e < NE; ++e) {
+                                const bool along = tid <= p - e * T;     // (p, j) with j <= p, else (j, p)
+                                const float vq = __uint_as_float(v[e - e0][q]);
+                                sum[e] = fmaf(along ? fp : up, along ? vq : __fmul_rn(vq, ni), sum[e]);
+                            }
                         }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
 #pragma unroll
@@ -690,6 +699,7 @@ void panel_kernel(PanelArgs a)
     pr.mw = m - __builtin_amdgcn_readfirstlane(tid & ~63);
     pr.gU = a.ws.U + (size_t)row * UCAP * a.ws.ldu;
     pr.ldu = a.ws.ldu;
+    pr.ursrc = __builtin_amdgcn_make_buffer_rsrc((void *)pr.gU, 0, UCAP * pr.ldu * 4, 0x00020000u);
     pr.old = a.old;
     double *gw = a.ws.w + (size_t)row * d;
     double *gd = a.ws.diag + (size_t)row * d;
@@ -741,7 +751,7 @@ void panel_kernel(PanelArgs a)
                     const int q = tid & 3;
 #pragma unroll 2
                     for (int r = r0; r < r0 + B; ++r) {
-                        const float u = pr.gU[(size_t)r * pr.ldu + tid + e * T], f = __fmul_rn(u, -sh.invd_old[r]);
+                        const float u = pr.gU[u_index(r, tid + e * T, pr.ldu)], f = __fmul_rn(u, -sh.invd_old[r]);
                         // (all lanes read their neighbours before any of them chooses)
                         const float u0 = quad_bcast<0>(u), u1 = quad_bcast<1>(u), u2 = quad_bcast<2>(u), u3 = quad_bcast<3>(u);
                         const float f1 = quad_bcast<1>(f), f2 = quad_bcast<2>(f), f3 = quad_bcast<3>(f);
@@ -884,12 +894,16 @@ void panel_kernel(PanelArgs a)
             go[jn[e]] = st.og[e];
             gmap[jn[e]] = j;
             if (st.og[e] >= 0) Wo[st.og[e]] = (float)st.w[e];
-            // this panel's vectors u_r, in the new index order
+            // this panel's vectors u_r, in the new index order (a row that ended within four of them has no use for them)
 #pragma unroll
-            for (int r = 0; r < B; ++r)
-                if (r < nbv)
-                    pr.gU[(size_t)(a.old + r) * a.ws.ldu + jn[e]] =
-                        (r < BR) ? st.u[r < BR ? r : 0][e] : ul[(r - BR) * (T * EPT) + j];
+            for (int r = 0; r < B; r += 4)
+                if (r < nbv) {
+                    uintx4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        v[q] = __float_as_uint(r < BR ? st.u[r < BR ? r + q : 0][e] : ul[(r + q - BR) * (T * EPT) + j]);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, pr.ursrc, jn[e] * 16, ((a.old + r) >> 2) * pr.ldu * 16, 0);
+                }
         }
     }
     if constexpr (OLD) {
@@ -897,18 +911,15 @@ void panel_kernel(PanelArgs a)
         // whole before any of it is written
         if (a.last) {
 #pragma unroll 1
-            for (int r = 0; r < a.old; r += 2) {
-                float v[2][EPT];
+            for (int r = 0; r < a.old; r += 4) {
+                const int at = (r >> 2) * pr.ldu * 16;
+                uintx4 v[EPT];
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int e = 0; e < EPT; ++e) v[q][e] = pr.gU[(size_t)(r + q) * pr.ldu + tid + e * T];
+                for (int e = 0; e < EPT; ++e) v[e] = __builtin_amdgcn_raw_buffer_load_b128(pr.ursrc, tid * 16, at + e * T * 16, 0);
                 __syncthreads();
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int e = 0; e < EPT; ++e)
-                        if (jn[e] >= 0) pr.gU[(size_t)(r + q) * pr.ldu + jn[e]] = v[q][e];
+                for (int e = 0; e < EPT; ++e)
+                    if (jn[e] >= 0) __builtin_amdgcn_raw_buffer_store_b128(v[e], pr.ursrc, jn[e] * 16, at, 0);
             }
         }
     }

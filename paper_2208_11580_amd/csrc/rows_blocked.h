@@ -15,8 +15,6 @@ constexpr int BMAX = 64;       // rank of a bulk elimination of pruned indices, 
 constexpr int UCAP = 2 * BMAX; // vectors per row in U: an outer block's, or a bulk elimination's in and out
 constexpr int kGone = (int)0x80000000;   // `orig` of an index eliminated since the last compaction
 constexpr int kPanelDynLds = 160 * 1024 - 6144;   // what a panel's static LDS leaves of a CU's
-constexpr int FT = 128;        // flush tile edge
-constexpr int FLD = FT + 4;    // padded LDS row of the flush operand tiles
 
 // Layout of a row's private matrix after its first flush ("row-quad" layout): element (i, j) is at
 // float index ((i / 4) * ld + j) * 4 + i % 4, i.e. four consecutive rows of a column sit together.
@@ -28,10 +26,17 @@ __host__ __device__ inline size_t quad_index(int i, int j, int ld)
     return ((size_t)(i >> 2) * ld + j) * 4 + (i & 3);
 }
 
+// Entry j of vector k of a row's U: four vectors of a column sit together, so that the panel writes and reads, and the
+// flush reads, four of them at a time.
+__host__ __device__ inline size_t u_index(int k, int j, int ldu)
+{
+    return ((size_t)(k >> 2) * ldu + j) * 4 + (k & 3);
+}
+
 struct BlockedWs {
     float *Abuf[2];     // R x d x d each
-    float *U;           // R x UCAP x ldu
-    int ldu;            // leading dimension of U: d rounded up to a multiple of 4 (16-byte rows)
+    float *U;           // R x UCAP x ldu (u_index)
+    int ldu;            // leading dimension of U: d rounded up to a multiple of 4
     float *invd;        // R x UCAP   1 / a_r of U's vectors
     int *map;           // R x d     (new compact index -> old compact index)
     double *w;          // R x d     (compact)

@@ -28,9 +28,8 @@
 //                 entries of the vectors while every thread fetches its part of A0[p,:] (barrier 2),
 //                 then the row is corrected, w / diag are updated and u_s is kept.  When the panel
 //                 ends the steps' records and the vectors (for the flush) are written.
-//   flush_kernel  A0_new = compact(A0 - U diag(1/a) U^T): 128x128 tiles on v_mfma_f32_32x32x2_f32,
-//                 one workgroup per strip of 128 or 256 rows of one row's matrix (only the lower
-//                 triangle is kept).  The eliminated rows and columns are dropped while writing
+//   flush_kernel  A0_new = compact(A0 - U diag(1/a) U^T): tiles of 32 x 64 on the fp32 matrix cores, one
+//                 wavefront each (only the lower triangle is kept).  The eliminated rows and columns are dropped while writing
 //                 (out of place, two buffers), so the matrix shrinks with the live set and later
 //                 blocks cost (m/d)^2 of the first.
 //
@@ -269,12 +268,14 @@ __global__ __launch_bounds__(512) void dead_apply_kernel(DeadArgs a)
 #pragma unroll
             for (int r = 0; r < BMAX; ++r) g[r] = G[(size_t)r * ldu + j];
             double dsum = 0.0;
+            float u4[4];
 #pragma unroll
             for (int k = 0; k < BMAX; ++k) {
                 float acc = 0.f;
 #pragma unroll
                 for (int r = 0; r <= k; ++r) acc = fmaf(Tl[k][r], g[r], acc);
-                U[(size_t)k * ldu + jnew] = acc;
+                u4[k % 4] = acc;
+                if (k % 4 == 3) *reinterpret_cast<float4 *>(U + u_index(k - 3, jnew, ldu)) = make_float4(u4[0], u4[1], u4[2], u4[3]);
                 dsum += (double)acc * (double)acc;
                 // one row of T at a time (otherwise its LDS reads are all issued up front)
                 __builtin_amdgcn_sched_barrier(0);
@@ -326,33 +327,20 @@ struct FlushArgs {
     int old_swz;             // layout of A_old: 0 plain row-major, 1 row-quad (A_new is always row-quad)
     float *A_new;
     size_t new_row_stride;
-    int ld_new;
-    int d, R, strips;
+    int ld_new;              // = the live size after the flush of every row that still has steps to do
+    int d, R;
+    int strips;              // of 128 rows
     int keep;                // the new matrices stay in the caches
-    int chunks;              // groups of KMAX vectors that this flush applies (one panel each, or half of one above 72 steps)
+    int chunks;              // groups of K vectors that this flush applies (one panel each, or half of one above 72 steps)
     BlockedWs ws;
 };
 
-// One workgroup (8 waves) per 128-row strip of one row's matrix; it walks the strip's 128-column
-// tiles up to and including the diagonal one: the matrix is symmetric, so only its lower triangle
-// is kept (the panel reads row p as "row part + column part").  In a diagonal tile the entries
-// above the diagonal are neither read nor (except as don't-care slots of a 4-row store) written.  Wave (wm, wn) owns a 64 x 32 sub-tile = two 32x32 MFMA accumulators, which are loaded
-// straight from the old matrix (one dword per lane: 32 consecutive columns of a row per half
-// wave, i.e. whole 128-byte lines) and stored straight to the new one.  Accesses to the matrices
-// are raw buffer loads / stores: a 32-bit byte offset per access instead of a 64-bit address
-// (register pressure), and the hardware range check (offset >= size reads 0 / drops the store)
-// replaces the per-element predicates.  A tile's loads are issued before its MFMAs, which do not
-// depend on them.
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kBufWord3 = 0x00020000u;   // raw buffer, 32-bit data format
 constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: "out of range"
 // Cache policy bits of the matrix accesses (gfx950 buffer instructions: 1 = sc0, 2 = nt, 16 = sc1).
 // The new matrix is written once and next read by another kernel: streaming stores keep it from
-// displacing the U tiles and the old matrix's lines in L2 (flush 19.9 -> 18.9 ms on the 256 x 2304
-// layer; nt, sc0+nt and sc1+nt within 1 % of each other, sc bits alone no change).  The loads stay
-// cached: a lane's four rows of a column share sectors over four consecutive loads, and streaming
-// loads made the kernel 25 % slower.
-constexpr int kMatLoadPolicy = 0;
+// displacing the vectors and the old matrix's lines in L2.
 constexpr int kMatStorePolicy = 2 | 16;
 
 // The stores go through the caches in two cases.  (1) The live size is no multiple of 4: a wave's stores then begin and
@@ -365,252 +353,253 @@ constexpr int kMatStorePolicy = 2 | 16;
 // at 4 bit 23.9 against 22.9.
 constexpr double kKeepBytes = 256e6;
 
-// K vectors are applied at once, and up to JMAX groups of K one after the other: every row that still
-// has steps to do has exactly K x chunks deferred eliminations (a row with fewer has finished and is
-// skipped).  A strip is HALVES x 128 rows tall: the U tile
-// of a column block, once in LDS, serves all the strip's halves (loading it is the expensive part
-// of a tile next to the matrix traffic itself), and the F tile covers the whole strip.
-template <int KMAX, int HALVES, int JMAX>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void flush_kernel(FlushArgs a)
+// x[v] = x[v + 1] from Z on
+template <int Z, int N>
+__device__ __forceinline__ void close_from(float (&x)[N])
 {
-    constexpr int SR = HALVES * FT;          // rows per strip
-    static_assert(JMAX == 1 || HALVES == 1, "a strip's U tile changes within a tile");
-    __shared__ __align__(16) float Fs[JMAX * KMAX][SR + 4];
-    __shared__ __align__(16) float Us[KMAX][FLD];
-    __shared__ int rowoff_s[SR];   // byte offset of each strip row in the old matrix
-    __shared__ int rowold_s[SR];   // its old compact index
+#pragma unroll
+    for (int v = Z; v + 1 < N; ++v) x[v] = x[v + 1];
+}
 
-    // Workgroups are dealt round-robin to the 8 XCDs: all strips of one row stay on one XCD, so
-    // that its U panel and index map stay in that XCD's L2.  Within an XCD the rows go in groups
-    // of G, and a group's workgroups run strip-major (the longest strip of each of its rows, then
-    // the next longest, ...): long strips start first, and workgroups that start together take
-    // equally long.  Measured against one row's strips in a run (lengths in a sawtooth): 10 % less
-    // time per launch, 20 % where the strip count is a multiple of 4 (every fourth workgroup of
-    // an XCD then got the long strips); G = 4, 8, 16, 32 gave 21.0, 20.3, 19.8, 20.4 ms of flush
-    // time on the 256 x 2304 layer (22.2 ms before).
-    const int L = blockIdx.x;
-    const int nx = gridDim.x / (8 * a.strips);            // rows per XCD
-    constexpr int G = 16;
-    const int grp = (L / 8) / (G * a.strips), within = (L / 8) - grp * G * a.strips;
-    const int rig = nx - G * grp < G ? nx - G * grp : G;  // rows in this group
-    const int strip = a.strips - 1 - within / rig;
-    const int row = (G * grp + within % rig) * 8 + (L % 8);
+// the same from z on (uniform), by a branch to the group of four that z lies in; z is in groups LO .. HI - 1
+template <int LO, int HI, int N>
+__device__ __forceinline__ void close_gap(float (&x)[N], int z)
+{
+    if constexpr (HI - LO == 1) {
+#pragma unroll
+        for (int v = LO * 4; v < LO * 4 + 4; ++v)
+            if (v + 1 < N) x[v] = v >= z ? x[v + 1] : x[v];
+        if constexpr (LO * 4 + 4 < N) close_from<LO * 4 + 4, N>(x);
+    } else {
+        constexpr int MID = (LO + HI) / 2;
+        if (z < MID * 4) close_gap<LO, MID>(x, z);
+        else close_gap<MID, HI>(x, z);
+    }
+}
+
+// value of position P of the caller's 16-lane row
+template <int P>
+__device__ __forceinline__ float row16_bcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + P, 0xf, 0xf, false));
+}
+
+// A_new = compact(A_old - U diag(1/a) U^T) on the lower triangle, K vectors at a time from zero and `chunks` such
+// groups (<= J) one after the other.  Every row that still has steps to do has exactly K x chunks deferred
+// eliminations and the same live size (a row with fewer has finished and is skipped).
+//
+// A wave forms a tile of 32 rows x 64 columns by itself: no LDS, no barrier; the four waves of a workgroup take
+// 128 rows of the same columns.  The product runs on v_mfma_f32_4x4x1 with one operand broadcast: its 16 blocks
+// are 64 columns, one per lane, and the same four rows, so that a lane holds a column of the tile and the registers
+// its rows.  What a row needs is then uniform over the wave: where it lay in the old matrix is a scalar, and the
+// old matrix is read whole quads of rows at a time (16 bytes a lane, 1 KB a load) although the rows of a new quad
+// lie in two or three old ones -- the eliminated rows are closed up in registers (QUADS).  (With 32x32x2 the two
+// halves of a wave hold different rows; there the same entries were read singly, four loads over the same lines.)
+// An operand is read 16 bytes at a time as well: four vectors of a column (U's layout).
+//
+// What bounds it: HBM (8 bytes per entry of the new triangle; without any product and operand the same loads and stores
+// take 0.72 .. 0.8 of its time) and, not quite overlapped at four waves a SIMD, the matrix cores and the waves' start: some
+// 4 us up to a tile's first entries, of 12 in all.  Before, a workgroup of eight waves walked a strip of 128 or 256 rows on
+// 32x32x2 tiles with its operands in LDS.  In us, before and now: 256 rows, 2208 columns left, 48 vectors 1285, 1115; 1904, 56
+// vectors 968, 878; 1296, 72 vectors 525, 508; 880, 64 vectors 234, 218; 3072 rows, 672, 48 vectors 1590, 1390; 320, 2 x 40
+// vectors 605, 548; 203 rows, 1067, 72 vectors 322, 299; 547, 64 vectors 110, 92; 64 rows, 384, 64 vectors 29, 19; 256 rows, 4416,
+// 4 x 24 vectors 6420, 6020; 2880, 2 x 40 vectors 2660, 2305; 3936, 64 vectors 4010, 3595.  But from the shared H^-1, 256 rows,
+// 2256 left, 48 vectors: 783, 911.  Tried: several tiles a wave (each store then stands in front of the next tile's operands,
+// whose wait is one for the store: 1120 -> 1400); 64 x 64 a wave (registers); a workgroup's operands in LDS, one tile each (1500).
+template <int K, int J, bool QUADS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void flush_kernel(FlushArgs a)
+{
+    static_assert(K % 4 == 0 && K * J <= UCAP, "vectors come in groups of four");
+    constexpr int NG = (K + 7) / 8;             // groups of 8 vectors (the last may be one of 4)
+    constexpr int NB = J > 1 ? 2 : 3;           // groups in flight
+    constexpr int NQ = 10;                      // quads of old rows that 32 rows may reach into
+    constexpr int ND = (K + 31) / 32;
+    // Workgroups are dealt round-robin to the 8 XCDs: all tiles of one row of the layer stay on one XCD, whose L2
+    // holds its vectors.
+    const int L = blockIdx.x, xcd = L & 7;
+    const int per_row = a.strips * (a.strips + 1);
+    const int ri = (L >> 3) / per_row, t = (L >> 3) - ri * per_row, row = ri * 8 + xcd;
     if (row >= a.R) return;
-    const int chunks = JMAX == 1 ? 1 : a.chunks;
-    if (a.ws.nb[row] != KMAX * chunks || a.ws.done[row] >= a.ws.total[row]) return;
-    constexpr int nb = KMAX;
-    const int mn = a.ws.m[row];             // live size after the block (new compact space)
-    const int i0 = strip * SR;
-    if (i0 >= mn) return;
-
-    const int d = a.d;
-    const int *map = a.ws.map + (size_t)row * d;
-    const int ldu = a.ws.ldu;
-    const float *U = a.ws.U + (size_t)row * UCAP * ldu;    // u_k in the new compact order, 16-byte aligned rows
-    const float *invd = a.ws.invd + (size_t)row * UCAP;
-    const int ldo = a.ld_old, ldn = a.ld_new;
-    constexpr int nbp = (nb + 1) & ~1;
-    __amdgpu_buffer_rsrc_t rold = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(a.A_old + (size_t)row * a.old_row_stride), 0, (int)(((size_t)d * d + 3) / 4 * 16), kBufWord3);
-    __amdgpu_buffer_rsrc_t rnew = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(a.A_new + (size_t)row * a.new_row_stride), 0, ((mn + 3) >> 2) * ldn * 16, kBufWord3);
-    const int swz = a.old_swz;
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (waves with the same wn share a SIMD and have the more work in a diagonal tile the smaller wn is;
-    // odd strips number them the other way round, so that two workgroups on a CU even that out)
-    const int wm = wave >> 2, wn = (strip & 1) ? 3 - (wave & 3) : wave & 3;
-    const int jl = wn * 32 + (lane & 31);
-    const int lrow = 4 * (lane >> 5);        // the lane-dependent part of the accumulator row
+    // strip s has 2 (s + 1) column tiles
+    int strip = (int)((__builtin_sqrtf(4.f * t + 1.f) - 1.f) * 0.5f);
+    if ((strip + 1) * (strip + 2) <= t) ++strip;
+    if (strip * (strip + 1) > t) --strip;
+    strip = __builtin_amdgcn_readfirstlane(strip);
+    const int mn = a.ld_new;
+    const int r0 = strip * 128 + wave * 32, c0 = (t - strip * (strip + 1)) * 64;
+    if (r0 >= mn || c0 > r0) return;
+    const int nb = a.ws.nb[row], done = a.ws.done[row], total = a.ws.total[row];   // (waited for below)
 
-    // F tile: F[k][i] = -u_k[i] / a_k for the strip's rows (four rows per 16-byte load; rows
-    // beyond mn only reach outputs that are never stored); byte offsets of the strip's old rows
-    for (int idx = tid; idx < (JMAX == 1 ? nbp : nb * chunks) * (SR / 4); idx += 512) {
-        int k = idx / (SR / 4), i = (idx % (SR / 4)) * 4;
-        int ii = i0 + i;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (k < nb * chunks && ii < mn) {
-            v = *reinterpret_cast<const float4 *>(U + (size_t)k * ldu + ii);
-            const float s = -invd[k];
-            v.x = __fmul_rn(v.x, s); v.y = __fmul_rn(v.y, s); v.z = __fmul_rn(v.z, s); v.w = __fmul_rn(v.w, s);
+    const int d = a.d, ldu = a.ws.ldu, ldo = a.ld_old, ldn = a.ld_new, swz = a.old_swz;
+    __amdgpu_buffer_rsrc_t rmap = __builtin_amdgcn_make_buffer_rsrc((void *)(a.ws.map + (size_t)row * d), 0, mn * 4, kBufWord3);
+    __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc((void *)(a.ws.U + (size_t)row * UCAP * ldu), 0,
+                                                                  UCAP * ldu * 4, kBufWord3);
+    __amdgpu_buffer_rsrc_t rinv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.ws.invd + (size_t)row * UCAP), 0, UCAP * 4, kBufWord3);
+    const int il = lane & 31, kl = lane >> 5;
+    const int nr = mn - r0 < 32 ? mn - r0 : 32;          // rows of the tile
+    const int jcol = c0 + lane;
+    // lane l: old index of row l % 32, of column l (beyond the end 0)
+    const int orow = __builtin_amdgcn_raw_buffer_load_b32(rmap, (r0 + il) * 4, 0, 0);
+    const int jold = __builtin_amdgcn_raw_buffer_load_b32(rmap, jcol * 4, 0, 0);
+    // -1 / a of the vectors: register q, position 4 g + i of a 16-lane row: vector 32 q + 8 g + i (upper lanes: + 4)
+    float ninv[J][ND];
+#pragma unroll
+    for (int ch = 0; ch < J; ++ch)
+#pragma unroll
+        for (int q = 0; q < ND; ++q) {
+            const int k = ch * K + 32 * q + 8 * ((lane & 15) >> 2) + (lane & 3) + 4 * kl;
+            ninv[ch][q] = -__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rinv, k * 4, 0, 0));
         }
-        *reinterpret_cast<float4 *>(&Fs[k][i]) = v;
+    // the operands of 8 vectors: rows (lower lanes the first four vectors, upper lanes the others), columns
+    const int va = (kl * ldu + r0 + il) * 16, vb = jcol * 16, step = ldu * 16;
+    uintx4 ua[NB], ub[NB][2];
+    int at = 0;
+    auto fetch = [&](int gg) {
+        asm volatile("" : "+s"(at));                      // (a running offset; and not ahead of what stands before it)
+        const int b = gg % NB;
+        const bool half = K % 8 && gg % NG == NG - 1;
+        ua[b] = __builtin_amdgcn_raw_buffer_load_b128(ru, va, at, 0);
+        ub[b][0] = __builtin_amdgcn_raw_buffer_load_b128(ru, vb, at, 0);
+        if (!half) ub[b][1] = __builtin_amdgcn_raw_buffer_load_b128(ru, vb, at + step, 0);
+        at += half ? step : 2 * step;
+    };
+#pragma unroll
+    for (int g = 0; g < NB && g < NG * J; ++g) fetch(g);
+    __builtin_amdgcn_sched_barrier(0);
+    const int chunks = J == 1 ? 1 : a.chunks;
+    if (nb != K * chunks || done >= total) return;
+
+    // ---- the old entries
+    __amdgpu_buffer_rsrc_t rold = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.A_old + (size_t)row * a.old_row_stride), 0, swz ? (d + 3) / 4 * d * 16 : d * d * 4, kBufWord3);
+    constexpr int NX = QUADS ? NQ * 4 : 32;
+    float x[NX];
+    const int o_first = __builtin_amdgcn_readfirstlane(orow), o_last = __builtin_amdgcn_readlane(orow, nr - 1);
+    const int quad0 = o_first >> 2;
+    const bool fits = QUADS && o_last - quad0 * 4 < NQ * 4;
+    const int colo = jcol < mn ? jold * (QUADS || swz ? 16 : 4) : kFar;
+    // row by row: from the plain layout whole lines, from the quads 4 of every 16 bytes
+    auto rows_singly = [&](int om) {
+#pragma unroll
+        for (int v = 0; v < 32; ++v) {
+            const int o = __builtin_amdgcn_readlane(om, v), lim = v < nr ? o : -1;     // columns up to the diagonal
+            const int ro = QUADS || swz ? ((o >> 2) * ldo * 4 + (o & 3)) * 4 : o * ldo * 4;
+            x[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rold, jold > lim ? kFar : colo, ro, 0));
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);     // (their offsets do not all fit the scalar registers)
+        }
+    };
+    if constexpr (QUADS) {
+        // (a column's quads from the one with its diagonal entry on; no branches, which would hold up the loads)
+        const int lo = (jold >> 2) - quad0;
+        int n = (fits ? (o_last >> 2) - quad0 + 1 : 0) - lo;
+        n = n < 0 ? 0 : n;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int off = (unsigned)(q - lo) < (unsigned)n ? colo : kFar;
+            const uintx4 v = __builtin_amdgcn_raw_buffer_load_b128(rold, off, (quad0 + q) * ldo * 16, 0);
+            x[4 * q] = __uint_as_float(v.x); x[4 * q + 1] = __uint_as_float(v.y);
+            x[4 * q + 2] = __uint_as_float(v.z); x[4 * q + 3] = __uint_as_float(v.w);
+        }
+    } else {
+        rows_singly(orow);
     }
-    for (int i = tid; i < SR; i += 512) {
-        int o = (i0 + i < mn) ? map[i0 + i] : -1;
-        rowold_s[i] = o;
-        rowoff_s[i] = (o < 0) ? kFar : swz ? ((o >> 2) * ldo * 4 + (o & 3)) * 4 : o * ldo * 4;
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- The update is summed on the matrix cores into accumulators that start at zero while the old entries are on
+    // their way, and added to them once per group: an entry takes one rounding per group at its own magnitude, and the
+    // matrix comes out as if each group had been flushed by itself.  A group is a panel that shares the flush, or half
+    // of a panel of 80.
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    floatx4 sum[8];
+    // (Several groups of vectors, where the matrix cores are the tighter bound: the wave in the higher slot of a SIMD
+    // goes first, so that the four do not all wait and all multiply together.  3072 x 768, 320 columns left, 2 x 40
+    // vectors: 573 -> 548 us; 256 x 4608, 3816 left, 3 x 28: 4228 -> 4134.  One group of 48 or more: 1 % slower.)
+    if constexpr (J > 1) {
+        switch (__builtin_amdgcn_s_getreg(6148) & 3) {     // HW_ID, bits 0 .. 3: the wave's slot
+        case 0: __builtin_amdgcn_s_setprio(0); break;
+        case 1: __builtin_amdgcn_s_setprio(1); break;
+        case 2: __builtin_amdgcn_s_setprio(2); break;
+        default: __builtin_amdgcn_s_setprio(3); break;
+        }
     }
-
-    // U tile staging: KMAX x 128 floats by 512 threads, four consecutive columns (16 bytes) each
-    constexpr int UV = (KMAX * (FT / 4) + 511) / 512;
-    float4 ureg[UV];
-    static_assert(JMAX == 1 || KMAX % 2 == 0, "chunks follow each other in pairs of k");
-    auto fetch_u = [&](int j0, int chunk = 0) {
 #pragma unroll
-        for (int h = 0; h < UV; ++h) {
-            int idx = tid + h * 512;
-            int k = idx / (FT / 4), j = (idx % (FT / 4)) * 4;
-            // a group that starts below mn may end beyond it: those columns hold old values of
-            // the same buffer and only reach outputs that are never stored
-            ureg[h] = (k < nb && j0 + j < mn) ? *reinterpret_cast<const float4 *>(U + (size_t)(chunk * KMAX + k) * ldu + j0 + j)
-                                               : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    auto stash_u = [&]() {
+    for (int ch = 0; ch < J; ++ch) {
+        if (J > 1 && ch >= chunks) break;
 #pragma unroll
-        for (int h = 0; h < UV; ++h) {
-            int idx = tid + h * 512;
-            int k = idx / (FT / 4), j = (idx % (FT / 4)) * 4;
-            if (KMAX * (FT / 4) % 512 == 0 || k < KMAX) *reinterpret_cast<float4 *>(&Us[k][j]) = ureg[h];
-        }
-    };
-    // strictly-lower tiles: element (i, j) sits at old[map i][map j]; rb = first strip row of the tile
-    auto fetch_c = [&](floatx16(&c)[2], int jold, int rb) {
-        const int joldB = (jold < 0) ? kFar : swz ? jold * 16 : jold * 4;
+        for (int q = 0; q < 8; ++q) sum[q] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int g = 0; g < NG; ++g) {
+            const int gg = ch * NG + g, b = gg % NB;
+            const bool half = K % 8 && g == NG - 1;
+            const float inv = ninv[ch][g / 4];
+            const float s0 = g % 4 == 0 ? row16_bcast<0>(inv) : g % 4 == 1 ? row16_bcast<4>(inv) : g % 4 == 2 ? row16_bcast<8>(inv) : row16_bcast<12>(inv);
+            const float s1 = g % 4 == 0 ? row16_bcast<1>(inv) : g % 4 == 1 ? row16_bcast<5>(inv) : g % 4 == 2 ? row16_bcast<9>(inv) : row16_bcast<13>(inv);
+            const float s2 = g % 4 == 0 ? row16_bcast<2>(inv) : g % 4 == 1 ? row16_bcast<6>(inv) : g % 4 == 2 ? row16_bcast<10>(inv) : row16_bcast<14>(inv);
+            const float s3 = g % 4 == 0 ? row16_bcast<3>(inv) : g % 4 == 1 ? row16_bcast<7>(inv) : g % 4 == 2 ? row16_bcast<11>(inv) : row16_bcast<15>(inv);
+            const float fa[4] = {__fmul_rn(__uint_as_float(ua[b].x), s0), __fmul_rn(__uint_as_float(ua[b].y), s1),
+                                 __fmul_rn(__uint_as_float(ua[b].z), s2), __fmul_rn(__uint_as_float(ua[b].w), s3)};
+            // block q + 8 h of the first operand: rows 4 q .. of vector 4 h + i
+#define OBC_MF(q, h) sum[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(fa[i], __uint_as_float(ub[b][h][i]), sum[q], 4, (q) + 8 * (h), 0);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                int ro = rowoff_s[rb + wm * 64 + mt * 32 + 8 * (v >> 2) + lrow + (v & 3)];
-                c[mt][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rold, ro + joldB, 0, kMatLoadPolicy));
+            for (int i = 0; i < 4; ++i) {
+                OBC_MF(0, 0) OBC_MF(1, 0) OBC_MF(2, 0) OBC_MF(3, 0) OBC_MF(4, 0) OBC_MF(5, 0) OBC_MF(6, 0) OBC_MF(7, 0)
             }
-    };
-    // the diagonal tile: only entries on or below the diagonal exist
-    auto fetch_c_diag = [&](floatx16(&c)[2], int jold, int rb) {
+            if (!half) {
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                int oi = rowold_s[rb + wm * 64 + mt * 32 + 8 * (v >> 2) + lrow + (v & 3)];
-                int off = (jold < 0 || jold > oi) ? kFar
-                          : swz ? (((oi >> 2) * ldo + jold) * 4 + (oi & 3)) * 4 : (oi * ldo + jold) * 4;
-                c[mt][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rold, off, 0, kMatLoadPolicy));
-            }
-    };
-    auto old_col = [&](int j) { return (j < mn) ? map[j] : -1; };
-    // halves of the strip that hold rows at all
-    const int nh = (mn - i0 + FT - 1) / FT < HALVES ? (mn - i0 + FT - 1) / FT : HALVES;
-
-    // The strip's tiles in the order they are visited: column block j0 = 0, 128, ...; within a
-    // column block the halves hf whose rows reach down to it (rows i0 + 128 hf .. >= j0).
-    // (j0, hf) -> the next one; returns false after the last.
-    auto advance = [&](int &j0, int &hf) {
-        if (hf + 1 < nh) { hf += 1; return true; }
-        j0 += FT;
-        if (j0 >= mn) return false;
-        // first half whose diagonal block is at or beyond column block j0
-        int h0 = (j0 - i0) / FT;
-        if (j0 <= i0) h0 = 0;
-        if (h0 >= nh) return false;
-        hf = h0;
-        return true;
-    };
-    auto fetch_tile = [&](floatx16(&c)[2], int jold, int j0, int hf) {
-        if (j0 == i0 + hf * FT) fetch_c_diag(c, jold, hf * FT);
-        else fetch_c(c, jold, hf * FT);
-    };
-
-    // Per tile: the loads of the old entries are issued first, the rank-K update is summed on the
-    // matrix cores into accumulators that start at zero while those loads are in flight, and the
-    // two are added once at the end.  (Summing into the loaded entries instead would round every
-    // one of the K partial sums at the magnitude of the matrix entry; this way the update, which is
-    // small next to the entry, is rounded at its own magnitude, and the entry takes one rounding
-    // per block.  The loads overlap with the same tile's MFMAs instead of the previous tile's.)
-    int j0 = 0, hf = 0;
-    int jold = old_col(jl);
-    fetch_u(0);
-    __syncthreads();                           // rowoff_s / rowold_s visible
-    stash_u();
-    __syncthreads();                           // Us and Fs visible
-    floatx16 old[2], sum[2];
-    for (;;) {
-        fetch_tile(old, jold, j0, hf);
-        int j0n = j0, hfn = hf;
-        const bool more = advance(j0n, hfn);
-        const bool new_col = more && j0n != j0;
-        int joldn = jold;
-        if (new_col) {
-            if (JMAX == 1) fetch_u(j0n);
-            joldn = old_col(j0n + jl);
-        }
-        const int kl = lane >> 5, il = lane & 31;
-        const int rb = hf * FT;
-        // The wave's two 32 x 32 pieces: one that lies above the diagonal or beyond the matrix on the
-        // whole has nothing to add (a sixth of the pieces at 720 columns, more below: 3072 x 768, 4 bit,
-        // 16.75 -> 16.05 ms; 256 x 2304 24.5 -> 23.9 ms).
-        const int r0 = rb + wm * 64;
-        bool need[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-            need[mt] = j0 + wn * 32 < mn && i0 + r0 + mt * 32 < mn && j0 + wn * 32 <= i0 + r0 + mt * 32 + 31;
-        // (several groups of vectors: each group's update is summed from zero and added on its own, so that
-        // the matrix comes out as if each had been flushed by itself.  A group is a panel that shares the
-        // flush, or half of a panel of 80 steps.)
-        for (int ch = 0; ch < chunks; ++ch) {
-            if (JMAX > 1 && ch > 0) {
-                __syncthreads();               // everyone is done reading Us
-                stash_u();
-                __syncthreads();
-            }
-            if (JMAX > 1) {
-                if (ch + 1 < chunks) fetch_u(j0, ch + 1);
-                else if (new_col) fetch_u(j0n);
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) { sum[0][v] = 0.f; sum[1][v] = 0.f; }
-            auto mma = [&](auto both, int mt0) {
-#pragma unroll
-                for (int kk = 0; kk < nbp; kk += 2) {
-                    const int kf = JMAX == 1 ? kk + kl : ch * KMAX + kk + kl;
-                    const float b0 = Us[kk + kl][wn * 32 + il];
-                    if constexpr (both) {
-                        const float a0 = Fs[kf][r0 + il], a1 = Fs[kf][r0 + 32 + il];
-                        sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, sum[0], 0, 0, 0);
-                        sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, sum[1], 0, 0, 0);
-                    } else {
-                        const float a0 = Fs[kf][r0 + mt0 * 32 + il];
-                        if (mt0) sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, sum[1], 0, 0, 0);
-                        else sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, sum[0], 0, 0, 0);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    OBC_MF(0, 1) OBC_MF(1, 1) OBC_MF(2, 1) OBC_MF(3, 1) OBC_MF(4, 1) OBC_MF(5, 1) OBC_MF(6, 1) OBC_MF(7, 1)
                 }
-            };
-            if (need[0] && need[1]) mma(std::true_type{}, 0);
-            else if (need[0]) mma(std::false_type{}, 0);
-            else if (need[1]) mma(std::false_type{}, 1);
+            }
+#undef OBC_MF
+            // (the products stay in front of the next loads, whose operands would otherwise all be in flight at once)
+            asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]), "+v"(sum[4]), "+v"(sum[5]),
+                         "+v"(sum[6]), "+v"(sum[7]));
+            if (gg + NB < NG * J) fetch(gg + NB);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (QUADS && ch == 0) {
+            // the tile's 32 rows to the front: over the first quad's earlier rows, then over the rows that were
+            // eliminated behind row v
+            if (o_first & 1) close_from<0, NX>(x);
+            if (o_first & 2) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                old[0][v] = __fadd_rn(old[0][v], sum[0][v]);
-                old[1][v] = __fadd_rn(old[1][v], sum[1][v]);
+                for (int v = 0; v + 2 < NX; ++v) x[v] = x[v + 2];
+            }
+            const int below = __builtin_amdgcn_update_dpp(0, orow, 0x130, 0xf, 0xf, false);   // wave_shl:1, of all lanes
+            const int gap = below - orow - 1;
+            unsigned long long gaps = fits ? __ballot(gap > 0 && lane + 1 < nr) : 0ull;
+            while (gaps) {
+                const int v = __builtin_ctzll(gaps);
+                int n = __builtin_amdgcn_readlane(gap, v);
+                do close_gap<0, 8>(x, v + 1); while (--n > 0);
+                gaps &= gaps - 1;
+            }
+            if (!fits) {
+                int om = orow;
+                asm volatile("" : "+v"(om));              // (nothing of this is formed ahead)
+                rows_singly(om);
             }
         }
-        // store: a lane's registers 4q .. 4q+3 are four consecutive rows of its column = one
-        // 16-byte slot of the row-quad layout
-        const int jcol = j0 + jl;
-        const int colB = (jcol < mn) ? jcol * 16 : kFar;
-        const bool on_diag = (j0 == i0 + rb);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int q = 0; q < 8; ++q)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int qrow = i0 + rb + wm * 64 + mt * 32 + 8 * q + lrow;   // first row of the quad
-                const int quad = qrow >> 2;
-                if (on_diag && jcol > qrow + 3) continue;                   // wholly above the diagonal
-                uintx4 v4 = {__float_as_uint(old[mt][4 * q]), __float_as_uint(old[mt][4 * q + 1]),
-                             __float_as_uint(old[mt][4 * q + 2]), __float_as_uint(old[mt][4 * q + 3])};
-                if (a.keep) __builtin_amdgcn_raw_buffer_store_b128(v4, rnew, quad * ldn * 16 + colB, 0, 0);
-                else __builtin_amdgcn_raw_buffer_store_b128(v4, rnew, quad * ldn * 16 + colB, 0, kMatStorePolicy);
-            }
-        if (!more) break;
-        if (new_col) {
-            __syncthreads();                   // everyone is done reading Us
-            stash_u();
-            __syncthreads();                   // the new Us visible
-        }
-        j0 = j0n;
-        hf = hfn;
-        jold = joldn;
+            for (int i = 0; i < 4; ++i) x[4 * q + i] = __fadd_rn(x[4 * q + i], sum[q][i]);
+    }
+
+    // ---- store: four consecutive rows of a column = one 16-byte slot of the row-quad layout (slots wholly above the
+    // diagonal are left out)
+    __amdgpu_buffer_rsrc_t rnew = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.A_new + (size_t)row * a.new_row_stride), 0, ((mn + 3) >> 2) * ldn * 16, kBufWord3);
+    const int coln = jcol < mn ? jcol * 16 : kFar;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int off = jcol > r0 + 4 * q + 3 ? kFar : coln, qo = (r0 / 4 + q) * ldn * 16;
+        const uintx4 v = {__float_as_uint(x[4 * q]), __float_as_uint(x[4 * q + 1]), __float_as_uint(x[4 * q + 2]),
+                          __float_as_uint(x[4 * q + 3])};
+        if (a.keep) __builtin_amdgcn_raw_buffer_store_b128(v, rnew, off, qo, 0);
+        else __builtin_amdgcn_raw_buffer_store_b128(v, rnew, off, qo, kMatStorePolicy);
     }
 }
 
@@ -666,8 +655,12 @@ constexpr int flush_groups(int K)
 {
     return K == 24 ? 4 : K == 28 ? 3 : K == 40 ? 2 : K == 48 || K == 56 || K == 64 || K == 72 ? 1 : 0;
 }
-// ... and panels of more than 72 vectors go as two groups (the operand tiles of two workgroups have to fit in a CU's LDS)
+// ... and panels of more than 72 vectors go as two groups
 constexpr int flush_split(int B) { return B > 72 ? 2 : 1; }
+// The least live size over a group's vectors at which a flush reads whole quads of the old matrix; below, too many tiles'
+// rows lie in more than ten of them.  In us, single rows and quads, 64 vectors: 256 rows, 560 columns left 118, 111; 368 52.2,
+// 52.6; 240 30.5, 31.2; 203 rows, 547 100, 92; 291 36, 39; 3072 rows, 176 201, 211; 2 x 40 vectors, 320 607, 573; 240 361, 342.
+constexpr int kQuadsMinRatio = 6;
 
 // what a flush reads has room in U and an instance of the kernel, whatever number of panels it serves
 constexpr bool flush_serves(const Variant &v)
@@ -790,29 +783,31 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         fa.A_new = bw.Abuf[nxt];
         fa.new_row_stride = mat_stride;
         fa.ld_new = m_next;
-        // strips of 256 rows where two workgroups' tiles fit in a CU's LDS, else 128
-        const int halves = (K <= 48 && chunks == 1) ? 2 : 1;
         fa.chunks = chunks;
         fa.keep = m_next % 4 != 0 || (double)R * m_next * m_next * 2.0 <= kKeepBytes;
-        fa.strips = (m_next + halves * FT - 1) / (halves * FT);
+        fa.strips = (m_next + 127) / 128;
         const int rows8 = (R + 7) / 8 * 8;
+        // whole quads of the old matrix where 32 rows nearly always come from ten of them
+        const bool quads = swz && m_next >= kQuadsMinRatio * K;
         {
             // one triangle of the surviving m_next x m_next part of every row's inverse is read and
             // written once
             const double tri = 0.5 * (double)m_next * (m_next + 1.0);   // entries of one triangle
             obc_scope sc(ctx, OBC_KERNEL_FLUSH, (double)R * 8.0 * tri, (double)R * 2.0 * K * chunks * tri);
-            const dim3 grid(fa.strips * rows8);
-            switch (chunks > 1 ? -K : K) {
-            case 24: flush_kernel<24, 2, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 28: flush_kernel<28, 2, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 40: flush_kernel<40, 2, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 48: flush_kernel<48, 2, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 56: flush_kernel<56, 1, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 64: flush_kernel<64, 1, 1><<<grid, 512, 0, st>>>(fa); break;
-            case 72: flush_kernel<72, 1, 1><<<grid, 512, 0, st>>>(fa); break;
-            case -24: flush_kernel<24, 1, flush_groups(24)><<<grid, 512, 0, st>>>(fa); break;
-            case -28: flush_kernel<28, 1, flush_groups(28)><<<grid, 512, 0, st>>>(fa); break;
-            case -40: flush_kernel<40, 1, flush_groups(40)><<<grid, 512, 0, st>>>(fa); break;
+            const dim3 grid(fa.strips * (fa.strips + 1) * rows8);
+            auto launch = [&](auto k) {
+                constexpr int KK = decltype(k)::value, J = flush_groups(KK);
+                if (quads) flush_kernel<KK, J, true><<<grid, 256, 0, st>>>(fa);
+                else flush_kernel<KK, J, false><<<grid, 256, 0, st>>>(fa);
+            };
+            switch (K) {
+            case 24: launch(std::integral_constant<int, 24>{}); break;
+            case 28: launch(std::integral_constant<int, 28>{}); break;
+            case 40: launch(std::integral_constant<int, 40>{}); break;
+            case 48: launch(std::integral_constant<int, 48>{}); break;
+            case 56: launch(std::integral_constant<int, 56>{}); break;
+            case 64: launch(std::integral_constant<int, 64>{}); break;
+            case 72: launch(std::integral_constant<int, 72>{}); break;
             default: return obc_fail(ctx, OBC_ERR_BAD_ARG, "row solver: no flush kernel for block size %d", K);
             }
         }

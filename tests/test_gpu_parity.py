@@ -295,6 +295,33 @@ def test_small_widths_without_a_workspace(obc, orc):
     ctx.close()
 
 
+@pytest.mark.parametrize("run", [1, 2, 3, 5, 8, 9, 13, 64])
+def test_flush_closes_up_runs_of_eliminated_rows(obc, orc, run):
+    """The flush takes a tile's rows from whole groups of four rows of the old matrix and closes them up.  Zero weights
+    are pruned first, in index order: the first panel's 64 at the row's start, the second's in runs of `run` that begin
+    at every residue of 4 (a row's place moves them), up to more than a tile's rows can reach over."""
+    d, R = 602, 4
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=4 * d)
+    Hinv = _hinv(obc, X)
+    for r in range(R):
+        W[r, :64] = 0.0
+        left, at = 64, 70 + r
+        while left:
+            n = min(run, left)
+            W[r, at:at + n] = 0.0
+            left, at = left - n, at + n + 7 - n % 2
+    _check_prune(obc, orc, W, Hinv, 330, (0, 0), 2)
+
+
+@pytest.mark.parametrize("left", [31, 32, 33, 63, 65, 127, 129, 383, 384, 385, 447, 513])
+def test_flush_at_tile_edges(obc, orc, left):
+    """`left` live columns after two flushes of 64: ends of the tiles of 32 x 64, of the strips of 128 rows, and the
+    live size from which whole groups of rows are read (384)."""
+    d = left + 128
+    W, X = _layer("conv64x576", d_col=d, d_row=3, n_samples=4 * d)
+    _check_prune(obc, orc, W, _hinv(obc, X), d, (0, 0), 2)
+
+
 @pytest.mark.parametrize("d,k", [(2305, 90), (2344, 100), (3073, 100), (3200, 130), (4097, 60), (4608, 130)])
 def test_panels_that_share_a_flush(obc, orc, d, k):
     """Widths above 2304: several panels per flush, the group cut short where the live size changes the
