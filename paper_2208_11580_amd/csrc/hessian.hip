@@ -19,8 +19,8 @@
 // order by a second kernel, which also mirrors the upper tiles into the lower triangle (H comes out
 // exactly symmetric) -- no float atomics, results are deterministic.
 //
-// Bound by the matrix cores' issue and the loads' latency (half of the bf16 rate): 2304 x 50 000 in
-// 1.52 ms, 175 TFLOP/s of the d^2 N flop (fp32 MFMA: 2.37 ms, 112); 576 x 50 000 0.150 ms (0.326).
+// Bound by the matrix cores' issue and the loads' latency (three fifths of what a bare bf16 loop sustains, 1.75 PFLOP/s
+// of 2.5): 2304 x 50 000 in 1.45 ms, 183 TFLOP/s of the d^2 N flop (fp32 MFMA: 2.37 ms, 112); 576 x 50 000 0.141 ms (0.326).
 #include "common.h"
 
 namespace {
@@ -229,35 +229,50 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
     // One slab's six products, the smallest first, summed from zero on the matrix cores and added to
     // the running sums by the vector ALU.  (Fed straight into the running sums, the small products
     // would each be lost below their last bit: m m, always positive on the diagonal, left a bias of
-    // -2e-6 there.)  `between(b)` runs after the b-th column of accumulators.
+    // -2e-6 there.)  One accumulator's six products are a chain; the vector instructions -- the additions of the
+    // accumulator before it, and what `between(u)` does for the u-th -- are dealt between them, so that a wave keeps
+    // both units busy by itself: the waves of a SIMD meet at every slab's barrier and would otherwise multiply
+    // together and add together (2304 x 50 000 in four batches and its inverse 2.98 -> 2.91 ms; in one batch, with the
+    // cross moment and the re-fit, 3.65 -> 3.56).
+    constexpr int NU = MT * NT;
     auto mma = [&](int stage, auto between) {
-        bf16x8 fa[3][MT];
+        bf16x8 fa[3][MT], fb[3];
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
             for (int a = 0; a < MT; ++a) fa[pl][a] = frag(stage, 0, pl, wm * MT + a);
         constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+        floatx16 t[2];
 #pragma unroll
-        for (int b = 0; b < NT; ++b) {
-            bf16x8 fb[3];
+        for (int u = 0; u <= NU; ++u) {
+            const int a = u % MT, b = u / MT;
+            if (u < NU) {
+                if (a == 0) {
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) fb[pl] = frag(stage, 1, pl, wn * NT + b);
-            floatx16 t[MT];
+                    for (int pl = 0; pl < 3; ++pl) fb[pl] = frag(stage, 1, pl, wn * NT + b);
+                }
 #pragma unroll
-            for (int a = 0; a < MT; ++a)
+                for (int v = 0; v < 16; ++v) t[u & 1][v] = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) t[a][v] = 0.f;
+                for (int i = 0; i < 6; ++i)
+                    t[u & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa[i]][a], fb[pb[i]], t[u & 1], 0, 0, 0);
+                between(u);
+            }
+            if (u > 0) {
 #pragma unroll
-            for (int i = 0; i < 6; ++i)
+                for (int v = 0; v < 16; ++v)
+                    acc[(u - 1) % MT][(u - 1) / MT][v] = __fadd_rn(acc[(u - 1) % MT][(u - 1) / MT][v], t[(u - 1) & 1][v]);
+            }
+            if (u < NU) {
 #pragma unroll
-                for (int a = 0; a < MT; ++a)
-                    t[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa[i]][a], fb[pb[i]], t[a], 0, 0, 0);
-            between(b);
-#pragma unroll
-            for (int a = 0; a < MT; ++a)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[a][b][v] = __fadd_rn(acc[a][b][v], t[a][v]);
-            __builtin_amdgcn_sched_barrier(0);   // (one column at a time: registers)
+                for (int i = 0; i < 6; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one matrix instruction,
+                    if (u % (NU / 4) == 0) __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);    // and its share of vector ones
+                    else __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);   // (one accumulator at a time: registers)
+            if (u == NU - 1) __syncthreads();
         }
     };
 
@@ -273,19 +288,19 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
             for (int h = 0; h < 2; ++h) { fetch_any(0, h, 1); fetch_any(1, h, 1); }
     }
     __syncthreads();
-    // Stage s holds slab s, the registers hold slab s + 1: it is split and stored into the other
-    // stage, and slab s + 2 requested, among slab s's matrix instructions.  One barrier per slab.
+    // Stage s % 2 holds slab s, the registers hold slab s + 1: it is split and stored into the other
+    // stage, and slab s + 2 requested, among slab s's matrix instructions.  One barrier per slab, behind its last
+    // read and store and ahead of its last additions.
     int s = 0;
     for (; (int64_t)(s + 3) * BK <= kend - kbeg; ++s) {
         const int cur = s & 1;
-        mma(cur, [&](int b) {
-#pragma unroll
-            for (int i = 4 / NT * b; i < 4 / NT * (b + 1); ++i) {
+        mma(cur, [&](int u) {
+            if (u % (NU / 4) == 0) {
+                const int i = u / (NU / 4);
                 stash(cur ^ 1, i >> 1, i & 1);
                 fetch(i >> 1, i & 1, s + 2);
             }
         });
-        __syncthreads();
     }
     for (; s < nsplit; ++s) {
         const int cur = s & 1;
@@ -294,7 +309,6 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
         if (s + 2 < nsplit)
             for (int h = 0; h < 2; ++h) { fetch_any(0, h, s + 2); fetch_any(1, h, s + 2); }
         mma(cur, [](int) {});
-        __syncthreads();
     }
 
     // The plain form of the piece: where an input was too small to split, or where a NaN came out -- an
