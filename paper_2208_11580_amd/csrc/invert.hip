@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(StepArgs s)
     });
     __syncthreads();
     // (the factor itself is not needed again: T and G carry the step)
-    potrf_wg_core(s.Tnext, s.status, OBC_ERR_NOT_SPD, lds);
+    potrf_wg_core(s.Tnext, Mi, s.status, OBC_ERR_NOT_SPD, lds);
     __syncthreads();                            // T of the next block, in LDS where the factorisation left it
     tile_mma(acc, Bs, Bs);                      // G = T^T T
     tile_each(acc, [&](int i, int j, double v) { s.Gnext[i * NB + j] = v; });
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256) void chol_first_kernel(const float *H, int d, 
         Bs[i * PL + j] = 0.0;
     }
     __syncthreads();
-    potrf_wg_core(T, status, OBC_ERR_NOT_SPD, lds);
+    potrf_wg_core(T, bs, status, OBC_ERR_NOT_SPD, lds);
     __syncthreads();
     doublex4 acc[2][2];
     tile_mma(acc, Bs, Bs);

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
             Bs[i * PL + j] = 0.0;
         });
         __syncthreads();
-        potrf_wg_core(Lk, a.status, OBC_ERR_NUMERIC, lds);
+        potrf_wg_core(Lk, Mi, a.status, OBC_ERR_NUMERIC, lds);
     } else {
         double rl[16];
         tile_fetch(rl, Lk, NB, NB, NB);

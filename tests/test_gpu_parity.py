@@ -154,6 +154,19 @@ def test_invert_matches_oracle(obc, orc, d):
     assert np.linalg.norm(A @ H64 - np.eye(d)) / np.sqrt(d) < 1e-4
 
 
+@pytest.mark.parametrize("d", [2, 15, 16, 17, 31, 33, 47, 48, 49, 63, 64, 65, 79, 81, 112, 113, 127, 129])
+def test_invert_at_sub_block_edges(obc, d):
+    """Last blocks of every number of 16-column sub-blocks, with and without padding.  A fp64 inverse rounded to fp32
+    is off by half a unit, 6e-8 of an entry; the condition number, about 10, leaves the fp64 part of it below that."""
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn(d, 10 * d + 50, generator=gen, device="cuda")
+    H = obc.obc_hessian(X)
+    ref = torch.linalg.inv(H.double().cpu())
+    A = obc.obc_invert(H)
+    assert torch.equal(A, A.T)
+    assert float((A.double().cpu() - ref).norm() / ref.norm()) < 1e-7
+
+
 def test_invert_reports_non_spd(obc):
     import paper_2208_11580_amd as pkg
 
