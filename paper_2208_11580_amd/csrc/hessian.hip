@@ -382,8 +382,10 @@ void nt_partial_kernel(const float *__restrict__ Ya, int da, int64_t lda, const 
 // mirrored piece goes through LDS so that it is written along rows too.  (Below the diagonal of a
 // diagonal piece the mirror image is taken as well: the two halves of such a tile add their cross
 // products in opposite order.)
+// damp_rel >= 0, with one workgroup only (d <= 32): the dampening is done here, with the sum in dampen_kernel's order
+// (whose 1024 terms are zeros but for the first d).
 __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restrict__ partial, int S,
-                                                          int d, int accumulate, float *__restrict__ H)
+                                                          int d, int accumulate, float damp_rel, float *H)
 {
     __shared__ float Tt[32][33];
     const int pi = blockIdx.y, pj = blockIdx.x;           // 32 x 32 piece (pi, pj)
@@ -409,6 +411,22 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(const float *__restric
         const int64_t e = (int64_t)i * d + j;
         const float s = Tt[tx][ty + 8 * r];
         H[e] = accumulate ? H[e] + s : s;
+    }
+    if (damp_rel >= 0.f && gridDim.x == 1) {
+        __shared__ double red[32];
+        __syncthreads();                                  // (the workgroup's own stores, read back through its cache)
+        const int j = threadIdx.x;
+        float h = 0.f;
+        if (j < 32) {
+            h = j < d ? H[(int64_t)j * d + j] : 0.f;
+            red[j] = (double)h;
+        }
+        __syncthreads();
+        for (int w = 16; w > 0; w >>= 1) {
+            if (j < w) red[j] += red[j + w];
+            __syncthreads();
+        }
+        if (j < d) H[(int64_t)j * d + j] = h + (float)((double)damp_rel * red[0] / (double)d);
     }
 }
 
@@ -485,9 +503,9 @@ int obc_hessian(obc_ctx *ctx, const float *X, int d, int64_t N, int64_t ldx, flo
     int rc = launch_nt<true>(ctx, p, X, d, ldx, X, d, ldx, N, partial);
     if (rc != OBC_OK) return rc;
     const unsigned np32 = (unsigned)((d + 31) / 32);
-    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, p.S, d, accumulate, H);
+    syrk_reduce_kernel<<<dim3(np32, np32), 256, 0, ctx->stream>>>(partial, p.S, d, accumulate, damp_rel, H);
     OBC_LAUNCH_CHECK(ctx, "syrk_reduce_kernel");
-    if (damp_rel >= 0.f) {
+    if (damp_rel >= 0.f && np32 > 1) {
         dampen_kernel<<<1, 1024, 0, ctx->stream>>>(H, d, damp_rel);
         OBC_LAUNCH_CHECK(ctx, "dampen_kernel");
     }
