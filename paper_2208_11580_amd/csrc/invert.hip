@@ -57,11 +57,13 @@ __device__ __forceinline__ void solve_tile(const double *T, double *Yp, int d, i
     tile_each(acc, [&](int i, int j, double v) { if (i < bs && j < Nc) Yp[(int64_t)i * d + j] = v; });
 }
 
-// the solve of the block row that starts at row k0
-__global__ __launch_bounds__(256) void solve_row_kernel(const double *__restrict__ T, double *__restrict__ Y, int d, int k0, int bs)
+// the solves of the last block row, which starts at row k0, and (y = 1) of the one before, which is whole: T and T - NB x NB
+__global__ __launch_bounds__(256) void solve_rows_kernel(const double *__restrict__ T, double *__restrict__ Y, int d, int k0, int bs)
 {
     __shared__ double lds[2 * NB * PL];
+    if (blockIdx.y) { T -= NB * NB; k0 -= NB; bs = NB; }
     const int c0 = blockIdx.x * NB, nc = k0 + bs;
+    if (c0 >= nc) return;
     solve_tile(T, Y + (int64_t)k0 * d + c0, d, bs, (nc - c0 < NB) ? nc - c0 : NB, lds, lds + NB * PL);
 }
 
@@ -351,9 +353,7 @@ int factor_inverse(obc_ctx *ctx, const float *H, int d, void *ws, double **Yout)
             chol_step_kernel<<<dim3((unsigned)(tm > tc ? tm : tc), (unsigned)tm, 3), 256, 0, st>>>(sa);
         } else {
             // the last block column: finish the previous block row and this one
-            if (bsprev > 0)
-                solve_row_kernel<<<(kprev0 + bsprev + NB - 1) / NB, 256, 0, st>>>(Tk - (int64_t)NB * NB, Y, d, kprev0, bsprev);
-            solve_row_kernel<<<(nc + NB - 1) / NB, 256, 0, st>>>(Tk, Y, d, k0, bs);
+            solve_rows_kernel<<<dim3((nc + NB - 1) / NB, bsprev > 0 ? 2 : 1), 256, 0, st>>>(Tk, Y, d, k0, bs);
         }
         kprev0 = k0;
         bsprev = bs;
