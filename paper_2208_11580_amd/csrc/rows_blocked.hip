@@ -327,7 +327,8 @@ struct FlushArgs {
     int old_swz;             // layout of A_old: 0 plain row-major, 1 row-quad (A_new is always row-quad)
     float *A_new;
     size_t new_row_stride;
-    int ld_new;              // = the live size after the flush of every row that still has steps to do
+    int ld_new;
+    int m;                   // live size after the flush of every row that still has steps to do
     int d, R;
     int strips;              // of 128 rows
     int keep;                // the new matrices stay in the caches
@@ -343,14 +344,10 @@ constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: 
 // displacing the vectors and the old matrix's lines in L2.
 constexpr int kMatStorePolicy = 2 | 16;
 
-// The stores go through the caches in two cases.  (1) The live size is no multiple of 4: a wave's stores then begin and
-// end inside 64-byte sectors, and two waves' halves of a sector meet in L2 only if they are kept there.  In ms, pruned,
-// streaming and cached: 203 x 1283 5.11, 4.90; 768 x 767 4.46, 4.34; 203 x 1999 15.14, 14.20; 100 x 2301 13.81, 13.09;
-// 12 x 4095 32.6, 31.6; 256 x 2303 at 4 bit 26.7, 25.2; 3071 x 765 at 4 bit 16.9, 16.3.  (2) All rows' new matrices
-// together fit the 256 MB memory-side cache, where the next panels find the rows that they fetch: 64 x 576 2:4 507,
-// 500 us; 128 x 1536 5.21, 5.18 ms; 768 x 768 4.05, 4.05.  Larger aligned ones only displace what is of use: with a
-// limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800 6.93 against 6.84; without one 256 x 2304
-// at 4 bit 23.9 against 22.9.
+// The stores go through the caches where all rows' new matrices together fit the 256 MB memory-side cache, in which the
+// next panels find the rows that they fetch: 64 x 576 2:4 507, 500 us; 128 x 1536 5.21, 5.18 ms; 768 x 768 4.05, 4.05.
+// Larger ones only displace what is of use: with a limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800
+// 6.93 against 6.84; without one 256 x 2304 at 4 bit 23.9 against 22.9.
 constexpr double kKeepBytes = 256e6;
 
 // x[v] = x[v + 1] from Z on
@@ -427,7 +424,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     if ((strip + 1) * (strip + 2) <= t) ++strip;
     if (strip * (strip + 1) > t) --strip;
     strip = __builtin_amdgcn_readfirstlane(strip);
-    const int mn = a.ld_new;
+    const int mn = a.m;
     const int r0 = strip * 128 + wave * 32, c0 = (t - strip * (strip + 1)) * 64;
     if (r0 >= mn || c0 > r0) return;
     const int nb = a.ws.nb[row], done = a.ws.done[row], total = a.ws.total[row];   // (waited for below)
@@ -759,7 +756,13 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     fa.d = d; fa.R = R; fa.ws = bw;
 
     int host_total = (mode == MODE_QUANT || live) ? d : k_steps;   // upper bound over the rows
-    const size_t mat_stride = obc_align_up((size_t)d * d, 4);   // floats between two rows' matrices
+    // Floats between two rows' matrices, and between two quads of a matrix: multiples of 256 bytes, so that a wave's stores
+    // are whole lines at any live size.  (They fit what was laid out: a flush leaves d - 24 columns at most, rounded up to
+    // 16, in d - 24 rows, rounded up to 4.)  In ms, with the live size as the distance and, where it was no multiple of 4,
+    // stores through the caches, and with this: 256 x 2303 at 4 bit 23.36, 21.91; 3071 x 765 at 4 bit 15.53, 14.81; 768 x 767
+    // pruned 5.01, 4.78; 203 x 1283 at 8 bit 4.62, 4.51; 203 x 1999 pruned 17.08, 16.72; 40 x 4095 44.0, 43.0; 64 x 577 1.200,
+    // 1.187; aligned 256 x 2304 at 4 bit 21.84, 21.83.
+    const size_t mat_stride = (size_t)d * d / 64 * 64;
     int host_done = 0;
     int cur = -1;            // -1: the shared H^-1; otherwise index into Abuf
     int ld_cur = d;
@@ -782,9 +785,10 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         fa.old_swz = swz;
         fa.A_new = bw.Abuf[nxt];
         fa.new_row_stride = mat_stride;
-        fa.ld_new = m_next;
+        fa.m = m_next;
+        fa.ld_new = (m_next + 15) / 16 * 16;
         fa.chunks = chunks;
-        fa.keep = m_next % 4 != 0 || (double)R * m_next * m_next * 2.0 <= kKeepBytes;
+        fa.keep = (double)R * m_next * m_next * 2.0 <= kKeepBytes;
         fa.strips = (m_next + 127) / 128;
         const int rows8 = (R + 7) / 8 * 8;
         // whole quads of the old matrix where 32 rows nearly always come from ten of them
