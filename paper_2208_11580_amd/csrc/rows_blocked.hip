@@ -683,6 +683,24 @@ static_assert(flush_serves_all(), "a panel's steps, or those of the panels that 
 // it, against 80 throughout: 1536 x 384 1615, 1688; 3072 x 512 5553, 5642; 768 x 512 1582, 1574.
 constexpr bool longer_panels(int m) { return m <= 272 || (m - 256 + 79) / 80 < (m - 256 + 47) / 48; }
 
+// How many panels share a flush.  What the flushes save must exceed the re-reading of the earlier panels' vectors.  A
+// flush takes the longer the more rows there are and the wider they are; the re-reading stands in each step's chain
+// however few they are.  In us, pruned from that width down, a flush after each panel, after two, three and four:
+// 280 steps (40 a panel) 1 x 2800 1332, 2005; 8 x 3072 1642, 2274; 64 x 3072 4050, 4202; 96 x 3072 5391, 5206; 96 x 2800
+// 4637, 4636; 128 x 2500 4715, 4681; 192 x 2400 5863, 5845; 256 x 2650 9511, 8339 (below the best line 96 x 2500 3825, 3984).
+// 288 steps (24) 2 x 4400 2850, 3020, 3427, 3884; 4 x 4400 3235, 3190, 3576, 4030; 24 x 4608 6367, 4806, 4808, 5417; 48 x 4608
+// 10280, 6742, 6776, 7240; 64 x 4608 12938, 8271, 7918, 8292; 96 x 4608 18227, 11132, 10175, 10164; 256 x 4608 43764, 25196,
+// 22525, 21954; blocks of four 4 x 4400 3327, 3606, 4187, 4883; 16 x 4608 5180, 4591, 4963, 5605; 64 x 4608 13093, 8892, 8915, 9578.
+// 28 a panel share three at any row count (336 steps: 96 x 3700 12943, 8998, 8946; 192 x 3700 23505, 14943, 14254), though
+// fewer would be better with few rows (48 x 3700 7734, 5737, 6338; 8 x 3700 3434, 3496, 3932).
+// (Not with block pruning's larger state at 40 steps: 40 x 3000 in blocks 18.57 ms, 19.15 shared.)
+int shared_panels(const Variant &v, int m, int R)
+{
+    if (v.J == 2) return m >= 2416 && R >= 96 ? 2 : 1;
+    if (v.J == 4) return R >= 96 ? 4 : R >= 64 ? 3 : R > 2 ? 2 : 1;
+    return v.J;
+}
+
 const Variant *pick_variant(int m, int R, int mode)
 {
     if (R >= kSharedCuMinRows && m > 256 && mode != MODE_BLOCK)
@@ -865,18 +883,9 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         pa.swz = swz;
         // Panels that share a flush, as long as the live size keeps this variant.  Before the flush the
         // index space keeps its size, and a panel finds the earlier ones' vectors in memory.
-        // (What a flush saves must exceed the re-reading.  Above 3072 columns, 24 and 28 steps a panel, it
-        // does from one row on.  At 40 steps it depends on the rows and the width -- 280 steps from that
-        // width down, pruned, in us, flushed after each panel against shared: 192 x 2500 7173, 6560; 128 x 2500
-        // 4941, 4905; 192 x 2800 8633, 7347; 96 x 2650 5061, 4694; 96 x 2800 4881, 4876; 64 x 2950 4488, 4344;
-        // 32 x 3072 3386, 3283; 128 x 3072 7001, 6432; but 96 x 2500 4129, 4215; 64 x 2500 3237, 3413; 64 x 2800
-        // 3781, 3955; 32 x 2500 2629, 2664; 8 x 2800 2522, 2615.  The line is not everywhere the best: 192 x 2400
-        // 6524, 6374 and 512 x 2400 14874, 14915 lie below it, 64 x 3072 4368, 4438 and 8 x 3072 2760, 2806 above.
-        // Not with block pruning's larger state: 40 x 3000 in blocks 18.57 against 19.15 ms, though 240 steps of
-        // 256 x 3000 take 10.4 against 8.5.)
         PanelLaunch *first = mode == MODE_BLOCK ? v->launch_block : v->launch;
         PanelLaunch *next = mode == MODE_BLOCK ? v->launch_block_old : v->launch_old;
-        const int most = next && (m_max >= 2816 || (R >= 96 && m_max >= 2416)) ? v->J : 1;
+        const int most = next ? shared_panels(*v, m_max, R) : 1;
         int panels = 1;
         while (panels < most && host_done + panels * v->B < host_total &&
                pick_variant(m_max - panels * v->B, R, mode) == v) ++panels;

@@ -394,6 +394,18 @@ def test_shared_flushes_leave_no_trace(obc, mode):
         assert torch.equal(many[:8], few)
 
 
+@pytest.mark.parametrize("d,R", [(2900, 96), (4200, 96), (4200, 64), (4200, 3)])
+def test_the_panels_that_share_a_flush_follow_the_rows(obc, d, R):
+    """How many panels of 24 or 40 steps share a flush (four, three, two, none) depends on the rows; a row's results
+    do not.  Past a whole group and the change to panels of 28 steps."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=d + 500)
+    Hinv = _hinv(obc, X)
+    many = obc.obc_prune_rows(W, Hinv, k_steps=150, strategy=2)
+    few = obc.obc_prune_rows(W[:2].contiguous(), Hinv, k_steps=150, strategy=2)
+    for name in ("order", "loss", "W"):
+        assert torch.equal(many[name][:2], few[name]), name
+
+
 @pytest.mark.parametrize("strategy", [1, 2])
 @pytest.mark.parametrize("nm", [(2, 4), (4, 8)])
 def test_prune_rows_n_m(obc, orc, strategy, nm):
