@@ -632,10 +632,12 @@ constexpr Variant kVariants[] = {
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 // Three of these fit on one CU (registers and LDS), two where a thread owns one index; with several times more
-// rows than CUs that hides a row's latency behind the steps of two others.  From three rows per CU on, in ms, with
-// 1024 x 1 and with these: 768 x 400 pruned 1.13, 1.00; 768 x 768 pruned 4.25, 4.06, at 4 bit 4.32, 4.05; 1536 x 600 4.95, 4.30;
-// 3072 x 512 at 4 bit 6.09, 5.58; 3072 x 768 pruned 15.98, 15.19, at 4 bit 16.49, 15.26.  Against: a last round of few rows, 1024 x 512
-// 2.02, 2.17; 1024 x 768 5.46, 5.69.  512 rows are two full rounds of the wider ones: 512 x 512 1.16, 1.26, 512 x 768 2.91, 3.11.
+// rows than CUs that hides a row's latency behind the steps of two others.  Past two full rounds of the wider ones, in us, with
+// 1024 x 1 and with these: 513 x 400 pruned 928, 816, at 4 bit 1008, 807; 513 x 512 1304, 1263 and 1399, 1246; 576 x 600 2217,
+// 1851 and 2287, 1833; 700 x 768 3853, 3543 and 3942, 3534; 768 x 768 4053, 3757 and 4141, 3736; 1536 x 600 4694, 4069; 3072 x 768
+// 15453, 14537 and 16075, 14691.  (Fewer than 768 rows pruned take them above 352 columns only, one workgroup being done before
+// three fill a CU: 513 x 300 487, 502; 700 x 300 534, 550; at 4 bit 549, 493.)  Against: 512 x 512 1107, 1210, 512 x 768 2775, 2825; a
+// last round of few rows, 1024 x 512 pruned 1928, 2133, at 4 bit 2062, 2098; 1024 x 768 5221, 5312 and 5391, 5285.
 // With two owned indices the same registers and LDS hold 80 steps.
 // Block pruning never takes them: its state does not fit beside them (83 registers in scratch memory at 256 x 3), and the
 // steps of 1024 x 1, which are not a loop, are the faster ones at every width and row count: 768 x 260 497 against 531 us,
@@ -644,7 +646,7 @@ constexpr Variant kSharedCuVariants[] = {
     {512, 80, launch_panel_256_2_56_24, nullptr},
     {768, 48, launch_panel_256_3_32_16, nullptr},
 };
-constexpr int kSharedCuMinRows = 768;
+constexpr int kSharedCuMinRows = 513;
 
 // A flush applies K vectors at once, or several groups of K one after the other: as many as there is an instance for
 // (0: none).
@@ -703,7 +705,8 @@ int shared_panels(const Variant &v, int m, int R)
 
 const Variant *pick_variant(int m, int R, int mode)
 {
-    if (R >= kSharedCuMinRows && m > 256 && mode != MODE_BLOCK)
+    const int least = R >= 3 * 256 || mode == MODE_QUANT ? 256 : 352;
+    if (R >= kSharedCuMinRows && m > least && mode != MODE_BLOCK)
         for (const Variant &v : kSharedCuVariants)
             if (m <= v.cap && (v.B != 80 || longer_panels(m))) return &v;
     for (int i = 0; i < kNumVariants; ++i)

@@ -1182,6 +1182,15 @@ def test_panels_of_72_and_80_steps(obc, orc, R, d, k):
         _check_quant(obc, orc, W, Hinv, 4, 2, rows=rows)
 
 
+@pytest.mark.parametrize("R,d,k", [(512, 353, 120), (513, 257, 60), (513, 352, 120), (513, 353, 120), (640, 600, 270)])
+def test_three_rows_per_cu_past_512_rows(obc, orc, R, d, k):
+    """Both sides of the row count from which three workgroups share a CU, and of the widths from which OBQ and pruning do."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
+    Hinv = _hinv(obc, X)
+    _check_prune(obc, orc, W, Hinv, k, (0, 0), 2, rows=[0, R - 1])
+    _check_quant(obc, orc, W, Hinv, 4, 2, rows=[0, R - 1])
+
+
 def test_edge_cases_of_the_widened_entry_points(obc, orc):
     """Smallest shapes and degenerate masks: one sample, one column, one block, rows whose weights are
     all pruned already, every row with enough pruned weights for the bulk elimination."""
