@@ -29,9 +29,10 @@
 //                 then the row is corrected, w / diag are updated and u_s is kept.  When the panel
 //                 ends the steps' records and the vectors (for the flush) are written.
 //   flush_kernel  A0_new = compact(A0 - U diag(1/a) U^T): tiles of 32 x 64 on the fp32 matrix cores, one
-//                 wavefront each (only the lower triangle is kept).  The eliminated rows and columns are dropped while writing
-//                 (out of place, two buffers), so the matrix shrinks with the live set and later
-//                 blocks cost (m/d)^2 of the first.
+//                 wavefront each (only the lower triangle is kept).  The eliminated rows and columns are dropped
+//                 while writing (out of place, two buffers), so the matrix shrinks with the live set and later
+//                 blocks cost (m/d)^2 of the first.  A large first one is flush_first_kernel: strips of 128 or 256
+//                 rows with the vectors in LDS.
 //
 // The first block reads the shared H^-1 directly, so no per-row copy of it is ever made.
 // Already-pruned weights (quantization or pruning of survivors) are eliminated first, in index
@@ -400,9 +401,9 @@ __device__ __forceinline__ float row16_bcast(float v)
 // 32x32x2 tiles with its operands in LDS.  In us, before and now: 256 rows, 2208 columns left, 48 vectors 1285, 1115; 1904, 56
 // vectors 968, 878; 1296, 72 vectors 525, 508; 880, 64 vectors 234, 218; 3072 rows, 672, 48 vectors 1590, 1390; 320, 2 x 40
 // vectors 605, 548; 203 rows, 1067, 72 vectors 322, 299; 547, 64 vectors 110, 92; 64 rows, 384, 64 vectors 29, 19; 256 rows, 4416,
-// 4 x 24 vectors 6420, 6020; 2880, 2 x 40 vectors 2660, 2305; 3936, 64 vectors 4010, 3595.  But from the shared H^-1, 256 rows,
-// 2256 left, 48 vectors: 783, 911.  Tried: several tiles a wave (each store then stands in front of the next tile's operands,
-// whose wait is one for the store: 1120 -> 1400); 64 x 64 a wave (registers); a workgroup's operands in LDS, one tile each (1500).
+// 4 x 24 vectors 6420, 6020; 2880, 2 x 40 vectors 2660, 2305; 3936, 64 vectors 4010, 3595.  From the shared H^-1, where only
+// the new matrices go to HBM, the strips are the faster form (flush_first_kernel).  Tried: several tiles a wave (each store
+// then stands in front of the next tile's operands, whose wait is one for the store: 1120 -> 1400); 64 x 64 a wave (registers); a workgroup's operands in LDS, one tile each (1500).
 template <int K, int J, bool QUADS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void flush_kernel(FlushArgs a)
 {
@@ -600,6 +601,186 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
+// The first flush of a call where there is enough of it (kStripEntries): all rows read the same plain H^-1, which the
+// caches hold, and the operands weigh most -- with 48 vectors a 32 x 64 tile reads 2.2 bytes of them per byte that it stores.
+// So a workgroup of eight waves keeps them in LDS: it takes a strip of HALVES x 128 rows of one row's matrix, whose
+// F = -u / a it holds throughout, and walks its column blocks of 128, whose vectors serve all its halves.  Wave (wm, wn)
+// owns 64 x 32 entries of a 128 x 128 tile: two 32x32x2 accumulators, one sum per group of K vectors as in flush_kernel,
+// the same bits.  The old entries come as whole lines (32 columns of a row per half wave), before the tile's products.
+constexpr int FT = 128;        // tile edge
+template <int K, int HALVES, int J>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void flush_first_kernel(FlushArgs a)
+{
+    constexpr int SR = HALVES * FT;            // rows per strip
+    static_assert(K % 4 == 0 && K * J <= UCAP && (J == 1 || HALVES == 1), "a strip's vectors change within a tile");
+    __shared__ __align__(16) float Fs[J * K][SR + 4];
+    __shared__ __align__(16) float Us[K][FT + 4];
+    __shared__ unsigned rowoff_s[SR];          // byte offset of each strip row in H^-1
+
+    // All strips of one row on one XCD; there the rows go in groups of G, a group strip by strip, the longest first:
+    // long strips start first, and workgroups that start together take equally long and read the same rows of H^-1.
+    const int L = blockIdx.x;
+    const int strips = (a.m + SR - 1) / SR;
+    const int nx = gridDim.x / (8 * strips);              // rows per XCD
+    constexpr int G = 16;
+    const int grp = (L / 8) / (G * strips), within = (L / 8) - grp * G * strips;
+    const int rig = nx - G * grp < G ? nx - G * grp : G;  // rows in this group
+    const int strip = strips - 1 - within / rig;
+    const int row = (G * grp + within % rig) * 8 + (L % 8);
+    if (row >= a.R) return;
+    const int chunks = J == 1 ? 1 : a.chunks;
+    if (a.ws.nb[row] != K * chunks || a.ws.done[row] >= a.ws.total[row]) return;
+    const int d = a.d, mn = a.m, i0 = strip * SR;
+    const int *map = a.ws.map + (size_t)row * d;
+    const int ldu = a.ws.ldu, ldn = a.ld_new;
+    const float *U = a.ws.U + (size_t)row * UCAP * ldu;
+    const float *invd = a.ws.invd + (size_t)row * UCAP;
+    __amdgpu_buffer_rsrc_t rold = __builtin_amdgcn_make_buffer_rsrc((void *)a.A_old, 0, d * d * 4, kBufWord3);
+    __amdgpu_buffer_rsrc_t rnew = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.A_new + (size_t)row * a.new_row_stride), 0, ((mn + 3) >> 2) * ldn * 16, kBufWord3);
+    const int tid = threadIdx.x, lane = tid & 63, kl = lane >> 5, il = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (waves with the same wn share a SIMD and have the more work in a diagonal tile the smaller wn is;
+    // odd strips number them the other way round, so that two workgroups on a CU even that out)
+    const int wm = wave >> 2, wn = (strip & 1) ? 3 - (wave & 3) : wave & 3;
+    const int jl = wn * 32 + il;
+
+    for (int idx = tid; idx < K * chunks / 4 * SR; idx += 512) {
+        const int k = idx / SR * 4, i = idx % SR;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i0 + i < mn) v = *reinterpret_cast<const float4 *>(U + u_index(k, i0 + i, ldu));
+        Fs[k][i] = __fmul_rn(v.x, -invd[k]);
+        Fs[k + 1][i] = __fmul_rn(v.y, -invd[k + 1]);
+        Fs[k + 2][i] = __fmul_rn(v.z, -invd[k + 2]);
+        Fs[k + 3][i] = __fmul_rn(v.w, -invd[k + 3]);
+    }
+    for (int i = tid; i < SR; i += 512) rowoff_s[i] = (i0 + i < mn) ? (unsigned)(map[i0 + i] * d) * 4u : (unsigned)kFar;
+
+    // a column block's vectors: four of a column (16 bytes) each, in registers until everyone is done with the last
+    constexpr int UV = (K / 4 * FT + 511) / 512;
+    float4 ureg[UV];
+    auto fetch_u = [&](int j0, int chunk) {
+#pragma unroll
+        for (int h = 0; h < UV; ++h) {
+            const int idx = tid + h * 512, k = idx / FT * 4, j = j0 + idx % FT;
+            ureg[h] = (k < K && j < mn) ? *reinterpret_cast<const float4 *>(U + u_index(chunk * K + k, j, ldu))
+                                        : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    auto stash_u = [&]() {
+#pragma unroll
+        for (int h = 0; h < UV; ++h) {
+            const int idx = tid + h * 512, k = idx / FT * 4, j = idx % FT;
+            if (k < K) {
+                Us[k][j] = ureg[h].x;
+                Us[k + 1][j] = ureg[h].y;
+                Us[k + 2][j] = ureg[h].z;
+                Us[k + 3][j] = ureg[h].w;
+            }
+        }
+    };
+    auto old_col = [&](int j) { return j < mn ? (unsigned)map[j] * 4u : (unsigned)kFar; };
+    // halves of the strip that hold rows at all
+    const int nh = (mn - i0 + FT - 1) / FT < HALVES ? (mn - i0 + FT - 1) / FT : HALVES;
+    // the next tile: column blocks in order, and in each the halves whose rows reach down to it; false after the last
+    auto advance = [&](int &j0, int &hf) {
+        if (hf + 1 < nh) { hf += 1; return true; }
+        j0 += FT;
+        if (j0 >= mn) return false;
+        hf = j0 <= i0 ? 0 : (j0 - i0) / FT;
+        return hf < nh;
+    };
+
+    int j0 = 0, hf = 0;
+    unsigned colo = old_col(jl);
+    fetch_u(0, 0);
+    stash_u();
+    __syncthreads();                           // Us, Fs and rowoff_s visible
+    for (;;) {
+        const int rb = hf * FT + wm * 64;      // the wave's first strip row
+        // a 32 x 32 piece that lies above the diagonal or beyond the matrix has nothing to add
+        bool need[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+            need[mt] = j0 + wn * 32 < mn && i0 + rb + mt * 32 < mn && j0 + wn * 32 <= i0 + rb + mt * 32 + 31;
+        // the old entries (those above the diagonal of a piece that it crosses only reach slots that nobody reads)
+        floatx16 old[2], sum[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const unsigned co = need[mt] ? colo : (unsigned)kFar;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                old[mt][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    rold, (int)(rowoff_s[rb + mt * 32 + 8 * (v >> 2) + 4 * kl + (v & 3)] + co), 0, 0));
+        }
+        int j0n = j0, hfn = hf;
+        const bool more = advance(j0n, hfn), new_col = more && j0n != j0;
+        unsigned colon = colo;
+        if (new_col) {
+            if (J == 1) fetch_u(j0n, 0);
+            colon = old_col(j0n + jl);
+        }
+        for (int ch = 0; ch < chunks; ++ch) {
+            if (J > 1 && ch > 0) {
+                __syncthreads();               // everyone is done reading Us
+                stash_u();
+                __syncthreads();
+            }
+            if (J > 1) {
+                if (ch + 1 < chunks) fetch_u(j0, ch + 1);
+                else if (new_col) fetch_u(j0n, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { sum[0][v] = 0.f; sum[1][v] = 0.f; }
+            auto mma = [&](auto both, int mt0) {
+#pragma unroll
+                for (int kk = 0; kk < K; kk += 2) {
+                    const int kf = J == 1 ? kk + kl : ch * K + kk + kl;
+                    const float b0 = Us[kk + kl][jl];
+                    if constexpr (both) {
+                        sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(Fs[kf][rb + il], b0, sum[0], 0, 0, 0);
+                        sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(Fs[kf][rb + 32 + il], b0, sum[1], 0, 0, 0);
+                    } else if (mt0) {
+                        sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(Fs[kf][rb + 32 + il], b0, sum[1], 0, 0, 0);
+                    } else {
+                        sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(Fs[kf][rb + il], b0, sum[0], 0, 0, 0);
+                    }
+                }
+            };
+            if (need[0] && need[1]) mma(std::true_type{}, 0);
+            else if (need[0]) mma(std::false_type{}, 0);
+            else if (need[1]) mma(std::false_type{}, 1);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                old[0][v] = __fadd_rn(old[0][v], sum[0][v]);
+                old[1][v] = __fadd_rn(old[1][v], sum[1][v]);
+            }
+        }
+        // ---- store: registers 4q .. 4q+3 are four consecutive rows of the lane's column, one slot of the row-quad layout
+        const int jcol = j0 + jl, colB = jcol < mn ? jcol * 16 : kFar;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int qrow = i0 + rb + mt * 32 + 8 * q + 4 * kl;
+                const int off = jcol > qrow + 3 ? kFar : (qrow >> 2) * ldn * 16 + colB;
+                const uintx4 v = {__float_as_uint(old[mt][4 * q]), __float_as_uint(old[mt][4 * q + 1]),
+                                  __float_as_uint(old[mt][4 * q + 2]), __float_as_uint(old[mt][4 * q + 3])};
+                if (a.keep) __builtin_amdgcn_raw_buffer_store_b128(v, rnew, off, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b128(v, rnew, off, 0, kMatStorePolicy);
+            }
+        if (!more) break;
+        if (new_col) {
+            __syncthreads();                   // everyone is done reading Us
+            stash_u();
+            __syncthreads();                   // the new Us visible
+        }
+        j0 = j0n;
+        hf = hfn;
+        colo = colon;
+    }
+}
+
 // ------------------------------------------------------------------------------------- host side
 struct Variant {
     int cap;   // largest live size it handles (T * EPT)
@@ -660,6 +841,13 @@ constexpr int flush_split(int B) { return B > 72 ? 2 : 1; }
 // rows lie in more than ten of them.  In us, single rows and quads, 64 vectors: 256 rows, 560 columns left 118, 111; 368 52.2,
 // 52.6; 240 30.5, 31.2; 203 rows, 547 100, 92; 291 36, 39; 3072 rows, 176 201, 211; 2 x 40 vectors, 320 607, 573; 240 361, 342.
 constexpr int kQuadsMinRatio = 6;
+
+// Entries of all rows' new matrices from which the first flush goes by strips (flush_first_kernel); fewer do not give the
+// CUs enough of its long workgroups.  Calls of one flush and one step after it, in us, by tiles and by strips: 256 x 2304 1254,
+// 1109; 512 x 2304 2577, 2243; 256 x 2048 1113, 1030; 256 x 1536 790, 778; 3072 x 768 2172, 1991; 768 x 3072 12061, 10911; 256 x
+// 4608 10278, 9431; blocks 256 x 3072 2097, 1778; at 510 .. 550 million entries 128 x 2048 652, 637; 1024 x 768 695, 667; below
+// 64 x 2304 475, 492; 203 x 1283 514, 529; 32 x 4000 1809, 1821; 8 x 2304 264, 377 (but 64 x 2760 603, 591).
+constexpr double kStripEntries = 5e8;
 
 // what a flush reads has room in U and an instance of the kernel, whatever number of panels it serves
 constexpr bool flush_serves(const Variant &v)
@@ -820,9 +1008,15 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
             const double tri = 0.5 * (double)m_next * (m_next + 1.0);   // entries of one triangle
             obc_scope sc(ctx, OBC_KERNEL_FLUSH, (double)R * 8.0 * tri, (double)R * 2.0 * K * chunks * tri);
             const dim3 grid(fa.strips * (fa.strips + 1) * rows8);
+            const bool strips = cur < 0 && (double)R * m_next * m_next >= kStripEntries;
             auto launch = [&](auto k) {
                 constexpr int KK = decltype(k)::value, J = flush_groups(KK);
-                if (quads) flush_kernel<KK, J, true><<<grid, 256, 0, st>>>(fa);
+                constexpr int H = KK <= 48 ? 2 : 1;     // two workgroups' vectors in a CU's LDS
+                if (strips && chunks == 1)
+                    flush_first_kernel<KK, H, 1><<<(m_next + H * FT - 1) / (H * FT) * rows8, 512, 0, st>>>(fa);
+                else if (strips)
+                    flush_first_kernel<KK, 1, J><<<fa.strips * rows8, 512, 0, st>>>(fa);
+                else if (quads) flush_kernel<KK, J, true><<<grid, 256, 0, st>>>(fa);
                 else flush_kernel<KK, J, false><<<grid, 256, 0, st>>>(fa);
             };
             switch (K) {

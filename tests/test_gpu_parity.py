@@ -335,6 +335,44 @@ def test_flush_at_tile_edges(obc, orc, left):
     _check_prune(obc, orc, W, _hinv(obc, X), d, (0, 0), 2)
 
 
+@pytest.mark.parametrize("mode,d,R,few,k", [
+    ("prune", 2096, 128, 2, 100), ("prune", 2097, 128, 2, 100), ("quant", 2225, 110, 2, 2225), ("prune", 2303, 100, 2, 100),
+    ("blocks", 2304, 100, 2, 100), ("prune", 1999, 140, 2, 120), ("prune", 1283, 360, 2, 150), ("prune", 1000, 600, 2, 130),
+    ("prune", 768, 1024, 768, 100), ("prune", 512, 3072, 768, 200), ("prune", 2801, 96, 2, 170), ("blocks", 2904, 64, 2, 100),
+    ("prune", 4000, 40, 2, 180), ("blocks", 3996, 40, 2, 180), ("prune", 4608, 96, 2, 200), ("prune", 4600, 64, 2, 150),
+    ("prune", 4601, 25, 2, 100), ("dead", 2304, 101, 2, 40)])
+def test_first_flush_by_strips_and_by_tiles(obc, orc, mode, d, R, few, k):
+    """Five hundred million entries in all rows' matrices send the first flush to strips of 128 or 256 rows; the same rows
+    in a smaller call go by tiles, bit for bit the same.  Every number of vectors and of panels that share the flush,
+    ends at, before and behind the strips' and their tiles' edges, then past a second flush; one row against the oracle."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=d + 500)
+    Hinv = _hinv(obc, X)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    live = torch.ones(R, d, dtype=torch.uint8, device="cuda")
+    if mode == "dead":                       # one bulk elimination of 64 in every row, and 6 one by one
+        live.scatter_(1, torch.rand(R, d, generator=gen, device="cuda").topk(70, dim=1).indices, 0)
+
+    def solve(n):
+        w = W[:n].contiguous()
+        if mode == "blocks":
+            r = obc.obc_prune_blocks(w, Hinv, 4, k_blocks=k // 4)
+            return r["order"], r["loss"], r["W"]
+        if mode == "quant":
+            delta, offset, maxq = obc.obc_minmax_grid(w, 4)
+            r = obc.obc_quant_rows(w, Hinv, delta, offset, maxq)
+            return r["order"], r["loss"], r["W"], r["codes"]
+        r = obc.obc_prune_rows(w, Hinv, k_steps=k, live=live[:n].contiguous() if mode == "dead" else None)
+        return r["order"], r["loss"], r["W"]
+
+    many, less = solve(R), solve(few)
+    for a, b in zip(many, less):
+        assert torch.equal(a[:few], b)
+    if mode == "prune":
+        st = RowParity()
+        check_row(orc, st, "prune", _np(Hinv), _np(W[R - 1]), _np(many[0][R - 1]), _np(many[1][R - 1]), _np(many[2][R - 1]), k)
+        st.assert_order_rule()
+
+
 @pytest.mark.parametrize("d,k", [(2305, 90), (2344, 100), (3073, 100), (3200, 130), (4097, 60), (4608, 130)])
 def test_panels_that_share_a_flush(obc, orc, d, k):
     """Widths above 2304: several panels per flush, the group cut short where the live size changes the
