@@ -891,12 +891,16 @@ int shared_panels(const Variant &v, int m, int R)
     return v.J;
 }
 
-const Variant *pick_variant(int m, int R, int mode)
+// `left`: steps that the call has still to do (an upper bound over the rows).  Below 768 rows the shorter panels of three
+// rows per CU are not taken where one panel of 64 steps ends the call and they would need a flush and a second one, in us,
+// with them and without: 600 x 600, 56 steps 297, 261; 640 x 768, 60 419, 328; 767 x 768, 64 488, 359; 700 x 768, 100 (48 and
+// 52) 875, 643.
+const Variant *pick_variant(int m, int R, int mode, int left)
 {
     const int least = R >= 3 * 256 || mode == MODE_QUANT ? 256 : 352;
     if (R >= kSharedCuMinRows && m > least && mode != MODE_BLOCK)
         for (const Variant &v : kSharedCuVariants)
-            if (m <= v.cap && (v.B != 80 || longer_panels(m))) return &v;
+            if (m <= v.cap && (v.B != 80 || longer_panels(m)) && !(R < 3 * 256 && left > v.B && left <= 64)) return &v;
     for (int i = 0; i < kNumVariants; ++i)
         if (m <= kVariants[i].cap) return &kVariants[i];
     return nullptr;
@@ -1073,7 +1077,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
 
     while (host_done < host_total) {
         const int m_max = d - host_done;
-        const Variant *v = pick_variant(m_max, R, mode);
+        const Variant *v = pick_variant(m_max, R, mode, host_total - host_done);
         int swz;
         cur_matrix(&pa.A_cur, &pa.a_row_stride, &swz);
         pa.ld = ld_cur;
@@ -1084,8 +1088,9 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         PanelLaunch *next = mode == MODE_BLOCK ? v->launch_block_old : v->launch_old;
         const int most = next ? shared_panels(*v, m_max, R) : 1;
         int panels = 1;
-        while (panels < most && host_done + panels * v->B < host_total &&
-               pick_variant(m_max - panels * v->B, R, mode) == v) ++panels;
+        for (int ahead = v->B; panels < most && host_done + ahead < host_total &&
+                               pick_variant(m_max - ahead, R, mode, host_total - host_done - ahead) == v; ahead += v->B)
+            ++panels;
         for (int j = 0; j < panels; ++j) {
             pa.old = j * v->B;
             pa.last = j == panels - 1;

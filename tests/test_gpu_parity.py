@@ -1229,6 +1229,20 @@ def test_three_rows_per_cu_past_512_rows(obc, orc, R, d, k):
     _check_quant(obc, orc, W, Hinv, 4, 2, rows=[0, R - 1])
 
 
+@pytest.mark.parametrize("R,d,k,nm,panels", [(513, 520, 56, (0, 0), 1), (640, 768, 64, (0, 0), 1), (767, 768, 49, (0, 0), 1),
+                                             (600, 600, 60, (2, 4), 1), (700, 768, 100, (0, 0), 2), (700, 768, 48, (0, 0), 1),
+                                             (640, 600, 65, (0, 0), 2)])
+def test_few_steps_past_512_rows_end_without_another_flush(obc, orc, R, d, k, nm, panels):
+    """513 .. 767 rows of 513 .. 768 columns: 49 to 64 steps that are left are one panel, not one of 48 and a rest."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
+    Hinv = _hinv(obc, X)
+    obc.obc_profile_begin()
+    obc.obc_prune_rows(W, Hinv, k_steps=k, nm=nm, strategy=2)
+    stat = obc.obc_profile_end()
+    assert stat["panel"]["launches"] == panels and stat["flush"]["launches"] == panels - 1
+    _check_prune(obc, orc, W, Hinv, k, nm, 2, rows=[0, R - 1])
+
+
 def test_edge_cases_of_the_widened_entry_points(obc, orc):
     """Smallest shapes and degenerate masks: one sample, one column, one block, rows whose weights are
     all pruned already, every row with enough pruned weights for the bulk elimination."""
