@@ -865,6 +865,32 @@ constexpr bool flush_serves_all()
 }
 static_assert(flush_serves_all(), "a panel's steps, or those of the panels that share a flush, without a flush kernel");
 
+// Floats between two rows' matrices, and between two quads of a matrix with m live columns: multiples of 256 bytes, so that
+// a wave's stores are whole lines at any live size.  In ms, with the live size as the distance and, where it was no
+// multiple of 4, stores through the caches, and with this: 256 x 2303 at 4 bit 23.36, 21.91; 3071 x 765 at 4 bit 15.53, 14.81;
+// 768 x 767 pruned 5.01, 4.78; 203 x 1283 at 8 bit 4.62, 4.51; 203 x 1999 pruned 17.08, 16.72; 40 x 4095 44.0, 43.0; 64 x 577
+// 1.200, 1.187; aligned 256 x 2304 at 4 bit 21.84, 21.83.
+constexpr size_t matrix_stride(int d) { return (size_t)d * d / 64 * 64; }
+constexpr int quad_ld(int m) { return (m + 15) / 16 * 16; }
+
+// The first flush leaves the largest matrix; the padded distances have to leave it within its row's share of what was
+// laid out, d * d floats.
+constexpr bool matrix_fits(int d, int steps)
+{
+    const int m = d - steps;
+    return m <= 0 || (size_t)(m + 3) / 4 * 4 * quad_ld(m) <= matrix_stride(d);
+}
+constexpr bool matrices_fit()
+{
+    int fewest = BMAX;
+    for (const Variant &v : kVariants) fewest = v.B < fewest ? v.B : fewest;
+    for (const Variant &v : kSharedCuVariants) fewest = v.B < fewest ? v.B : fewest;
+    for (int d = BMAX + 1; d <= kVariants[kNumVariants - 1].cap; ++d)
+        if (!matrix_fits(d, fewest)) return false;
+    return true;
+}
+static_assert(matrices_fit(), "a flush that eliminates too little for the padded matrix it leaves");
+
 // Panels of 80 steps where they reach 256 live columns, from which on a thread owns one index, in fewer panels than
 // those of 48 do; where both take as many (273..304 and 337..352 columns) the shorter ones leave more of the steps to
 // the cheaper variant.  Up to 272 columns 80 steps save one of the panels below 256 instead.  In us, pruned, with 80 and
@@ -969,13 +995,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
     fa.d = d; fa.R = R; fa.ws = bw;
 
     int host_total = (mode == MODE_QUANT || live) ? d : k_steps;   // upper bound over the rows
-    // Floats between two rows' matrices, and between two quads of a matrix: multiples of 256 bytes, so that a wave's stores
-    // are whole lines at any live size.  (They fit what was laid out: a flush leaves d - 24 columns at most, rounded up to
-    // 16, in d - 24 rows, rounded up to 4.)  In ms, with the live size as the distance and, where it was no multiple of 4,
-    // stores through the caches, and with this: 256 x 2303 at 4 bit 23.36, 21.91; 3071 x 765 at 4 bit 15.53, 14.81; 768 x 767
-    // pruned 5.01, 4.78; 203 x 1283 at 8 bit 4.62, 4.51; 203 x 1999 pruned 17.08, 16.72; 40 x 4095 44.0, 43.0; 64 x 577 1.200,
-    // 1.187; aligned 256 x 2304 at 4 bit 21.84, 21.83.
-    const size_t mat_stride = (size_t)d * d / 64 * 64;
+    const size_t mat_stride = matrix_stride(d);
     int host_done = 0;
     int cur = -1;            // -1: the shared H^-1; otherwise index into Abuf
     int ld_cur = d;
@@ -999,7 +1019,7 @@ int blocked_launch(obc_ctx *ctx, int mode, const float *W, const float *Hinv, in
         fa.A_new = bw.Abuf[nxt];
         fa.new_row_stride = mat_stride;
         fa.m = m_next;
-        fa.ld_new = (m_next + 15) / 16 * 16;
+        fa.ld_new = quad_ld(m_next);
         fa.chunks = chunks;
         fa.keep = (double)R * m_next * m_next * 2.0 <= kKeepBytes;
         fa.strips = (m_next + 127) / 128;
