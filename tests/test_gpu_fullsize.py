@@ -318,13 +318,14 @@ def test_width_4608_quantize_survivors(obc, orc):
     assert int(c[live != 0].min()) >= 0 and int(c[live != 0].max()) <= maxq
 
 
-@pytest.mark.parametrize("d_col,kb", [(2400, 30), (3200, 32), (4200, 36)])
-def test_wide_block_pruning_first_blocks(obc, orc, d_col, kb):
+@pytest.mark.parametrize("d_col,kb,rows", [(2400, 30, 2), (3200, 32, 2), (4200, 36, 2), (4200, 36, 3), (4200, 36, 64),
+                                           (4200, 36, 96)])
+def test_wide_block_pruning_first_blocks(obc, orc, d_col, kb, rows):
     """Block pruning (blocks of 4) above 2304 columns runs on the panel variants with six, eight and
-    nine owned indices per thread (blocks of 40, 28 and 24 steps, which share a flush in threes and fours
-    at the latter two); the oracle replays the first block steps (three of the 40, more than one such
-    group and its flush of the others) of one row."""
-    W, X, _ = obc_inputs.make_layer("ffn768x3072", device="cuda", d_row=2, d_col=d_col, n_samples=8000)
+    nine owned indices per thread: panels of 40 steps with a flush each, of 28 that share one in threes, and
+    of 24 that share none with two rows, and one in twos, threes and fours with 3, 64 and 96.  The oracle replays
+    the first block steps (three panels of the 40, more than one group and its flush of the others) of one row."""
+    W, X, _ = obc_inputs.make_layer("ffn768x3072", device="cuda", d_row=rows, d_col=d_col, n_samples=8000)
     R, d = W.shape
     assert d == d_col
     Hinv = obc.obc_invert(obc.obc_hessian(X))

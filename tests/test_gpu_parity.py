@@ -373,11 +373,14 @@ def test_first_flush_by_strips_and_by_tiles(obc, orc, mode, d, R, few, k):
         st.assert_order_rule()
 
 
-@pytest.mark.parametrize("d,k", [(2305, 90), (2344, 100), (3073, 100), (3200, 130), (4097, 60), (4608, 130)])
-def test_panels_that_share_a_flush(obc, orc, d, k):
-    """Widths above 2304: several panels per flush, the group cut short where the live size changes the
-    variant, the last step inside a group."""
-    W, X = _layer("conv64x576", d_col=d, d_row=2, n_samples=2 * d)
+@pytest.mark.parametrize("d,k,R", [(2305, 90, 2), (2344, 100, 2), (3073, 100, 2), (3200, 130, 2), (4097, 60, 2), (4608, 130, 2),
+                                   (2900, 130, 96), (3073, 130, 96), (4097, 60, 96), (4608, 130, 3), (4608, 130, 64),
+                                   (4608, 130, 96)])
+def test_panels_that_share_a_flush(obc, orc, d, k, R):
+    """Widths above 2304: a flush after each panel or after several, as width and rows have it (24 steps a panel: none
+    shared with two rows, two with 3, three with 64, four with 96; 28: three; 40: two with 96), the group cut short
+    where the live size changes the variant, the last step inside a group."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
     _check_prune(obc, orc, W, _hinv(obc, X), k, (0, 0), 2, rows=[1])
 
 
@@ -392,12 +395,12 @@ def test_panel_account_counts_the_vectors_read_again(obc):
     assert stat["launches"] == 3 and stat["bytes"] == 2 * 28 * 4 * 3200 * (1 + (1 + 28) + (1 + 56))
 
 
-@pytest.mark.parametrize("d,k", [(3200, 130), (4200, 150)])
-def test_wide_quantization_and_n_m_first_steps(obc, orc, d, k):
-    """OBQ and the N:M rule on panels that share a flush, past one group of three or four: the first steps
-    of a row against the oracle (OBQ follows the GPU's order; a pick may be above the least score by no
-    more than fp32 storage explains)."""
-    W, X = _layer("conv64x576", d_col=d, d_row=2, n_samples=2 * d)
+@pytest.mark.parametrize("d,k,R", [(3200, 130, 2), (4200, 150, 2), (4200, 150, 96)])
+def test_wide_quantization_and_n_m_first_steps(obc, orc, d, k, R):
+    """OBQ and the N:M rule on panels that share a flush, past one group of three (28 steps a panel, any rows) or
+    four (24 steps, 96 rows), and on panels of 24 that do not (two rows): the first steps of a row against the
+    oracle (OBQ follows the GPU's order; a pick may be above the least score by no more than fp32 storage explains)."""
+    W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=2 * d)
     Hinv = _hinv(obc, X)
     _check_prune(obc, orc, W, Hinv, k, (2, 4), 2, rows=[1])
     delta, offset, maxq = obc.obc_minmax_grid(W, 4)
@@ -432,16 +435,28 @@ def test_shared_flushes_leave_no_trace(obc, mode):
         assert torch.equal(many[:8], few)
 
 
+@pytest.mark.parametrize("mode", ["prune", "n_m", "quant", "blocks"])
 @pytest.mark.parametrize("d,R", [(2900, 96), (4200, 96), (4200, 64), (4200, 3)])
-def test_the_panels_that_share_a_flush_follow_the_rows(obc, d, R):
+def test_the_panels_that_share_a_flush_follow_the_rows(obc, d, R, mode):
     """How many panels of 24 or 40 steps share a flush (four, three, two, none) depends on the rows; a row's results
     do not.  Past a whole group and the change to panels of 28 steps."""
     W, X = _layer("conv64x576", d_col=d, d_row=R, n_samples=d + 500)
     Hinv = _hinv(obc, X)
-    many = obc.obc_prune_rows(W, Hinv, k_steps=150, strategy=2)
-    few = obc.obc_prune_rows(W[:2].contiguous(), Hinv, k_steps=150, strategy=2)
-    for name in ("order", "loss", "W"):
-        assert torch.equal(many[name][:2], few[name]), name
+
+    def solve(rows):
+        if mode == "quant":
+            delta, offset, maxq = obc.obc_minmax_grid(rows, 4)
+            r = obc.obc_quant_rows(rows, Hinv, delta, offset, maxq, strategy=2)
+        elif mode == "blocks":
+            r = obc.obc_prune_blocks(rows, Hinv, 4, k_blocks=38)
+        else:
+            r = obc.obc_prune_rows(rows, Hinv, k_steps=150, nm=(2, 4) if mode == "n_m" else (0, 0), strategy=2)
+        return [r[name] for name in ("order", "loss", "W", "codes") if r.get(name) is not None]
+
+    many, few = solve(W), solve(W[:2].contiguous())
+    assert len(many) == (4 if mode == "quant" else 3)
+    for a, b in zip(many, few):
+        assert torch.equal(a[:2], b)
 
 
 @pytest.mark.parametrize("strategy", [1, 2])
@@ -484,7 +499,7 @@ def test_prune_rows_zero_weights_and_ties(obc, orc, strategy):
 
 
 @pytest.mark.parametrize("R,d", [(768, 320), (768, 600), (2, 1100), (2, 1700), (2, 2200), (2, 2500), (96, 2500),
-                                 (2, 3400), (2, 4400)])
+                                 (2, 3400), (2, 4400), (96, 4400)])
 def test_ties_among_several_owned_indices(obc, R, d):
     """Exact ties go to the least index, also where a thread owns several: of a wave's candidates the least
     may sit on a higher lane than another one, of the waves' candidates in a later wave.  Every variant with
