@@ -58,6 +58,29 @@ def test_hessian_matches_oracle(obc, orc, d, N, pad):
     assert np.linalg.norm(_np(Hacc) - ref0) / np.linalg.norm(ref0) < 2e-6
 
 
+@pytest.mark.parametrize("d", [1, 5, 24, 31, 32, 33, 100])
+def test_hessian_dampening_with_the_last_batch(obc, d):
+    """Up to 32 columns the launch that sums the slices dampens too, above a launch of its own: lambda is the stated
+    share of the mean diagonal, formed in fp64 and rounded, added with one rounding; nothing else changes, in one batch
+    and with the last of two."""
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn(d, 300, generator=gen, device="cuda") + 0.5
+    A, B = X[:, :130].contiguous(), X[:, 130:].contiguous()
+
+    def two(damp):
+        H = obc.obc_hessian(A, damp_rel=-1.0)
+        return obc.obc_hessian(B, damp_rel=damp, H=H, accumulate=True)
+
+    for solve in (lambda damp: obc.obc_hessian(X, damp_rel=damp), two):
+        plain, damped = solve(-1.0).cpu(), solve(0.01).cpu()
+        h = plain.diagonal().double()
+        lam = float(np.float32(0.01)) * h.mean()
+        err = (damped.diagonal().double() - (h + lam)).abs()
+        assert bool((err <= 2.0 ** -24 * (h + lam) + 1.01 * 2.0 ** -24 * lam).all()), float(err.max())
+        off = ~torch.eye(d, dtype=torch.bool)
+        assert torch.equal(damped[off], plain[off])
+
+
 @pytest.mark.parametrize("d,N,off,pad", [(1, 1, 0, 0), (5, 15, 1, 1), (127, 16, 0, 1), (128, 17, 2, 2), (129, 33, 3, 0),
                                          (256, 64, 0, 3), (1153, 1000, 1, 0), (2049, 49, 0, 1)])
 def test_second_moments_at_tile_edges(obc, d, N, off, pad):
