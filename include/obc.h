@@ -106,7 +106,8 @@ int obc_membench(obc_ctx *ctx, int kind, int streaming, const void *src, void *d
                  int reps, double *ms_per_pass);
 
 /* What the matrix cores of this GPU sustain on nothing but independent MFMA instructions, four
- * wavefronts on every SIMD: kind 0 = v_mfma_f32_32x32x2_f32 (the flush's instruction), kind 1 =
+ * wavefronts on every SIMD: kind 0 = v_mfma_f32_32x32x2_f32 (the first flush's instruction; the others'
+ * v_mfma_f32_4x4x1, of the same nominal rate, sustains 151 TFLOP/s where this one does 155), kind 1 =
  * v_mfma_f64_16x16x4_f64 (the factorisation's).  Every wavefront issues 4 * iters instructions per
  * pass; one warm-up pass and `reps` timed ones on the context's stream.  Returns the mean
  * milliseconds per pass and the flops of a pass.  Synchronous. */

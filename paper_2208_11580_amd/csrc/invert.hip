@@ -9,8 +9,8 @@
 //   1. A = double(H);  blocked right-looking Cholesky A = L L^T with 64-wide block columns, one
 //      launch per block column (chol_step_kernel): every 64 x 64 tile of the trailing update forms
 //      the piece of the panel it needs itself, the workgroup of the next diagonal block goes on to
-//      factor that block and invert its factor on a single wavefront (16 x 16 sub-blocks in
-//      registers, the rest of the block on the fp64 matrix core out of LDS).
+//      factor that block and invert its factor (one wavefront the columns' chain, a 16-column panel in
+//      registers; the other three the sub-blocks' inverses and products, out of LDS).
 //   2. Y = L^-1 by right-looking blocked forward substitution on the identity, in the same launches.
 //   3. H^-1 = Y^T Y, lower tiles only, mirrored on store so the result is exactly symmetric.
 // All GEMMs run on the fp64 matrix cores (v_mfma_f64_16x16x4_f64), 64x64 tiles staged through LDS.
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void slab_gemm_kernel(const double *__restrict
 // Every z = 0 / 1 workgroup forms its own Q = P_i G in LDS first: the panel solve that used to be a
 // launch of its own on the stream's serial chain now costs each tile one more small product.  The
 // workgroup of tile (0, 0), the first one dispatched, keeps the block it has just updated -- the next
-// diagonal block -- in LDS, factors it there on one wavefront, and leaves T and G for the next step.
+// diagonal block -- in LDS, factors it there with its four wavefronts, and leaves T and G for the next step.
 // Per step the stream waits for: one trip to memory, two tile products, one 64 x 64 factorisation,
 // one product out of LDS.
 struct StepArgs {
@@ -326,10 +326,10 @@ int factor_inverse(obc_ctx *ctx, const float *H, int d, void *ws, double **Yout)
     double *Y = (double *)(base + mat);
     double *Lb = (double *)(base + 2 * mat);
     // 1 + 2. Cholesky A = L L^T and Y = L^-1 together, block column by block column, one launch per
-    // step (chol_step_kernel); the first diagonal block comes with the set-up, the last block row
-    // has launches of its own.  (Y starts as the identity: forward substitution on the identity, right-looking;
-    // before step kb its block row kb holds I_kb - sum_{j<kb} L[kb,j] Y[j], non-zero only in columns
-    // < k0 + bs.)
+    // step (chol_step_kernel); the first diagonal block comes with the set-up, the solves of the last two
+    // block rows are a launch of their own.  (Y starts as the identity: forward substitution on the identity,
+    // right-looking; before step kb its block row kb holds I_kb - sum_{j<kb} L[kb,j] Y[j], non-zero only in
+    // columns < k0 + bs.)
     double *Gb = Lb + (int64_t)nblk * NB * NB;
     const int64_t per = ((int64_t)d * d + 1023) / 1024;          // workgroups at four elements a thread
     chol_first_kernel<<<1 + (unsigned)(per < 2048 ? per : 2048), 256, 0, st>>>(H, d, A, Y, Lb, Gb, nullptr, ctx->d_status);
@@ -352,7 +352,7 @@ int factor_inverse(obc_ctx *ctx, const float *H, int d, void *ws, double **Yout)
             const int tm = (m + NB - 1) / NB, tc = (nc + NB - 1) / NB;
             chol_step_kernel<<<dim3((unsigned)(tm > tc ? tm : tc), (unsigned)tm, 3), 256, 0, st>>>(sa);
         } else {
-            // the last block column: finish the previous block row and this one
+            // the last block column: finish the previous block row and this one, in one launch
             solve_rows_kernel<<<dim3((nc + NB - 1) / NB, bsprev > 0 ? 2 : 1), 256, 0, st>>>(Tk, Y, d, k0, bs);
         }
         kprev0 = k0;

@@ -346,9 +346,9 @@ constexpr int kFar = 0x40000000;              // byte offset beyond any matrix: 
 constexpr int kMatStorePolicy = 2 | 16;
 
 // The stores go through the caches where all rows' new matrices together fit the 256 MB memory-side cache, in which the
-// next panels find the rows that they fetch: 64 x 576 2:4 507, 500 us; 128 x 1536 5.21, 5.18 ms; 768 x 768 4.05, 4.05.
-// Larger ones only displace what is of use: with a limit of 640 MB 768 x 768 4.11, 1024 x 600 3.37 against 3.29, 100 x 1800
-// 6.93 against 6.84; without one 256 x 2304 at 4 bit 23.9 against 22.9.
+// next panels find the rows that they fetch; larger ones only displace what is of use.  In us, with no limit, 640 MB, 256 MB
+// and none through the caches: 64 x 576 2:4 459, 459, 459, 469; 203 x 1283 at 8 bit 4490, 4485, 4410, 4425; 768 x 768 pruned
+// 3882, 3776, 3733, 3742; 256 x 2304 at 4 bit 22483, 21861, 21826, 21807; 64 x 3072 pruned 20227, 19720, 19615, 19653.
 constexpr double kKeepBytes = 256e6;
 
 // x[v] = x[v + 1] from Z on
@@ -397,13 +397,10 @@ __device__ __forceinline__ float row16_bcast(float v)
 //
 // What bounds it: HBM (8 bytes per entry of the new triangle; without any product and operand the same loads and stores
 // take 0.72 .. 0.8 of its time) and, not quite overlapped at four waves a SIMD, the matrix cores and the waves' start: some
-// 4 us up to a tile's first entries, of 12 in all.  Before, a workgroup of eight waves walked a strip of 128 or 256 rows on
-// 32x32x2 tiles with its operands in LDS.  In us, before and now: 256 rows, 2208 columns left, 48 vectors 1285, 1115; 1904, 56
-// vectors 968, 878; 1296, 72 vectors 525, 508; 880, 64 vectors 234, 218; 3072 rows, 672, 48 vectors 1590, 1390; 320, 2 x 40
-// vectors 605, 548; 203 rows, 1067, 72 vectors 322, 299; 547, 64 vectors 110, 92; 64 rows, 384, 64 vectors 29, 19; 256 rows, 4416,
-// 4 x 24 vectors 6420, 6020; 2880, 2 x 40 vectors 2660, 2305; 3936, 64 vectors 4010, 3595.  From the shared H^-1, where only
-// the new matrices go to HBM, the strips are the faster form (flush_first_kernel).  Tried: several tiles a wave (each store
-// then stands in front of the next tile's operands, whose wait is one for the store: 1120 -> 1400); 64 x 64 a wave (registers); a workgroup's operands in LDS, one tile each (1500).
+// 4 us up to a tile's first entries, of 12 in all.  In us, by strips (the form of flush_first_kernel) and by tiles: 256 rows,
+// 2208 columns left, 48 vectors 1285, 1115; 880, 64 vectors 234, 218; 3072 rows, 672, 48 vectors 1590, 1390; 64 rows, 384, 64
+// vectors 29, 19; 256 rows, 2880, 2 x 40 vectors 2660, 2305.  Several tiles a wave are slower: each store then stands in
+// front of the next tile's operands, whose wait is one for the store (1115 -> 1400).
 template <int K, int J, bool QUADS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void flush_kernel(FlushArgs a)
 {
@@ -813,12 +810,11 @@ constexpr Variant kVariants[] = {
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 // Three of these fit on one CU (registers and LDS), two where a thread owns one index; with several times more
-// rows than CUs that hides a row's latency behind the steps of two others.  Past two full rounds of the wider ones, in us, with
-// 1024 x 1 and with these: 513 x 400 pruned 928, 816, at 4 bit 1008, 807; 513 x 512 1304, 1263 and 1399, 1246; 576 x 600 2217,
-// 1851 and 2287, 1833; 700 x 768 3853, 3543 and 3942, 3534; 768 x 768 4053, 3757 and 4141, 3736; 1536 x 600 4694, 4069; 3072 x 768
-// 15453, 14537 and 16075, 14691.  (Fewer than 768 rows pruned take them above 352 columns only, one workgroup being done before
-// three fill a CU: 513 x 300 487, 502; 700 x 300 534, 550; at 4 bit 549, 493.)  Against: 512 x 512 1107, 1210, 512 x 768 2775, 2825; a
-// last round of few rows, 1024 x 512 pruned 1928, 2133, at 4 bit 2062, 2098; 1024 x 768 5221, 5312 and 5391, 5285.
+// rows than CUs that hides a row's latency behind the steps of two others.  So from past two full rounds of the wider ones
+// on, pruning with less than three rows per CU only above 352 columns (below, one workgroup is done before three fill a
+// CU).  In us, with 1024 x 1 and with these: 513 x 512 pruned 1304, 1263, at 4 bit 1399, 1246; 700 x 768 3853, 3543 and 3942,
+// 3534; 3072 x 768 15453, 14537 and 16075, 14691; left out: 512 x 768 2775, 2825; 700 x 300 pruned 534, 550.  A last round of
+// few rows loses: 1024 x 512 pruned 1928, 2133.
 // With two owned indices the same registers and LDS hold 80 steps.
 // Block pruning never takes them: its state does not fit beside them (83 registers in scratch memory at 256 x 3), and the
 // steps of 1024 x 1, which are not a loop, are the faster ones at every width and row count: 768 x 260 497 against 531 us,
@@ -901,15 +897,14 @@ constexpr bool longer_panels(int m) { return m <= 272 || (m - 256 + 79) / 80 < (
 
 // How many panels share a flush.  What the flushes save must exceed the re-reading of the earlier panels' vectors.  A
 // flush takes the longer the more rows there are and the wider they are; the re-reading stands in each step's chain
-// however few they are.  In us, pruned from that width down, a flush after each panel, after two, three and four:
-// 280 steps (40 a panel) 1 x 2800 1332, 2005; 8 x 3072 1642, 2274; 64 x 3072 4050, 4202; 96 x 3072 5391, 5206; 96 x 2800
-// 4637, 4636; 128 x 2500 4715, 4681; 192 x 2400 5863, 5845; 256 x 2650 9511, 8339 (below the best line 96 x 2500 3825, 3984).
-// 288 steps (24) 2 x 4400 2850, 3020, 3427, 3884; 4 x 4400 3235, 3190, 3576, 4030; 24 x 4608 6367, 4806, 4808, 5417; 48 x 4608
-// 10280, 6742, 6776, 7240; 64 x 4608 12938, 8271, 7918, 8292; 96 x 4608 18227, 11132, 10175, 10164; 256 x 4608 43764, 25196,
-// 22525, 21954; blocks of four 4 x 4400 3327, 3606, 4187, 4883; 16 x 4608 5180, 4591, 4963, 5605; 64 x 4608 13093, 8892, 8915, 9578.
-// 28 a panel share three at any row count (336 steps: 96 x 3700 12943, 8998, 8946; 192 x 3700 23505, 14943, 14254), though
-// fewer would be better with few rows (48 x 3700 7734, 5737, 6338; 8 x 3700 3434, 3496, 3932).
-// (Not with block pruning's larger state at 40 steps: 40 x 3000 in blocks 18.57 ms, 19.15 shared.)
+// however few they are.  In us, a flush after each panel, after two, three and four:
+//   40 a panel, 280 steps: 8 x 3072 1642, 2274; 64 x 3072 4050, 4202; 96 x 3072 5391, 5206; 128 x 2500 4715, 4681; 256 x 2650
+//     9511, 8339 (below the best line 96 x 2500 3825, 3984); not with block pruning's larger state, 40 x 3000 18570, 19150
+//   24 a panel, 288 steps: 2 x 4400 2850, 3020, 3427, 3884; 24 x 4608 6367, 4806, 4808, 5417; 64 x 4608 12938, 8271, 7918,
+//     8292; 256 x 4608 43764, 25196, 22525, 21954; in blocks 4 x 4400 3327, 3606, 4187, 4883; 64 x 4608 13093, 8892, 8915, 9578
+//   28 a panel, 336 steps: 192 x 3700 23505, 14943, 14254.  They share three at any row count -- the account of what three
+//     such panels read is pinned at two rows -- though fewer are better with few rows: 48 x 3700 7734, 5737, 6338; 8 x 3700
+//     3434, 3496, 3932
 int shared_panels(const Variant &v, int m, int R)
 {
     if (v.J == 2) return m >= 2416 && R >= 96 ? 2 : 1;
