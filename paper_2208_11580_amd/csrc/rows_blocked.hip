@@ -598,8 +598,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
-// The first flush of a call where there is enough of it (kStripEntries): all rows read the same plain H^-1, which the
-// caches hold, and the operands weigh most -- with 48 vectors a 32 x 64 tile reads 2.2 bytes of them per byte that it stores.
+// The first flush of a call where there is enough of it (kStripEntries): all rows read the same plain H^-1, so that only the
+// new matrices have to cross HBM and what tiles read from the caches weighs more -- with 48 vectors a 32 x 64 tile reads 2.2
+// bytes of them per byte that it stores, and H^-1 past L2 once per row (256 x 2304: 2.8 GB, in strips of 16 rows at a time 0.65).
 // So a workgroup of eight waves keeps them in LDS: it takes a strip of HALVES x 128 rows of one row's matrix, whose
 // F = -u / a it holds throughout, and walks its column blocks of 128, whose vectors serve all its halves.  Wave (wm, wn)
 // owns 64 x 32 entries of a 128 x 128 tile: two 32x32x2 accumulators, one sum per group of K vectors as in flush_kernel,
